@@ -108,3 +108,25 @@ def test_image_tiles_on_a_gbuffer(torch_cuda):
     fo = oracle.eval_mixture(mix["mean"], mix["factor"], mix["weight"], mix["colour"], x[idx])
     assert np.abs(fo).max() > 1e-3
     assert normwise(f[idx], fo) <= 1e-4
+
+
+@pytest.mark.parametrize("n,p", [(2, 1), (3, 2), (5, 1), (7, 3), (7, 6), (12, 1), (12, 11)])
+def test_condition_every_split(torch_cuda, n, p):
+    """The first and last split of small, odd and the largest n, at the
+    tolerances of test_condition_matches_the_oracle."""
+    from paper_2405_20067_amd import ngd
+    k = 131
+    mix = inputs.gen_mixture(n, k, "cube", (5.0, 50.0), 2.0, seed=n + p)
+    xc = np.ascontiguousarray(mix["mean"][5, p:])
+    m = ngd.Mixture(n, k)
+    m.update(dev(mix["mean"]), dev(mix["factor"]), dev(mix["weight"]), dev(mix["colour"]))
+    cm, cf, cw, cc = [host(t) for t in m.condition(p, xc)]
+    om, of, ow, _ = oracle.condition(mix["mean"], mix["factor"], mix["weight"], mix["colour"],
+                                     p, xc)
+    live = ow > 1e-30 * ow.max()
+    np.testing.assert_allclose(cm[live], om[live], rtol=0, atol=2e-5 * np.abs(om).max())
+    cov_g, cov_o = _cov(cf.astype(np.float64), p), _cov(of, p)
+    scale = np.abs(cov_o).reshape(k, -1).max(1)[:, None, None]
+    assert np.all(np.abs(cov_g - cov_o) <= 1e-4 * scale)
+    assert normwise(cw, ow) <= 1e-5
+    np.testing.assert_array_equal(cc, mix["colour"])
