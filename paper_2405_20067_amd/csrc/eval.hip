@@ -36,74 +36,86 @@ namespace ngd {
 namespace {
 
 constexpr int kEvalThreads = 256;
-template <int N>
-__global__ __launch_bounds__(kEvalThreads) void k_eval_dense(int64_t k, int64_t q,
-                                                             const float *__restrict__ rec,
-                                                             const float *__restrict__ queries,
-                                                             float *__restrict__ out)
-{
-    using Lay = RecLayout<N>;
-    const int64_t p = int64_t(blockIdx.x) * kEvalThreads + threadIdx.x;
-    const bool valid = p < q;
-    float x[N];
-#pragma unroll
-    for (int a = 0; a < N; ++a) x[a] = valid ? queries[p * N + a] : 0.0f;
-    float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
-    float blk[Lay::PF], nxt[Lay::PF];
-    if (k > 0) load_block<N>(nxt, rec);
-    for (int64_t i = 0; i < k; ++i) {
-#pragma unroll
-        for (int e = 0; e < Lay::PF; ++e) blk[e] = nxt[e];
-        if (i + 1 < k) load_block<N>(nxt, rec + (i + 1) * Lay::R);
-        eval_pair<N, false>(blk, rec + i * Lay::R, x, valid, 0.0f, f0, f1, f2);
-    }
-    if (valid) {
-        out[p * 3 + 0] = f0;
-        out[p * 3 + 1] = f1;
-        out[p * 3 + 2] = f2;
-    }
-}
 
-// The same direct sum for batches too small to fill the chip one query per
-// lane: a workgroup takes 64 queries (lane = query) and its 4 waves split
-// the Gaussians into 4 consecutive ranges; the 4 partial sums are added in
-// range order through LDS, so the result does not depend on scheduling.
-constexpr int kSplit = kEvalThreads / kWave;
-template <int N>
-__global__ __launch_bounds__(kEvalThreads) void k_eval_dense_split(
-    int64_t k, int64_t q, const float *__restrict__ rec, const float *__restrict__ queries,
-    float *__restrict__ out)
+// The plain direct sum.  A lane holds NQ queries, so that a record's scalar
+// loads and their waits serve NQ distances; records alternate between two
+// register blocks, the next one's load issued after the wait for the current.
+// SPLIT: the workgroup's W waves take the same 64 NQ queries and split the
+// Gaussians into W consecutive ranges; the partial sums are added in range
+// order through LDS, so the result does not depend on scheduling.  Otherwise
+// each wave has its own queries and sums all Gaussians.
+// Bound by the vector operations (N = 4: 25 issue slots a pair with the exp).
+// K = 256, Q = 65,536, n = 4: 16.6 us, 10 of them vector issue; with one
+// query a lane and 4 waves (whose records came through vector loads) 41.9 us.
+template <int N, int NQ, int W, bool SPLIT>
+__global__ __launch_bounds__(W *kWave) void k_eval_dense(int64_t k, int64_t q,
+                                                         const float *__restrict__ rec,
+                                                         const float *__restrict__ queries,
+                                                         float *__restrict__ out)
 {
     using Lay = RecLayout<N>;
-    __shared__ float part[kSplit][3][kWave];
+    constexpr int kQ = NQ * kWave;   // queries of a wave
     const int w = int(threadIdx.x) / kWave, lane = lane_id();
-    const int64_t p = int64_t(blockIdx.x) * kWave + lane;
-    const bool valid = p < q;
-    float x[N];
+    const int64_t p0 = (SPLIT ? int64_t(blockIdx.x) : int64_t(blockIdx.x) * W + w) * kQ;
+    float x[NQ][N], f[NQ][3];
 #pragma unroll
-    for (int a = 0; a < N; ++a) x[a] = valid ? queries[p * N + a] : 0.0f;
-    const int64_t per = (k + kSplit - 1) / kSplit;
-    const int64_t i0 = w * per, i1 = (i0 + per < k) ? i0 + per : k;
-    float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
-    float blk[Lay::PF], nxt[Lay::PF];
-    if (i0 < i1) load_block<N>(nxt, rec + i0 * Lay::R);
-    for (int64_t i = i0; i < i1; ++i) {
+    for (int u = 0; u < NQ; ++u) {
+        const int64_t p = p0 + u * kWave + lane;
 #pragma unroll
-        for (int e = 0; e < Lay::PF; ++e) blk[e] = nxt[e];
-        if (i + 1 < i1) load_block<N>(nxt, rec + (i + 1) * Lay::R);
-        eval_pair<N, false>(blk, rec + i * Lay::R, x, valid, 0.0f, f0, f1, f2);
+        for (int a = 0; a < N; ++a) x[u][a] = p < q ? queries[p * N + a] : 0.0f;
+        f[u][0] = f[u][1] = f[u][2] = 0.0f;
     }
-    part[w][0][lane] = f0;
-    part[w][1][lane] = f1;
-    part[w][2][lane] = f2;
-    __syncthreads();
-    if (w == 0 && valid) {
+    // 32-bit uniform indices (k < 2^31) and unconditional loads (past the
+    // range, its last record again): the records then go through scalar loads
+    const int per = uniform(int(SPLIT ? (k + W - 1) / W : k));
+    const int i0 = SPLIT ? uniform(w) * per : 0;
+    const int n = uniform(int(i0 >= k ? 0 : (k - i0 < per ? k - i0 : per)));
+    float bufA[Lay::PF], bufB[Lay::PF];
+    auto add = [&](const float(&blk)[Lay::PF], ConstRec r) {
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            float acc = part[0][ch][lane];
+        for (int u = 0; u < NQ; ++u)
+            eval_pair<N, false>(blk, r, x[u], true, 0.0f, f[u][0], f[u][1], f[u][2]);
+    };
+    if (n > 0) {
+        ConstRec r = const_rec(rec) + int64_t(i0) * Lay::R;
+        ConstRec last = r + int64_t(n - 1) * Lay::R;
+        load_block<N>(bufA, r);
+        for (int left = n; left > 0; left -= 2) {
+            ConstRec r1 = left > 1 ? r + Lay::R : last;
+            ConstRec r2 = left > 2 ? r + 2 * Lay::R : last;
+            wait_scalar_then(r1);
+            load_block<N>(bufB, r1);
+            add(bufA, r);
+            if (left == 1) break;
+            wait_scalar_then(r2);
+            load_block<N>(bufA, r2);
+            add(bufB, r1);
+            r = r2;
+        }
+    }
+    if constexpr (SPLIT) {
+        __shared__ float part[W][3][kQ];
 #pragma unroll
-            for (int v = 1; v < kSplit; ++v) acc += part[v][ch][lane];
-            out[p * 3 + ch] = acc;
+        for (int u = 0; u < NQ; ++u)
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) part[w][ch][u * kWave + lane] = f[u][ch];
+        __syncthreads();
+        // consecutive threads on consecutive outputs
+        for (int e = int(threadIdx.x); e < 3 * kQ; e += W * kWave) {
+            const int s = e / 3, ch = e - 3 * s;
+            if (p0 + s >= q) break;
+            float acc = part[0][ch][s];
+#pragma unroll
+            for (int v = 1; v < W; ++v) acc += part[v][ch][s];
+            out[p0 * 3 + e] = acc;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            const int64_t p = p0 + u * kWave + lane;
+            if (p >= q) break;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) out[p * 3 + ch] = f[u][ch];
         }
     }
 }
@@ -279,18 +291,19 @@ template <int N>
 hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q, float *out,
                    hipStream_t s)
 {
-    // one query per lane while that gives every SIMD several waves;
-    // smaller batches split the Gaussians over the waves of a workgroup
-    if (q >= (int64_t(1) << 18) || mix->k < 4 * kSplit) {
-        const unsigned blocks = unsigned((q + kEvalThreads - 1) / kEvalThreads);
-        k_eval_dense<N><<<blocks, kEvalThreads, 0, s>>>(mix->k, q, mix->rec.as<float>(), queries,
-                                                        out);
-    } else {
-        const unsigned blocks = unsigned((q + kWave - 1) / kWave);
-        k_eval_dense_split<N><<<blocks, kEvalThreads, 0, s>>>(mix->k, q, mix->rec.as<float>(),
-                                                              queries, out);
-    }
-    return hipGetLastError();
+    // Four queries a lane while that still gives every SIMD about four waves
+    // (the Gaussians split over 4, then 16 waves as the batch shrinks), two
+    // and one below that.
+    auto go = [&](auto kern, int per_block, int waves) {
+        kern<<<unsigned((q + per_block - 1) / per_block), waves * kWave, 0, s>>>(
+            mix->k, q, mix->rec.as<float>(), queries, out);
+        return hipGetLastError();
+    };
+    if (q >= (int64_t(1) << 20)) return go(k_eval_dense<N, 4, 4, false>, 16 * kWave, 4);
+    if (q >= (int64_t(1) << 18)) return go(k_eval_dense<N, 4, 4, true>, 4 * kWave, 4);
+    if (q >= (int64_t(1) << 16)) return go(k_eval_dense<N, 4, 16, true>, 4 * kWave, 16);
+    if (q >= (int64_t(1) << 15)) return go(k_eval_dense<N, 2, 16, true>, 2 * kWave, 16);
+    return go(k_eval_dense<N, 1, 16, true>, kWave, 16);
 }
 
 template <int N>

@@ -23,10 +23,17 @@ template <int N> struct RecLayout {
     static constexpr int K2 = N < 6 ? N : 6;
 };
 
+// A record as constant memory: a wave-uniform address then always takes a
+// scalar load, also inside a loop whose waits the compiler takes for stores.
+typedef const __attribute__((address_space(4))) float *ConstRec;
+__device__ __forceinline__ ConstRec const_rec(const float *r)
+{
+    return reinterpret_cast<ConstRec>(reinterpret_cast<uintptr_t>(r));
+}
+
 // Record field e: from the prefetched block when e < PF, else from memory.
-template <int N, int E>
-__device__ __forceinline__ float field(const float (&blk)[RecLayout<N>::PF],
-                                       const float *__restrict__ r)
+template <int N, int E, class P>
+__device__ __forceinline__ float field(const float (&blk)[RecLayout<N>::PF], P r)
 {
     if constexpr (E < RecLayout<N>::PF)
         return blk[E];
@@ -35,10 +42,10 @@ __device__ __forceinline__ float field(const float (&blk)[RecLayout<N>::PF],
 }
 
 // Rows [R0, R1) of y = S'(x - m), accumulated into msq; d holds x - m.
-template <int N, int R0, int R1>
-__device__ __forceinline__ void rows(const float (&blk)[RecLayout<N>::PF],
-                                     const float *__restrict__ r, const float (&x)[N],
-                                     float (&d)[N], float (&y)[N], float &msq)
+template <int N, int R0, int R1, class P>
+__device__ __forceinline__ void rows(const float (&blk)[RecLayout<N>::PF], P r,
+                                     const float (&x)[N], float (&d)[N], float (&y)[N],
+                                     float &msq)
 {
     if constexpr (R0 < R1) {
         d[R0] = x[R0] - field<N, R0>(blk, r);
@@ -58,11 +65,10 @@ __device__ __forceinline__ void rows(const float (&blk)[RecLayout<N>::PF],
 // Returns whether the wave kept the pair (the same for every lane).  With
 // COUNT, st[0..2] count the pairs that passed the first and second checks
 // and were kept (wave-uniform counters).
-template <int N, bool SKIP, bool ACC = true, bool COUNT = false>
-__device__ __forceinline__ bool eval_pair(const float (&blk)[RecLayout<N>::PF],
-                                          const float *__restrict__ r, const float (&x)[N],
-                                          bool valid, float skip, float &f0, float &f1,
-                                          float &f2, uint32_t *st = nullptr)
+template <int N, bool SKIP, bool ACC = true, bool COUNT = false, class P = const float *>
+__device__ __forceinline__ bool eval_pair(const float (&blk)[RecLayout<N>::PF], P r,
+                                          const float (&x)[N], bool valid, float skip, float &f0,
+                                          float &f1, float &f2, uint32_t *st = nullptr)
 {
     using Lay = RecLayout<N>;
     float d[N], y[N];
@@ -91,9 +97,20 @@ __device__ __forceinline__ bool eval_pair(const float (&blk)[RecLayout<N>::PF],
     return true;
 }
 
-template <int N>
-__device__ __forceinline__ void load_block(float (&blk)[RecLayout<N>::PF],
-                                           const float *__restrict__ r)
+// Waits for every scalar load in flight; loads through `next` stay behind the
+// wait (the pointer is made anew after it), so that the wait never covers
+// them -- scalar loads complete out of order and can only be waited for all
+// together.
+__device__ __forceinline__ void wait_scalar_then(ConstRec &next)
+{
+    uintptr_t u = reinterpret_cast<uintptr_t>(next);
+    __builtin_amdgcn_s_waitcnt(kWaitScalar);
+    asm volatile("" : "+s"(u));
+    next = reinterpret_cast<ConstRec>(u);
+}
+
+template <int N, class P>
+__device__ __forceinline__ void load_block(float (&blk)[RecLayout<N>::PF], P r)
 {
 #pragma unroll
     for (int e = 0; e < RecLayout<N>::PF; ++e) blk[e] = r[e];
