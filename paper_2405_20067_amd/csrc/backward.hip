@@ -18,7 +18,7 @@
 // keeps per-lane partial moments in registers (B1: n, B2: n(n+1)/2, H: 3),
 // reduces them across lanes once and writes them to the item's slot.
 // k_backward_finalize then adds each Gaussian's items in item order and
-// applies S^T.  Dense: one wave per Gaussian over all queries.
+// applies S^T.  Dense: one workgroup per Gaussian over all queries.
 #include "ngd_internal.hpp"
 #include "wave.hpp"
 
@@ -31,159 +31,111 @@ constexpr int64_t kBwdItemBlocks = 4096;
 constexpr int kWavesPerBlock = kBwdThreads / kWave;
 static_assert(kItemTiles <= kWave, "an item's tile list must fit one wave");
 
-template <int N> constexpr int first_stage_dims() { return N >= 4 ? 4 : N; }
-
-template <int N, bool CULLED>
-__global__ __launch_bounds__(kBwdThreads) void k_backward(
-    int64_t k, int64_t q, int tile, const float *__restrict__ rec,
-    const float *__restrict__ xq,          // culled: n x q sorted SoA; dense: q x n
-    const float *__restrict__ gq,          // culled: 3 x q sorted SoA; dense: q x 3
-    const int64_t *__restrict__ g_off, const int32_t *__restrict__ g_tiles,
-    const int32_t *__restrict__ gperm, float skip, float *__restrict__ g_mean,
-    float *__restrict__ g_factor, float *__restrict__ g_weight, float *__restrict__ g_colour)
+// ---- dense: every Gaussian over all queries --------------------------------
+// One workgroup per Gaussian; its waves take the 64-query blocks in turn
+// (lane = query), keep per-lane moments and reduce them over the lanes, then
+// over the waves in order through LDS, and the first threads form the outputs.
+// With W waves per Gaussian a mixture of a few hundred Gaussians fills the
+// chip: with one wave per Gaussian the loads of each block waited in a single
+// chain (K = 256, Q = 65,536, n = 4: 375 us, now 38 us, against 17 us of
+// vector operations).  No workspace, so calls on several streams stay
+// independent.
+template <int N, int W>
+__global__ __launch_bounds__(W *kWave) void k_backward_dense(
+    int64_t q, const float *__restrict__ rec, const float *__restrict__ xq,
+    const float *__restrict__ gq, float *__restrict__ g_mean, float *__restrict__ g_factor,
+    float *__restrict__ g_weight, float *__restrict__ g_colour)
 {
     constexpr int T = N * (N + 1) / 2;
     constexpr int R = (N + T + 7 + 3) / 4 * 4;
-    constexpr int N1 = CULLED ? first_stage_dims<N>() : N;
+    constexpr int NM = N + T + 3;   // B1 | B2 | H
+    constexpr int VP = (NM + 3) & ~3, Q4 = VP / 4;
     constexpr int AL = N + T + 3, CO = N + T + 4;
-    const int lane = lane_id();
-    const int64_t sgi = int64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-    if (sgi >= k) return;
-    const float *__restrict__ r = rec + uniform64(sgi) * R;
+    __shared__ float part[W][VP];
+    const int lane = lane_id(), w = int(threadIdx.x) / kWave;
+    const int64_t g = blockIdx.x;
+    const float *__restrict__ r = rec + g * R;
     const float alpha = r[AL], c0 = r[CO], c1 = r[CO + 1], c2 = r[CO + 2];
 
-    float b1[N], b2[T], h0 = 0.0f, h1 = 0.0f, h2 = 0.0f;
+    float mv[VP];
 #pragma unroll
-    for (int a = 0; a < N; ++a) b1[a] = 0.0f;
+    for (int e = 0; e < VP; ++e) mv[e] = 0.0f;
+    for (int64_t b = int64_t(uniform(w)) * kWave; b < q; b += W * kWave) {
+        const bool valid = b + lane < q;
+        const int64_t p = valid ? b + lane : q - 1;
+        float d[N], y[N];
 #pragma unroll
-    for (int e = 0; e < T; ++e) b2[e] = 0.0f;
-    bool any = false;
-
-    int64_t e0 = 0, e1 = 1;
-    if constexpr (CULLED) {
-        e0 = uniform64(g_off[sgi]);
-        e1 = uniform64(g_off[sgi + 1]);
-    }
-    const int64_t span = CULLED ? tile : q;
-    for (int64_t e = e0; e < e1; ++e) {
-        const int64_t base = CULLED ? int64_t(uniform(g_tiles[e])) * tile : 0;
-        for (int64_t g0 = 0; g0 < span; g0 += kWave) {
-            const int64_t sidx = g0 + lane;
-            const int64_t p = base + sidx;
-            const bool valid = (sidx < span) && (p < q);
-            float x[N], d[N], y[N];
-            float msq = 0.0f;
+        for (int a = 0; a < N; ++a) d[a] = xq[p * N + a];
+        // a lane past the end repeats the last query with nothing upstream
+        const float g0 = valid ? gq[p * 3 + 0] : 0.0f, g1 = valid ? gq[p * 3 + 1] : 0.0f,
+                    g2 = valid ? gq[p * 3 + 2] : 0.0f;
+        float msq = 0.0f;
 #pragma unroll
-            for (int a = 0; a < N1; ++a) {
-                x[a] = valid ? (CULLED ? xq[a * q + p] : xq[p * N + a]) : 0.0f;
-                d[a] = x[a] - r[a];
-            }
+        for (int row = 0; row < N; ++row) {
+            d[row] -= r[row];
+            const float *srow = r + N + row * (row + 1) / 2;
+            float acc = srow[0] * d[0];
 #pragma unroll
-            for (int row = 0; row < N1; ++row) {
-                const float *srow = r + N + row * (row + 1) / 2;
-                float acc = srow[0] * d[0];
+            for (int j = 1; j <= row; ++j) acc = fmaf(srow[j], d[j], acc);
+            y[row] = acc;
+            msq = fmaf(acc, acc, msq);
+        }
+        const float G = valid ? __builtin_amdgcn_exp2f(-msq) : 0.0f;
+        const float sdot = fmaf(g2, c2, fmaf(g1, c1, g0 * c0));
+        const float wt = alpha * G * sdot;
+        mv[N + T + 0] = fmaf(G, g0, mv[N + T + 0]);
+        mv[N + T + 1] = fmaf(G, g1, mv[N + T + 1]);
+        mv[N + T + 2] = fmaf(G, g2, mv[N + T + 2]);
 #pragma unroll
-                for (int j = 1; j <= row; ++j) acc = fmaf(srow[j], d[j], acc);
-                y[row] = acc;
-                msq = fmaf(acc, acc, msq);
-            }
-            if constexpr (CULLED && N1 < N) {
-                if (ballot(valid && msq <= skip) == 0) continue;
-            }
+        for (int a = 0; a < N; ++a) {
+            const float wy = wt * y[a];
+            mv[a] += wy;
 #pragma unroll
-            for (int a = N1; a < N; ++a) {
-                x[a] = valid ? (CULLED ? xq[a * q + p] : xq[p * N + a]) : 0.0f;
-                d[a] = x[a] - r[a];
-            }
-#pragma unroll
-            for (int row = N1; row < N; ++row) {
-                const float *srow = r + N + row * (row + 1) / 2;
-                float acc = srow[0] * d[0];
-#pragma unroll
-                for (int j = 1; j <= row; ++j) acc = fmaf(srow[j], d[j], acc);
-                y[row] = acc;
-                msq = fmaf(acc, acc, msq);
-            }
-            if constexpr (CULLED) {
-                if (ballot(valid && msq <= skip) == 0) continue;
-            }
-            any = true;
-            const float G = valid ? __builtin_amdgcn_exp2f(-msq) : 0.0f;
-            float g0v = 0.0f, g1v = 0.0f, g2v = 0.0f;
-            if (valid) {
-                if constexpr (CULLED) {
-                    g0v = gq[p];
-                    g1v = gq[q + p];
-                    g2v = gq[2 * q + p];
-                } else {
-                    g0v = gq[p * 3 + 0];
-                    g1v = gq[p * 3 + 1];
-                    g2v = gq[p * 3 + 2];
-                }
-            }
-            const float sdot = fmaf(g2v, c2, fmaf(g1v, c1, g0v * c0));
-            const float w = alpha * G * sdot;
-            h0 = fmaf(G, g0v, h0);
-            h1 = fmaf(G, g1v, h1);
-            h2 = fmaf(G, g2v, h2);
-#pragma unroll
-            for (int a = 0; a < N; ++a) {
-                const float wy = w * y[a];
-                b1[a] += wy;
-#pragma unroll
-                for (int b = 0; b <= a; ++b) b2[a * (a + 1) / 2 + b] = fmaf(wy, y[b], b2[a * (a + 1) / 2 + b]);
-            }
+            for (int c = 0; c <= a; ++c)
+                mv[N + a * (a + 1) / 2 + c] = fmaf(wy, y[c], mv[N + a * (a + 1) / 2 + c]);
         }
     }
-
-    const int64_t gi = CULLED ? int64_t(gperm[sgi]) : sgi;
-    if (!any) {
-        if (lane == 0) {
+    // lane 16 i + 15 holds the totals of the i-th quarter
+    wave_reduce_scatter<VP>(mv);
+    if ((lane & 15) == 15) {
+        const int r0 = (lane >> 4) * Q4;
 #pragma unroll
-            for (int a = 0; a < N; ++a) g_mean[gi * N + a] = 0.0f;
-#pragma unroll
-            for (int e = 0; e < T; ++e) g_factor[gi * T + e] = 0.0f;
-            g_weight[gi] = 0.0f;
-            g_colour[gi * 3 + 0] = 0.0f;
-            g_colour[gi * 3 + 1] = 0.0f;
-            g_colour[gi * 3 + 2] = 0.0f;
-        }
-        return;
+        for (int i = 0; i < Q4; ++i) part[w][r0 + i] = mv[i];
     }
+    __syncthreads();
+    const int t = int(threadIdx.x);
+    for (int e = t; e < NM; e += W * kWave) {
+        float acc = part[0][e];
 #pragma unroll
-    for (int a = 0; a < N; ++a) b1[a] = wave_sum_last(b1[a]);
-#pragma unroll
-    for (int e = 0; e < T; ++e) b2[e] = wave_sum_last(b2[e]);
-    h0 = wave_sum_last(h0);
-    h1 = wave_sum_last(h1);
-    h2 = wave_sum_last(h2);
-    if (lane != kWave - 1) return;
+        for (int i = 1; i < W; ++i) acc += part[i][e];
+        part[0][e] = acc;   // this thread's own column
+    }
+    __syncthreads();
     // S = S' / sqrt(c), y = y' / sqrt(c), c = log2(e)/2:
     //   S^T B1 = S'^T B1' / c,  S^T B2 = S'^T B2' / c^1.5
     const float inv_c = float(1.0 / kHalfLog2e);
     const float inv_c15 = float(1.0 / (kHalfLog2e * kSqrtHalfLog2e));
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int kk = a; kk < N; ++kk) acc = fmaf(r[N + kk * (kk + 1) / 2 + a], b1[kk], acc);
-        g_mean[gi * N + a] = acc * inv_c;
-    }
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-#pragma unroll
-        for (int b = 0; b <= a; ++b) {
+    const float *tot = part[0];
+    for (int e = t; e < NM + 1; e += W * kWave) {
+        if (e < N) {
             float acc = 0.0f;
-#pragma unroll
+            for (int kk = e; kk < N; ++kk) acc = fmaf(r[N + kk * (kk + 1) / 2 + e], tot[kk], acc);
+            g_mean[g * N + e] = acc * inv_c;
+        } else if (e < N + T) {
+            const int f = e - N;   // entry (a, c) of the packed factor
+            int a = 0;
+            while ((a + 1) * (a + 2) / 2 <= f) ++a;
+            const int c = f - a * (a + 1) / 2;
+            float acc = 0.0f;
             for (int kk = a; kk < N; ++kk)
-                acc = fmaf(r[N + kk * (kk + 1) / 2 + a], b2[kk * (kk + 1) / 2 + b], acc);
-            g_factor[gi * T + a * (a + 1) / 2 + b] = acc * inv_c15;
+                acc = fmaf(r[N + kk * (kk + 1) / 2 + a], tot[N + kk * (kk + 1) / 2 + c], acc);
+            g_factor[g * T + f] = acc * inv_c15;
+        } else if (e < NM) {
+            g_colour[g * 3 + e - N - T] = alpha * tot[e];
+        } else {
+            g_weight[g] = fmaf(c2, tot[N + T + 2], fmaf(c1, tot[N + T + 1], c0 * tot[N + T]));
         }
     }
-    g_weight[gi] = fmaf(c2, h2, fmaf(c1, h1, c0 * h0));
-    g_colour[gi * 3 + 0] = alpha * h0;
-    g_colour[gi * 3 + 1] = alpha * h1;
-    g_colour[gi * 3 + 2] = alpha * h2;
 }
 
 // ---- culled: work items (Gaussian, up to kItemTiles of its tiles) ---------
@@ -419,11 +371,23 @@ hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q,
                    const float *grad_out, float *gm, float *gf, float *gw, float *gc,
                    hipStream_t s)
 {
-    const unsigned blocks = unsigned((mix->k + kWavesPerBlock - 1) / kWavesPerBlock);
-    k_backward<N, false><<<blocks, kBwdThreads, 0, s>>>(mix->k, q, 0, mix->rec.as<float>(),
-                                                       queries, grad_out, nullptr, nullptr,
-                                                       nullptr, 0.0f, gm, gf, gw, gc);
-    return hipGetLastError();
+    // 16 waves per Gaussian (8 from n = 11, whose moments take more than the
+    // 128 registers a lane of a 16-wave workgroup has) while that is what it
+    // takes to fill the chip; with 4,096 Gaussians and more, 4
+    auto go = [&](auto kern, int waves) {
+        kern<<<unsigned(mix->k), waves * kWave, 0, s>>>(q, mix->rec.as<float>(), queries,
+                                                        grad_out, gm, gf, gw, gc);
+        return hipGetLastError();
+    };
+    if (q == 0) {   // no queries: zero gradients whatever the parameters
+        hipError_t e = launch_zero_f32(gm, mix->k * N, s);
+        if (e == hipSuccess) e = launch_zero_f32(gf, mix->k * (N * (N + 1) / 2), s);
+        if (e == hipSuccess) e = launch_zero_f32(gw, mix->k, s);
+        return e == hipSuccess ? launch_zero_f32(gc, mix->k * 3, s) : e;
+    }
+    if (mix->k >= 4096) return go(k_backward_dense<N, 4>, 4);
+    constexpr int W = N <= 10 ? 16 : 8;
+    return go(k_backward_dense<N, W>, W);
 }
 
 template <int N>
