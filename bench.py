@@ -309,19 +309,20 @@ def forward_roofline(w, m, cull, dev, prec, name, t, cand_pairs):
     """Roofline of one path's culled forward kernel.  `t` is its launch time
     (median over the timed steps, HIP events on the library's stream).
 
-    FP32 (ALU bound): the float32 flops the kernel executes, counted by the
-    same kernel in a counting mode on the same cull (its staged checks skip
-    most of the candidate pairs' rows), against the non-packed FP32 peak.
-    BF16-MFMA (matrix-core bound): the algorithmic contraction, one
-    multiply-add per quadratic feature for every (query, candidate) pair the
-    cull kept, against the dense BF16 peak; what the kernel executes (three
-    split products, padded k-steps) is reported beside it."""
+    Both precisions run the same kernels: the matrix-core filter, then the
+    float32 evaluation of the pairs it does not skip.  `fp32` prices the
+    second (ALU bound): the float32 flops executed, from the pair counts of
+    the same kernels in a counting mode on the same cull, against the
+    non-packed FP32 peak.  `bf16_mfma` prices the first (matrix-core bound):
+    the algorithmic contraction, one multiply-add per quadratic feature for
+    every (query, candidate) pair the cull kept, against the dense 16-bit
+    peak; the padded k-steps it executes are reported beside it.  `t` covers
+    both kernels either way."""
     from paper_2405_20067_amd import ngd
     cnt = ngd.eval_stats(m, cull, dev["x"], precision=prec)
     f1, f2, f3, f4 = stage_flops(w.n)
-    valu = 64 * (f1 * cnt["filtered"] + f2 * cnt["pass1"] + f3 * cnt["pass2"]
-                 + f4 * cnt["kept"])
-    src = (KERNEL_SRC,) if name == "fp32" else (MFMA_SRC, KERNEL_SRC)
+    valu = 64 * ((f1 + f2 + f3) * cnt["filtered"] + f4 * cnt["kept"])
+    src = (MFMA_SRC, KERNEL_SRC)
     traffic = None
     tf = TRAFFIC_FILES[name]
     if os.path.exists(tf):
@@ -330,7 +331,8 @@ def forward_roofline(w, m, cull, dev, prec, name, t, cand_pairs):
             traffic = tr.get("hbm_bytes_per_launch")
     if name == "fp32":
         a = valu / t / 1e12
-        return dict(bound="alu", kernel="forward: k_eval_items + k_eval_reduce (ngd_eval)",
+        return dict(bound="alu", kernel="forward: k_filter_items + k_eval_items + "
+                                        "k_eval_reduce (ngd_eval)",
                     achieved=a, peak=FP32_VALU_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=a / FP32_VALU_PEAK_TFLOPS, traffic=traffic,
                     units=dict(group_candidate_pairs=cnt,
@@ -340,21 +342,19 @@ def forward_roofline(w, m, cull, dev, prec, name, t, cand_pairs):
                                candidate_pairs=cand_pairs,
                                launch_ms=t * 1e3))
     nf = 1 + w.n + w.n * (w.n + 1) // 2
-    ks = 1 + (w.n * (w.n + 1) // 2 + 15) // 16
+    ks = (8 * ((w.n * (w.n + 1) // 2 + 7) // 8) + 2 + w.n + 15) // 16
     alg = cand_pairs * mfma_pair_flops(w.n)
     a = alg / t / 1e12
-    return dict(bound="mfma", kernel="forward: k_mfma_filter (ngd_eval, NGD_BF16_MFMA; "
-                                     "its once-per-build records timed apart as "
-                                     "eval_prepare)",
+    return dict(bound="mfma", kernel="forward: k_filter_items + k_eval_items + "
+                                     "k_eval_reduce (ngd_eval, NGD_BF16_MFMA)",
                 achieved=a, peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
                 frac=a / BF16_MFMA_PEAK_TFLOPS, traffic=traffic,
                 units=dict(candidate_pairs=cand_pairs, features=nf,
                            flops_per_pair=mfma_pair_flops(w.n),
                            flops_per_launch=alg, launch_ms=t * 1e3,
                            group_candidate_pairs=cnt,
-                           executed_split_flops=cnt["examined"] * 64 * nf * 2 * 3,
-                           executed_padded_flops=cnt["examined"] * 64 * ks * 16 * 2 * 3,
-                           executed_split_tflops=cnt["examined"] * 64 * nf * 6 / t / 1e12,
+                           executed_padded_flops=cnt["examined"] * 64 * ks * 16 * 2,
+                           executed_padded_tflops=cnt["examined"] * 64 * ks * 32 / t / 1e12,
                            fp32_survivor_flops=valu,
                            fp32_survivor_tflops=valu / t / 1e12))
 
@@ -379,9 +379,8 @@ def run_workload(name: str, args, precisions, with_dense: bool, steps: int, warm
     f = torch.empty((w.q, 3), device="cuda")
     loss = torch.empty((1,), device="cuda")
     gout = torch.empty((w.q, 3), device="cuda")
-    # eval_prepare: what the forward derives once per cull build (the BF16
-    # path's coefficient records; nothing for FP32), timed apart so that
-    # `forward` is the forward kernel alone
+    # eval_prepare: what a forward derives once per cull build (the build
+    # itself forms it all, so nothing is left), timed apart
     stages = ["update", "cull_build", "eval_prepare", "forward", "loss", "backward"]
 
     def step(prec, ev=None):
@@ -708,8 +707,9 @@ def summarize_traffic(fetch_csv, write_csv, out_prefix):
              if r["Kernel_Name"].startswith(copy) and r["Counter_Name"] == "WRITE_SIZE")
     nbytes = 268435456
     ffac, wfac = nbytes / 1024 / cf, nbytes / 1024 / cw
-    paths = dict(fp32=(["k_eval_items<10, true, false>", "k_eval_reduce"], (KERNEL_SRC,)),
-                 bf16_mfma=(["k_mfma_filter<10, true, false>"], (MFMA_SRC, KERNEL_SRC)))
+    kernels = ["k_filter_items<10>", "k_eval_items<10, true, false>", "k_eval_reduce"]
+    paths = dict(fp32=(kernels, (MFMA_SRC, KERNEL_SRC)),
+                 bf16_mfma=(kernels, (MFMA_SRC, KERNEL_SRC)))
     lines = ["| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB |", "|---|---|---|---|"]
     for k in sorted(fe, key=lambda k: -fe[k][1]):
         if k in wr and fe[k][1] + wr[k][1] > 1024:

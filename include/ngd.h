@@ -224,21 +224,17 @@ int ngd_cull_destroy(ngd_cull *cull);
  *            certified below tau * 2^-20 are skipped without evaluation.
  *   queries  device, q x n
  *   out      device, q x 3, in the caller's query order
- *   precision NGD_FP32, or NGD_BF16_MFMA (needs a cull; its first use on a
- *            cull build derives the per-Gaussian coefficients, k x 260 bytes
- *            at n = 10, in library memory)
+ *   precision NGD_FP32, or NGD_BF16_MFMA (needs a cull).  With a cull both
+ *            skip pairs by the same certified matrix-core filter and evaluate
+ *            the others in float32
  * Does not synchronise. */
 int ngd_eval(const ngd_mixture *mix, const ngd_cull *cull, const float *queries,
              int64_t q, int precision, float *out, void *stream);
 
 /* Builds, ahead of ngd_eval, what a forward of `precision` derives once per
- * cull build: for NGD_BF16_MFMA the per-entry centred terms of the
- * matrix-core forward of Eq. 1-2 expanded (and the per-Gaussian quadratic
- * coefficients, which ngd_cull_build itself launches beside its own work when
- * it orders the Gaussians on its second stream; the tiles' centres come with
- * the cull's tile bounds); nothing for NGD_FP32.  ngd_eval builds them itself
- * when they are missing, so this call only moves that work out of the first
- * forward (for instance to time the forward kernel alone).
+ * cull build.  ngd_cull_build itself forms all that the forward reads (the
+ * filter's per-Gaussian coefficients, the tiles' centres), so this call checks
+ * its arguments and has nothing left to do.
  *   mix, cull, queries, q as for ngd_eval (a cull is required).
  * Returns NGD_E_INVAL for a NULL handle or an unknown precision,
  * NGD_E_STALE for a cull of another mixture version or queries.
@@ -250,12 +246,9 @@ int ngd_eval_prepare(const ngd_mixture *mix, const ngd_cull *cull, const float *
  * Runs the forward kernel of `precision` on the same cull in a counting mode
  * (no colours written) and returns in counts (host, 5 x int64): the
  * (64-query group, candidate) pairs examined, those not skipped by the
- * first filter (the matrix-core one with NGD_BF16_MFMA; with NGD_FP32 the
- * test of the group's bounding box against each Gaussian's per-coordinate
- * box of half-widths sqrt(2 ln2 skip V_ii), skip the forward's threshold),
- * those that then passed the first and the second Mahalanobis-bound check
- * (marginals over the first 3 and 6 coordinates), and those kept (evaluated
- * with exp and accumulated).
+ * filter (these are evaluated in float32), those of them below the skip
+ * threshold after the marginals over the first 3 and 6 coordinates, and those
+ * kept (below it in the end: accumulated).
  * `cull` and `queries`/q as for ngd_eval. */
 int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *queries,
                    int64_t q, int precision, int64_t *counts, void *stream);

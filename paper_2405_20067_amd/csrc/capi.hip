@@ -341,14 +341,14 @@ static void cull_release(ngd_cull *c)
                       &c->stats,   &c->item_cnt, &c->item_off,   &c->item_tile, &c->fpart,
                       &c->gitem_cnt, &c->gitem_off, &c->gitem_g, &c->gpart,   &c->gflag,
                       &c->g_ent,   &c->ent_tile, &c->act,       &c->eflag,   &c->eoff,
-                      &c->a_cnt,   &c->a_off,    &c->gbox_u,     &c->gbox,
+                      &c->a_cnt,   &c->a_off,
                       &c->kd_q.node_tab, &c->kd_q.slice_tab, &c->kd_g.node_tab,
                       &c->kd_g.slice_tab, &c->kd_work.idx[0], &c->kd_work.idx[1],
                       &c->kd_work.val[0], &c->kd_work.val[1], &c->kd_work.ext[0],
                       &c->kd_work.ext[1], &c->kd_work.hist, &c->kd_work.cnt,
                       &c->kd_work.dim,
-                      &c->kd_work.prefix, &c->kd_work.rank, &c->mrec, &c->mrow, &c->tcen,
-                      &c->eb0, &c->ebnd};
+                      &c->kd_work.prefix, &c->kd_work.rank, &c->mrec, &c->tcen,
+                      &c->fmask};
     for (DevBuf *b : bufs) b->release();
     KdWork *works[] = {&c->kd_work_g};
     for (KdWork *w : works) {
@@ -436,7 +436,6 @@ int ngd_cull_build(const ngd_mixture *mix, const float *queries, int64_t q,
          hipEventCreateWithFlags(&c->ev_sizes, hipEventDisableTiming) != hipSuccess))
         return bail(fail(NGD_E_NOMEM, "ngd_cull_build: device workspace allocation failed"));
     hipStream_t s = S(stream);
-    c->coef_next = false;
     hipError_t e = hipMemcpyAsync(c->proj.p, proj, sizeof(float) * p->n_proj * mix->n,
                                   hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = launch_cull_build_front(c, mix, queries, s);
@@ -470,8 +469,6 @@ int ngd_cull_build(const ngd_mixture *mix, const float *queries, int64_t q,
     if (!cull_reserve_lists(c))
         return bail(fail(NGD_E_NOMEM, "ngd_cull_build: candidate list allocation failed"));
     c->act_version = -1;
-    ++c->build_seq;
-    if (c->coef_next) c->coef_seq = c->build_seq;
     c->transposed = false;
     if (!fits) {
         e = launch_cull_build_lists(c, s, c->total, c->nitems);
@@ -544,21 +541,6 @@ static int check_cull(const char *fn, const ngd_mixture *mix, const ngd_cull *c,
     return NGD_OK;
 }
 
-// Coefficient records of the matrix-core forward: grown with the cull.
-static int reserve_mfma(const char *fn, ngd_cull *c)
-{
-    const size_t kk = size_t(c->k > 0 ? c->k : 1);
-    const size_t tt = size_t(c->ntiles > 0 ? c->ntiles : 1);
-    const size_t ee = size_t(c->total > 0 ? c->total : 1);
-    if (!c->mrec.ensure(kk * mfma_rec_bytes(c->n)) || !c->mrow.ensure(kk * sizeof(float)) ||
-        !c->tcen.ensure(tt * c->n * sizeof(float)) || !c->eb0.ensure(ee * 4 * 16) ||
-        !c->ebnd.ensure(ee * 16)) {
-        c->mrec_seq = -1;
-        return fail(NGD_E_NOMEM, "%s: coefficient records: allocation failed", fn);
-    }
-    return NGD_OK;
-}
-
 int ngd_eval(const ngd_mixture *mix, const ngd_cull *cull, const float *queries, int64_t q,
              int precision, float *out, void *stream)
 {
@@ -582,15 +564,7 @@ int ngd_eval(const ngd_mixture *mix, const ngd_cull *cull, const float *queries,
     if (mix->k == 0 || (cull && cull->nitems == 0)) {
         e = launch_zero_f32(out, 3 * q, S(stream));
     } else if (cull) {
-        if (precision == NGD_BF16_MFMA) {
-            // the coefficient records are a cache of the cull (grown on use)
-            ngd_cull *mc = const_cast<ngd_cull *>(cull);
-            const int rc = reserve_mfma("ngd_eval", mc);
-            if (rc) return rc;
-            e = launch_eval_mfma(mix, mc, out, nullptr, S(stream));
-        } else {
-            e = launch_eval_culled(mix, cull, out, S(stream));
-        }
+        e = launch_eval_culled(mix, cull, out, nullptr, S(stream));
         if (e == hipSuccess) cull->act_version = mix->version;
     } else {
         e = launch_eval_dense(mix, queries, q, out, S(stream));
@@ -608,13 +582,8 @@ int ngd_eval_prepare(const ngd_mixture *mix, const ngd_cull *cull, const float *
     if (mix->version == 0) return fail(NGD_E_STALE, "ngd_eval_prepare: mixture has no parameters yet");
     const int rc = check_cull("ngd_eval_prepare", mix, cull, queries, q);
     if (rc) return rc;
-    if (precision == NGD_FP32 || q == 0 || mix->k == 0 || cull->nitems == 0) return NGD_OK;
-    ngd_cull *mc = const_cast<ngd_cull *>(cull);
-    const int rr = reserve_mfma("ngd_eval_prepare", mc);
-    if (rr) return rr;
-    const hipError_t e = launch_mfma_prepare(mix, mc, S(stream));
-    if (e != hipSuccess) return hip_fail(e, "ngd_eval_prepare");
-    return NGD_OK;
+    (void)stream;
+    return NGD_OK;   // the build has formed everything the forward reads
 }
 
 int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *queries,
@@ -638,19 +607,10 @@ int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *qu
     std::lock_guard<std::mutex> lk(mu);
     if (!buf[dev].ensure(5 * sizeof(unsigned long long)))
         return fail(NGD_E_NOMEM, "ngd_eval_stats: workspace allocation failed");
-    if (precision == NGD_BF16_MFMA) {
-        const int rm = reserve_mfma("ngd_eval_stats", const_cast<ngd_cull *>(cull));
-        if (rm) return rm;
-    }
     unsigned long long host[5] = {0, 0, 0, 0, 0};
     e = hipMemcpyAsync(buf[dev].p, host, sizeof(host), hipMemcpyHostToDevice, S(stream));
-    if (e == hipSuccess) {
-        if (precision == NGD_BF16_MFMA)
-            e = launch_eval_mfma(mix, const_cast<ngd_cull *>(cull), nullptr,
-                                 buf[dev].as<unsigned long long>(), S(stream));
-        else
-            e = launch_eval_stats(mix, cull, buf[dev].as<unsigned long long>(), S(stream));
-    }
+    if (e == hipSuccess)
+        e = launch_eval_culled(mix, cull, nullptr, buf[dev].as<unsigned long long>(), S(stream));
     if (e == hipSuccess)
         e = hipMemcpyAsync(host, buf[dev].p, sizeof(host), hipMemcpyDeviceToHost, S(stream));
     if (e == hipSuccess) e = hipStreamSynchronize(S(stream));
@@ -691,14 +651,7 @@ int ngd_eval_backward(const ngd_mixture *mix, const ngd_cull *cull, const float 
         // without a forward on this cull and mixture version, decide them now
         e = hipSuccess;
         if (cull->act_version != mix->version && cull->nitems > 0) {
-            if (precision == NGD_BF16_MFMA) {
-                const int rm = reserve_mfma("ngd_eval_backward", const_cast<ngd_cull *>(cull));
-                if (rm) return rm;
-                e = launch_eval_mfma(mix, const_cast<ngd_cull *>(cull), nullptr, nullptr,
-                                     S(stream));
-            } else {
-                e = launch_eval_culled(mix, cull, nullptr, S(stream));
-            }
+            e = launch_eval_culled(mix, cull, nullptr, nullptr, S(stream));
             if (e == hipSuccess) cull->act_version = mix->version;
         }
         if (e == hipSuccess)

@@ -35,47 +35,16 @@ namespace {
 constexpr int kThreads = 256;
 
 // Per Gaussian: its projected means and the interval test's squared
-// half-widths (Eq. 3-4), and the box of the forward's per-wave test.
-//
-// The box: M = (x - m)^T V^-1 (x - m) >= (x_i - m_i)^2 / V_ii for every
-// coordinate i (V = L L^T; Cauchy-Schwarz), so a query with
-// |x_i - m_i| > sr sqrt(V_ii) has M above sr^2 whatever its other
-// coordinates.  sr^2 is the forward's skip threshold in units of M, widened
-// by (1 + 2^-8)^2 for the rounding of its float32 distances.  V_ii =
-// |row i of L|^2 and [m - r, m + r] are formed in float64 and the box is
-// rounded outwards to float16 (a looser box is still a certificate, and
-// half the bytes of float32 for the forward's per-pair reads); box holds
-// lo_0..lo_{n-1}, hi_0..hi_{n-1} per Gaussian as float16 bits, padded to
-// BSH halves (a multiple of 16 bytes), in the caller's order (gathered with
-// the records).
-// float16 bits of the largest float16 <= v (DOWN) or smallest >= v (up).
-// The nearest float16 of float(v) is one of the two float16 values around v
-// (rounding is monotone and float16 values are floats), so one step of the
-// bit pattern towards the right side suffices; overflow goes to +-inf.
-template <bool DOWN> __device__ __forceinline__ uint16_t half_outward(double v)
-{
-    const _Float16 h = _Float16(float(v));
-    uint16_t u = __builtin_bit_cast(uint16_t, h);
-    const double hv = double(float(h));
-    if (DOWN ? hv > v : hv < v) {
-        if ((u & 0x7fffu) == 0) u = DOWN ? 0x8001u : 0x0001u;   // +-0: smallest subnormal
-        else if ((u & 0x8000u) != 0) u = DOWN ? u + 1 : u - 1;  // negative: magnitude
-        else u = DOWN ? u - 1 : u + 1;                          // positive: magnitude
-    }
-    return u;
-}
-
+// half-widths (Eq. 3-4).
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
                                                          const float *__restrict__ rec, int R,
                                                          const float *__restrict__ lfac,
                                                          const float *__restrict__ proj,
                                                          float kappa2, float *__restrict__ g_mr,
-                                                         float *__restrict__ g_thr, double sr,
-                                                         float *__restrict__ box)
+                                                         float *__restrict__ g_thr)
 {
     constexpr int T = N * (N + 1) / 2;
-    constexpr int BSH = (2 * N + 7) / 8 * 8;
     const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
     if (i >= k) return;
     float m[N];
@@ -84,25 +53,6 @@ __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
     for (int a = 0; a < N; ++a) m[a] = rec[i * R + a];
 #pragma unroll
     for (int e = 0; e < T; ++e) L[e] = lfac[i * T + e];
-    uint16_t bx[BSH];
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-        double v = 0.0;
-#pragma unroll
-        for (int b = 0; b <= a; ++b) v = fma(L[a * (a + 1) / 2 + b], L[a * (a + 1) / 2 + b], v);
-        const double r = sr * sqrt(v);
-        bx[a] = half_outward<true>(double(m[a]) - r);
-        bx[N + a] = half_outward<false>(double(m[a]) + r);
-    }
-#pragma unroll
-    for (int e = 2 * N; e < BSH; ++e) bx[e] = 0;
-    uint4 *bo = reinterpret_cast<uint4 *>(box) + i * (BSH / 8);
-#pragma unroll
-    for (int e = 0; e < BSH / 8; ++e) {
-        const uint16_t *h = bx + 8 * e;
-        bo[e] = make_uint4(h[0] | uint32_t(h[1]) << 16, h[2] | uint32_t(h[3]) << 16,
-                           h[4] | uint32_t(h[5]) << 16, h[6] | uint32_t(h[7]) << 16);
-    }
     for (int j = 0; j < P; ++j) {
         const float *r = proj + j * N;
         float acc = 0.0f;
@@ -396,34 +346,22 @@ __global__ __launch_bounds__(1024) void k_tile_bounds(int64_t q, int tile, int P
     }
 }
 
-// Records and forward boxes of the Gaussians in their tile order: a block
-// moves 64 records of R floats and 64 boxes of B 4-byte words as float4s,
-// consecutive threads on consecutive float4s.
-__global__ __launch_bounds__(kThreads) void k_rec_gather(int64_t k, int R, int B,
+// Records of the Gaussians in their tile order: a block moves 64 records of R
+// floats as float4s, consecutive threads on consecutive float4s.
+__global__ __launch_bounds__(kThreads) void k_rec_gather(int64_t k, int R,
                                                          const int32_t *__restrict__ gperm,
                                                          const float *__restrict__ rec,
-                                                         const float *__restrict__ box,
-                                                         float *__restrict__ grec,
-                                                         float *__restrict__ gbox)
+                                                         float *__restrict__ grec)
 {
-    const int R4 = R / 4, B4 = B / 4;
+    const int R4 = R / 4;
     const int64_t s0 = int64_t(blockIdx.x) * kWave;
     const int cnt = int(k - s0 < kWave ? k - s0 : kWave);
-    {
-        const float4 *src = reinterpret_cast<const float4 *>(rec);
-        float4 *dst = reinterpret_cast<float4 *>(grec) + s0 * R4;
-        for (int e = threadIdx.x; e < cnt * R4; e += kThreads) {
-            const int sl = e / R4;
-            const int f = e - sl * R4;
-            dst[e] = src[int64_t(gperm[s0 + sl]) * R4 + f];
-        }
-    }
-    const float4 *src = reinterpret_cast<const float4 *>(box);
-    float4 *dst = reinterpret_cast<float4 *>(gbox) + s0 * B4;
-    for (int e = threadIdx.x; e < cnt * B4; e += kThreads) {
-        const int sl = e / B4;
-        const int f = e - sl * B4;
-        dst[e] = src[int64_t(gperm[s0 + sl]) * B4 + f];
+    const float4 *src = reinterpret_cast<const float4 *>(rec);
+    float4 *dst = reinterpret_cast<float4 *>(grec) + s0 * R4;
+    for (int e = threadIdx.x; e < cnt * R4; e += kThreads) {
+        const int sl = e / R4;
+        const int f = e - sl * R4;
+        dst[e] = src[int64_t(gperm[s0 + sl]) * R4 + f];
     }
 }
 
@@ -853,14 +791,14 @@ hipError_t gauss_limits(ngd_cull *c, int64_t k, int P, bool g_sorted, hipStream_
     return hipGetLastError();
 }
 
-// The Gaussians in their tile order, what the forward needs: records and the
-// boxes of its per-wave test.
+// The Gaussians in their tile order, what the forward needs: records, and the
+// records of its filter.
 hipError_t gauss_records(ngd_cull *c, const ngd_mixture *mix, int64_t k, int R, hipStream_t s)
 {
-    k_rec_gather<<<nblk(k, kWave), kThreads, 0, s>>>(
-        k, R, box_stride(c->n), c->gperm.as<int32_t>(), mix->rec.as<float>(),
-        c->gbox_u.as<float>(), c->grec.as<float>(), c->gbox.as<float>());
-    return hipGetLastError();
+    k_rec_gather<<<nblk(k, kWave), kThreads, 0, s>>>(k, R, c->gperm.as<int32_t>(),
+                                                     mix->rec.as<float>(), c->grec.as<float>());
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_mfma_coef(c->n, c, s) : e;
 }
 
 template <int N>
@@ -883,13 +821,9 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
         forked = true;
     }
     if (k > 0) {
-        // the forward drops a pair at exp2(-M log2(e) / 2) < tau 2^-margin:
-        // its boxes' half-widths are sr sqrt(V_ii)
-        const double skip = -std::log2(double(c->params.tau)) + kSkipLog2Margin;
-        const double sr = std::sqrt(2.0 * std::log(2.0) * skip) * (1.0 + 0x1p-8);
         k_gauss_proj<N><<<nblk(k, kThreads), kThreads, 0, forked ? c->side : s>>>(
             k, P, mix->rec.as<float>(), R, mix->lfac.as<float>(), c->proj.as<float>(), c->kappa2,
-            c->g_mr.as<float>(), c->g_thr.as<float>(), sr, c->gbox_u.as<float>());
+            c->g_mr.as<float>(), c->g_thr.as<float>());
     }
     const int64_t nparts = (q + kThreads - 1) / kThreads;
     // With the k-d tiling of the queries the projection kernel's block
@@ -960,9 +894,8 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
         }
         // the Gaussians' side goes on while the queries' order finishes:
         // first the interval test's limits (the join point), then what only
-        // the forward reads -- the ordered records, the boxes and the
-        // matrix-core forward's per-Gaussian coefficients -- which the main
-        // stream waits for only at the end of the front half
+        // the forward reads -- the ordered records and its filter's -- which
+        // the main stream waits for only at the end of the front half
         if (forked && e == hipSuccess) {
             e = gauss_limits(c, k, P, true, c->side);
             gauss_done = true;
@@ -973,8 +906,6 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
             if (e == hipSuccess) {
                 side_open = true;
                 e = gauss_records(c, mix, k, R, c->side);
-                if (e == hipSuccess) e = launch_mfma_coef(N, c, c->side);
-                c->coef_next = e == hipSuccess;
             }
             if (e != hipSuccess) {
                 (void)hipEventRecord(c->ev_join, c->side);
@@ -1292,6 +1223,7 @@ bool cull_reserve_lists(ngd_cull *c)
     ok &= c->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>({kRadixMaxBins * nb, T, kk, tot})));
     ok &= c->item_tile.ensure(sizeof(int32_t) * size_t(c->nitems > 0 ? c->nitems : 1));
     ok &= c->fpart.ensure(sizeof(float) * 3 * size_t(c->nitems) * size_t(c->params.tile));
+    ok &= c->fmask.ensure(size_t(kItemCands / 8) * size_t(c->nitems) * size_t(groups));
     ok &= c->gitem_g.ensure(sizeof(int32_t) * size_t(c->gitems_cap > 0 ? c->gitems_cap : 1));
     ok &= c->gpart.ensure(sizeof(float) * nm * size_t(c->gitems_cap));
     ok &= c->gflag.ensure(sizeof(int32_t) * size_t(c->gitems_cap > 0 ? c->gitems_cap : 1));
@@ -1333,11 +1265,8 @@ bool cull_reserve_front(ngd_cull *c)
     if (c->params.tiling == 0) ok &= c->qr_s.ensure(sizeof(float) * P * qq);
     ok &= c->grec.ensure(sizeof(float) * kk * rec_stride(int(n)));
     ok &= c->mrec.ensure(kk * mfma_rec_bytes(int(n)));
-    ok &= c->mrow.ensure(sizeof(float) * kk);
     ok &= c->g_mr_s.ensure(sizeof(float) * P * kk);
     ok &= c->g_ub.ensure(sizeof(float) * P * kk);
-    ok &= c->gbox.ensure(sizeof(float) * kk * box_stride(int(n)));
-    ok &= c->gbox_u.ensure(sizeof(float) * kk * box_stride(int(n)));
     ok &= c->g_lb.ensure(sizeof(float) * P * kk);
     ok &= c->masks.ensure(sizeof(uint64_t) * std::max<int64_t>(c->nchunks, 1) *
                           std::max<int64_t>(c->tpad, 64));

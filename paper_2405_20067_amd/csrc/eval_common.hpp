@@ -1,6 +1,5 @@
-// Per-pair evaluation shared by the forward kernels (eval.hip,
-// eval_mfma.hip): record layout, the staged rows of y = S'(x - m) with the
-// certified skip checks, and the uniform record loads.
+// Shared by the forward kernels (eval.hip, eval_mfma.hip): record layout, the
+// rows of y = S'(x - m), and the uniform record loads.
 #pragma once
 
 #include <utility>
@@ -19,8 +18,6 @@ template <int N> struct RecLayout {
     static constexpr int R = (N + T + 7 + 3) / 4 * 4;
     static constexpr int AC = N + T;
     static constexpr int PF = R < 32 ? R : 32;   // floats loaded ahead
-    static constexpr int K1 = N < 3 ? N : 3;      // stage boundaries
-    static constexpr int K2 = N < 6 ? N : 6;
 };
 
 // A record as constant memory: a wave-uniform address then always takes a
@@ -60,41 +57,19 @@ __device__ __forceinline__ void rows(const float (&blk)[RecLayout<N>::PF], P r,
     }
 }
 
-// Accumulates one Gaussian into f for this lane's query x.  With SKIP,
-// returns early when the whole wave can drop the pair.
-// Returns whether the wave kept the pair (the same for every lane).  With
-// COUNT, st[0..2] count the pairs that passed the first and second checks
-// and were kept (wave-uniform counters).
-template <int N, bool SKIP, bool ACC = true, bool COUNT = false, class P = const float *>
-__device__ __forceinline__ bool eval_pair(const float (&blk)[RecLayout<N>::PF], P r,
-                                          const float (&x)[N], bool valid, float skip, float &f0,
-                                          float &f1, float &f2, uint32_t *st = nullptr)
+// Accumulates one Gaussian into f for this lane's query x.
+template <int N, class P>
+__device__ __forceinline__ void eval_pair(const float (&blk)[RecLayout<N>::PF], P r,
+                                          const float (&x)[N], float &f0, float &f1, float &f2)
 {
     using Lay = RecLayout<N>;
     float d[N], y[N];
     float msq = 0.0f;
-    rows<N, 0, Lay::K1>(blk, r, x, d, y, msq);
-    if constexpr (SKIP && Lay::K1 < N) {
-        if (ballot(valid && msq <= skip) == 0) return false;
-    }
-    if constexpr (COUNT) ++st[0];
-    rows<N, Lay::K1, Lay::K2>(blk, r, x, d, y, msq);
-    if constexpr (SKIP && Lay::K2 < N && Lay::K1 < Lay::K2) {
-        if (ballot(valid && msq <= skip) == 0) return false;
-    }
-    if constexpr (COUNT) ++st[1];
-    rows<N, Lay::K2, N>(blk, r, x, d, y, msq);
-    if constexpr (SKIP) {
-        if (ballot(valid && msq <= skip) == 0) return false;
-    }
-    if constexpr (COUNT) ++st[2];
-    if constexpr (ACC) {
-        const float g = __builtin_amdgcn_exp2f(-msq);
-        f0 = fmaf(g, field<N, Lay::AC + 0>(blk, r), f0);
-        f1 = fmaf(g, field<N, Lay::AC + 1>(blk, r), f1);
-        f2 = fmaf(g, field<N, Lay::AC + 2>(blk, r), f2);
-    }
-    return true;
+    rows<N, 0, N>(blk, r, x, d, y, msq);
+    const float g = __builtin_amdgcn_exp2f(-msq);
+    f0 = fmaf(g, field<N, Lay::AC + 0>(blk, r), f0);
+    f1 = fmaf(g, field<N, Lay::AC + 1>(blk, r), f1);
+    f2 = fmaf(g, field<N, Lay::AC + 2>(blk, r), f2);
 }
 
 // Waits for every scalar load in flight; loads through `next` stay behind the

@@ -1,48 +1,65 @@
-// Culled forward with a matrix-core filter: the Mahalanobis distance of
-// every (query, candidate) pair of a tile as one BF16 MFMA contraction
-// of quadratic query features against per-Gaussian quadratic coefficients.
+// Culled forward: the pairs of every (tile, candidate) filtered by a
+// matrix-core contraction, the survivors evaluated in float32.
 //
 // The quadratic form (Sec. 3.1, Eq. 1-2, in exp2 units, S' = sqrt(log2(e)/2)
-// L^-1, P' = S'^T S'):
-//   M'(x) = |S'(x - m)|^2
-//         = sum_{i<=j} C_ij x'_i x'_j + sum_i b'_i x'_i + a',
-//   x' = x - c, m' = m - c, C_ii = P'_ii, C_ij = 2 P'_ij (i < j),
-//   b' = -2 S'^T (S' m'),  a' = |S' m'|^2,
-// with c the centre of the tile's query box, so that the features stay
-// small and the expanded form does not cancel away its own accuracy.  The
-// feature vector (1, x', x'_i x'_j) has 1 + N + N(N+1)/2 entries (66 at
-// N = 10), laid out as one k-step of 16 for the constant and linear terms
-// and ceil(N(N+1)/2 / 16) k-steps for the quadratic ones.
+// L^-1, P = S'^T S'):
+//   M(x) = |S'(x - m)|^2
+//        = sum_{i<=j} C_ij x'_i x'_j + sum_i b_i x'_i + a,
+//   x' = x - c, m' = m - c, C_ii = P_ii, C_ij = 2 P_ij (i < j),
+//   b = -2 P m',  a = m'^T P m',
+// with c the centre of the tile's query box, so that the features stay small
+// and the expanded form does not cancel away its own accuracy.  Features and
+// coefficients are float16, one product each (v_mfma_f32_32x32x16_f16,
+// float32 accumulation); a is held as a sum of two float16 values, and so is
+// each b_i where the k-steps have room for it.
 //
-// Precision: features and coefficients are split into bf16 pairs
-// v = hi + lo + r, |r| <= 2^-16 |v|, and the contraction takes the three
-// products hi*hi + hi*lo + lo*hi with fp32 accumulation
-// (v_mfma_f32_32x32x16_bf16).  Its error against the exact form is below
-// 2^-13 * sum_k |F_k| |C_k| (a generous bound: split and omitted lo*lo terms
-// give about 3 * 2^-16, accumulation of at most 3 * 96 exact products about
-// 2^-16).  Over a 64-query group with h_i = max |x'_i| that sum is at most
-//   R' |h|^2 + |b'|_1 max h + |a'|,   R' = max row sum of |S'|^T |S'|,
-// and the fp32 rounding of b' adds at most 2^-18 R' |m'|_1 max h.  A
-// candidate is skipped for the whole group only when the smallest M' of the
-// group minus that bound exceeds the skip threshold log2(1/tau) + 20, the
-// same certificate the fp32 kernel applies (G < tau 2^-20).  Every
-// candidate that is not skipped is evaluated exactly as in the fp32 kernel
-// (the same staged code, lane = query), so the colours carry fp32 accuracy;
-// they differ from the fp32 kernel's only by pairs below the certificate.
+// The bound.  Per Gaussian, P is formed in float64 and rounded to float16
+// (P~, relative 2^-11), and b and a follow from P~ in float32, so the
+// contraction is that of (x - m)^T P~ (x - m) up to the rounding of the
+// features (2^-11 each) and of b (2^-11 when it has one value).  With
+// R = max row sum of |P| (at least the spectral norm of |P|), q = max |x'|
+// and h = max |x'|_inf over a 64-query group, the result is off by at most
+//   g (R ((|m'| + q)^2 + q^2) + k_b |b|_1 h),  g = 2^-11 * 1.25,
+// k_b = 2 (1 where b has two values); the quarter covers the float32
+// accumulation (96 terms: 2^-16.4), b's and a's own float32 rounding
+// (2^-19), and x' and m' (2^-23).  A candidate is skipped for a whole group
+// only when the group's smallest value minus that bound exceeds
+// log2(1/tau) + 20, i.e. only pairs with G < tau 2^-20; every other pair is
+// evaluated in float32 (lane = query) with the same threshold, so the colours
+// are the float32 ones whatever the filter's rounding.
 //
-// Once per cull build: the quadratic coefficients of every ordered Gaussian
-// (float64 P', then bf16 hi / lo) and for every candidate entry (tile,
-// Gaussian) the centred constant and linear coefficients and bound terms --
-// one thread per entry; the centre of every tile's query box comes with the
-// cull's tile bounds.
-// Filter kernel, one workgroup per tile (up to 256 queries in 4 waves):
-// per wave the query features as MFMA A fragments (rows = queries, 2 blocks
-// of 32); the entries' B fragments staged in LDS in double-buffered chunks of
-// 64 (the next chunk loaded straight into LDS while the current one is
-// computed); per block of
-// 32 entries 3 x KS x 2 MFMAs and the certified group test; the (entry,
-// group) flag records whether the pair may contribute.  The
-// float32 items kernel then evaluates only the flagged pairs (eval.hip).
+// Scales, powers of two all: s per Gaussian puts max |C| s in [2^7, 2^8);
+// sigma per tile puts max |x'| sigma in (8, 16], so the quadratic features
+// (sigma x'_i)(sigma x'_j) stay within 2^8; the linear features carry 2^11
+// and the constant one 2^15.  A column's accumulator is then K M with
+// K = sigma^2 s.  `a` saturates (a smaller constant only keeps more); a
+// Gaussian or tile outside the ranges (non-finite, b or K too large) gets an
+// infinite bound and is never skipped.
+//
+// One product instead of the three of a hi / lo split costs 2.4% of the pairs
+// passing instead of 1.5% (10-D, 2^20 queries), for a third of the matrix
+// work and half the coefficients.
+//
+// k_filter_items: one workgroup per item (a tile's queries, up to kItemCands of
+// its candidates), 4 waves of 64 queries.  256 candidates at a time: each wave
+// brings 64 records into LDS (16-byte global-to-LDS loads), lane = candidate
+// forms b, a and the bound terms beside them, then every wave contracts all
+// 256 against its queries, 32 at a time, and writes the survivors as one bit
+// per (candidate, group).  Nothing else per (tile, candidate) passes through
+// memory.
+// k_eval_items: the survivors in float32, a wave per (item, group), its queries
+// in registers, records through scalar loads.  A kernel of its own because it
+// needs the most waves in flight where the filter's LDS and registers leave
+// three per SIMD: with the evaluation as the filter's last phase the 10-D image
+// (K = 262,144, 800 x 800) took 6.15 ms, in two kernels 0.87 + 3.27.
+//
+// Measured against the forwards before it (a box test per group, or a bf16
+// hi / lo filter over precomputed per-entry terms): 10-D, K = 262,144,
+// Q = 2^20, 1.59 (float32) and 1.12 ms (bf16) -> 0.29 filter + 0.20 evaluation;
+// the image, 22% of whose pairs are kept, 7.72 -> 4.14 ms.  The filter is
+// bound by the gathers of its records (160 B a candidate and tile at 10-D),
+// the evaluation of the image by its vector operations (80 of about 114 issue
+// slots a pair).
 #include <cmath>
 #include <type_traits>
 
@@ -53,26 +70,40 @@
 namespace ngd {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMThreads = 256;
-constexpr int kCh = 64;       // entries staged in LDS at a time (one per lane)
-static_assert(kCh == kWave, "a wave loads the indices of one chunk");
-constexpr float kGammaQ = 1.0f / 8192.0f;     // 2^-13
-constexpr float kGammaB = 1.0f / 262144.0f;   // 2^-18
+constexpr int kWaves = kMThreads / kWave;
+constexpr float kGamma = 1.25f / 2048.0f;
+constexpr float kLinFeat = 2048.0f;      // 2^11
+constexpr float kConstFeat = 32768.0f;   // 2^15
+constexpr float kF16Max = 65504.0f;
+constexpr int kItemChunks = kItemCands / kWave;   // 64-bit masks of an item and group
+static_assert(kItemCands % kMThreads == 0, "whole rounds of columns");
 
-template <int N> struct Feat {
+// Slots of the contraction: T quadratic ones padded to units of 8, then the
+// constant (two), the linear ones, and (LO) their low parts.  A record is QU
+// units of 16 bytes of quadratic coefficients, then m (N), R s and s as
+// floats; in LDS the linear units take the place of the latter.
+template <int N> struct Filt {
     static constexpr int T = N * (N + 1) / 2;
-    static constexpr int KQ = (T + 15) / 16;   // quadratic k-steps
-    static constexpr int KS = 1 + KQ;          // plus constant and linear
-    static_assert(N + 1 <= 16, "constant and linear terms fill one k-step");
+    static constexpr int QU = (T + 7) / 8;
+    static constexpr int KS = (8 * QU + 2 + N + 15) / 16;   // k-steps
+    static constexpr int U = 2 * KS;                        // units of a column
+    static constexpr int L0 = 8 * QU;                       // first constant slot
+    static constexpr bool LO = L0 + 2 + 2 * N <= 16 * KS;
+    static constexpr int MU = (N + 2 + 3) / 4;
+    static constexpr int RU = QU + MU;                      // units of a record
+    static constexpr int META = U > RU ? U : RU;            // the bound terms' unit
+    static constexpr int ST = (META + 1) | 1;               // odd: no bank conflicts
 };
 
-// Quadratic slot q -> (i, j), i <= j, the upper triangle by rows.
+// Quadratic slot q -> (i, j), i <= j, the upper triangle by rows; -1 past T.
 template <int N> struct QuadTable {
-    int i[Feat<N>::KQ * 16];
-    int j[Feat<N>::KQ * 16];
+    int i[Filt<N>::QU * 8];
+    int j[Filt<N>::QU * 8];
     constexpr QuadTable() : i(), j()
     {
         int q = 0;
@@ -82,7 +113,7 @@ template <int N> struct QuadTable {
                 j[q] = b;
                 ++q;
             }
-        for (; q < Feat<N>::KQ * 16; ++q) {
+        for (; q < Filt<N>::QU * 8; ++q) {
             i[q] = -1;
             j[q] = -1;
         }
@@ -90,552 +121,599 @@ template <int N> struct QuadTable {
 };
 template <int N> inline constexpr QuadTable<N> kQuad{};
 
-__device__ __forceinline__ void split_bf16(float v, __bf16 &hi, __bf16 &lo)
-{
-    hi = __bf16(v);
-    lo = __bf16(v - float(hi));
-}
-
-// Per ordered Gaussian: the quadratic coefficients as bf16 hi / lo pairs in
-// B-fragment order -- for quadratic k-step ks and half h, 8 hi then 8 lo --
-// and R' = max row sum of |S'|^T |S'|.  P' is formed in float64.
+// Per ordered Gaussian: its record of the contraction.  P is formed in
+// float64 from the record's S'.
 template <int N>
 __global__ __launch_bounds__(256) void k_mfma_coef(int64_t k, const float *__restrict__ grec,
-                                                   __bf16 *__restrict__ mrec,
-                                                   float *__restrict__ rrow)
+                                                   f16x8 *__restrict__ mrec)
 {
-    using Fe = Feat<N>;
+    using Fi = Filt<N>;
     constexpr int R = RecLayout<N>::R;
-    const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (s >= k) return;
-    const float *r = grec + s * R + N;   // S' packed lower by rows
-    double S[Fe::T];
+    const int64_t g = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (g >= k) return;
+    const float *r = grec + g * R;
+    double S[Fi::T];
 #pragma unroll
-    for (int e = 0; e < Fe::T; ++e) S[e] = double(r[e]);
+    for (int e = 0; e < Fi::T; ++e) S[e] = double(r[N + e]);
     auto sidx = [](int row, int col) { return row * (row + 1) / 2 + col; };
-    __bf16 *o = mrec + s * (Fe::KQ * 32);
+    float cf[Fi::QU * 8];
+    float rs[N];
+    float cmax = 0.0f;
+    bool ok = true;
 #pragma unroll
-    for (int q = 0; q < Fe::KQ * 16; ++q) {
-        float cf = 0.0f;
+    for (int a = 0; a < N; ++a) rs[a] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < Fi::QU * 8; ++q) {
+        cf[q] = 0.0f;
         if (kQuad<N>.i[q] >= 0) {
             const int a = kQuad<N>.i[q], b = kQuad<N>.j[q];   // a <= b
             double p = 0.0;
 #pragma unroll
             for (int row = 0; row < N; ++row)
                 if (row >= b) p += S[sidx(row, a)] * S[sidx(row, b)];
-            cf = float(a == b ? p : 2.0 * p);
+            cf[q] = float(a == b ? p : 2.0 * p);
+            rs[a] += fabsf(float(p));
+            if (a != b) rs[b] += fabsf(float(p));
+            cmax = fmaxf(cmax, fabsf(cf[q]));
+            ok = ok && fabsf(cf[q]) < INFINITY;
         }
-        __bf16 hi, lo;
-        split_bf16(cf, hi, lo);
-        const int ks = q / 16, h = (q % 16) / 8, e = q % 8;
-        o[(ks * 2 + h) * 16 + e] = hi;
-        o[(ks * 2 + h) * 16 + 8 + e] = lo;
     }
-    double best = 0.0;
+    float best = 0.0f;
 #pragma unroll
-    for (int a = 0; a < N; ++a) {
-        double rs = 0.0;
+    for (int a = 0; a < N; ++a) best = fmaxf(best, rs[a]);
+    // s: the power of two that puts cmax s into [2^7, 2^8)
+    const int e = int(__float_as_uint(cmax) >> 23) - 127;
+    ok = ok && e > -90 && e < 90;
+    const float s = ok ? __uint_as_float(uint32_t(7 - e + 127) << 23) : 1.0f;
+    f16x8 *o = mrec + g * Fi::RU;
 #pragma unroll
-        for (int b = 0; b < N; ++b) {
+    for (int u = 0; u < Fi::QU; ++u) {
+        f16x8 v;
 #pragma unroll
-            for (int row = 0; row < N; ++row) {
-                if (row >= a && row >= b) rs += fabs(S[sidx(row, a)]) * fabs(S[sidx(row, b)]);
-            }
-        }
-        best = rs > best ? rs : best;
+        for (int i = 0; i < 8; ++i) v[i] = ok ? _Float16(cf[8 * u + i] * s) : _Float16(0.0f);
+        o[u] = v;
     }
-    rrow[s] = float(best) * (1.0f + 1.0f / 1048576.0f);
+    float mt[Fi::MU * 4];
+#pragma unroll
+    for (int i = 0; i < Fi::MU * 4; ++i) mt[i] = 0.0f;
+#pragma unroll
+    for (int a = 0; a < N; ++a) mt[a] = r[a];
+    mt[N] = ok ? best * s * (1.0f + 1.0f / 1048576.0f) : INFINITY;
+    mt[N + 1] = s;
+#pragma unroll
+    for (int u = 0; u < Fi::MU; ++u)
+        o[Fi::QU + u] = __builtin_bit_cast(
+            f16x8, f32x4{mt[4 * u], mt[4 * u + 1], mt[4 * u + 2], mt[4 * u + 3]});
 }
 
-// Per candidate entry (tile, Gaussian): the centred constant and linear
-// coefficients a' = |S'm'|^2, b' = -2 S'^T (S'm'), m' = m - c_tile, as the
-// k-step-0 B fragments (per half: 8 bf16 hi, 8 bf16 lo), and the bound terms
-// (|a'|, |b'|_1, |m'|_1, R').
+// Feature of slot `slot` for sigma-scaled coordinates u.
+template <int N, int SLOT> __device__ __forceinline__ float feature(const float (&u)[N], float one)
+{
+    using Fi = Filt<N>;
+    if constexpr (SLOT < Fi::L0) {
+        if constexpr (kQuad<N>.i[SLOT] >= 0)
+            return u[kQuad<N>.i[SLOT]] * u[kQuad<N>.j[SLOT]];
+        else
+            return 0.0f;
+    } else if constexpr (SLOT < Fi::L0 + 2) {
+        return one;
+    } else if constexpr (SLOT < Fi::L0 + 2 + N) {
+        return u[SLOT - Fi::L0 - 2] * kLinFeat;
+    } else if constexpr (Fi::LO && SLOT < Fi::L0 + 2 + 2 * N) {
+        return u[SLOT - Fi::L0 - 2 - N] * kLinFeat;
+    } else {
+        return 0.0f;
+    }
+}
+
+// masks: per (item, group) kItemChunks words, bit = candidate not skipped.
 template <int N>
-__global__ __launch_bounds__(256) void k_mfma_entry(int64_t total,
-                                                    const int32_t *__restrict__ cand,
-                                                    const int32_t *__restrict__ ent_tile,
-                                                    const float *__restrict__ grec,
-                                                    const float *__restrict__ rrow,
-                                                    const float *__restrict__ tcen,
-                                                    bf16x8 *__restrict__ eb0,
-                                                    float4 *__restrict__ ebnd)
+__global__ __launch_bounds__(kMThreads, 3) void k_filter_items(
+    int64_t q, int tile, const f16x8 *__restrict__ mrec, const float *__restrict__ tcen,
+    const float *__restrict__ qs, const int64_t *__restrict__ tile_off,
+    const int32_t *__restrict__ cand, const int32_t *__restrict__ item_tile,
+    const int64_t *__restrict__ item_off, float skip, uint64_t *__restrict__ masks)
 {
-    constexpr int R = RecLayout<N>::R;
-    // the record's mean and factor: NV float4s, staged per wave in LDS by
-    // 16-byte global-to-LDS loads in rounds of 64 consecutive slots (each
-    // round reads whole stretches of records), at an odd stride per entry
-    // so that the lanes' reads meet no bank conflicts
-    constexpr int NV = (N + RecLayout<N>::T + 3) / 4;
-    constexpr int kSt = NV | 1;
-    __shared__ float4 s_rec[256 / kWave][kWave * kSt];
-    const int w = int(threadIdx.x) / kWave, lane = lane_id();
-    // consecutive blocks (neighbouring tiles' entries, which share
-    // Gaussians) on one XCD, so that they share its L2
-    const int64_t ew = xcd_block(blockIdx.x, gridDim.x) * 256 + w * kWave;   // the wave's first entry
-    if (ew >= total) return;                                    // uniform over the wave
-    const int nw = int(total - ew < kWave ? total - ew : kWave);
-    const int64_t e = ew + lane;
-    const int spl = lane < nw ? cand[e] : 0;
-#pragma unroll
-    for (int i = 0; i < kSt; ++i) {
-        const int sl = i * kWave + lane;
-        const int j = sl / kSt, v = sl - j * kSt;
-        const int spj = __shfl(spl, j, kWave);
-        if (v < NV && j < nw)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(grec + int64_t(spj) * R + 4 * v),
-                (__attribute__((address_space(3))) void *)(&s_rec[w][i * kWave]), 16, 0, 0);
-    }
-    // the wave reads only what its own loads wrote
-    __builtin_amdgcn_s_waitcnt(0);
-    if (lane >= nw) return;
-    const int sp = spl;
-    float r[NV * 4];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const float4 u = s_rec[w][lane * kSt + v];
-        r[4 * v + 0] = u.x;
-        r[4 * v + 1] = u.y;
-        r[4 * v + 2] = u.z;
-        r[4 * v + 3] = u.w;
-    }
-    const float *c = tcen + int64_t(ent_tile[e]) * N;
-    float mp[N], y[N], b[N];
-    float m1 = 0.0f;
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-        mp[a] = r[a] - c[a];
-        m1 += fabsf(mp[a]);
-    }
-    float a0 = 0.0f;
-#pragma unroll
-    for (int row = 0; row < N; ++row) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int col = 0; col <= row; ++col)
-            acc = fmaf(r[N + row * (row + 1) / 2 + col], mp[col], acc);
-        y[row] = acc;
-        a0 = fmaf(acc, acc, a0);
-    }
-    float b1 = 0.0f;
-#pragma unroll
-    for (int col = 0; col < N; ++col) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int row = col; row < N; ++row)
-            acc = fmaf(r[N + row * (row + 1) / 2 + col], y[row], acc);
-        b[col] = -2.0f * acc;
-        b1 += fabsf(b[col]);
-    }
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-        bf16x8 vhi, vlo;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int slot = 8 * hh + k;
-            const float v = slot == 0 ? a0 : (slot <= N ? b[slot - 1] : 0.0f);
-            __bf16 hi, lo;
-            split_bf16(v, hi, lo);
-            vhi[k] = hi;
-            vlo[k] = lo;
-        }
-        eb0[e * 4 + hh * 2 + 0] = vhi;
-        eb0[e * 4 + hh * 2 + 1] = vlo;
-    }
-    ebnd[e] = make_float4(fabsf(a0), b1, m1, rrow[sp]);
-}
+    using Fi = Filt<N>;
+    constexpr int KS = Fi::KS, ST = Fi::ST;
+    __shared__ f16x8 s_col[kMThreads * ST];
+    __shared__ float s_hm[kWaves];
 
-// OUT: the colours are accumulated and written (caller order); otherwise
-// only the (entry, group) flags.  COUNT (with OUT = false): the counters
-// stats[0..4] = (examined, not skipped by the matrix filter, passed check 1,
-// passed check 2, kept) are added.
-template <int N, bool OUT, bool COUNT>
-__global__ __launch_bounds__(kMThreads, 3) void k_mfma_filter(
-    int64_t q, int tile, const bf16x8 *__restrict__ mrec, const bf16x8 *__restrict__ eb0,
-    const float4 *__restrict__ ebnd, const float *__restrict__ tcen,
-    const float *__restrict__ qs, const float *__restrict__ grec,
-    const int64_t *__restrict__ tile_off, const int32_t *__restrict__ cand,
-    const int32_t *__restrict__ perm, float skip, uint8_t *__restrict__ act,
-    float *__restrict__ out, unsigned long long *__restrict__ stats)
-{
-    using Fe = Feat<N>;
-    using Lay = RecLayout<N>;
-    constexpr int KS = Fe::KS, KQ = Fe::KQ;
-    // Per buffer, three regions of 16-byte slots, each entry's units padded
-    // to an odd stride so that 8 and 16 consecutive entries fall on distinct
-    // bank groups: the k-step-0 units (half * 2 + {hi, lo}) of the entries,
-    // their quadratic units ((k-step - 1) * 2 + half) * 2 + {hi, lo}, and
-    // their bound terms |a'|, |b'|_1, |m'|_1, R' (consecutive).
-    constexpr int kMU = KQ * 4;                  // quadratic units per entry
-    constexpr int kStA = 5, kStB = kMU + 1;      // entry strides
-    constexpr int kOffB = kCh * kStA, kOffC = kOffB + kCh * kStB;
-    constexpr int kBufSlots = kOffC + kCh;
-    __shared__ bf16x8 s_lds[2][kBufSlots];
+    const int64_t it = xcd_block(blockIdx.x, gridDim.x);   // neighbouring tiles share an L2
+    const int64_t t = uniform(item_tile[it]);
+    const int64_t c1 = uniform64(tile_off[t + 1]);
+    const int64_t e0 = uniform64(tile_off[t]) + (it - uniform64(item_off[t])) * kItemCands;
+    const int ne = uniform(int(c1 - e0 < kItemCands ? c1 - e0 : kItemCands));
 
-    // one workgroup per tile (and part of a tile of more than 256 queries):
-    // the query features are formed once for all of the tile's candidates
-    // neighbouring tiles, which share candidates, on one XCD (one L2)
-    const int64_t t = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t e0 = uniform64(tile_off[t]), e1 = uniform64(tile_off[t + 1]);
-
-    const int lane = lane_id(), w = int(threadIdx.x) / kWave, h = lane / 32;
+    const int lane = lane_id(), w = uniform(int(threadIdx.x) / kWave), h = lane / 32;
     const int s = int(blockIdx.y) * kMThreads + int(threadIdx.x);
-    const int64_t p = t * tile + s;
-    const bool valid = (s < tile) && (p < q);
+    const bool live = ballot(s < tile && t * tile + s < q) != 0;   // the wave has queries
+    const int ngroups = (tile + kWave - 1) / kWave;
+    uint64_t *__restrict__ mine_m = masks + (it * ngroups + s / kWave) * kItemChunks;
+
     float cen[N];
 #pragma unroll
     for (int a = 0; a < N; ++a) cen[a] = tcen[t * N + a];
-
-    // The coordinates this lane needs, loaded first and all together (from
-    // a valid row, the tile's first, where a row is past the tile's end):
-    // its own query's (the wave's half-widths) and its row of each of the
-    // two A row blocks.
-    float xo[N], xb[2][N];
-    bool vrow[2];
+    // the wave's 64 rows, two blocks of 32; rows past the end repeat the
+    // group's first query (a wave without queries: the tile's first)
+    f16x8 fa[2][KS];
+    float hq, hm;
+    float sig;
     {
-        const int64_t pc = valid ? p : t * tile;
-#pragma unroll
-        for (int a = 0; a < N; ++a) xo[a] = qs[a * q + pc];
+        float xr[2][N];
+        float m1 = 0.0f, m2 = 0.0f;
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
-            const int sr = w * kWave + int(blockIdx.y) * kMThreads + rb * 32 + (lane % 32);
+            const int sg = int(blockIdx.y) * kMThreads + w * kWave;
+            const int sr = sg + rb * 32 + (lane % 32);
             const int64_t pr = t * tile + sr;
-            vrow[rb] = (sr < tile) && (pr < q);
-            const int64_t prc = vrow[rb] ? pr : t * tile;
+            const int64_t pc = (sr < tile && pr < q) ? pr : t * tile + (live ? sg : 0);
+            float n2 = 0.0f;
 #pragma unroll
-            for (int a = 0; a < N; ++a) xb[rb][a] = qs[a * q + prc];
+            for (int a = 0; a < N; ++a) {
+                xr[rb][a] = qs[a * q + pc] - cen[a];
+                m1 = fmaxf(m1, fabsf(xr[rb][a]));
+                n2 = fmaf(xr[rb][a], xr[rb][a], n2);
+            }
+            m2 = fmaxf(m2, n2);
         }
-    }
-    // this wave's half-widths about the centre
-    float h2 = 0.0f, hm = 0.0f;
+        hm = wave_max_nonneg(m1);
+        hq = sqrtf(wave_max_nonneg(m2)) * (1.0f + 1.0f / 1048576.0f);
+        if (lane == 0) s_hm[w] = hm;
+        __syncthreads();
+        float ht = s_hm[0];
 #pragma unroll
-    for (int a = 0; a < N; ++a) {
-        const float ha = wave_max_nonneg(valid ? fabsf(xo[a] - cen[a]) : 0.0f);
-        h2 = fmaf(ha, ha, h2);
-        hm = fmaxf(hm, ha);
-    }
-    h2 *= 1.0f + 1.0f / 1048576.0f;
-
-    // A fragments: rows are the wave's queries (two blocks of 32).  Every
-    // lane forms all 16 features of each k-step for its row (indices known
-    // at compile time), then keeps the half h = lane / 32 it holds.
-    bf16x8 ahi[2][KS], alo[2][KS];
+        for (int i = 1; i < kWaves; ++i) ht = fmaxf(ht, s_hm[i]);
+        // a tile much smaller than its distance from the origin: the scale
+        // of that distance, so that b stays in range
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-        const bool vr = vrow[rb];
-        float xr[N];
+        for (int a = 0; a < N; ++a) ht = fmaxf(ht, fabsf(cen[a]) * (1.0f / 1024.0f));
+        // ht sigma in (8, 16]
+        const int e = int(__float_as_uint(ht) >> 23) - 127;
+        sig = (e > -60 && e < 60) ? __uint_as_float(uint32_t(3 - e + 127) << 23) : 1.0f;
 #pragma unroll
-        for (int a = 0; a < N; ++a) xr[a] = vr ? xb[rb][a] - cen[a] : 0.0f;
+        for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            float f[16];
+            for (int a = 0; a < N; ++a) xr[rb][a] *= sig;
+            // every lane forms all the features (indices known at compile time)
+            // and keeps those of its half
+            [&]<int... I>(std::integer_sequence<int, I...>) {
+                float f[16 * KS] = {feature<N, I>(xr[rb], kConstFeat)...};
 #pragma unroll
-            for (int slot = 0; slot < 16; ++slot) {
-                f[slot] = 0.0f;
-                if (ks == 0) {
-                    if (slot == 0)
-                        f[slot] = vr ? 1.0f : 0.0f;
-                    else if (slot <= N)
-                        f[slot] = xr[slot - 1];
-                } else {
-                    const int qq = (ks - 1) * 16 + slot;
-                    if (kQuad<N>.i[qq] >= 0) f[slot] = xr[kQuad<N>.i[qq]] * xr[kQuad<N>.j[qq]];
+                for (int e = 0; e < 8 * KS; ++e) {
+                    const float lo = f[e / 8 * 16 + e % 8], hi = f[e / 8 * 16 + 8 + e % 8];
+                    fa[rb][e / 8][e % 8] = _Float16(h ? hi : lo);
                 }
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float v = h ? f[8 + e] : f[e];
-                __bf16 hi, lo;
-                split_bf16(v, hi, lo);
-                ahi[rb][ks][e] = hi;
-                alo[rb][ks][e] = lo;
-            }
-        }
-    }
-    // all 64 queries of the group valid: no row masking in the group test;
-    // none valid (past the tile's end): the wave only loads and meets
-    const bool full = ballot(valid) == ~uint64_t(0);
-    const bool live = ballot(valid) != 0;
-    uint32_t rowvalid = 0;   // bit rb * 16 + r: accumulator element r of row block rb
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 8 * (r / 4) + 4 * h + (r % 4);
-            const int sq = w * kWave + int(blockIdx.y) * kMThreads + rb * 32 + row;
-            if (sq < tile && t * tile + sq < q) rowvalid |= 1u << (rb * 16 + r);
+            }(std::make_integer_sequence<int, 16 * KS>{});
         }
     }
 
-    const int ngroups = (tile + kWave - 1) / kWave;
-    const int grp = s / kWave;
-    unsigned long long n_exam = 0, n_pass = 0;
-
-    // Chunks of kCh entries staged in LDS, double-buffered: the workgroup
-    // issues the loads of chunk c + 1 straight into LDS (global_load_lds,
-    // 16 bytes per lane, lane l of a wave to slot M0 + l) while it computes
-    // chunk c, then waits for them and meets at one barrier.
-    // The workgroup is always kMThreads threads (waves whose rows are all
-    // past the tile's end only load and meet).  Each region is loaded in
-    // rounds of kMThreads slots, a wave's 64 lanes on 64 consecutive slots;
-    // a lane on a padding slot or an entry past the list's end loads
-    // nothing.
-    auto load_region = [&](auto region, int buf, int64_t ch, int nch, int cv) {
-        constexpr int R = decltype(region)::value;
-        constexpr int off = R == 0 ? 0 : (R == 1 ? kOffB : kOffC);
-        constexpr int len = R == 0 ? kCh * kStA : (R == 1 ? kCh * kStB : kCh);
-        constexpr int st = R == 0 ? kStA : (R == 1 ? kStB : 1);
-        constexpr int units = R == 0 ? 4 : (R == 1 ? kMU : 1);
+    for (int base = 0; base < ne; base += kMThreads) {
+        if (base != 0) __syncthreads();   // the last chunk's readers are done
+        // ---- columns: this wave's 64 candidates
+        const int ew = base + w * kWave;
+        const int nw = ne - ew < kWave ? ne - ew : kWave;   // may be <= 0
+        if (nw > 0) {
+            const int ci = lane < nw ? cand[e0 + ew + lane] : 0;
+            f16x8 *col = s_col + w * kWave * ST;
 #pragma unroll
-        for (int k = 0; k < (len + kMThreads - 1) / kMThreads; ++k) {
-            const int wbase = k * kMThreads + w * kWave;   // this wave's first slot
-            if (wbase >= len) break;                       // uniform over the wave
-            const int sl = wbase + lane;
-            const int j = sl / st, u = sl - j * st;
-            // a wave-uniform base and a 32-bit lane offset (in 16-byte units)
-            const bf16x8 *base;
-            uint32_t o;
-            if constexpr (R == 0) {
-                base = eb0 + ch * 4;
-                o = uint32_t(j * 4 + u);
-            } else if constexpr (R == 1) {
-                base = mrec;
-                o = uint32_t(__shfl(cv, j & (kWave - 1), kWave)) * kMU + uint32_t(u);
-            } else {
-                base = reinterpret_cast<const bf16x8 *>(ebnd + ch);
-                o = uint32_t(j);
+            for (int i = 0; i < ST; ++i) {
+                const int sl = i * kWave + lane;
+                const int j = sl / ST, u = sl - j * ST;
+                const int cj = __shfl(ci, j, kWave);
+                if (u < Fi::RU && j < nw)
+                    __builtin_amdgcn_global_load_lds(
+                        (const __attribute__((address_space(1))) void *)(mrec +
+                                                                         int64_t(cj) * Fi::RU + u),
+                        (__attribute__((address_space(3))) void *)(col + i * kWave), 16, 0, 0);
             }
-            const bf16x8 *src = base + o;
-            if (sl < len && u < units && j < nch)
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void *)(src),
-                    (__attribute__((address_space(3))) void *)(&s_lds[buf][off + wbase]), 16, 0,
-                    0);
+            __builtin_amdgcn_s_waitcnt(0);   // the wave reads only its own loads
+            asm volatile("" ::: "memory");
+            f16x8 *mine = col + lane * ST;
+            float mt[Fi::MU * 4];
+#pragma unroll
+            for (int u = 0; u < Fi::MU; ++u) {
+                const f32x4 v = __builtin_bit_cast(f32x4, mine[Fi::QU + u]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mt[4 * u + i] = v[i];
+            }
+            const float Rs = mt[N], sc = mt[N + 1];
+            float mp[N], tb[N];
+            float mm = 0.0f;
+#pragma unroll
+            for (int a = 0; a < N; ++a) {
+                mp[a] = mt[a] - cen[a];
+                mm = fmaf(mp[a], mp[a], mm);
+                tb[a] = 0.0f;
+            }
+            // tb = 2 s P~ m'
+            [&]<int... QI>(std::integer_sequence<int, QI...>) {
+                f16x8 v;
+                ((
+                     [&] {
+                         if constexpr (QI % 8 == 0) v = mine[QI / 8];
+                         if constexpr (kQuad<N>.i[QI] >= 0) {
+                             constexpr int a = kQuad<N>.i[QI], b = kQuad<N>.j[QI];
+                             const float cv = float(v[QI % 8]);
+                             if constexpr (a == b) {
+                                 tb[a] = fmaf(cv, mp[a] + mp[a], tb[a]);
+                             } else {
+                                 tb[a] = fmaf(cv, mp[b], tb[a]);
+                                 tb[b] = fmaf(cv, mp[a], tb[b]);
+                             }
+                         }
+                     }()),
+                 ...);
+            }(std::make_integer_sequence<int, 8 * Fi::QU>{});
+            float as = 0.0f, b1 = 0.0f, bmax = 0.0f;
+            float lin[8 * (Fi::U - Fi::QU)];
+#pragma unroll
+            for (int i = 0; i < 8 * (Fi::U - Fi::QU); ++i) lin[i] = 0.0f;
+            const float bscale = -sig / kLinFeat;
+#pragma unroll
+            for (int a = 0; a < N; ++a) {
+                as = fmaf(tb[a], mp[a], as);
+                b1 += fabsf(tb[a]);
+                const float v = tb[a] * bscale;
+                bmax = fmaxf(bmax, fabsf(v));
+                lin[2 + a] = v;
+                if constexpr (Fi::LO) lin[2 + N + a] = v - float(_Float16(v));
+            }
+            const float sig2 = sig * sig;
+            const float ac = fmaxf(0.5f * as * sig2 * (1.0f / kConstFeat), 0.0f);
+            lin[0] = fminf(ac, kF16Max);
+            lin[1] = fminf(ac - float(_Float16(lin[0])), kF16Max);
+#pragma unroll
+            for (int u = 0; u < Fi::U - Fi::QU; ++u) {
+                f16x8 v;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = _Float16(lin[8 * u + i]);
+                mine[Fi::QU + u] = v;
+            }
+            // skip iff the minimum exceeds T0 + T1 q + T2 q^2 + T3 h; the 1
+            // covers float16's least steps (values below 2^-14)
+            const float K = sig2 * sc, rk = kGamma * Rs * sig2;
+            float t0 = fmaf(rk, mm, fmaf(skip, K, 1.0f));
+            if (!(bmax < 65000.0f) || !(K > 0x1p-60f && K < 0x1p60f)) t0 = INFINITY;
+            mine[Fi::META] = __builtin_bit_cast(
+                f16x8, f32x4{t0, 2.0f * rk * sqrtf(mm), 2.0f * rk,
+                             (Fi::LO ? 1.0f : 2.0f) * kGamma * b1 * sig2});
         }
-    };
-    auto load_chunk = [&](int buf, int64_t ch, int cv) {
-        const int nch = int((e1 - ch < kCh) ? e1 - ch : kCh);   // entries present
-        load_region(std::integral_constant<int, 0>{}, buf, ch, nch, cv);
-        load_region(std::integral_constant<int, 1>{}, buf, ch, nch, cv);
-        load_region(std::integral_constant<int, 2>{}, buf, ch, nch, cv);
-    };
-    auto cand_of = [&](int64_t ch) { return (ch + lane < e1) ? cand[ch + lane] : 0; };
-    if (e0 < e1) load_chunk(0, e0, cand_of(e0));
-    int cv_next = cand_of(e0 + kCh);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
-    uint32_t st[3] = {0u, 0u, 0u};
-    int buf = 0;
-    for (int64_t ch = e0; ch < e1; ch += kCh) {
-        const bool more = ch + kCh < e1;
-        if (more) load_chunk(buf ^ 1, ch + kCh, cv_next);
-        const int cv_after = cand_of(ch + 2 * kCh);
-        const int n = int((e1 - ch < kCh) ? e1 - ch : kCh);
-        if constexpr (COUNT) {
-            // a group past the tile's end counts its pairs as examined, as
-            // the float32 kernel does
-            if (!live) n_exam += uint64_t(n);
-        }
-        for (int cb = 0; live && cb < n; cb += 32) {
-            const int jl = cb + (lane % 32);
-            const bool jv = jl < n;
-            const int jc = jv ? jl : cb;   // idle lanes: a valid row, column ignored
-            bf16x8 bhi[KS], blo[KS];
+        __syncthreads();
+        // ---- the contraction: 32 columns at a time against the wave's rows
+        const int nb = ne - base < kMThreads ? ne - base : kMThreads;
+        if (live) {
+            uint32_t lowm = 0;
+            for (int cb = 0; cb < nb; cb += 32) {
+                const int jl = cb + (lane % 32);
+                const f16x8 *colp = s_col + jl * ST;
+                f32x16 acc0 = {}, acc1 = {};
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int sl = ks == 0 ? jc * kStA + h * 2
-                                       : kOffB + jc * kStB + ((ks - 1) * 2 + h) * 2;
-                bhi[ks] = s_lds[buf][sl];
-                blo[ks] = s_lds[buf][sl + 1];
-            }
-            const bf16x8 bdv = s_lds[buf][kOffC + jc];
-            const float4 bd = *reinterpret_cast<const float4 *>(&bdv);
-            f32x16 acc0 = {}, acc1 = {};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo[0][ks], bhi[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo[1][ks], bhi[ks], acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[0][ks], blo[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[1][ks], blo[ks], acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[0][ks], bhi[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[1][ks], bhi[ks], acc1, 0, 0, 0);
-            }
-            // certified group test of the entry in this lane's column: the
-            // smallest M' over the group's rows, as a signed-integer minimum
-            // of the float bits -- exact among non-negative values, and any
-            // negative value (rounding below 0) stays negative, which keeps
-            // the candidate, as it must
-            int mi = 0x7f800000;   // +inf
-            if (full) {
+                for (int ks = 0; ks < KS; ++ks) {
+                    const f16x8 b = colp[2 * ks + h];
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[0][ks], b, acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[1][ks], b, acc1, 0, 0, 0);
+                }
+                const f32x4 bd = __builtin_bit_cast(f32x4, colp[Fi::META]);
+                const float thr =
+                    fmaf(bd[3], hm, fmaf(fmaf(bd[2], hq, bd[1]), hq, bd[0]));
+                // the smallest value over the group's rows as a signed-integer
+                // minimum of the float bits: exact among non-negative values,
+                // and any negative one (rounding below 0) stays negative,
+                // which keeps the candidate, as it must
+                int mi = 0x7f800000;   // +inf
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     mi = min(mi, min(__float_as_int(acc0[r]), __float_as_int(acc1[r])));
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    if (rowvalid & (1u << r)) mi = min(mi, __float_as_int(acc0[r]));
-                    if (rowvalid & (1u << (16 + r))) mi = min(mi, __float_as_int(acc1[r]));
+                const bool pass = jl < nb && !(__int_as_float(mi) > thr);
+                const uint64_t bal = ballot(pass);
+                const uint32_t both = uint32_t(bal) | uint32_t(bal >> 32);
+                if (cb & 32) {
+                    if (lane == 0) mine_m[(base + cb) / kWave] = uint64_t(both) << 32 | lowm;
+                } else {
+                    lowm = both;
+                    if (cb + 32 >= nb && lane == 0) mine_m[(base + cb) / kWave] = lowm;
                 }
             }
-            const float mn = __int_as_float(mi);
-            const float bound =
-                kGammaQ * (bd.w * h2 + bd.y * hm + bd.x) + kGammaB * bd.w * bd.z * hm;
-            const bool pass = jv && !(mn - bound > skip);
-            const uint64_t bal = ballot(pass);
-            if constexpr (COUNT) {
-                n_exam += uint64_t(n - cb < 32 ? n - cb : 32);
-                n_pass += uint64_t(__popc(uint32_t(bal) | uint32_t(bal >> 32)));
-            }
-            if (lane < 32 && jv && grp < ngroups)
-                act[(ch + jl) * ngroups + grp] =
-                    uint8_t(((bal >> lane) | (bal >> (lane + 32))) & 1u);
         }
-        // the next chunk in LDS, and every wave done with this one
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        buf ^= 1;
-        cv_next = cv_after;
     }
-    // The pairs the filter kept are evaluated in float32 by the staged code
-    // of the float32 kernel (lane = its own query), in ascending entry order
-    // per group, each record fetched with wave-uniform loads one pair ahead;
-    // the flag becomes the kept decision.  The flags read are this wave's
-    // own (written above, complete after the last wait).
-    if (live && grp < ngroups) {
-        float x[N];
-        {
-            // the row index made opaque here, so that the compiler does not
-            // keep its N addresses live through the loop above
-            int pc = int(valid ? s : 0);
-            asm volatile("" : "+v"(pc));
-            const float *qp = qs + t * tile + pc;
+}
+
+// A record's fields in order -- m, S' by rows, alpha c -- as NP parts of PS
+// floats, each one run of scalar loads; two parts (64 to 80 scalar registers)
+// are held at a time, the one in use and the one in flight.
+template <int N> struct Parts {
+    static constexpr int F = N + N * (N + 1) / 2 + 3;
+    static constexpr int NP = F <= 40 ? 1 : (F <= 72 ? 2 : 3);
+    static constexpr int PS = ((F + NP - 1) / NP + 3) / 4 * 4;
+    static_assert(NP * PS <= RecLayout<N>::R && F - 3 >= (NP - 1) * PS, "parts");
+};
+
+template <int N, int P>
+__device__ __forceinline__ void load_part(float (&blk)[Parts<N>::PS], ConstRec r)
+{
 #pragma unroll
-            for (int a = 0; a < N; ++a) x[a] = qp[a * q];
+    for (int e = 0; e < Parts<N>::PS; ++e) blk[e] = r[P * Parts<N>::PS + e];
+}
+
+// Waits for the part in flight, then sends for the next one; the scheduler
+// keeps the arithmetic of the one that has arrived behind the loads.
+template <int N, int P>
+__device__ __forceinline__ void next_part(float (&blk)[Parts<N>::PS], ConstRec &r)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    wait_scalar_then(r);
+    load_part<N, P>(blk, r);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// One lane's evaluation of a pair, field by field; the sums are those of rows
+// y_r = sum_j S'_rj d_j, msq = sum_r y_r^2 in ascending order.
+template <int N> struct PairState {
+    float d[N], acc, msq;
+    bool c1, c2;   // COUNT: the wave passed the checks after 3 and 6 rows
+};
+
+template <int N, int E, bool COUNT>
+__device__ __forceinline__ void pair_field(PairState<N> &st, const float (&x)[N], float v,
+                                           uint64_t vmask, float skip)
+{
+    constexpr int T = N * (N + 1) / 2;
+    if constexpr (E < N) {
+        st.d[E] = x[E] - v;
+    } else if constexpr (E < N + T) {
+        constexpr int f = E - N;
+        constexpr int row = [] {
+            int r = 0;
+            while ((r + 1) * (r + 2) / 2 <= f) ++r;
+            return r;
+        }();
+        constexpr int col = f - row * (row + 1) / 2;
+        st.acc = col == 0 ? v * st.d[0] : fmaf(v, st.d[col], st.acc);
+        if constexpr (col == row) st.msq = row == 0 ? st.acc * st.acc : fmaf(st.acc, st.acc, st.msq);
+        if constexpr (COUNT && col == row) {
+            if constexpr (row + 1 == 3 && N > 3) st.c1 = (ballot(st.msq <= skip) & vmask) != 0;
+            if constexpr (row + 1 == 6 && N > 6) st.c2 = (ballot(st.msq <= skip) & vmask) != 0;
         }
-        float bufA[Lay::PF], bufB[Lay::PF];
-        for (int64_t ch = e0; ch < e1; ch += kWave) {
-            const int n = int((e1 - ch < kWave) ? e1 - ch : kWave);
-            uint8_t *fl = act + (ch + lane) * ngroups + grp;
-            uint64_t todo = ballot(lane < n && *fl != 0);
-            if (todo == 0) continue;
-            const int vidx = (lane < n) ? cand[ch + lane] : 0;
-            uint32_t kept = 0;
-            int ja = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            load_block<N>(bufA, grec + int64_t(__builtin_amdgcn_readlane(vidx, ja)) * Lay::R);
-            while (ja >= 0) {
-                const int64_t ia = __builtin_amdgcn_readlane(vidx, ja);
-                const int jb = todo ? __builtin_ctzll(todo) : -1;
-                __builtin_amdgcn_s_waitcnt(kWaitScalar);
-                if (jb >= 0) {
-                    todo &= todo - 1;
-                    load_block<N>(bufB,
-                                  grec + int64_t(__builtin_amdgcn_readlane(vidx, jb)) * Lay::R);
+    }
+}
+
+template <int N, int P, bool COUNT>
+__device__ __forceinline__ void pair_part(PairState<N> &st, const float (&x)[N],
+                                          const float (&blk)[Parts<N>::PS], uint64_t vmask,
+                                          float skip)
+{
+    [&]<int... I>(std::integer_sequence<int, I...>) {
+        (pair_field<N, P * Parts<N>::PS + I, COUNT>(st, x, blk[I], vmask, skip), ...);
+    }(std::make_integer_sequence<int, Parts<N>::PS>{});
+}
+
+// OUT: the colours are accumulated; otherwise only the (entry, group) flags.
+// COUNT (with OUT = false): stats[0..4] += (pairs examined, not skipped by the
+// filter, below the threshold after 3 rows, after 6 rows, kept).
+template <int N, bool OUT, bool COUNT>
+__global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
+    int64_t q, int tile, const uint64_t *__restrict__ masks, const float *__restrict__ qs,
+    const float *__restrict__ grec, const int64_t *__restrict__ tile_off,
+    const int32_t *__restrict__ cand, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ item_tile, const int64_t *__restrict__ item_off, float skip,
+    uint8_t *__restrict__ act, float *__restrict__ out, float *__restrict__ part,
+    unsigned long long *__restrict__ stats)
+{
+    using Pa = Parts<N>;
+    constexpr int R = RecLayout<N>::R, AC = N + N * (N + 1) / 2;
+    __shared__ int32_t s_idx[kWaves][kItemCands];    // the survivors' Gaussians
+    __shared__ uint16_t s_pos[kWaves][kItemCands];   // their places in the item
+    __shared__ uint32_t s_kept[kWaves][kItemCands / 32];
+    const int64_t it = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t t = uniform(item_tile[it]);
+    const int64_t i0 = uniform64(item_off[t]);
+    const int64_t nit = uniform64(item_off[t + 1]) - i0;
+    const int64_t c1 = uniform64(tile_off[t + 1]);
+    const int64_t e0 = uniform64(tile_off[t]) + (it - i0) * kItemCands;
+    const int ne = uniform(int(c1 - e0 < kItemCands ? c1 - e0 : kItemCands));
+    const int lane = lane_id(), w = uniform(int(threadIdx.x) / kWave);
+    const int s = int(blockIdx.y) * kMThreads + int(threadIdx.x);
+    const int64_t p = t * tile + s;
+    const bool valid = (s < tile) && (p < q);
+    const uint64_t vmask = ballot(valid);
+    const int ngroups = (tile + kWave - 1) / kWave;
+    const int grp = uniform(s / kWave);
+    if (vmask == 0) {   // a group past the end: its pairs count as examined
+        if constexpr (COUNT) {
+            if (lane == 0 && grp < ngroups) atomicAdd(&stats[0], (unsigned long long)(ne));
+        }
+        return;
+    }
+    float x[N];
+    {
+        const int64_t pc = valid ? p : t * tile;
+#pragma unroll
+        for (int a = 0; a < N; ++a) x[a] = qs[a * q + pc];
+    }
+    // the survivors listed first (this wave's part of LDS only), so that the
+    // evaluation below runs through them without stopping at each word
+    int cnt = 0;
+    {
+        int32_t cv[kItemChunks];
+#pragma unroll
+        for (int c = 0; c < kItemChunks; ++c)
+            cv[c] = c * kWave + lane < ne ? cand[e0 + c * kWave + lane] : 0;
+#pragma unroll
+        for (int c = 0; c < kItemChunks; ++c) {
+            if (c * kWave < ne) {
+                const uint64_t m = uint64_t(
+                    uniform64(int64_t(masks[(it * ngroups + grp) * kItemChunks + c])));
+                if ((m >> lane) & 1) {
+                    const int o = cnt + __popcll(m & lanemask_lt());
+                    s_idx[w][o] = cv[c];
+                    s_pos[w][o] = uint16_t(c * kWave + lane);
                 }
-                if (eval_pair<N, true, OUT, COUNT>(bufA, grec + ia * Lay::R, x, valid, skip, f0,
-                                                   f1, f2, st))
-                    kept = (lane == ja) ? 1u : kept;
-#pragma unroll
-                for (int e = 0; e < Lay::PF; ++e) bufA[e] = bufB[e];
-                ja = jb;
+                cnt += __builtin_popcountll(m);
             }
-            if (lane < n) *fl = uint8_t(kept);
         }
+        if (lane < kItemCands / 32) s_kept[w][lane] = 0;
+    }
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+
+    float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
+    uint32_t n1 = 0, n2 = 0, nk = 0;
+    const ConstRec recs = const_rec(grec);
+    for (int li = 0; li < cnt; li += kWave) {
+        const int n = cnt - li < kWave ? cnt - li : kWave;
+        const int vidx = lane < n ? s_idx[w][li + lane] : 0;
+        uint64_t km = 0;
+        // the pair's last part in blk: the decision, and the colours
+        auto finish = [&](const PairState<N> &st, const float(&blk)[Pa::PS], int j) {
+            const bool kept = (ballot(st.msq <= skip) & vmask) != 0;
+            if constexpr (COUNT) {
+                const bool k1 = N > 3 ? st.c1 : true, k2 = N > 6 ? st.c2 : k1;
+                n1 += k1;
+                n2 += k2;
+                nk += kept;
+            }
+            if (!kept) return;
+            km |= uint64_t(1) << j;
+            if constexpr (OUT) {
+                constexpr int o = AC - (Pa::NP - 1) * Pa::PS;
+                const float g = __builtin_amdgcn_exp2f(-st.msq);
+                f0 = fmaf(g, blk[o + 0], f0);
+                f1 = fmaf(g, blk[o + 1], f1);
+                f2 = fmaf(g, blk[o + 2], f2);
+            }
+        };
+        // past the last survivor the first one's record again (not used)
+        auto rec_of = [&](int j) {
+            return recs + int64_t(__builtin_amdgcn_readlane(vidx, j < n ? j : 0)) * R;
+        };
+        ConstRec r = rec_of(0);
+        float b0[Pa::PS], b1[Pa::PS];
+        load_part<N, 0>(b0, r);
+        if constexpr (Pa::NP == 1) {
+            for (int j = 0; j < n; j += 2) {
+                PairState<N> st;
+                ConstRec r1 = rec_of(j + 1);
+                next_part<N, 0>(b1, r1);
+                pair_part<N, 0, COUNT>(st, x, b0, vmask, skip);
+                finish(st, b0, j);
+                if (j + 1 >= n) break;
+                r = rec_of(j + 2);
+                next_part<N, 0>(b0, r);
+                pair_part<N, 0, COUNT>(st, x, b1, vmask, skip);
+                finish(st, b1, j + 1);
+            }
+        } else {
+            for (int j = 0; j < n; ++j) {
+                PairState<N> st;
+                next_part<N, 1>(b1, r);
+                pair_part<N, 0, COUNT>(st, x, b0, vmask, skip);
+                if constexpr (Pa::NP == 3) {
+                    next_part<N, 2>(b0, r);
+                    pair_part<N, 1, COUNT>(st, x, b1, vmask, skip);
+                    r = rec_of(j + 1);
+                    next_part<N, 0>(b1, r);
+                    pair_part<N, 2, COUNT>(st, x, b0, vmask, skip);
+                    finish(st, b0, j);
+#pragma unroll
+                    for (int e = 0; e < Pa::PS; ++e) b0[e] = b1[e];
+                } else {
+                    r = rec_of(j + 1);
+                    next_part<N, 0>(b0, r);
+                    pair_part<N, 1, COUNT>(st, x, b1, vmask, skip);
+                    finish(st, b1, j);
+                }
+            }
+        }
+        if ((km >> lane) & 1) {
+            const int o = s_pos[w][li + lane];
+            atomicOr(&s_kept[w][o / 32], 1u << (o % 32));
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < kItemChunks; ++c) {
+        const int o = c * kWave + lane;
+        if (o < ne) act[(e0 + o) * ngroups + grp] = uint8_t((s_kept[w][o / 32] >> (o % 32)) & 1u);
     }
     if constexpr (COUNT) {
-        if (lane == 0 && grp < ngroups) {
-            atomicAdd(&stats[0], n_exam);
-            atomicAdd(&stats[1], n_pass);
-            atomicAdd(&stats[2], static_cast<unsigned long long>(st[0]));
-            atomicAdd(&stats[3], static_cast<unsigned long long>(st[1]));
-            atomicAdd(&stats[4], static_cast<unsigned long long>(st[2]));
+        if (lane == 0) {
+            atomicAdd(&stats[0], static_cast<unsigned long long>(ne));
+            atomicAdd(&stats[1], static_cast<unsigned long long>(cnt));
+            atomicAdd(&stats[2], static_cast<unsigned long long>(n1));
+            atomicAdd(&stats[3], static_cast<unsigned long long>(n2));
+            atomicAdd(&stats[4], static_cast<unsigned long long>(nk));
         }
     }
-    if constexpr (OUT) {
-        if (valid) {
-            const int64_t o = perm[p];
-            out[o * 3 + 0] = f0;
-            out[o * 3 + 1] = f1;
-            out[o * 3 + 2] = f2;
-        }
+    if constexpr (!OUT) return;
+    if (!valid) return;
+    if (nit == 1) {
+        const int64_t o = perm[p];
+        out[o * 3 + 0] = f0;
+        out[o * 3 + 1] = f1;
+        out[o * 3 + 2] = f2;
+    } else {
+        float *pp = part + it * 3 * int64_t(tile);
+        pp[s] = f0;
+        pp[tile + s] = f1;
+        pp[2 * tile + s] = f2;
     }
 }
 
-template <int N>
-hipError_t mfma_prepare_n(ngd_cull *c, hipStream_t s)
+template <int N> hipError_t coef_n(ngd_cull *c, hipStream_t s)
 {
-    hipError_t e;
-    if (c->mrec_seq != c->build_seq) {
-        // once per cull build: per-Gaussian quadratic coefficients (unless
-        // the build launched them beside its own work) and the per-entry
-        // centred coefficients (the tile centres come with the cull's tile
-        // bounds)
-        if (c->coef_seq != c->build_seq && c->k > 0)
-            k_mfma_coef<N><<<unsigned((c->k + 255) / 256), 256, 0, s>>>(
-                c->k, c->grec.as<float>(), c->mrec.as<__bf16>(), c->mrow.as<float>());
-        if (c->total > 0)
-            k_mfma_entry<N><<<unsigned((c->total + 255) / 256), 256, 0, s>>>(
-                c->total, c->cand.as<int32_t>(), c->ent_tile.as<int32_t>(), c->grec.as<float>(),
-                c->mrow.as<float>(), c->tcen.as<float>(), c->eb0.as<bf16x8>(),
-                c->ebnd.as<float4>());
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        c->mrec_seq = c->build_seq;
-    }
-    return hipSuccess;
+    k_mfma_coef<N><<<unsigned((c->k + 255) / 256), 256, 0, s>>>(c->k, c->grec.as<float>(),
+                                                               c->mrec.as<f16x8>());
+    return hipGetLastError();
 }
 
 template <int N>
-hipError_t mfma_n(ngd_cull *c, float *out, unsigned long long *stats, hipStream_t s)
+hipError_t culled_n(const ngd_cull *c, float *out, unsigned long long *stats, hipStream_t s)
 {
     const int tile = c->params.tile;
     const unsigned gy = unsigned((tile + kMThreads - 1) / kMThreads);
     const float skip = float(-std::log2(double(c->params.tau)) + kSkipLog2Margin);
-    hipError_t e = mfma_prepare_n<N>(c, s);
-    if (e != hipSuccess) return e;
-    if (c->ntiles > 0) {
-        // every tile's workgroup writes its queries' colours (zeros for a
-        // tile with no candidates)
-        const dim3 grid(unsigned(c->ntiles), gy);
-        auto go = [&](auto kern, float *o, unsigned long long *st) {
-            kern<<<grid, kMThreads, 0, s>>>(c->q, tile, c->mrec.as<bf16x8>(), c->eb0.as<bf16x8>(),
-                                            c->ebnd.as<float4>(), c->tcen.as<float>(),
-                                            c->qs.as<float>(), c->grec.as<float>(),
-                                            c->tile_off.as<int64_t>(), c->cand.as<int32_t>(),
-                                            c->perm.as<int32_t>(), skip, c->act.as<uint8_t>(), o,
-                                            st);
+    if (c->nitems > 0) {
+        const dim3 grid(unsigned(c->nitems), gy);
+        k_filter_items<N><<<grid, kMThreads, 0, s>>>(
+            c->q, tile, c->mrec.as<f16x8>(), c->tcen.as<float>(), c->qs.as<float>(),
+            c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->item_tile.as<int32_t>(),
+            c->item_off.as<int64_t>(), skip, c->fmask.as<uint64_t>());
+        // no idle waves for tiles of fewer than 256 queries
+        const int threads = tile < kMThreads ? (tile + kWave - 1) / kWave * kWave : kMThreads;
+        auto go = [&](auto kern) {
+            kern<<<grid, threads, 0, s>>>(
+                c->q, tile, c->fmask.as<uint64_t>(), c->qs.as<float>(), c->grec.as<float>(),
+                c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->perm.as<int32_t>(),
+                c->item_tile.as<int32_t>(), c->item_off.as<int64_t>(), skip,
+                c->act.as<uint8_t>(), out, c->fpart.as<float>(), stats);
         };
         if (stats)
-            go(k_mfma_filter<N, false, true>, nullptr, stats);
+            go(k_eval_items<N, false, true>);
         else if (out)
-            go(k_mfma_filter<N, true, false>, out, nullptr);
+            go(k_eval_items<N, true, false>);
         else
-            go(k_mfma_filter<N, false, false>, nullptr, nullptr);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+            go(k_eval_items<N, false, false>);
     }
-    return hipSuccess;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !out) return e;
+    return launch_eval_reduce(c, out, s);
 }
 
 }  // namespace
 
 size_t mfma_rec_bytes(int n)
 {
-    const int t = n * (n + 1) / 2;
-    return size_t((t + 15) / 16) * 32 * sizeof(uint16_t);
+    return size_t((tri(n) + 7) / 8 + (n + 2 + 3) / 4) * sizeof(f16x8);
 }
-
-size_t mfma_entry_bytes() { return 4 * sizeof(bf16x8) + sizeof(float4); }
 
 hipError_t launch_mfma_coef(int n, ngd_cull *c, hipStream_t s)
 {
     if (c->k == 0) return hipSuccess;
     switch (n) {
-#define NGD_CASE(NN)                                                                           \
-    case NN:                                                                                   \
-        k_mfma_coef<NN><<<unsigned((c->k + 255) / 256), 256, 0, s>>>(                          \
-            c->k, c->grec.as<float>(), c->mrec.as<__bf16>(), c->mrow.as<float>());             \
-        return hipGetLastError();
+#define NGD_CASE(NN) \
+    case NN: return coef_n<NN>(c, s);
         NGD_CASE(1) NGD_CASE(2) NGD_CASE(3) NGD_CASE(4) NGD_CASE(5) NGD_CASE(6)
         NGD_CASE(7) NGD_CASE(8) NGD_CASE(9) NGD_CASE(10) NGD_CASE(11) NGD_CASE(12)
 #undef NGD_CASE
@@ -643,26 +721,13 @@ hipError_t launch_mfma_coef(int n, ngd_cull *c, hipStream_t s)
     }
 }
 
-hipError_t launch_mfma_prepare(const ngd_mixture *mix, ngd_cull *c, hipStream_t s)
+hipError_t launch_eval_culled(const ngd_mixture *mix, const ngd_cull *c, float *out,
+                              unsigned long long *stats, hipStream_t s)
 {
     if (c->q == 0 || c->ntiles == 0) return hipSuccess;
     switch (mix->n) {
 #define NGD_CASE(NN) \
-    case NN: return mfma_prepare_n<NN>(c, s);
-        NGD_CASE(1) NGD_CASE(2) NGD_CASE(3) NGD_CASE(4) NGD_CASE(5) NGD_CASE(6)
-        NGD_CASE(7) NGD_CASE(8) NGD_CASE(9) NGD_CASE(10) NGD_CASE(11) NGD_CASE(12)
-#undef NGD_CASE
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_eval_mfma(const ngd_mixture *mix, ngd_cull *c, float *out,
-                            unsigned long long *stats, hipStream_t s)
-{
-    if (c->q == 0 || c->ntiles == 0) return hipSuccess;
-    switch (mix->n) {
-#define NGD_CASE(NN) \
-    case NN: return mfma_n<NN>(c, out, stats, s);
+    case NN: return culled_n<NN>(c, out, stats, s);
         NGD_CASE(1) NGD_CASE(2) NGD_CASE(3) NGD_CASE(4) NGD_CASE(5) NGD_CASE(6)
         NGD_CASE(7) NGD_CASE(8) NGD_CASE(9) NGD_CASE(10) NGD_CASE(11) NGD_CASE(12)
 #undef NGD_CASE

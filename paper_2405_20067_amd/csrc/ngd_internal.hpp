@@ -33,9 +33,6 @@ inline int tri(int n) { return n * (n + 1) / 2; }
 // floats: m (n) | S' = sqrt(kHalfLog2e) L^-1 packed lower by rows (tri) |
 // alpha*c (3) | alpha (1) | c (3) | padding to a multiple of 4.
 inline int rec_stride(int n) { return (n + tri(n) + 7 + 3) / 4 * 4; }
-// 4-byte words per Gaussian of the forward's box: n lows, then n highs, as
-// float16, padded to a multiple of 16 bytes
-inline int box_stride(int n) { return (2 * n + 7) / 8 * 4; }
 
 // Device allocation through the configurable allocator; reports the
 // matching release function (NULL: hipFree) and its context.
@@ -166,9 +163,6 @@ struct ngd_cull {
     ngd::DevBuf grec;          // k x rec_stride float, sorted Gaussians
     ngd::DevBuf g_mr_s;             // n_proj x k float, sorted Gaussians
     ngd::DevBuf g_ub, g_lb;         // n_proj x k float, sorted: the interval test's limits
-    ngd::DevBuf gbox_u, gbox;       // k x box_stride(n) words, caller's order and
-                                    // sorted: per coordinate, the range outside which
-                                    // the forward keeps no query
     ngd::DevBuf masks;         // nchunks x tpad uint64
     ngd::DevBuf seg_cnt;       // nseg x ntiles int32 (counts, then prefixes)
     ngd::DevBuf tile_cnt;      // ntiles int32
@@ -208,16 +202,10 @@ struct ngd_cull {
     // second stream's work (the forward's per-Gaussian data)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_done = nullptr;
     hipEvent_t ev_sizes = nullptr;   // the list sizes have reached the host
-    // matrix-core forward: quadratic coefficients of the ordered Gaussians
-    ngd::DevBuf mrec;          // k x mfma_rec_bytes(n): bf16 hi / lo pairs
-    ngd::DevBuf mrow;          // k float: bound factor R'
+    // the forward's filter: quadratic coefficients of the ordered Gaussians
+    ngd::DevBuf mrec;          // k x mfma_rec_bytes(n)
     ngd::DevBuf tcen;          // ntiles x n float: centre of each tile's query box
-    ngd::DevBuf eb0;           // total x 64 B: centred constant / linear terms, bf16
-    ngd::DevBuf ebnd;          // total x 4 float: bound terms of each entry
-    int64_t build_seq = 0;     // builds of this handle
-    int64_t mrec_seq = -1;     // build the per-entry records belong to
-    int64_t coef_seq = -1;     // build the per-Gaussian coefficients (mrec, mrow) belong to
-    bool coef_next = false;    // the build in progress has launched them
+    ngd::DevBuf fmask;         // nitems x groups x kItemCands bits: the filter's survivors
 };
 
 namespace ngd {
@@ -260,29 +248,18 @@ hipError_t launch_cull_transpose_full(ngd_cull *c, hipStream_t s);
 
 hipError_t launch_eval_dense(const ngd_mixture *mix, const float *queries, int64_t q,
                              float *out, hipStream_t s);
-// Counting run of the culled forward (flags written, no colours): adds
-// (pairs examined, passed check 1, passed check 2, kept) to stats[0..3].
-hipError_t launch_eval_stats(const ngd_mixture *mix, const ngd_cull *c,
-                             unsigned long long *stats, hipStream_t s);
-// Culled forward; with out == nullptr only the keep/skip flags are written.
+// Adds the partial sums of tiles with several items, zeros tiles with none.
 hipError_t launch_eval_reduce(const ngd_cull *c, float *out, hipStream_t s);
-// Culled forward with the BF16 MFMA filter (eval_mfma.hip).  out: colours;
-// out == nullptr: keep/skip flags only; stats != nullptr: counting mode,
+// Culled forward (eval_mfma.hip).  out: colours; out == nullptr: keep/skip
+// flags only; stats != nullptr (with out == nullptr): counting mode,
 // stats[0..4] = (group-candidate pairs examined, not skipped by the matrix
-// filter, passed check 1, passed check 2, kept).  Builds the coefficient
-// records (c->mrec, c->mrow, reserved by the caller) once per cull build.
-// The matrix-core coefficient records of the current cull build (once per
-// build; launch_eval_mfma builds them itself when they are missing).
-hipError_t launch_mfma_prepare(const ngd_mixture *mix, ngd_cull *c, hipStream_t s);
-hipError_t launch_eval_mfma(const ngd_mixture *mix, ngd_cull *c, float *out,
-                            unsigned long long *stats, hipStream_t s);
-size_t mfma_rec_bytes(int n);
-// The per-Gaussian coefficients of the matrix-core forward (c->mrec, c->mrow)
-// from the cull's ordered records c->grec, on stream s.
-hipError_t launch_mfma_coef(int n, ngd_cull *c, hipStream_t s);
-size_t mfma_entry_bytes();
+// filter, passed check 1, passed check 2, kept).
 hipError_t launch_eval_culled(const ngd_mixture *mix, const ngd_cull *c, float *out,
-                              hipStream_t s);
+                              unsigned long long *stats, hipStream_t s);
+size_t mfma_rec_bytes(int n);
+// The filter's per-Gaussian records (c->mrec) from the cull's ordered records
+// c->grec, on stream s.
+hipError_t launch_mfma_coef(int n, ngd_cull *c, hipStream_t s);
 hipError_t launch_backward_dense(const ngd_mixture *mix, const float *queries, int64_t q,
                                  const float *grad_out, float *g_mean, float *g_factor,
                                  float *g_weight, float *g_colour, hipStream_t s);
