@@ -1285,9 +1285,9 @@ bool cull_reserve_front(ngd_cull *c)
         // the queries' k-d plan only with the k-d tiling (tiling 2 keeps the
         // caller's order); the Gaussians' with both
         if (c->params.tiling == 0)
-            ok &= kd_plan(c->kd_q, q, c->params.tile, std::min(c->params.tile, kWave)) &&
+            ok &= kd_plan(c->kd_q, q, c->params.tile, std::min(c->params.tile, kWave), P) &&
                   kd_reserve(c->kd_work, c->kd_q, q, P);
-        ok &= kd_plan(c->kd_g, k, kWave, kWave);
+        ok &= kd_plan(c->kd_g, k, kWave, kWave, P);
         ok = ok && kd_reserve(c->kd_work_g, c->kd_g, k, P);
         if (ok && !c->side) ok = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) == hipSuccess;
         if (ok && !c->ev_fork)

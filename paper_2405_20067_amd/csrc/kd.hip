@@ -12,9 +12,9 @@
 // rank split on a stable order, run boundaries depend only on
 // (n, leaf, sub), and the host lays them out level by level.
 //
-// Upper levels (nodes of more than kLocalMax points) run one level at a
-// time over all of the level's nodes, each node cut into slices (one
-// workgroup each), in five launches:
+// Levels with a node of more than kNodeMax points run one level at a time
+// over all of the level's nodes, each node cut into slices (one workgroup
+// each), in five launches:
 //   hist 0   per slice of kHistSlice points: the node's split projection
 //            (largest extent, from the node's min / max accumulated by the
 //            previous level's scatter; for the root by a pass over its
@@ -33,10 +33,15 @@
 //            and projection values move to the next buffer, the children's
 //            min / max are accumulated for the next split, and the node's
 //            histograms are cleared for the next level
-// Nodes of at most kLocalMax points finish their whole subtree in one
-// workgroup each (k_kd_local): the order and the sort keys stay in LDS, and
-// every level of the subtree is one bitonic sort of (run, key, position)
-// over blocks of the smallest power-of-two length that holds every run.
+// Levels of nodes of at most kNodeMax points take two launches: the selection
+// by a workgroup per node (k_kd_select), with the node's keys in registers and
+// the histograms in LDS, and the same scatter.
+// Subtrees finish in one workgroup each: nodes of at most kSubMax points in
+// k_kd_subtree, which holds the points' keys in LDS, for up to 16 projections
+// and runs that start at multiples of 64 points; otherwise nodes of at most
+// kLocalMax points in k_kd_local, where every level of the subtree is one
+// bitonic sort of (run, key, position) over blocks of the smallest
+// power-of-two length that holds every run.
 #include <algorithm>
 #include <map>
 #include <vector>
@@ -65,6 +70,15 @@ constexpr unsigned kWideLocalBlocks = 512;   // subtrees for the 512-thread vari
 constexpr int kExtRep = 16;
 constexpr int kRootPer = 4;        // points per thread of the root's extents
 constexpr int kLocalRuns = 128;     // runs per subtree (8-bit run ids)
+// Nodes selected by one workgroup, in 10 to 18 us, where three histogram
+// rounds and a count take 21 and their gaps; at 32,768 points it took 35.
+constexpr int kNodeMax = 16384;
+constexpr int kNodeThreads = 1024;
+static_assert(kNodeMax == 16 * kNodeThreads, "16 keys a thread");
+constexpr int kSubMax = 2048;
+constexpr int kSubThreads = 1024;
+constexpr int kSubProj = 16;
+constexpr int kSubChunks = kSubMax / kWave;
 constexpr int kLocalSplit = 64;     // runs split at one level of a subtree
 
 // node table row: start, size, n_left (-1: leaf), first slice, end slice,
@@ -227,7 +241,7 @@ __device__ void block_select(const int32_t *__restrict__ h, int width, uint32_t 
 // sel_pre / sel_rank: 3 x max_nodes, the state after rounds 0, 1, 2.
 __global__ __launch_bounds__(kHistThreads) void k_kd_hist(
     const int64_t *__restrict__ nodes, const int64_t *__restrict__ slices, int64_t node0,
-    int64_t hslice0, int64_t max_nodes, int64_t n, int P, int round,
+    int64_t hslice0, int64_t max_nodes, int64_t hist_nodes, int64_t n, int P, int round,
     const float *__restrict__ vin, const uint32_t *__restrict__ ext,
     uint32_t *__restrict__ ext_next, int32_t *__restrict__ dim, uint32_t *__restrict__ sel_pre,
     int64_t *__restrict__ sel_rank, int32_t *__restrict__ hist)
@@ -299,7 +313,7 @@ __global__ __launch_bounds__(kHistThreads) void k_kd_hist(
         const uint32_t p0 = round == 1 ? 0u : sel_pre[nd];
         const int64_t r0 = round == 1 ? nleft : sel_rank[nd];
         int64_t r1;
-        block_select<kHistThreads>(hist + ((round - 1) * max_nodes + nd) * kBins,
+        block_select<kHistThreads>(hist + ((round - 1) * hist_nodes + nd) * kBins,
                                    kWidth[round - 1], p0, r0, &pre, &r1);
         if (first && threadIdx.x == 0) {
             sel_pre[(round - 1) * max_nodes + nd] = pre;
@@ -318,7 +332,7 @@ __global__ __launch_bounds__(kHistThreads) void k_kd_hist(
         if (valid && match) atomicAdd(&h[(key >> shift) & mask], 1);
     }
     __syncthreads();
-    int32_t *nh = hist + (round * max_nodes + nd) * kBins;
+    int32_t *nh = hist + (round * hist_nodes + nd) * kBins;
     for (int b = threadIdx.x; b < kBins; b += kHistThreads)
         if (h[b]) atomicAdd(&nh[b], h[b]);
 }
@@ -328,8 +342,8 @@ __global__ __launch_bounds__(kHistThreads) void k_kd_hist(
 // that go left), then the slice's points below and equal to the pivot.
 __global__ __launch_bounds__(kThreads) void k_kd_count(
     const int64_t *__restrict__ nodes, const int64_t *__restrict__ slices, int64_t node0,
-    int64_t slice0, int64_t max_nodes, int64_t n, const float *__restrict__ vin,
-    const int32_t *__restrict__ dim, uint32_t *__restrict__ sel_pre,
+    int64_t slice0, int64_t max_nodes, int64_t hist_nodes, int64_t n,
+    const float *__restrict__ vin, const int32_t *__restrict__ dim, uint32_t *__restrict__ sel_pre,
     int64_t *__restrict__ sel_rank, const int32_t *__restrict__ hist, int64_t *__restrict__ cnt)
 {
     const int64_t sl = blockIdx.x;
@@ -348,7 +362,7 @@ __global__ __launch_bounds__(kThreads) void k_kd_count(
         }
         uint32_t pivot;
         int64_t r;
-        block_select<kThreads>(hist + (2 * max_nodes + nd) * kBins, kWidth[2],
+        block_select<kThreads>(hist + (2 * hist_nodes + nd) * kBins, kWidth[2],
                                sel_pre[max_nodes + nd], sel_rank[max_nodes + nd], &pivot, &r);
         if (sl + slice0 == nodes[nd * kNodeCols + 3] && threadIdx.x == 0) {
             sel_pre[2 * max_nodes + nd] = pivot;
@@ -370,26 +384,35 @@ __global__ __launch_bounds__(kThreads) void k_kd_count(
     }
 }
 
-// Block-wide exclusive prefix count of a flag (position order), with total.
-__device__ __forceinline__ int block_flag_scan(bool f, int *total)
+// Minima over the wave of V keys per lane, scattered as wave_reduce_scatter
+// does: lane 16 r + 15 holds those of keys [r V/4, (r + 1) V/4) in v[0 .. V/4).
+template <int V> __device__ __forceinline__ void wave_umin_scatter(uint32_t (&v)[V])
 {
-    __shared__ int wc[kThreads / kWave];
-    const int lane = lane_id(), w = threadIdx.x / kWave;
-    const uint64_t b = ballot(f);
-    const int before_lane = __popcll(b & lanemask_lt());
-    if (lane == 0) wc[w] = __popcll(b);
-    __syncthreads();
-    int before = 0, all = 0;
+    static_assert(V % 4 == 0, "keys in four equal rows");
+    constexpr int H = V / 2, Q = V / 4;
 #pragma unroll
-    for (int i = 0; i < kThreads / kWave; ++i) {
-        before += (i < w) ? wc[i] : 0;
-        all += wc[i];
+    for (int i = 0; i < H; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v[i], v[i + H], false, false);
+        v[i] = min(uint32_t(r[0]), uint32_t(r[1]));
     }
-    __syncthreads();
-    *total = all;
-    return before + before_lane;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v[i], v[i + Q], false, false);
+        v[i] = min(uint32_t(r[0]), uint32_t(r[1]));
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        v[i] = dpp_umin<kDppRowShr1>(v[i]);
+        v[i] = dpp_umin<kDppRowShr2>(v[i]);
+        v[i] = dpp_umin<kDppRowShr4>(v[i]);
+        v[i] = dpp_umin<kDppRowShr8>(v[i]);
+    }
 }
 
+// Moves a slice's points to their node's children: ranks inside the slice by
+// ballots, the projections four at a time (a thread's four points of each: 16
+// loads in flight), the children's min / max on the way.  Bound by the 2 x 68 B
+// a point.
 template <int PMAX>
 __global__ __launch_bounds__(kThreads) void k_kd_scatter(
     const int64_t *__restrict__ nodes, const int64_t *__restrict__ slices, int64_t node0,
@@ -397,16 +420,23 @@ __global__ __launch_bounds__(kThreads) void k_kd_scatter(
     const float *__restrict__ vin, const int32_t *__restrict__ dim,
     const uint32_t *__restrict__ prefix, const int64_t *__restrict__ rank,
     const int64_t *__restrict__ cnt, int32_t *__restrict__ idx_out, float *__restrict__ vout,
-    uint32_t *__restrict__ ext_next, int32_t *__restrict__ hist, int64_t max_nodes)
+    uint32_t *__restrict__ ext_next, int32_t *__restrict__ hist, int64_t max_nodes,
+    int64_t hist_nodes)
 {
+    constexpr int S = kSlice / kThreads, W = kThreads / kWave, JU = 4;
+    static_assert(S * W == 16, "one row of lanes scans the (strip, wave) counts");
+    __shared__ int lw[S * W], ew[S * W];
+    __shared__ uint32_t e4[W][4 * PMAX];
     const int64_t sl = blockIdx.x;
-    const int64_t s0 = slices[sl * kSliceCols + 0], len = slices[sl * kSliceCols + 1];
+    const int64_t s0 = slices[sl * kSliceCols + 0];
+    const int len = int(slices[sl * kSliceCols + 1]);
     const int64_t nd = slices[sl * kSliceCols + 2] - node0;
     const int64_t *row = nodes + nd * kNodeCols;
     const int64_t start = row[0], size = row[1], nleft = row[2];
+    const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
     const int d = dim[nd];
     if (d < 0) {   // a leaf: its points stay where they are
-        for (int64_t i = threadIdx.x; i < len; i += kThreads) {
+        for (int64_t i = tid; i < len; i += kThreads) {
             const int64_t pos = s0 + i;
             idx_out[pos] = idx_in ? idx_in[pos] : int32_t(pos);
 #pragma unroll
@@ -415,79 +445,282 @@ __global__ __launch_bounds__(kThreads) void k_kd_scatter(
         }
         return;
     }
+    uint32_t key[S];
+    int32_t id[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int i = u * kThreads + tid;
+        key[u] = i < len ? orderable(vin[int64_t(d) * n + s0 + i]) : 0u;
+        id[u] = i < len ? (idx_in ? idx_in[s0 + i] : int32_t(s0 + i)) : 0;
+    }
     const int64_t sb = row[3] - slice0;   // the node's first slice
-    if (sl == sb) {   // the node's histograms, clean for the next level
+    if (hist && sl == sb) {   // the node's histograms, clean for the next level
         for (int r = 0; r < 3; ++r)
-            for (int b = threadIdx.x; b < kBins; b += kThreads)
-                hist[(r * max_nodes + nd) * kBins + b] = 0;
+            for (int b = tid; b < kBins; b += kThreads) hist[(r * hist_nodes + nd) * kBins + b] = 0;
     }
     // points below the pivot, and equal to it, in the node's earlier slices
     int64_t l_mine = 0, e_mine = 0;
-    for (int64_t s = sb + threadIdx.x; s < sl; s += kThreads) {
+    for (int64_t s = sb + tid; s < sl; s += kThreads) {
         l_mine += cnt[s * 2 + 0];
         e_mine += cnt[s * 2 + 1];
     }
-    int64_t l_before, e_before;
-    block_exscan(l_mine, &l_before);
-    block_exscan(e_mine, &e_before);
     const uint32_t pivot = prefix[nd];
     const int64_t need = rank[nd];   // pivot-equal points that go left
-    const int64_t lo = l_before + (need < e_before ? need : e_before);
-    const int64_t ro = (s0 - start) - lo;
-    const int64_t ch = row[5];
-    const bool track = ext_next != nullptr && ch >= 0;
-    uint32_t lmin[PMAX], lmax[PMAX], rmin[PMAX], rmax[PMAX];
+    uint64_t bl[S], be[S];
 #pragma unroll
-    for (int j = 0; j < PMAX; ++j) {
-        lmin[j] = rmin[j] = 0xffffffffu;
-        lmax[j] = rmax[j] = 0u;
-    }
-    int64_t run_eq = 0, run_left = 0;
-    for (int64_t base = 0; base < len; base += kThreads) {
-        const int64_t i = base + threadIdx.x;
-        const bool valid = i < len;
-        const int64_t pos = s0 + i;
-        // the point's values first, so their loads overlap the scans
-        float v[PMAX];
-#pragma unroll
-        for (int j = 0; j < PMAX; ++j) v[j] = (valid && j < P) ? vin[int64_t(j) * n + pos] : 0.0f;
-        const int32_t id = valid ? (idx_in ? idx_in[pos] : int32_t(pos)) : 0;
-        const uint32_t key = valid ? orderable(vin[int64_t(d) * n + pos]) : 0xffffffffu;
-        const bool is_less = valid && key < pivot;
-        const bool is_eq = valid && key == pivot;
-        int teq, tleft;
-        const int64_t eq_rank = e_before + run_eq + block_flag_scan(is_eq, &teq);
-        const bool left = is_less || (is_eq && eq_rank < need);
-        const int64_t left_rank = run_left + block_flag_scan(left, &tleft);
-        const int64_t dest = left ? start + lo + left_rank : start + nleft + ro + (i - left_rank);
-        run_eq += teq;
-        run_left += tleft;
-        // every destination lies in the node's own run (the counts agree);
-        // the test only guards the buffers should they ever not
-        if (valid && dest >= start && dest < start + size) {
-            idx_out[dest] = id;
-#pragma unroll
-            for (int j = 0; j < PMAX; ++j) {
-                if (j < P) {
-                    vout[int64_t(j) * n + dest] = v[j];
-                    if (track) {
-                        const uint32_t k = orderable(v[j]);
-                        if (left) {
-                            lmin[j] = min(lmin[j], k);
-                            lmax[j] = max(lmax[j], k);
-                        } else {
-                            rmin[j] = min(rmin[j], k);
-                            rmax[j] = max(rmax[j], k);
-                        }
-                    }
-                }
-            }
+    for (int u = 0; u < S; ++u) {
+        const bool valid = u * kThreads + tid < len;
+        bl[u] = ballot(valid && key[u] < pivot);
+        be[u] = ballot(valid && key[u] == pivot);
+        if (lane == 0) {
+            lw[u * W + w] = __popcll(bl[u]);
+            ew[u * W + w] = __popcll(be[u]);
         }
     }
-    if (track) {   // uniform
-        uint32_t *plane = ext_plane(ext_next, max_nodes, P);
-        block_merge_ext<PMAX>(lmin, lmax, P, plane, ch);
-        block_merge_ext<PMAX>(rmin, rmax, P, plane, ch + 1);
+    int64_t l_before, e_before;   // the scans' barriers publish lw and ew too
+    block_exscan(l_mine, &l_before);
+    block_exscan(e_mine, &e_before);
+    const int lv = lw[lane & 15], ev = ew[lane & 15];
+    const int lx = wave_inclusive_scan(lane < 16 ? lv : 0) - lv;
+    const int ex = wave_inclusive_scan(lane < 16 ? ev : 0) - ev;
+    int64_t dst[S];
+    bool left[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int i = u * kThreads + tid;
+        const int at = uniform(u * W + w);
+        const bool less = (bl[u] >> lane) & 1, eq = (be[u] >> lane) & 1;
+        const int64_t lb =
+            l_before + __builtin_amdgcn_readlane(lx, at) + __popcll(bl[u] & lanemask_lt());
+        const int64_t eb =
+            e_before + __builtin_amdgcn_readlane(ex, at) + __popcll(be[u] & lanemask_lt());
+        left[u] = less || (eq && eb < need);
+        const int64_t lr = lb + (eb < need ? eb : need);
+        dst[u] = left[u] ? start + lr : start + nleft + (s0 + i - start - lr);
+        // every destination lies in the node's own run (the counts agree);
+        // the test only guards the buffers should they ever not
+        if (i >= len || dst[u] < start || dst[u] >= start + size) dst[u] = -1;
+        if (dst[u] >= 0) idx_out[dst[u]] = id[u];
+    }
+    const int64_t ch = row[5];
+    const bool track = ext_next != nullptr && ch >= 0;
+#pragma unroll
+    for (int j0 = 0; j0 < PMAX; j0 += JU) {
+        if (j0 >= P) break;   // uniform
+        float v[JU][S];
+#pragma unroll
+        for (int jj = 0; jj < JU; ++jj)
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                const int i = u * kThreads + tid;
+                v[jj][u] = (j0 + jj < P && i < len) ? vin[int64_t(j0 + jj) * n + s0 + i] : 0.0f;
+            }
+        // left min, left ~max, right min, right ~max
+        uint32_t mm[4 * JU];
+#pragma unroll
+        for (int e = 0; e < 4 * JU; ++e) mm[e] = 0xffffffffu;
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            if (dst[u] < 0) continue;
+#pragma unroll
+            for (int jj = 0; jj < JU; ++jj) {
+                if (j0 + jj < P) vout[int64_t(j0 + jj) * n + dst[u]] = v[jj][u];
+                const uint32_t k = orderable(v[jj][u]);
+                mm[4 * jj + 0] = min(mm[4 * jj + 0], left[u] ? k : 0xffffffffu);
+                mm[4 * jj + 1] = min(mm[4 * jj + 1], left[u] ? ~k : 0xffffffffu);
+                mm[4 * jj + 2] = min(mm[4 * jj + 2], left[u] ? 0xffffffffu : k);
+                mm[4 * jj + 3] = min(mm[4 * jj + 3], left[u] ? 0xffffffffu : ~k);
+            }
+        }
+        if (track) {
+            wave_umin_scatter<4 * JU>(mm);
+            if ((lane & 15) == 15)
+#pragma unroll
+                for (int e = 0; e < JU; ++e) e4[w][4 * j0 + (lane >> 4) * JU + e] = mm[e];
+        }
+    }
+    if (!track) return;   // uniform
+    __syncthreads();
+    uint32_t *plane = ext_plane(ext_next, max_nodes, P);
+    for (int t = tid; t < 4 * P; t += kThreads) {
+        uint32_t m = 0xffffffffu;
+#pragma unroll
+        for (int i = 0; i < W; ++i) m = min(m, e4[i][t]);
+        if (m == 0xffffffffu) continue;   // no point on that side
+        uint32_t *x = &plane[((ch + (t & 3) / 2) * P + t / 4) * 2 + (t & 1)];
+        if (t & 1)
+            atomicMax(x, ~m);
+        else
+            atomicMin(x, m);
+    }
+}
+
+// The selection of a level whose nodes have at most S x 1024 points, a
+// workgroup per node, its keys in registers: split projection from the node's
+// extents; a histogram of 2,048 equal steps over the node's range on it, in
+// floats (a monotone map: its rounding only moves equal values together); the
+// points of the bin that holds the pivot's rank, ranked by (key, position).
+// More than kListMax of them (ties, infinite ranges) are resolved by radix
+// rounds instead, whose first digit, mostly exponent, puts most of a wave's
+// counts on a few LDS words.  Then the slices' counts.
+constexpr int kListMax = 256;
+template <int S>
+__global__ __launch_bounds__(kNodeThreads) void k_kd_select(
+    const int64_t *__restrict__ nodes, int64_t slice0, int64_t n, int P,
+    const float *__restrict__ vin, const uint32_t *__restrict__ ext, int64_t max_nodes,
+    uint32_t *__restrict__ ext_next, int32_t *__restrict__ dim, uint32_t *__restrict__ pre_out,
+    int64_t *__restrict__ rank_out, int64_t *__restrict__ cnt)
+{
+    constexpr int W = kNodeThreads / kWave;
+    static_assert(kNodeThreads == kSlice, "a strip of points is a slice");
+    __shared__ int h[kBins];
+    __shared__ int lcnt[S][W], ecnt[S][W];
+    __shared__ float s_ext[32], s_lo[32];
+    __shared__ uint64_t s_list[kListMax];
+    __shared__ int s_num, s_need;
+    __shared__ uint32_t s_pivot;
+    const int64_t nd = blockIdx.x;
+    const int64_t *row = nodes + nd * kNodeCols;
+    const int64_t start = row[0];
+    const int size = int(row[1]), nleft = int(row[2]);
+    const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
+    if (nleft < 0) {   // a leaf
+        if (tid == 0) dim[nd] = -1;
+        return;
+    }
+    // the projection of largest extent, the first on ties: 16 lanes per
+    // projection, one for each plane of its slots
+    static_assert(kExtRep == 16, "a row of lanes reduces the planes");
+    if (tid < 16 * P) {
+        const int j = tid / 16;
+        const uint32_t *x = ext + int64_t(tid % 16) * max_nodes * 2 * P + (nd * P + j) * 2;
+        uint32_t lo = x[0], nhi = ~x[1];
+        lo = dpp_umin<kDppRowShr1>(lo), nhi = dpp_umin<kDppRowShr1>(nhi);
+        lo = dpp_umin<kDppRowShr2>(lo), nhi = dpp_umin<kDppRowShr2>(nhi);
+        lo = dpp_umin<kDppRowShr4>(lo), nhi = dpp_umin<kDppRowShr4>(nhi);
+        lo = dpp_umin<kDppRowShr8>(lo), nhi = dpp_umin<kDppRowShr8>(nhi);
+        if (tid % 16 == 15) {
+            s_ext[j] = from_orderable(~nhi) - from_orderable(lo);
+            s_lo[j] = from_orderable(lo);
+        }
+    }
+    for (int b = tid; b < kBins; b += kNodeThreads) h[b] = 0;
+    if (tid == 0) s_num = 0;
+    __syncthreads();
+    int d = 0;
+    {
+        // an extent that is not a number counts only in the first place
+        const float e = lane < P ? s_ext[lane & 31] : 0.0f;
+        uint32_t ek = e == e ? orderable(e) : (lane == 0 ? 0xffffffffu : 0u);
+        if (lane >= P) ek = 0u;
+        const uint32_t best = __builtin_amdgcn_readlane(wave_umax_dpp(ek), kWave - 1);
+        d = __builtin_ctzll(ballot(ek == best));
+    }
+    const float *vd = vin + int64_t(d) * n + start;
+    uint32_t key[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int i = s * kNodeThreads + tid;
+        key[s] = i < size ? orderable(vd[i]) : 0u;
+    }
+    if (tid == 0) dim[nd] = d;
+    const int64_t ch = row[5];
+    if (ext_next && ch >= 0) {   // both children's slots, every plane
+        for (int t = tid; t < 2 * P * kExtRep; t += kNodeThreads) {
+            uint32_t *x = ext_next + int64_t(t / (2 * P)) * max_nodes * 2 * P +
+                          (ch * P + t % (2 * P)) * 2;
+            x[0] = 0xffffffffu;
+            x[1] = 0u;
+        }
+    }
+    // the key of rank nleft, and how many of its equals go left
+    uint32_t pivot = 0;
+    int64_t need = nleft;
+    const float vlo = s_lo[d], ve = s_ext[d];
+    float scale = (ve > 0.0f && ve < INFINITY) ? float(kBins) / ve : 0.0f;
+    if (!(scale < INFINITY)) scale = 0.0f;
+    auto bin_of = [&](uint32_t k) {
+        const float t = (from_orderable(k) - vlo) * scale;
+        return t > 0.0f ? min(int(t), kBins - 1) : 0;   // not a number: 0
+    };
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        if (s * kNodeThreads + tid < size) atomicAdd(&h[bin_of(key[s])], 1);
+    __syncthreads();
+    uint32_t bin;
+    int64_t r;
+    block_select<kNodeThreads>(h, 11, 0u, nleft, &bin, &r);
+    const int num = h[bin];
+    if (num <= kListMax) {   // uniform
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int i = s * kNodeThreads + tid;
+            if (i < size && bin_of(key[s]) == int(bin)) {
+                const int slot = atomicAdd(&s_num, 1);
+                if (slot < kListMax) s_list[slot] = uint64_t(key[s]) << 32 | uint32_t(i);
+            }
+        }
+        __syncthreads();
+        if (tid < num) {
+            const uint64_t mine = s_list[tid];
+            int rank = 0, eq = 0;
+            for (int i = 0; i < num; ++i) {
+                const uint64_t x = s_list[i];
+                rank += x < mine;
+                eq += x < mine && (x >> 32) == (mine >> 32);
+            }
+            if (rank == r) {
+                s_pivot = uint32_t(mine >> 32);
+                s_need = eq;
+            }
+        }
+        __syncthreads();
+        pivot = s_pivot;
+        need = s_need;
+    } else {
+#pragma unroll
+        for (int rd = 0; rd < 3; ++rd) {
+            __syncthreads();
+            for (int b = tid; b < kBins; b += kNodeThreads) h[b] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                if (s * kNodeThreads + tid < size &&
+                    (rd == 0 || (key[s] >> ((kShift[rd] + kWidth[rd]) & 31)) == pivot))
+                    atomicAdd(&h[(key[s] >> kShift[rd]) & ((1u << kWidth[rd]) - 1u)], 1);
+            __syncthreads();
+            uint32_t pre;
+            int64_t rank;
+            block_select<kNodeThreads>(h, kWidth[rd], pivot, need, &pre, &rank);
+            pivot = pre;
+            need = rank;
+        }
+    }
+    if (tid == 0) {
+        pre_out[nd] = pivot;
+        rank_out[nd] = need;
+    }
+    // the slices' points below and equal to the pivot
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const bool valid = s * kNodeThreads + tid < size;
+        const uint64_t bl = ballot(valid && key[s] < pivot), be = ballot(valid && key[s] == pivot);
+        if (lane == 0) {
+            lcnt[s][w] = __popcll(bl);
+            ecnt[s][w] = __popcll(be);
+        }
+    }
+    __syncthreads();
+    if (tid < S && int64_t(tid) * kSlice < size) {
+        int l = 0, e = 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            l += lcnt[tid][i];
+            e += ecnt[tid][i];
+        }
+        const int64_t sl = row[3] - slice0 + tid;
+        cnt[sl * 2 + 0] = l;
+        cnt[sl * 2 + 1] = e;
     }
 }
 
@@ -868,6 +1101,328 @@ __global__ __launch_bounds__(kLocalThreads) void k_kd_local(
     }
 }
 
+// ---- subtrees of at most kSubMax points, one workgroup each ----------------
+// For runs that start at multiples of 64 points: a chunk of 64 positions then
+// lies in one run, and a wave holds two chunks, a lane one point of each.  The
+// points' keys stay in LDS where they were loaded (16 projections x 2,048
+// points: 128 KB, one workgroup per CU); the order is an array of 16-bit
+// indices.  Per level: chunk extents by wave minima, the run's split
+// projection from them; a histogram of 256 equal steps over the run's range on
+// it, in floats (a monotone map, so that any rounding only moves points
+// between bins the same way for all), whose bin holding the pivot's rank
+// leaves a handful of points that one wave ranks; more than 64 of them
+// (ties, infinite ranges) are resolved by a radix descent instead.  Stable
+// partition by (key, position) against the pivot's.  Bound by its vector
+// operations and the chain of these steps: 36 us for one subtree, 107 for 512
+// (two rounds of the CUs; 10-D, 2^20 queries), where the sorts of k_kd_local
+// took 58 to 100 and, with the level above that they left, 300.
+__global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
+    const int64_t *__restrict__ nodes, int64_t n, int P, int leaf,
+    const int32_t *__restrict__ idx_in, const float *__restrict__ vin,
+    int32_t *__restrict__ idx_out, float *__restrict__ vout)
+{
+    constexpr int kRuns = kSubChunks;           // at most one run per chunk
+    constexpr int kSplits = kSubChunks / 2;     // a run that splits has two chunks
+    constexpr int kHBins = 256;
+    __shared__ uint32_t val[kSubProj][kSubMax];
+    __shared__ uint16_t ord[2][kSubMax];
+    // histograms of the splitting runs; then the pivot bin's points of each
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kSplits][kHBins];
+    __shared__ uint32_t cext[kSubChunks][2 * kSubProj];   // minima, ~maxima
+    __shared__ int rs[2][kRuns], rl[2][kRuns], rn[2][kRuns], rsi[2][kRuns];
+    __shared__ int nruns[2], nsplit[2];
+    __shared__ int srun[2][kSplits];                      // a splitting run's index
+    __shared__ int sbin[kSplits], srank[kSplits], scnt[kSplits], lcnt[kSplits];
+    __shared__ int sdim[kSplits];
+    __shared__ uint64_t spiv[kSplits];
+    __shared__ int ccnt[kSubChunks];
+    __shared__ int crun[2][kSubChunks];
+    const int64_t *row = nodes + int64_t(blockIdx.x) * kNodeCols;
+    const int64_t start = row[0];
+    const int m = int(row[1]);
+    const int tid = threadIdx.x, w = uniform(tid / kWave), lane = lane_id();
+    constexpr int kPer = kSubMax / kSubThreads;   // chunks per wave
+    static_assert(kPer == 2, "two chunks per wave");
+
+    // a run of length len: n_left when it splits, -1 when it does not
+    auto split_of = [&](int len) {
+        if (len <= kWave) return -1;
+        const int u = len > leaf ? leaf : kWave;
+        return ((len + u - 1) / u + 1) / 2 * u;
+    };
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kSubThreads;
+#pragma unroll
+        for (int j = 0; j < kSubProj; ++j)
+            if (j < P && i < m) val[j][i] = orderable(vin[int64_t(j) * n + start + i]);
+        ord[0][i] = uint16_t(i);
+    }
+    for (int b = tid; b < kSplits * kHBins; b += kSubThreads) (&hist[0][0])[b] = 0;
+    // chunks past the end stay in run 0, without points
+    if (tid < 2 * kSubChunks) crun[tid / kSubChunks][tid % kSubChunks] = 0;
+    if (tid == 0) {
+        rs[0][0] = 0;
+        rl[0][0] = m;
+        rn[0][0] = split_of(m);
+        rsi[0][0] = rn[0][0] >= 0 ? 0 : -1;
+        srun[0][0] = 0;
+        nruns[0] = 1;
+        nsplit[0] = rn[0][0] >= 0 ? 1 : 0;
+    }
+    __syncthreads();
+    int cur = 0;
+    while (true) {
+        const int ns = nsplit[cur];
+        if (ns == 0) break;   // uniform
+        int o[kPer], run[kPer], si[kPer];
+        bool in[kPer];
+        // the chunks' extents
+        {
+            uint32_t mm[2][2 * kSubProj];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int c = kPer * w + u, pos = c * kWave + lane;
+                run[u] = uniform(crun[cur][c]);
+                si[u] = uniform(rsi[cur][run[u]]);
+                in[u] = pos < m;
+                o[u] = in[u] ? ord[cur][pos] : 0;
+#pragma unroll
+                for (int j = 0; j < kSubProj; ++j) {
+                    const bool ok = in[u] && j < P && si[u] >= 0;
+                    const uint32_t k = ok ? val[j][o[u]] : 0u;
+                    mm[u][j] = ok ? k : 0xffffffffu;
+                    mm[u][kSubProj + j] = ok ? ~k : 0xffffffffu;
+                }
+            }
+            auto put = [&](uint32_t (&v)[2 * kSubProj], int c) {
+                wave_umin_scatter<2 * kSubProj>(v);
+                if ((lane & 15) == 15)
+#pragma unroll
+                    for (int e = 0; e < kSubProj / 2; ++e)
+                        cext[c][(lane >> 4) * (kSubProj / 2) + e] = v[e];
+            };
+            if (run[0] == run[1]) {   // one reduction for both
+#pragma unroll
+                for (int e = 0; e < 2 * kSubProj; ++e) mm[0][e] = min(mm[0][e], mm[1][e]);
+                if (lane < 2 * kSubProj) cext[kPer * w + 1][lane] = 0xffffffffu;
+                put(mm[0], kPer * w);
+            } else {
+                put(mm[0], kPer * w);
+                put(mm[1], kPer * w + 1);
+            }
+        }
+        __syncthreads();
+        // split projections; histograms over the runs' ranges on them
+        uint32_t key[kPer];
+        int bin[kPer];
+        int dim = 0;
+        float vlo = 0.0f, scale = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            key[u] = 0;
+            bin[u] = -1;
+            if (si[u] < 0) continue;   // uniform
+            if (u == 0 || run[u] != run[0]) {
+                const int c0 = rs[cur][run[u]] / kWave;
+                const int c1 = (rs[cur][run[u]] + rl[cur][run[u]] + kWave - 1) / kWave;
+                const int j = lane & 15;
+                uint32_t lo = 0xffffffffu, nhi = 0xffffffffu;
+                for (int c = c0 + (lane >> 4); c < c1; c += 4) {
+                    lo = min(lo, cext[c][j]);
+                    nhi = min(nhi, cext[c][kSubProj + j]);
+                }
+                lo = min(lo, uint32_t(__shfl_xor(int(lo), 16, kWave)));
+                lo = min(lo, uint32_t(__shfl_xor(int(lo), 32, kWave)));
+                nhi = min(nhi, uint32_t(__shfl_xor(int(nhi), 16, kWave)));
+                nhi = min(nhi, uint32_t(__shfl_xor(int(nhi), 32, kWave)));
+                // the largest extent, the first on ties; one that is not a
+                // number counts only in the first place
+                const float flo = from_orderable(lo), fhi = from_orderable(~nhi);
+                const float e = fhi - flo;
+                uint32_t ek = e == e ? orderable(e) : (j == 0 ? 0xffffffffu : 0u);
+                if (j >= P) ek = 0u;
+                const uint32_t best = __builtin_amdgcn_readlane(wave_umax_dpp(ek), kWave - 1);
+                const int l = __builtin_ctzll(ballot(ek == best));
+                dim = l & 15;
+                vlo = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(flo), l));
+                const float ext = __uint_as_float(
+                    __builtin_amdgcn_readlane(__float_as_uint(e), l));
+                scale = (ext > 0.0f && ext < INFINITY) ? float(kHBins) / ext : 0.0f;
+                if (!(scale < INFINITY)) scale = 0.0f;
+                if (lane == 0) sdim[si[u]] = dim;
+            }
+            if (in[u]) {
+                key[u] = val[dim][o[u]];
+                const float t = (from_orderable(key[u]) - vlo) * scale;
+                bin[u] = t > 0.0f ? min(int(t), kHBins - 1) : 0;   // not a number: 0
+                atomicAdd(&hist[si[u]][bin[u]], 1u);
+            }
+        }
+        __syncthreads();
+        // the bin of each splitting run's pivot, a wave per run; the run
+        // tables of the next level, wave 15 (runs in order of their starts)
+        if (w < ns) {
+            const int r = srun[cur][w];
+            const int want = rn[cur][r];
+            const uint4 c4 = *reinterpret_cast<const uint4 *>(&hist[w][4 * lane]);
+            const int c[4] = {int(c4.x), int(c4.y), int(c4.z), int(c4.w)};
+            const int sum = c[0] + c[1] + c[2] + c[3];
+            int cum = wave_inclusive_scan(sum) - sum;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (want >= cum && want < cum + c[i]) {
+                    sbin[w] = 4 * lane + i;
+                    srank[w] = want - cum;
+                    scnt[w] = c[i];
+                }
+                cum += c[i];
+            }
+            if (lane == 0) lcnt[w] = 0;
+        }
+        if (w == kSubThreads / kWave - 1) {
+            const int nr = nruns[cur];
+            const bool has = lane < nr;
+            const int s0 = has ? rs[cur][lane] : 0, len = has ? rl[cur][lane] : 0;
+            const int nl = has ? rn[cur][lane] : -1;
+            const uint64_t sp = ballot(nl >= 0);
+            const int at = lane + __popcll(sp & lanemask_lt());
+            const int l0 = nl >= 0 ? nl : len, l1 = len - l0;
+            const int n0 = split_of(l0), n1 = split_of(l1);
+            const uint64_t b0 = ballot(has && n0 >= 0), b1 = ballot(has && nl >= 0 && n1 >= 0);
+            const int k0 = __popcll(b0 & lanemask_lt()) + __popcll(b1 & lanemask_lt());
+            const int nx = cur ^ 1;
+            if (has) {
+                rs[nx][at] = s0;
+                rl[nx][at] = l0;
+                rn[nx][at] = n0;
+                rsi[nx][at] = n0 >= 0 ? k0 : -1;
+                if (n0 >= 0) srun[nx][k0] = at;
+                if (nl >= 0) {
+                    const int k1 = k0 + (n0 >= 0 ? 1 : 0);
+                    rs[nx][at + 1] = s0 + l0;
+                    rl[nx][at + 1] = l1;
+                    rn[nx][at + 1] = n1;
+                    rsi[nx][at + 1] = n1 >= 0 ? k1 : -1;
+                    if (n1 >= 0) srun[nx][k1] = at + 1;
+                }
+                for (int c = s0 / kWave; c * kWave < s0 + len; ++c)
+                    crun[nx][c] = at + (nl >= 0 && c * kWave >= s0 + l0 ? 1 : 0);
+            }
+            if (lane == 0) {
+                nruns[nx] = nr + __popcll(sp);
+                nsplit[nx] = __popcll(b0) + __popcll(b1);
+            }
+        }
+        __syncthreads();
+        // that bin's points, listed over the run's histogram
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            if (bin[u] >= 0 && bin[u] == sbin[si[u]]) {
+                const int slot = atomicAdd(&lcnt[si[u]], 1);
+                if (slot < kWave)
+                    reinterpret_cast<uint64_t *>(hist[si[u]])[slot] =
+                        uint64_t(key[u]) << 16 | uint32_t((kPer * w + u) * kWave + lane);
+            }
+        }
+        __syncthreads();
+        // each run's pivot (key, position): the first point that goes right
+        if (w < ns) {
+            const int cnt = scnt[w];
+            uint64_t piv = 0;
+            if (cnt <= kWave) {
+                const uint64_t e =
+                    lane < cnt ? reinterpret_cast<const uint64_t *>(hist[w])[lane] : ~uint64_t(0);
+                int rank = 0;
+                for (int i = 0; i < cnt; ++i) {
+                    const uint64_t x =
+                        uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(e >> 32), i))) << 32 |
+                        uint32_t(__builtin_amdgcn_readlane(uint32_t(e), i));
+                    rank += x < e;
+                }
+                const int l = __builtin_ctzll(ballot(lane < cnt && rank == srank[w]) |
+                                              uint64_t(1) << 63);
+                piv = uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(e >> 32), l))) << 32 |
+                      uint32_t(__builtin_amdgcn_readlane(uint32_t(e), l));
+            } else {
+                // bit by bit over the run's keys, then the position among
+                // the keys equal to the pivot's
+                const int r = srun[cur][w], d = sdim[w];
+                const int s0 = rs[cur][r], s1 = s0 + rl[cur][r];
+                uint32_t pre = 0;
+                int rank = rn[cur][r];
+                for (int bit = 31; bit >= 0; --bit) {
+                    int zeros = 0;
+                    for (int b = s0; b < s1; b += kWave) {
+                        const uint32_t k = b + lane < s1 ? val[d][ord[cur][b + lane]] : 0u;
+                        const bool z = b + lane < s1 && (k >> bit) == (pre << 1);
+                        zeros += __popcll(ballot(z));
+                    }
+                    pre <<= 1;
+                    if (rank >= zeros) {
+                        rank -= zeros;
+                        pre |= 1u;
+                    }
+                }
+                int at = s0;
+                for (int b = s0; b < s1; b += kWave) {
+                    const bool q = b + lane < s1 && val[d][ord[cur][b + lane]] == pre;
+                    const uint64_t bq = ballot(q);
+                    const int c = __popcll(bq);
+                    if (rank >= 0 && rank < c) {
+                        const uint64_t hit =
+                            ballot(q && __popcll(bq & lanemask_lt()) == rank);
+                        at = b + __builtin_ctzll(hit);
+                    }
+                    rank -= c;
+                }
+                piv = uint64_t(pre) << 16 | uint32_t(at);
+            }
+            if (lane == 0) spiv[w] = piv;
+            // clean for the next level
+            *reinterpret_cast<uint4 *>(&hist[w][4 * lane]) = make_uint4(0, 0, 0, 0);
+        }
+        __syncthreads();
+        // stable partition of every splitting run
+        uint64_t bl[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int c = kPer * w + u;
+            const uint64_t mine = uint64_t(key[u]) << 16 | uint32_t(c * kWave + lane);
+            bl[u] = si[u] >= 0 ? ballot(in[u] && mine < spiv[si[u]]) : 0;
+            if (lane == 0) ccnt[c] = __popcll(bl[u]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int c = kPer * w + u, pos = c * kWave + lane;
+            int np = pos;
+            if (si[u] >= 0) {   // uniform
+                const int s0 = rs[cur][run[u]];
+                const int v = lane >= s0 / kWave && lane < c ? ccnt[lane & (kSubChunks - 1)] : 0;
+                const int before = wave_last(wave_inclusive_scan(v));
+                const int lr = before + __popcll(bl[u] & lanemask_lt());
+                np = (bl[u] >> lane) & 1 ? s0 + lr : s0 + rn[cur][run[u]] + (pos - s0 - lr);
+            }
+            if (in[u] && np < m) ord[cur ^ 1][np] = uint16_t(o[u]);
+        }
+        __syncthreads();
+        cur ^= 1;
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kSubThreads;
+        if (i >= m) break;
+        const int o = ord[cur][i];
+        idx_out[start + i] = idx_in ? idx_in[start + o] : int32_t(start + o);
+        if (vout) {
+#pragma unroll
+            for (int j = 0; j < kSubProj; ++j)
+                if (j < P) vout[int64_t(j) * n + start + i] = from_orderable(val[j][o]);
+        }
+    }
+}
+
 inline unsigned nb(int64_t n, int per) { return unsigned((n + per - 1) / per); }
 
 // Leaves of a run of `size` points (the split rule above).
@@ -885,19 +1440,22 @@ int64_t count_leaves(int64_t size, int leaf, int sub, std::map<int64_t, int64_t>
 
 }  // namespace
 
-bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub)
+bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub, int P)
 {
-    if (pl.n == n && pl.leaf == leaf && pl.sub == sub) return true;
+    // subtrees in k_kd_subtree: every run then starts at a multiple of 64
+    const bool subtree = P <= kSubProj && sub == kWave && leaf % kWave == 0;
+    if (pl.n == n && pl.leaf == leaf && pl.sub == sub && pl.subtree == subtree) return true;
     pl.n = n;
     pl.leaf = leaf;
     pl.sub = sub;
+    pl.subtree = subtree;
     pl.levels.clear();
     pl.local = KdLevel{};
     pl.has_local = false;
     std::vector<int64_t> nodes, slices;
     std::vector<std::pair<int64_t, int64_t>> cur;
     if (n > 0) cur.push_back({0, n});
-    int64_t max_nodes = 0, max_slices = 0;
+    int64_t max_nodes = 0, max_slices = 0, hist_nodes = 0;
     std::map<int64_t, int64_t> memo;
     while (true) {
         bool any = false;
@@ -905,11 +1463,11 @@ bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub)
         for (auto &nd : cur) {
             any |= nd.second > sub;
             biggest = std::max(biggest, nd.second);
-            if (nd.second <= kLocalMax)
+            if (!subtree && nd.second <= kLocalMax)
                 most_leaves = std::max(most_leaves, count_leaves(nd.second, leaf, sub, memo));
         }
         if (!any) break;
-        if (biggest <= kLocalMax && most_leaves <= kLocalRuns) {
+        if (subtree ? biggest <= kSubMax : biggest <= kLocalMax && most_leaves <= kLocalRuns) {
             // the rest of every subtree in one workgroup each
             pl.local.node0 = int64_t(nodes.size()) / kNodeCols;
             for (auto &nd : cur)
@@ -919,6 +1477,8 @@ bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub)
             break;
         }
         KdLevel lv;
+        lv.biggest = biggest;
+        const bool sliced = biggest > kNodeMax;
         lv.node0 = int64_t(nodes.size()) / kNodeCols;
         lv.slice0 = int64_t(slices.size()) / kSliceCols;
         std::vector<std::pair<int64_t, int64_t>> next;
@@ -952,7 +1512,7 @@ bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub)
         for (int64_t nd = lv.node0; nd < lv.node1; ++nd) {
             const int64_t st = nodes[nd * kNodeCols + 0], sz = nodes[nd * kNodeCols + 1];
             nodes[nd * kNodeCols + 6] = int64_t(slices.size()) / kSliceCols;
-            for (int64_t s = st; s < st + sz; s += kHistSlice) {
+            for (int64_t s = st; sliced && s < st + sz; s += kHistSlice) {
                 slices.push_back(s);
                 slices.push_back(std::min<int64_t>(kHistSlice, st + sz - s));
                 slices.push_back(nd);
@@ -961,6 +1521,7 @@ bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub)
         }
         lv.hslice1 = int64_t(slices.size()) / kSliceCols;
         max_nodes = std::max(max_nodes, lv.node1 - lv.node0);
+        if (sliced) hist_nodes = std::max(hist_nodes, lv.node1 - lv.node0);
         max_slices = std::max(max_slices, lv.slice1 - lv.slice0);
         pl.levels.push_back(lv);
         cur.swap(next);
@@ -972,6 +1533,7 @@ bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub)
     }
     pl.max_nodes = max_nodes;
     pl.max_slices = max_slices;
+    pl.hist_nodes = hist_nodes;
     if (!pl.node_tab.ensure(sizeof(int64_t) * std::max<size_t>(nodes.size(), 1)) ||
         !pl.slice_tab.ensure(sizeof(int64_t) * std::max<size_t>(slices.size(), 1))) {
         pl.n = -1;
@@ -992,6 +1554,7 @@ bool kd_reserve(KdWork &w, const KdPlan &pl, int64_t n, int P)
 {
     const int64_t nn = std::max<int64_t>(n, 1);
     const int64_t ms = std::max<int64_t>(pl.max_slices, 1), mn = std::max<int64_t>(pl.max_nodes, 1);
+    const int64_t mh = std::max<int64_t>(pl.hist_nodes, 1);
     bool ok = true;
     ok &= w.idx[0].ensure(sizeof(int32_t) * nn);
     ok &= w.idx[1].ensure(sizeof(int32_t) * nn);
@@ -999,7 +1562,7 @@ bool kd_reserve(KdWork &w, const KdPlan &pl, int64_t n, int P)
     ok &= w.val[1].ensure(sizeof(float) * P * nn);
     ok &= w.ext[0].ensure(sizeof(uint32_t) * 2 * P * mn * kExtRep);
     ok &= w.ext[1].ensure(sizeof(uint32_t) * 2 * P * mn * kExtRep);
-    ok &= w.hist.ensure(sizeof(int32_t) * 3 * kBins * mn);
+    ok &= w.hist.ensure(sizeof(int32_t) * 3 * kBins * mh);
     ok &= w.cnt.ensure(sizeof(int64_t) * 2 * ms);
     ok &= w.dim.ensure(sizeof(int32_t) * mn);
     ok &= w.prefix.ensure(sizeof(uint32_t) * 3 * mn);
@@ -1024,16 +1587,17 @@ hipError_t kd_start(KdRun &r, const KdPlan &pl, KdWork &w, int P, const float *v
     r.done = n == 0;
     if (n == 0) return hipSuccess;
     const int64_t mn = std::max<int64_t>(pl.max_nodes, 1), ms = std::max<int64_t>(pl.max_slices, 1);
+    const int64_t mh = std::max<int64_t>(pl.hist_nodes, 1);
     if (pl.n != n || (pl.levels.empty() && !pl.has_local) || P < 1 || P > 32 ||
         w.idx[0].cap < sizeof(int32_t) * size_t(n) || w.idx[1].cap < sizeof(int32_t) * size_t(n) ||
         w.val[0].cap < sizeof(float) * P * size_t(n) ||
         w.val[1].cap < sizeof(float) * P * size_t(n) ||
         w.ext[0].cap < sizeof(uint32_t) * 2 * P * size_t(mn) * kExtRep ||
         w.ext[1].cap < sizeof(uint32_t) * 2 * P * size_t(mn) * kExtRep ||
-        w.hist.cap < sizeof(int32_t) * 3 * kBins * size_t(mn) ||
+        w.hist.cap < sizeof(int32_t) * 3 * kBins * size_t(mh) ||
         w.cnt.cap < sizeof(int64_t) * 2 * size_t(ms) || w.dim.cap < sizeof(int32_t) * size_t(mn) ||
         w.prefix.cap < sizeof(uint32_t) * 3 * size_t(mn) ||
-        w.rank.cap < sizeof(int64_t) * 3 * size_t(mn)) {
+        w.rank.cap < sizeof(int64_t) * 3 * size_t(mn) || (pl.subtree && P > kSubProj)) {
         r.done = true;
         return hipErrorInvalidValue;
     }
@@ -1049,6 +1613,7 @@ hipError_t kd_step(KdRun &r)
     const int64_t n = r.n;
     const hipStream_t s = r.s;
     const int64_t mn = std::max<int64_t>(pl.max_nodes, 1);
+    const int64_t mh = std::max<int64_t>(pl.hist_nodes, 1);
     const int64_t *nodes = pl.node_tab.as<int64_t>();
     const int64_t *slices = pl.slice_tab.as<int64_t>();
     int32_t *hist = w.hist.as<int32_t>();
@@ -1060,8 +1625,8 @@ hipError_t kd_step(KdRun &r)
     const size_t phase = r.phase++;
     if (phase == 0) {   // the root's extents
         if (nlev == 0) return hipSuccess;
-        k_kd_zero<<<nb(3 * kBins * mn, kThreads), kThreads, 0, s>>>(
-            hist, 3 * kBins * mn, w.ext[0].as<uint32_t>(), P, mn, r.root_given ? 1 : 0);
+        k_kd_zero<<<nb(3 * kBins * mh, kThreads), kThreads, 0, s>>>(
+            hist, 3 * kBins * mh, w.ext[0].as<uint32_t>(), P, mn, r.root_given ? 1 : 0);
         if (r.root_given) return hipGetLastError();
         const unsigned nr = nb(n, kThreads * kRootPer);
         if (P <= 16)
@@ -1073,28 +1638,38 @@ hipError_t kd_step(KdRun &r)
     if (phase <= nlev) {   // upper level phase - 1
         const size_t li = phase - 1;
         const KdLevel &lv = pl.levels[li];
-        const int64_t ns = lv.slice1 - lv.slice0;
         const int64_t *nt = nodes + lv.node0 * kNodeCols;
         const int64_t *st = slices + lv.slice0 * kSliceCols;
         uint32_t *ext = w.ext[li & 1].as<uint32_t>();
         uint32_t *ext_next = (li + 1 < nlev) ? w.ext[(li + 1) & 1].as<uint32_t>() : nullptr;
-        const int64_t *hst = slices + lv.hslice0 * kSliceCols;
-        const unsigned nhs = unsigned(lv.hslice1 - lv.hslice0);
-        for (int rd = 0; rd < 3; ++rd)
-            k_kd_hist<<<nhs, kHistThreads, 0, s>>>(nt, hst, lv.node0, lv.hslice0, mn, n, P, rd,
-                                                   r.vin, ext, ext_next, dim, prefix, rank, hist);
-        k_kd_count<<<unsigned(ns), kThreads, 0, s>>>(nt, st, lv.node0, lv.slice0, mn, n, r.vin,
-                                                     dim, prefix, rank, hist, cnt);
         int32_t *idx_out = w.idx[r.cur].as<int32_t>();
         float *vout = w.val[r.cur].as<float>();
+        const int64_t ns = lv.slice1 - lv.slice0;
+        const int64_t *hst = slices + lv.hslice0 * kSliceCols;
+        const unsigned nhs = unsigned(lv.hslice1 - lv.hslice0);
+        const bool one = lv.biggest <= kNodeMax;   // the selection in one launch
+        if (one) {
+            auto go = [&](auto kern) {
+                kern<<<unsigned(lv.node1 - lv.node0), kNodeThreads, 0, s>>>(
+                    nt, lv.slice0, n, P, r.vin, ext, mn, ext_next, dim, prefix + 2 * mn,
+                    rank + 2 * mn, cnt);
+            };
+            if (lv.biggest <= 4 * kNodeThreads) go(k_kd_select<4>);
+            else go(k_kd_select<16>);
+        }
+        for (int rd = 0; !one && rd < 3; ++rd)
+            k_kd_hist<<<nhs, kHistThreads, 0, s>>>(nt, hst, lv.node0, lv.hslice0, mn, mh, n, P, rd,
+                                                   r.vin, ext, ext_next, dim, prefix, rank, hist);
+        if (!one) k_kd_count<<<unsigned(ns), kThreads, 0, s>>>(nt, st, lv.node0, lv.slice0, mn, mh, n, r.vin,
+                                                     dim, prefix, rank, hist, cnt);
         if (P <= 16)
             k_kd_scatter<16><<<unsigned(ns), kThreads, 0, s>>>(
                 nt, st, lv.node0, lv.slice0, n, P, r.idx_in, r.vin, dim, prefix + 2 * mn,
-                rank + 2 * mn, cnt, idx_out, vout, ext_next, hist, mn);
+                rank + 2 * mn, cnt, idx_out, vout, ext_next, one ? nullptr : hist, mn, mh);
         else
             k_kd_scatter<32><<<unsigned(ns), kThreads, 0, s>>>(
                 nt, st, lv.node0, lv.slice0, n, P, r.idx_in, r.vin, dim, prefix + 2 * mn,
-                rank + 2 * mn, cnt, idx_out, vout, ext_next, hist, mn);
+                rank + 2 * mn, cnt, idx_out, vout, ext_next, one ? nullptr : hist, mn, mh);
         r.idx_in = idx_out;
         r.vin = vout;
         r.cur ^= 1;
@@ -1105,6 +1680,11 @@ hipError_t kd_step(KdRun &r)
     if (pl.has_local) {
         const int64_t *nt = nodes + pl.local.node0 * kNodeCols;
         const unsigned nl = unsigned(pl.local.node1 - pl.local.node0);
+        if (pl.subtree) {
+            k_kd_subtree<<<nl, kSubThreads, 0, s>>>(nt, n, P, pl.leaf, r.idx_in, r.vin, r.perm,
+                                                    r.vals_sorted);
+            return hipGetLastError();
+        }
         // 512 threads per subtree when every subtree's workgroup is resident
         // at once with them (three per CU), else 256 (seven per CU)
         auto go = [&](auto kern, int threads) {

@@ -55,6 +55,7 @@ struct DevBuf {
 // out on the host from (n, leaf, sub) alone and kept while they stay the same.
 struct KdLevel {
     int64_t node0 = 0, node1 = 0, slice0 = 0, slice1 = 0, hslice0 = 0, hslice1 = 0;
+    int64_t biggest = 0;           // points of its largest node
 };
 struct KdPlan {
     int64_t n = -1;
@@ -62,7 +63,9 @@ struct KdPlan {
     std::vector<KdLevel> levels;   // upper levels
     bool has_local = false;
     KdLevel local;                 // node rows of the subtree workgroups
+    bool subtree = false;          // finished by the subtree kernel whose keys stay in LDS
     int64_t max_nodes = 0, max_slices = 0;
+    int64_t hist_nodes = 0;        // nodes of the levels cut into slices
     DevBuf node_tab;    // rows: start, size, n_left (-1 leaf), slice begin / end, child,
                         // histogram slice begin / end
     DevBuf slice_tab;   // rows: start, length, node
@@ -71,7 +74,7 @@ struct KdWork {
     DevBuf idx[2], val[2], ext[2];
     DevBuf hist, cnt, dim, prefix, rank;
 };
-bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub);
+bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub, int P);
 bool kd_reserve(KdWork &w, const KdPlan &pl, int64_t n, int P);
 // Orders n points with P <= 32 projections (vals: P x n, point order) and
 // writes the order (position -> point) to perm and, when vals_sorted is not

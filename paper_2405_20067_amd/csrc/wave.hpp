@@ -193,6 +193,12 @@ __device__ __forceinline__ uint32_t wave_umin_dpp(uint32_t v)
     return v;
 }
 
+// One step of such a running minimum.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_umin(uint32_t v)
+{
+    return min(v, uint32_t(__builtin_amdgcn_update_dpp(-1, int(v), CTRL, 0xf, 0xf, false)));
+}
+
 __device__ __forceinline__ uint32_t wave_umax_dpp(uint32_t v)
 {
     v = max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kDppRowShr1, 0xf, 0xf, false)));

@@ -1,0 +1,71 @@
+"""The k-d order at the edges of its kernels, bit for bit against the CPU
+re-implementation: subtree sizes (2,048 points; 1,024 where runs do not start
+at multiples of 64 or there are more than 16 projections), nodes selected by
+one workgroup (16,384), tiles that leave uneven runs, and points whose
+projections tie in whole runs, which the histogram's bins cannot separate."""
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import case, dev
+from paper_2405_20067_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _check(mix, x, proj, tile):
+    from paper_2405_20067_amd import ngd
+    k, n = mix["mean"].shape
+    m = ngd.Mixture(n, k)
+    m.update(*(dev(mix[f]) for f in ("mean", "factor", "weight", "colour")))
+    p = ngd.default_params()
+    p.tile, p.n_proj = tile, proj.shape[0]
+    p.key_proj = min(p.key_proj, p.n_proj)
+    xd = dev(x)
+    c = ngd.Cull()
+    for _ in range(2):   # a rebuild in the same buffers gives the same
+        got = c.build(m, xd, proj, p).export()
+        want = oracle.cull(mix["mean"], mix["factor"], x, proj, tau=p.tau, tile=tile,
+                           key_proj=p.key_proj)
+        for f in ("perm", "gperm", "tile_off", "cand"):
+            np.testing.assert_array_equal(got[f], want[f], err_msg=f)
+
+
+@pytest.mark.parametrize("q", [65, 128, 2047, 2048, 2049, 4097, 16384, 16385, 40001])
+@pytest.mark.parametrize("tile", [64, 192, 256, 1024])
+def test_sizes(torch_cuda, q, tile):
+    # as many Gaussians as make their own order cross the same sizes
+    mix, x, proj = case(3, max(65, q // 2), q, seed=q + tile)
+    _check(mix, x, proj, tile)
+
+
+@pytest.mark.parametrize("n_proj", [1, 5, 16, 17, 32])
+def test_projection_counts(torch_cuda, n_proj):
+    mix, x, _ = case(4, 2500, 9000, seed=n_proj)
+    _check(mix, x, inputs.gen_projections(4, n_proj, seed=3), 256)
+
+
+@pytest.mark.parametrize("q", [1500, 5000, 30000])
+@pytest.mark.parametrize("what", ["same", "few", "steps", "one-off"])
+def test_ties(torch_cuda, q, what):
+    mix, x, proj = case(3, 3000, q, seed=q)
+    rng = np.random.default_rng(q)
+    if what == "same":          # every point the same
+        x = np.repeat(x[:1], q, axis=0)
+    elif what == "few":         # runs of equal points
+        x = x[rng.integers(0, 7, q)]
+    elif what == "steps":       # a coarse grid
+        x = np.round(x * 4.0) / 4.0
+    else:                       # one far point squeezes the rest into a bin
+        x[q // 2] = 1e6
+    mix["mean"][:] = x[rng.integers(0, q, 3000)]
+    _check(mix, np.ascontiguousarray(x, dtype=np.float32), proj, 256)
