@@ -19,6 +19,8 @@
 // reduces them across lanes once and writes them to the item's slot.
 // k_backward_finalize then adds each Gaussian's items in item order and
 // applies S^T.  Dense: one workgroup per Gaussian over all queries.
+#include <algorithm>
+
 #include "ngd_internal.hpp"
 #include "wave.hpp"
 
@@ -354,11 +356,14 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_finalize(
     g_colour[gi * 3 + 2] = alpha * h2;
 }
 
+// The upstream gradient in tile order; also clears the k kept-entry counts.
 __global__ __launch_bounds__(256) void k_gather_grad(int64_t q, const int32_t *__restrict__ perm,
                                                      const float *__restrict__ grad_out,
-                                                     float *__restrict__ gs)
+                                                     float *__restrict__ gs, int64_t k,
+                                                     int32_t *__restrict__ a_cnt)
 {
     const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (p < k) a_cnt[p] = 0;
     if (p >= q) return;
     const int64_t o = perm[p];
     gs[p] = grad_out[o * 3 + 0];
@@ -394,10 +399,8 @@ template <int N>
 hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, float *gm,
                     float *gf, float *gw, float *gc, hipStream_t s)
 {
-    if (c->q > 0) {
-        k_gather_grad<<<unsigned((c->q + 255) / 256), 256, 0, s>>>(
-            c->q, c->perm.as<int32_t>(), grad_out, c->gs.as<float>());
-    }
+    k_gather_grad<<<unsigned((std::max(c->q, c->k) + 255) / 256), 256, 0, s>>>(
+        c->q, c->perm.as<int32_t>(), grad_out, c->gs.as<float>(), c->k, c->a_cnt.as<int32_t>());
     hipError_t err = launch_backward_prepare(c, s);
     if (err != hipSuccess) return err;
     if (c->gitems_cap > 0) {

@@ -332,7 +332,7 @@ int ngd_mixture_destroy(ngd_mixture *mix)
 
 static void cull_release(ngd_cull *c)
 {
-    DevBuf *bufs[] = {&c->proj,    &c->qr,       &c->range_part, &c->qrange,  &c->g_mr,
+    DevBuf *bufs[] = {&c->qr,       &c->range_part, &c->gext_part, &c->qrange,  &c->g_mr,
                       &c->g_thr,   &c->keys0,    &c->keys1,      &c->vals0,   &c->vals1,
                       &c->radix_hist, &c->radix_off, &c->perm,   &c->gperm,   &c->qs,
                       &c->gs,      &c->tile_lo,  &c->tile_hi, &c->tbnd,   &c->sbnd,   &c->qr_s,    &c->grec,    &c->g_mr_s,
@@ -436,16 +436,11 @@ int ngd_cull_build(const ngd_mixture *mix, const float *queries, int64_t q,
          hipEventCreateWithFlags(&c->ev_sizes, hipEventDisableTiming) != hipSuccess))
         return bail(fail(NGD_E_NOMEM, "ngd_cull_build: device workspace allocation failed"));
     hipStream_t s = S(stream);
-    hipError_t e = hipMemcpyAsync(c->proj.p, proj, sizeof(float) * p->n_proj * mix->n,
-                                  hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_cull_build_front(c, mix, queries, s);
+    hipError_t e = launch_cull_build_front(c, mix, queries, proj, s);
     if (e != hipSuccess) return bail(hip_fail(e, "ngd_cull_build (projections, sort, test)"));
-    // the only device -> host read: list sizes, gathered into one copy
-    e = launch_gather_sizes(c, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->stats_host, c->stats.as<int64_t>() + 1, 3 * sizeof(int64_t),
-                           hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipEventRecord(c->ev_sizes, s);
+    // the only thing the host reads: the list sizes, which the front half's
+    // last kernel has stored in pinned memory
+    e = hipEventRecord(c->ev_sizes, s);
     // The lists go on at once into the buffers as they are (a rebuild of
     // similar size needs no more), so the device does not wait for the host
     // to read the sizes; lists that do not fit are built again below.

@@ -36,17 +36,29 @@ constexpr int kThreads = 256;
 
 // Per Gaussian: its projected means and the interval test's squared
 // half-widths (Eq. 3-4).
+// The projection vectors as a kernel argument: no copy to the device ahead of
+// the kernels, and uniform loads.
+template <int N> struct ProjArgs {
+    float r[NGD_MAX_PROJ * N];
+};
+
+// Also per block each projection's min and max key of its projected means,
+// for the root of their k-d order (part null: not needed).
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
                                                          const float *__restrict__ rec, int R,
                                                          const float *__restrict__ lfac,
-                                                         const float *__restrict__ proj,
+                                                         const ProjArgs<N> proj,
                                                          float kappa2, float *__restrict__ g_mr,
-                                                         float *__restrict__ g_thr)
+                                                         float *__restrict__ g_thr,
+                                                         uint32_t *__restrict__ part)
 {
     constexpr int T = N * (N + 1) / 2;
-    const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (i >= k) return;
+    __shared__ uint32_t smin[kThreads / kWave][NGD_MAX_PROJ], smax[kThreads / kWave][NGD_MAX_PROJ];
+    const int64_t i0 = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    const bool valid = i0 < k;
+    const int64_t i = valid ? i0 : k - 1;   // repeats the last one
+    const int w = threadIdx.x / kWave;
     float m[N];
     double L[T];
 #pragma unroll
@@ -54,11 +66,20 @@ __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
 #pragma unroll
     for (int e = 0; e < T; ++e) L[e] = lfac[i * T + e];
     for (int j = 0; j < P; ++j) {
-        const float *r = proj + j * N;
+        float r[N];
+#pragma unroll
+        for (int a = 0; a < N; ++a) r[a] = proj.r[j * N + a];
         float acc = 0.0f;
 #pragma unroll
         for (int a = 0; a < N; ++a) acc = fmaf(m[a], r[a], acc);
-        g_mr[j * k + i] = acc;
+        if (valid) g_mr[j * k + i] = acc;
+        if (part) {   // uniform
+            const uint32_t lo = wave_umin_dpp(orderable(acc)), hi = wave_umax_dpp(orderable(acc));
+            if (lane_id() == kWave - 1) {
+                smin[w][j] = lo;
+                smax[w][j] = hi;
+            }
+        }
         double s2 = 0.0;
 #pragma unroll
         for (int b = 0; b < N; ++b) {
@@ -68,7 +89,20 @@ __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
             s2 = fma(u, u, s2);
         }
         const float s2f = float(s2);
-        g_thr[j * k + i] = kappa2 * s2f;
+        if (valid) g_thr[j * k + i] = kappa2 * s2f;
+    }
+    if (!part) return;
+    __syncthreads();
+    if (int(threadIdx.x) < P) {
+        const int j = threadIdx.x;
+        uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+        for (int e = 0; e < kThreads / kWave; ++e) {
+            lo = min(lo, smin[e][j]);
+            hi = max(hi, smax[e][j]);
+        }
+        part[(int64_t(blockIdx.x) * P + j) * 2 + 0] = lo;
+        part[(int64_t(blockIdx.x) * P + j) * 2 + 1] = hi;
     }
 }
 
@@ -78,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
 template <int N, int PMAX, bool KEYS>
 __global__ __launch_bounds__(kThreads) void k_query_proj(int64_t q, int P,
                                                          const float *__restrict__ queries,
-                                                         const float *__restrict__ proj,
+                                                         const ProjArgs<N> proj,
                                                          float *__restrict__ qr,
                                                          float *__restrict__ part)
 {
@@ -94,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void k_query_proj(int64_t q, int P,
         if (j < P) {
             float acc = 0.0f;
 #pragma unroll
-            for (int a = 0; a < N; ++a) acc = fmaf(x[a], proj[j * N + a], acc);
+            for (int a = 0; a < N; ++a) acc = fmaf(x[a], proj.r[j * N + a], acc);
             if (valid) qr[j * q + p] = acc;
             if constexpr (KEYS) {
                 const uint32_t key = orderable(acc);
@@ -169,37 +203,6 @@ __global__ __launch_bounds__(kThreads) void k_range_final(int64_t nparts, int P,
     qrange[P + j] = hi;
     qrange[2 * P + j] =
         (hi > lo) ? float(double(1u << key_bits) / (double(hi) - double(lo))) : 0.0f;
-}
-
-// The k-d root's extents from the per-block key partials: ext[2j] and
-// ext[2j + 1] get projection j's min and max key; one block per projection.
-__global__ __launch_bounds__(kThreads) void k_root_keys(int64_t nparts, int P,
-                                                        const float *__restrict__ part,
-                                                        uint32_t *__restrict__ ext)
-{
-    __shared__ uint32_t slo[kThreads / kWave], shi[kThreads / kWave];
-    const int j = blockIdx.x;
-    const uint32_t *pk = reinterpret_cast<const uint32_t *>(part);
-    uint32_t lo = 0xffffffffu, hi = 0u;
-    for (int64_t b = threadIdx.x; b < nparts; b += kThreads) {
-        lo = min(lo, pk[(b * P + j) * 2 + 0]);
-        hi = max(hi, pk[(b * P + j) * 2 + 1]);
-    }
-    lo = wave_umin_dpp(lo);
-    hi = wave_umax_dpp(hi);
-    if (lane_id() == kWave - 1) {
-        slo[threadIdx.x / kWave] = lo;
-        shi[threadIdx.x / kWave] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-#pragma unroll
-    for (int i = 0; i < kThreads / kWave; ++i) {
-        lo = min(lo, slo[i]);
-        hi = max(hi, shi[i]);
-    }
-    ext[2 * j + 0] = lo;
-    ext[2 * j + 1] = hi;
 }
 
 // Locality key of row i of a P x n SoA array of projections.
@@ -449,13 +452,19 @@ __global__ __launch_bounds__(kThreads) void k_gauss_limits(
     g_lb[j * k + s] = lb;
 }
 
-// Bounds of every super-tile: the union of its tiles' boxes.
+// Bounds of every super-tile: the union of its tiles' boxes.  Also clears what
+// the interval test and the lists count into: nzero segment counts, and *most.
 __global__ __launch_bounds__(kThreads) void k_super_bounds(int64_t ntiles, int PP,
                                                            const float *__restrict__ tbnd,
-                                                           float *__restrict__ sbnd)
+                                                           float *__restrict__ sbnd,
+                                                           int64_t nzero,
+                                                           int32_t *__restrict__ seg_cnt,
+                                                           unsigned long long *__restrict__ most)
 {
     const int64_t nsup = (ntiles + kSuperTiles - 1) / kSuperTiles;
     const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    if (i < nzero) seg_cnt[i] = 0;
+    if (i == 0) *most = 0ull;
     if (i >= nsup * 2 * PP) return;
     const int64_t sp = i / (2 * PP);
     const int e = int(i - sp * 2 * PP);
@@ -595,6 +604,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_prefix(int64_t ntiles, int nse
         }
     }
     if (ok) tile_cnt[t] = run;
+    if (!maxc) return;   // uniform
     // counts are non-negative: their bit patterns order as unsigned
     const int most = __float_as_int(wave_max_nonneg(__int_as_float(run)));
     if (lane_id() == 0) atomicMax(maxc, static_cast<unsigned long long>(most));
@@ -615,7 +625,10 @@ __global__ __launch_bounds__(kThreads) void k_fill_cand(int64_t ntiles, int64_t 
                                                         const int64_t *__restrict__ tile_off,
                                                         int64_t cap,
                                                         int32_t *__restrict__ cand,
-                                                        int32_t *__restrict__ ent_tile)
+                                                        int32_t *__restrict__ ent_tile,
+                                                        const int64_t *__restrict__ item_off,
+                                                        int64_t cap_items,
+                                                        int32_t *__restrict__ item_tile)
 {
     __shared__ uint64_t sm[kFillTiles][kWave + 1];   // [tile][chunk]
     __shared__ int32_t stage[kThreads / kWave][kFillStage];
@@ -635,6 +648,9 @@ __global__ __launch_bounds__(kThreads) void k_fill_cand(int64_t ntiles, int64_t 
             const int64_t e = seg + 1 < int64_t(gridDim.y) ? seg_cnt[(seg + 1) * ntiles + t]
                                                            : tile_off[t + 1] - tile_off[t];
             has = e > b;
+            if (seg == 0)   // the tile's work items
+                for (int64_t i = item_off[t]; i < item_off[t + 1] && i < cap_items; ++i)
+                    item_tile[i] = int32_t(t);
         }
         run[threadIdx.x] = t < ntiles ? tile_off[t] + seg_cnt[seg * ntiles + t] : 0;
         // no entry at or past `cap` is written (lists longer than the
@@ -738,19 +754,11 @@ __global__ __launch_bounds__(kThreads) void k_item_fill(int64_t n, const int64_t
     for (int64_t j = ioff[i]; j < ioff[i + 1] && j < cap; ++j) owner[j] = int32_t(i);
 }
 
-__global__ void k_zero_u64(unsigned long long *p, int n)
+// The list sizes, stored for the host (null most: no lists).
+__global__ void k_sizes(int64_t *sizes, const int64_t *most, const int64_t *tile_end,
+                        const int64_t *item_end)
 {
-    if (int(threadIdx.x) < n) p[threadIdx.x] = 0ull;
-}
-
-// The list sizes next to the longest list, for one copy to the host:
-// stats[1] longest list (set by k_seg_prefix), stats[2] total, stats[3] items.
-__global__ void k_gather_sizes(int64_t *stats, const int64_t *tile_end, const int64_t *item_end)
-{
-    if (threadIdx.x == 0) {
-        stats[2] = *tile_end;
-        stats[3] = *item_end;
-    }
+    if (threadIdx.x == 0) store_sizes(sizes, most ? *most : 0, *tile_end, *item_end);
 }
 
 __global__ void k_iota(int32_t *p, int64_t n)
@@ -781,6 +789,23 @@ hipError_t launch_items(int64_t n, const int64_t *off, int per, DevBuf &cnt, Dev
     return scan_counts(cnt, ioff, n, scan_tmp, s);
 }
 
+// Offsets of the tiles' lists and items, and the sizes for the host: up to
+// kOneScanItems tiles in one launch, else in seven.
+hipError_t tile_offsets(ngd_cull *c, const int64_t *most, hipStream_t s)
+{
+    if (c->ntiles <= kOneScanItems)
+        return scan_items(c->tile_cnt, c->tile_off, kItemCands, c->item_off, c->ntiles,
+                          c->stats_host, s);
+    hipError_t e = scan_counts(c->tile_cnt, c->tile_off, c->ntiles, c->scan_tmp, s);
+    if (e == hipSuccess)
+        e = launch_items(c->ntiles, c->tile_off.as<int64_t>(), kItemCands, c->item_cnt,
+                         c->item_off, c->scan_tmp, s);
+    if (e != hipSuccess) return e;
+    k_sizes<<<1, 64, 0, s>>>(c->stats_host, most, c->tile_off.as<int64_t>() + c->ntiles,
+                             c->item_off.as<int64_t>() + c->ntiles);
+    return hipGetLastError();
+}
+
 // The Gaussians in their tile order, what the interval test needs: its
 // limits (g_sorted: the projected means are already in that order).
 hipError_t gauss_limits(ngd_cull *c, int64_t k, int P, bool g_sorted, hipStream_t s)
@@ -803,13 +828,15 @@ hipError_t gauss_records(ngd_cull *c, const ngd_mixture *mix, int64_t k, int R, 
 
 template <int N>
 hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *queries,
-                        hipStream_t s, bool &side_open)
+                        const float *proj, hipStream_t s, bool &side_open)
 {
     const int P = c->params.n_proj;
     const int64_t q = c->q, k = c->k;
     const int R = rec_stride(N);
     const int nbits = c->params.key_proj * c->params.key_bits;
     hipError_t e;
+    ProjArgs<N> pr = {};
+    std::copy(proj, proj + P * N, pr.r);
     // The Gaussians' projections feed only their own k-d order, which runs
     // on the second stream: with the k-d tiling (and more than one chunk of
     // Gaussians) they go there too, after the fork, so that the queries'
@@ -822,35 +849,36 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
     }
     if (k > 0) {
         k_gauss_proj<N><<<nblk(k, kThreads), kThreads, 0, forked ? c->side : s>>>(
-            k, P, mix->rec.as<float>(), R, mix->lfac.as<float>(), c->proj.as<float>(), c->kappa2,
-            c->g_mr.as<float>(), c->g_thr.as<float>());
+            k, P, mix->rec.as<float>(), R, mix->lfac.as<float>(), pr, c->kappa2,
+            c->g_mr.as<float>(), c->g_thr.as<float>(),
+            forked ? c->gext_part.as<uint32_t>() : nullptr);
     }
     const int64_t nparts = (q + kThreads - 1) / kThreads;
     // With the k-d tiling of the queries the projection kernel's block
     // extents are taken as keys, and their reduction is the root's extents
     // of the queries' k-d order (no pass of its own over the projections).
     const bool kd_queries = c->params.tiling == 0 && q > std::min(c->params.tile, kWave);
-    const bool root_keys =
-        kd_queries && c->kd_work.ext[0].cap >= sizeof(uint32_t) * 2 * size_t(P);
     if (q > 0) {
         auto go = [&](auto kern) {
-            kern<<<nblk(q, kThreads), kThreads, 0, s>>>(q, P, queries, c->proj.as<float>(),
-                                                        c->qr.as<float>(),
+            kern<<<nblk(q, kThreads), kThreads, 0, s>>>(q, P, queries, pr, c->qr.as<float>(),
                                                         c->range_part.as<float>());
         };
-        if (root_keys)
+        if (kd_queries)
             P <= 16 ? go(k_query_proj<N, 16, true>) : go(k_query_proj<N, 32, true>);
         else
             P <= 16 ? go(k_query_proj<N, 16, false>) : go(k_query_proj<N, 32, false>);
     }
-    if (root_keys)
-        k_root_keys<<<dim3(unsigned(P)), kThreads, 0, s>>>(nparts, P, c->range_part.as<float>(),
-                                                           c->kd_work.ext[0].as<uint32_t>());
-    else
+    if (c->params.tiling == 1)
         k_range_final<<<dim3(unsigned(P)), kThreads, 0, s>>>(nparts, P, c->params.key_bits,
                                                              c->range_part.as<float>(),
                                                              c->qrange.as<float>());
-    if ((e = hipGetLastError()) != hipSuccess) {
+    e = hipGetLastError();
+    if (e == hipSuccess && forked)
+        e = launch_kd_root(c->kd_g, c->kd_work_g, P, (k + kThreads - 1) / kThreads,
+                           c->gext_part.p, c->side);
+    if (e == hipSuccess && kd_queries)
+        e = launch_kd_root(c->kd_q, c->kd_work, P, nparts, c->range_part.p, s);
+    if (e != hipSuccess) {
         if (forked) {   // the main stream still waits for the second one
             (void)hipEventRecord(c->ev_join, c->side);
             (void)hipStreamWaitEvent(s, c->ev_join, 0);
@@ -880,11 +908,11 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
             k_iota<<<nblk(k, kThreads), kThreads, 0, s>>>(c->gperm.as<int32_t>(), k);
         }
         if (e == hipSuccess && q > 0) {
-            if (c->params.tiling == 2 || q <= std::min(c->params.tile, kWave)) {
+            if (!kd_queries) {
                 k_iota<<<nblk(q, kThreads), kThreads, 0, s>>>(c->perm.as<int32_t>(), q);
             } else {
                 e = kd_start(rq, c->kd_q, c->kd_work, P, c->qr.as<float>(), q,
-                             c->perm.as<int32_t>(), c->qr_s.as<float>(), s, root_keys);
+                             c->perm.as<int32_t>(), c->qr_s.as<float>(), s);
                 qr_s = c->qr_s.as<float>();
             }
         }
@@ -956,8 +984,10 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
                 queries, c->qs.as<float>(), c->tile_lo.as<float>(), c->tile_hi.as<float>(),
                 c->tbnd.as<float>(), c->tcen.as<float>());
         const int64_t nsup = (c->ntiles + kSuperTiles - 1) / kSuperTiles;
-        k_super_bounds<<<nblk(nsup * 2 * PP, kThreads), kThreads, 0, s>>>(
-            c->ntiles, PP, c->tbnd.as<float>(), c->sbnd.as<float>());
+        const int64_t nzero = int64_t(c->nseg) * c->ntiles;
+        k_super_bounds<<<nblk(std::max<int64_t>(nsup * 2 * PP, nzero), kThreads), kThreads, 0,
+                         s>>>(c->ntiles, PP, c->tbnd.as<float>(), c->sbnd.as<float>(), nzero,
+                              c->seg_cnt.as<int32_t>(), c->stats.as<unsigned long long>());
     }
     // the tiles' bounds above overlap the second stream's last kernels
     if (side_open && (e = hipStreamWaitEvent(s, c->ev_join, 0)) != hipSuccess) return e;
@@ -965,21 +995,16 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
         if ((e = gauss_limits(c, k, P, g_sorted, s)) != hipSuccess) return e;
         if ((e = gauss_records(c, mix, k, R, s)) != hipSuccess) return e;
     }
-    k_zero_u64<<<1, 64, 0, s>>>(reinterpret_cast<unsigned long long *>(c->stats.p), 2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (k == 0 || c->ntiles == 0) {
         // no pairs: every tile list is empty
         if (c->ntiles > 0)
             k_zero_i32<<<nblk(c->ntiles, kThreads), kThreads, 0, s>>>(c->tile_cnt.as<int32_t>(),
                                                                      c->ntiles);
-        e = scan_counts(c->tile_cnt, c->tile_off, c->ntiles, c->scan_tmp, s);
-        if (e != hipSuccess) return e;
-        return launch_items(c->ntiles, c->tile_off.as<int64_t>(), kItemCands, c->item_cnt, c->item_off, c->scan_tmp, s);
+        return tile_offsets(c, nullptr, s);
     }
     // interval test; it also counts the candidates per (chunk segment, tile)
     const int64_t per_seg = (c->nchunks + c->nseg - 1) / c->nseg;
-    k_zero_i32<<<nblk(int64_t(c->nseg) * c->ntiles, kThreads), kThreads, 0, s>>>(
-        c->seg_cnt.as<int32_t>(), int64_t(c->nseg) * c->ntiles);
     // 128 tiles per wave: the boxes of a wave's range (16 KB at 16
     // projections) stay in the scalar cache while the workgroups that share
     // the range (consecutive chunks, same y) test them; 512 tiles per wave
@@ -1004,18 +1029,17 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
     // per-tile counts -> offsets
     k_seg_prefix<<<nblk(c->ntiles, kThreads), kThreads, 0, s>>>(
         c->ntiles, c->nseg, c->seg_cnt.as<int32_t>(), c->tile_cnt.as<int32_t>(),
-        reinterpret_cast<unsigned long long *>(c->stats.as<int64_t>() + 1));
+        c->ntiles <= kOneScanItems ? nullptr : c->stats.as<unsigned long long>());
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = scan_counts(c->tile_cnt, c->tile_off, c->ntiles, c->scan_tmp, s);
-    if (e != hipSuccess) return e;
-    return launch_items(c->ntiles, c->tile_off.as<int64_t>(), kItemCands, c->item_cnt, c->item_off, c->scan_tmp, s);
+    return tile_offsets(c, c->stats.as<int64_t>(), s);
 }
 
 template <int N>
-hipError_t front_n(ngd_cull *c, const ngd_mixture *mix, const float *queries, hipStream_t s)
+hipError_t front_n(ngd_cull *c, const ngd_mixture *mix, const float *queries, const float *proj,
+                   hipStream_t s)
 {
     bool side_open = false;
-    hipError_t e = front_body_n<N>(c, mix, queries, s, side_open);
+    hipError_t e = front_body_n<N>(c, mix, queries, proj, s, side_open);
     if (side_open) {
         // the second stream's work past the interval test's join point ends
         // before the front half does, whatever happened in between
@@ -1029,11 +1053,11 @@ hipError_t front_n(ngd_cull *c, const ngd_mixture *mix, const float *queries, hi
 }  // namespace
 
 hipError_t launch_cull_build_front(ngd_cull *c, const ngd_mixture *mix, const float *queries,
-                                   hipStream_t s)
+                                   const float *proj, hipStream_t s)
 {
     switch (c->n) {
 #define NGD_CASE(NN) \
-    case NN: return front_n<NN>(c, mix, queries, s);
+    case NN: return front_n<NN>(c, mix, queries, proj, s);
         NGD_CASE(1) NGD_CASE(2) NGD_CASE(3) NGD_CASE(4) NGD_CASE(5) NGD_CASE(6)
         NGD_CASE(7) NGD_CASE(8) NGD_CASE(9) NGD_CASE(10) NGD_CASE(11) NGD_CASE(12)
 #undef NGD_CASE
@@ -1041,27 +1065,19 @@ hipError_t launch_cull_build_front(ngd_cull *c, const ngd_mixture *mix, const fl
     }
 }
 
-hipError_t launch_gather_sizes(ngd_cull *c, hipStream_t s)
-{
-    k_gather_sizes<<<1, 64, 0, s>>>(c->stats.as<int64_t>(), c->tile_off.as<int64_t>() + c->ntiles,
-                                    c->item_off.as<int64_t>() + c->ntiles);
-    return hipGetLastError();
-}
-
 hipError_t launch_cull_build_lists(ngd_cull *c, hipStream_t s, int64_t cap_ent,
                                    int64_t cap_items)
 {
-    if (c->ntiles == 0) return hipSuccess;
-    if (cap_items > 0)
-        k_item_fill<<<nblk(c->ntiles, kThreads), kThreads, 0, s>>>(
-            c->ntiles, c->item_off.as<int64_t>(), cap_items, c->item_tile.as<int32_t>());
-    if (cap_ent == 0 || c->k == 0) return hipGetLastError();
+    // without room for an entry there is none for an item: nothing to write
+    if (c->ntiles == 0 || cap_ent == 0 || c->k == 0) return hipSuccess;
     const int64_t per_seg = (c->nchunks + c->nseg - 1) / c->nseg;
     dim3 sgrid(nblk(c->ntiles, kFillTiles), unsigned(c->nseg));
     k_fill_cand<<<sgrid, kThreads, 0, s>>>(c->ntiles, c->tpad, c->nchunks, per_seg,
                                            c->masks.as<uint64_t>(), c->seg_cnt.as<int32_t>(),
                                            c->tile_off.as<int64_t>(), cap_ent,
-                                           c->cand.as<int32_t>(), c->ent_tile.as<int32_t>());
+                                           c->cand.as<int32_t>(), c->ent_tile.as<int32_t>(),
+                                           c->item_off.as<int64_t>(), cap_items,
+                                           c->item_tile.as<int32_t>());
     return hipGetLastError();
 }
 
@@ -1157,7 +1173,6 @@ hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
 {
     const int64_t k = c->k, total = c->total;
     const int groups = (c->params.tile + kWave - 1) / kWave;
-    if (k > 0) k_zero_i32<<<nblk(k, kThreads), kThreads, 0, s>>>(c->a_cnt.as<int32_t>(), k);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (total > 0) {
@@ -1183,9 +1198,14 @@ hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
     } else {
         c->a_ent_buf = 0;
     }
-    e = scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
-    if (e != hipSuccess) return e;
-    e = launch_items(k, c->a_off.as<int64_t>(), kItemTiles, c->gitem_cnt, c->gitem_off, c->scan_tmp, s);
+    if (k <= kOneScanItems) {
+        e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, nullptr, s);
+    } else {
+        e = scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
+        if (e == hipSuccess)
+            e = launch_items(k, c->a_off.as<int64_t>(), kItemTiles, c->gitem_cnt, c->gitem_off,
+                             c->scan_tmp, s);
+    }
     if (e != hipSuccess) return e;
     if (k > 0 && c->gitems_cap > 0)
         k_item_fill<<<nblk(k, kThreads), kThreads, 0, s>>>(k, c->gitem_off.as<int64_t>(),
@@ -1241,9 +1261,9 @@ bool cull_reserve_front(ngd_cull *c)
     const int64_t nparts = (qq + kThreads - 1) / kThreads;
     const int64_t scan_n = std::max<int64_t>({kRadixMaxBins * nb_sort, T, kk});
     bool ok = true;
-    ok &= c->proj.ensure(sizeof(float) * P * n);
     ok &= c->qr.ensure(sizeof(float) * P * qq);
     ok &= c->range_part.ensure(sizeof(float) * 2 * P * nparts);
+    ok &= c->gext_part.ensure(sizeof(uint32_t) * 2 * P * ((kk + kThreads - 1) / kThreads));
     ok &= c->qrange.ensure(sizeof(float) * 3 * P);
     ok &= c->g_mr.ensure(sizeof(float) * P * kk);
     ok &= c->g_thr.ensure(sizeof(float) * P * kk);

@@ -698,6 +698,8 @@ hipError_t culled_n(const ngd_cull *c, float *out, unsigned long long *stats, hi
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !out) return e;
+    // as many items as tiles and none with two: every tile has written its own
+    if (c->nitems == c->ntiles && c->max_per_tile <= kItemCands) return hipSuccess;
     return launch_eval_reduce(c, out, s);
 }
 

@@ -17,8 +17,8 @@
 // each), in five launches:
 //   hist 0   per slice of kHistSlice points: the node's split projection
 //            (largest extent, from the node's min / max accumulated by the
-//            previous level's scatter; for the root by a pass over its
-//            slices), then the histogram of the first radix digit (11, 11,
+//            previous level's scatter; for the root from the projections'
+//            kernel's partials), then the histogram of the first radix digit (11, 11,
 //            10 bits of the order-preserving key), added into the node's
 //            round-0 histogram
 //   hist 1,2 per slice: the bin of the previous round's histogram that holds
@@ -68,7 +68,6 @@ constexpr unsigned kWideLocalBlocks = 512;   // subtrees for the 512-thread vari
 // of the many workgroups of one node (all of them, at the root) spread over
 // as many cache lines; readers reduce the planes.
 constexpr int kExtRep = 16;
-constexpr int kRootPer = 4;        // points per thread of the root's extents
 constexpr int kLocalRuns = 128;     // runs per subtree (8-bit run ids)
 // Nodes selected by one workgroup, in 10 to 18 us, where three histogram
 // rounds and a count take 21 and their gaps; at 32,768 points it took 35.
@@ -94,85 +93,49 @@ __device__ __forceinline__ uint32_t *ext_plane(uint32_t *ext, int64_t max_nodes,
     return ext + int64_t(blockIdx.x % kExtRep) * max_nodes * 2 * P;
 }
 
-// Clears the histograms; resets the root's min / max key slots (P
-// projections) of planes first_plane.. to their identities.
-__global__ __launch_bounds__(kThreads) void k_kd_zero(int32_t *__restrict__ p, int64_t n,
-                                                      uint32_t *__restrict__ ext, int P,
-                                                      int64_t max_nodes, int first_plane)
+// The root's extents from per-block partials: block (j, 0) reduces projection
+// j into plane 0 and puts the other planes at their identities; the blocks
+// (., y > 0) clear the histograms.
+__global__ __launch_bounds__(kThreads) void k_kd_root(int64_t nparts, int P,
+                                                      const uint32_t *__restrict__ part,
+                                                      uint32_t *__restrict__ ext,
+                                                      int64_t max_nodes,
+                                                      int32_t *__restrict__ hist, int64_t nhist)
 {
-    const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (i < n) p[i] = 0;
-    if (i >= int64_t(P) * first_plane && i < int64_t(P) * kExtRep) {
-        uint32_t *e = ext + (i / P) * max_nodes * 2 * P + 2 * (i % P);
-        e[0] = 0xffffffffu;
-        e[1] = 0u;
+    if (blockIdx.y > 0) {
+        const int64_t step = int64_t(gridDim.x) * (gridDim.y - 1) * kThreads;
+        for (int64_t i = (int64_t(blockIdx.y - 1) * gridDim.x + blockIdx.x) * kThreads +
+                         threadIdx.x;
+             i < nhist; i += step)
+            hist[i] = 0;
+        return;
     }
-}
-
-// Workgroup min / max of per-thread keys for projections j < P, merged into
-// ext[(node * P + j) * 2 + {0, 1}] by atomics (order-independent).
-template <int PMAX>
-__device__ void block_merge_ext(const uint32_t (&kmin)[PMAX], const uint32_t (&kmax)[PMAX],
-                                int P, uint32_t *ext, int64_t node)
-{
-    __shared__ uint32_t smin[kThreads / kWave][PMAX], smax[kThreads / kWave][PMAX];
-    const int w = threadIdx.x / kWave;
-    // wave minima / maxima by DPP (no LDS traffic), totals in lane 63
-#pragma unroll
-    for (int j = 0; j < PMAX; ++j) {
-        if (j < P) {
-            const uint32_t a = wave_umin_dpp(kmin[j]), b = wave_umax_dpp(kmax[j]);
-            if (lane_id() == kWave - 1) {
-                smin[w][j] = a;
-                smax[w][j] = b;
-            }
-        }
+    __shared__ uint32_t slo[kThreads / kWave], shi[kThreads / kWave];
+    const int j = blockIdx.x;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    for (int64_t b = threadIdx.x; b < nparts; b += kThreads) {
+        lo = min(lo, part[(b * P + j) * 2 + 0]);
+        hi = max(hi, part[(b * P + j) * 2 + 1]);
+    }
+    lo = wave_umin_dpp(lo);
+    hi = wave_umax_dpp(hi);
+    if (lane_id() == kWave - 1) {
+        slo[threadIdx.x / kWave] = lo;
+        shi[threadIdx.x / kWave] = hi;
     }
     __syncthreads();
-    if (threadIdx.x < P) {
-        const int j = threadIdx.x;
-        uint32_t a = 0xffffffffu, b = 0u;
+    if (threadIdx.x >= kExtRep) return;
+    lo = 0xffffffffu, hi = 0u;
+    if (threadIdx.x == 0) {
 #pragma unroll
         for (int i = 0; i < kThreads / kWave; ++i) {
-            a = min(a, smin[i][j]);
-            b = max(b, smax[i][j]);
-        }
-        if (a != 0xffffffffu) atomicMin(&ext[(node * P + j) * 2 + 0], a);
-        if (b != 0u) atomicMax(&ext[(node * P + j) * 2 + 1], b);
-    }
-    __syncthreads();
-}
-
-// The root's min / max: kRootPer points per thread, all P of their loads
-// in flight together.
-template <int PMAX>
-__global__ __launch_bounds__(kThreads) void k_kd_root_ext(int64_t n, int P,
-                                                          const float *__restrict__ vin,
-                                                          uint32_t *__restrict__ ext,
-                                                          int64_t max_nodes)
-{
-    uint32_t kmin[PMAX], kmax[PMAX];
-#pragma unroll
-    for (int j = 0; j < PMAX; ++j) {
-        kmin[j] = 0xffffffffu;
-        kmax[j] = 0u;
-    }
-    const int64_t i0 = int64_t(blockIdx.x) * kThreads * kRootPer + threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < kRootPer; ++u) {
-        const int64_t i = i0 + int64_t(u) * kThreads;
-        if (i < n) {
-#pragma unroll
-            for (int j = 0; j < PMAX; ++j) {
-                if (j < P) {
-                    const uint32_t key = orderable(vin[int64_t(j) * n + i]);
-                    kmin[j] = min(kmin[j], key);
-                    kmax[j] = max(kmax[j], key);
-                }
-            }
+            lo = min(lo, slo[i]);
+            hi = max(hi, shi[i]);
         }
     }
-    block_merge_ext<PMAX>(kmin, kmax, P, ext_plane(ext, max_nodes, P), 0);
+    uint32_t *e = ext + int64_t(threadIdx.x) * max_nodes * 2 * P + 2 * j;
+    e[0] = lo;
+    e[1] = hi;
 }
 
 // Block exclusive scan of one count per thread (THREADS threads).  Every
@@ -1570,11 +1533,24 @@ bool kd_reserve(KdWork &w, const KdPlan &pl, int64_t n, int P)
     return ok;
 }
 
+hipError_t launch_kd_root(const KdPlan &pl, KdWork &w, int P, int64_t nparts, const void *part,
+                          hipStream_t s)
+{
+    if (pl.levels.empty()) return hipSuccess;   // one subtree: it finds its extents itself
+    const int64_t mn = std::max<int64_t>(pl.max_nodes, 1);
+    if (w.ext[0].cap < sizeof(uint32_t) * 2 * P * size_t(mn) * kExtRep ||
+        w.hist.cap < sizeof(int32_t) * 3 * kBins * size_t(pl.hist_nodes))
+        return hipErrorInvalidValue;
+    k_kd_root<<<dim3(unsigned(P), pl.hist_nodes > 0 ? 17 : 1), kThreads, 0, s>>>(
+        nparts, P, static_cast<const uint32_t *>(part), w.ext[0].as<uint32_t>(), mn,
+        w.hist.as<int32_t>(), 3 * kBins * pl.hist_nodes);
+    return hipGetLastError();
+}
+
 hipError_t kd_start(KdRun &r, const KdPlan &pl, KdWork &w, int P, const float *vals, int64_t n,
-                    int32_t *perm, float *vals_sorted, hipStream_t s, bool root_given)
+                    int32_t *perm, float *vals_sorted, hipStream_t s)
 {
     r = KdRun{};
-    r.root_given = root_given;
     r.pl = &pl;
     r.w = &w;
     r.P = P;
@@ -1623,20 +1599,8 @@ hipError_t kd_step(KdRun &r)
     int64_t *cnt = w.cnt.as<int64_t>();
     const size_t nlev = pl.levels.size();
     const size_t phase = r.phase++;
-    if (phase == 0) {   // the root's extents
-        if (nlev == 0) return hipSuccess;
-        k_kd_zero<<<nb(3 * kBins * mh, kThreads), kThreads, 0, s>>>(
-            hist, 3 * kBins * mh, w.ext[0].as<uint32_t>(), P, mn, r.root_given ? 1 : 0);
-        if (r.root_given) return hipGetLastError();
-        const unsigned nr = nb(n, kThreads * kRootPer);
-        if (P <= 16)
-            k_kd_root_ext<16><<<nr, kThreads, 0, s>>>(n, P, r.vals, w.ext[0].as<uint32_t>(), mn);
-        else
-            k_kd_root_ext<32><<<nr, kThreads, 0, s>>>(n, P, r.vals, w.ext[0].as<uint32_t>(), mn);
-        return hipGetLastError();
-    }
-    if (phase <= nlev) {   // upper level phase - 1
-        const size_t li = phase - 1;
+    if (phase < nlev) {   // an upper level
+        const size_t li = phase;
         const KdLevel &lv = pl.levels[li];
         const int64_t *nt = nodes + lv.node0 * kNodeCols;
         const int64_t *st = slices + lv.slice0 * kSliceCols;
@@ -1703,15 +1667,6 @@ hipError_t kd_step(KdRun &r)
     if (e == hipSuccess && r.vals_sorted)
         e = hipMemcpyAsync(r.vals_sorted, r.vin, sizeof(float) * P * n, hipMemcpyDeviceToDevice,
                            s);
-    return e;
-}
-
-hipError_t kd_order(const KdPlan &pl, KdWork &w, int P, const float *vals, int64_t n,
-                    int32_t *perm, float *vals_sorted, hipStream_t s)
-{
-    KdRun r;
-    hipError_t e = kd_start(r, pl, w, P, vals, n, perm, vals_sorted, s);
-    while (e == hipSuccess && !r.done) e = kd_step(r);
     return e;
 }
 

@@ -78,13 +78,10 @@ bool kd_plan(KdPlan &pl, int64_t n, int leaf, int sub, int P);
 bool kd_reserve(KdWork &w, const KdPlan &pl, int64_t n, int P);
 // Orders n points with P <= 32 projections (vals: P x n, point order) and
 // writes the order (position -> point) to perm and, when vals_sorted is not
-// null, the projections in that order (P x n).  Needs a plan with at least
-// one split (n > sub).
-hipError_t kd_order(const KdPlan &pl, KdWork &w, int P, const float *vals, int64_t n,
-                    int32_t *perm, float *vals_sorted, hipStream_t s);
-// The same, enqueued phase by phase (the root, each upper level, the
-// subtrees), so that two orders on two streams can be enqueued alternately:
-// kd_start checks the buffers, each kd_step enqueues one phase until done.
+// null, the projections in that order (P x n); needs a plan with at least one
+// split (n > sub).  Enqueued phase by phase (each upper level, the subtrees),
+// so that two orders on two streams can be enqueued alternately: kd_start
+// checks the buffers, each kd_step enqueues one phase until done.
 struct KdRun {
     const KdPlan *pl = nullptr;
     KdWork *w = nullptr;
@@ -99,13 +96,14 @@ struct KdRun {
     const float *vin = nullptr;
     int cur = 0;
     bool done = true;
-    // the root's min / max keys are already in plane 0 of w.ext[0] (slots
-    // 2j and 2j + 1 of projection j), written by the caller ahead of the run
-    bool root_given = false;
 };
 hipError_t kd_start(KdRun &r, const KdPlan &pl, KdWork &w, int P, const float *vals, int64_t n,
-                    int32_t *perm, float *vals_sorted, hipStream_t s, bool root_given = false);
+                    int32_t *perm, float *vals_sorted, hipStream_t s);
 hipError_t kd_step(KdRun &r);
+// Ahead of the run: the root's min / max keys from per-block partials (part:
+// nparts x P x (min, max) keys), and the run's histograms cleared.
+hipError_t launch_kd_root(const KdPlan &pl, KdWork &w, int P, int64_t nparts, const void *part,
+                          hipStream_t s);
 
 }  // namespace ngd
 
@@ -145,9 +143,9 @@ struct ngd_cull {
     int64_t tpad = 0;          // ntiles rounded up to 64
     int nseg = 0;              // chunk segments used by the list build
     // device buffers
-    ngd::DevBuf proj;          // n_proj x n float
     ngd::DevBuf qr;            // n_proj x q float (caller order)
-    ngd::DevBuf range_part;    // per-block min/max partials
+    ngd::DevBuf range_part;    // per-block min/max partials of the queries
+    ngd::DevBuf gext_part;     // per-block min/max keys of the projected means
     ngd::DevBuf qrange;        // n_proj lo | n_proj hi | n_proj scale (float)
     ngd::DevBuf g_mr, g_thr;   // n_proj x k float (caller order)
     ngd::DevBuf keys0, keys1, vals0, vals1;   // radix sort ping-pong
@@ -195,8 +193,8 @@ struct ngd_cull {
     ngd::DevBuf gpart;         // gitems_cap x (n + tri + 3) float: moments
     ngd::DevBuf gflag;         // gitems_cap int32: item had contributing pairs
     ngd::DevBuf scan_tmp;      // scan block sums
-    ngd::DevBuf stats;         // 4 int64: -, max per tile, total, items
-    int64_t *stats_host = nullptr;  // pinned: max per tile, total, items
+    ngd::DevBuf stats;         // 1 int64: max per tile (many tiles)
+    int64_t *stats_host = nullptr;  // pinned: max per tile, total, items, stored by the build
     ngd::KdPlan kd_q, kd_g;    // k-d tiling plans of the queries and the Gaussians
     ngd::KdWork kd_work;       // query k-d work
     ngd::KdWork kd_work_g;     // Gaussian k-d work (runs concurrently, on `side`)
@@ -238,9 +236,7 @@ hipError_t launch_compose_backward(int n, int64_t kp, int64_t kc, const int32_t 
                                    hipStream_t s);
 
 hipError_t launch_cull_build_front(ngd_cull *c, const ngd_mixture *mix,
-                                   const float *queries, hipStream_t s);
-// stats[1..3] = longest list, total, items (device) for one copy to the host.
-hipError_t launch_gather_sizes(ngd_cull *c, hipStream_t s);
+                                   const float *queries, const float *proj, hipStream_t s);
 // The lists of a built front: entries below cap_ent and items below
 // cap_items are written (the buffers' capacities, or the exact sizes).
 hipError_t launch_cull_build_lists(ngd_cull *c, hipStream_t s, int64_t cap_ent,
@@ -271,7 +267,8 @@ hipError_t launch_backward_culled(const ngd_mixture *mix, ngd_cull *c,
                                   float *g_weight, float *g_colour, hipStream_t s);
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 // Groups the entries with a kept query group by Gaussian (a_cnt, a_off, the
-// sorted entries in vals0/vals1) and builds the backward work items.
+// sorted entries in vals0/vals1) and builds the backward work items; a_cnt
+// is zero on entry.
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s);
 // Mean squared error over q x 3 and its gradient; rel_eps > 0: each error
 // weighted by 1 / (|f| + rel_eps)^2, the weight held constant.
@@ -304,8 +301,29 @@ hipError_t radix_sort(int64_t n, const int64_t *n_dev, int nbits, DevBuf &k0, De
 // the total).  `tmp` must hold scan_tmp_bytes(n) bytes.
 // The capacities of in (n int32), out (n + 1 int64) and tmp are checked on
 // the host first (hipErrorInvalidValue when one is too small).
+constexpr int64_t kOneScan = 16384;   // counts scanned by one workgroup
+// With the items of the counts beside their offsets, always by one workgroup:
+// up to this many the rounds cost less than the eight launches otherwise.
+constexpr int64_t kOneScanItems = 65536;
 size_t scan_tmp_bytes(int64_t n);
 hipError_t scan_counts(const DevBuf &in, DevBuf &out, int64_t n, DevBuf &tmp, hipStream_t s);
+// The same with the offsets of ceil(count / per) in items (n + 1 int64) and,
+// when sizes is not null, (largest count, total, items) stored there; sizes is
+// memory the host reads after the stream has passed.
+hipError_t scan_items(const DevBuf &in, DevBuf &out, int per, DevBuf &items, int64_t n,
+                      int64_t *sizes, hipStream_t s);
+
+#if defined(__HIPCC__)
+// Stores that the host sees once the kernel is done.
+__device__ __forceinline__ void store_sizes(int64_t *sizes, int64_t most, int64_t total,
+                                            int64_t items)
+{
+    __hip_atomic_store(&sizes[0], most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&sizes[1], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&sizes[2], items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+}
+#endif
 
 // Sizes the cull's buffers need before the lists are built, and after the
 // number of candidates is known.

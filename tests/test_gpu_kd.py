@@ -1,7 +1,7 @@
 """The k-d order at the edges of its kernels, bit for bit against the CPU
 re-implementation: subtree sizes (2,048 points; 1,024 where runs do not start
 at multiples of 64 or there are more than 16 projections), nodes selected by
-one workgroup (16,384), tiles that leave uneven runs, and points whose
+one workgroup (16,384), tiles that leave uneven runs, many tiles, and points whose
 projections tie in whole runs, which the histogram's bins cannot separate."""
 
 import numpy as np
@@ -69,3 +69,11 @@ def test_ties(torch_cuda, q, what):
         x[q // 2] = 1e6
     mix["mean"][:] = x[rng.integers(0, q, 3000)]
     _check(mix, np.ascontiguousarray(x, dtype=np.float32), proj, 256)
+
+
+@pytest.mark.parametrize("q", [4096, 4097, 65536, 65537])
+def test_tile_counts(torch_cuda, q):
+    # as many tiles as queries: the lists' offsets by one workgroup, in one
+    # round, in several, and by the general scans
+    mix, x, proj = case(2, 70, q, seed=q)
+    _check(mix, x, proj, 1)
