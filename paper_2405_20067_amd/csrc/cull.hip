@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <utility>
 
+#include "eval_common.hpp"
 #include "ngd_internal.hpp"
 #include "wave.hpp"
 
@@ -65,6 +66,8 @@ __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
     for (int a = 0; a < N; ++a) m[a] = rec[i * R + a];
 #pragma unroll
     for (int e = 0; e < T; ++e) L[e] = lfac[i * T + e];
+    const int st = thr_stride(P);
+    float4 row;
     for (int j = 0; j < P; ++j) {
         float r[N];
 #pragma unroll
@@ -89,7 +92,14 @@ __global__ __launch_bounds__(kThreads) void k_gauss_proj(int64_t k, int P,
             s2 = fma(u, u, s2);
         }
         const float s2f = float(s2);
-        if (valid) g_thr[j * k + i] = kappa2 * s2f;
+        // four thresholds of the row at a time
+        const float thr = kappa2 * s2f;
+        if ((j & 3) == 0) row.x = thr;
+        if ((j & 3) == 1) row.y = thr;
+        if ((j & 3) == 2) row.z = thr;
+        if ((j & 3) == 3) row.w = thr;
+        if (valid && ((j & 3) == 3 || j == P - 1))
+            reinterpret_cast<float4 *>(g_thr + i * st)[j / 4] = row;
     }
     if (!part) return;
     __syncthreads();
@@ -349,25 +359,6 @@ __global__ __launch_bounds__(1024) void k_tile_bounds(int64_t q, int tile, int P
     }
 }
 
-// Records of the Gaussians in their tile order: a block moves 64 records of R
-// floats as float4s, consecutive threads on consecutive float4s.
-__global__ __launch_bounds__(kThreads) void k_rec_gather(int64_t k, int R,
-                                                         const int32_t *__restrict__ gperm,
-                                                         const float *__restrict__ rec,
-                                                         float *__restrict__ grec)
-{
-    const int R4 = R / 4;
-    const int64_t s0 = int64_t(blockIdx.x) * kWave;
-    const int cnt = int(k - s0 < kWave ? k - s0 : kWave);
-    const float4 *src = reinterpret_cast<const float4 *>(rec);
-    float4 *dst = reinterpret_cast<float4 *>(grec) + s0 * R4;
-    for (int e = threadIdx.x; e < cnt * R4; e += kThreads) {
-        const int sl = e / R4;
-        const int f = e - sl * R4;
-        dst[e] = src[int64_t(gperm[s0 + sl]) * R4 + f];
-    }
-}
-
 // ---- the interval test restated as two comparisons ------------------------
 // For a Gaussian with projected mean m and threshold thr = fl(kappa^2 sigma^2)
 // on projection j, Eq. 5 keeps a box [lo, hi] iff
@@ -380,9 +371,10 @@ __global__ __launch_bounds__(kThreads) void k_rec_gather(int64_t k, int R,
 // test per (lane, box, projection) is then two comparisons, with exactly the
 // outcome of the formula (finite bounds and means; thr < 0 keeps nothing,
 // U = L = NaN).  Each limit is found by bisection over the ordered bit
-// patterns of the floats, which needs only the monotonicity; it starts from a
-// bracket of 8 units in the last place about the arithmetic guess and falls
-// back to the whole range when that bracket does not hold the change.
+// patterns of the floats, which needs only the monotonicity; it tries the
+// arithmetic guess and its neighbours first, then a bracket of 8 units in the
+// last place about it, and falls back to the whole range when that bracket
+// does not hold the change.
 
 // ordered image of a non-NaN float: keys compare as the floats do
 __device__ __forceinline__ int32_t fkey(float x)
@@ -408,6 +400,15 @@ __device__ int32_t last_true(const Pred &pred, float guess, int32_t lo, int32_t 
     // invariant: pred(lo) true, pred(hi) false
     if (guess == guess) {
         const int64_t g = fkey(guess);
+        // mostly the guess itself or a neighbour
+        if (g - 1 > lo && g + 1 < hi) {
+            const int32_t a = int32_t(g);
+            if (pred(fkey_inv(a))) {
+                if (!pred(fkey_inv(a + 1))) return a;
+            } else if (pred(fkey_inv(a - 1))) {
+                return a - 1;
+            }
+        }
         const int32_t a = int32_t(g - 8 > lo ? g - 8 : lo);
         const int32_t b = int32_t(g + 8 < hi ? g + 8 : hi);
         if (pred(fkey_inv(a))) lo = a;
@@ -423,33 +424,77 @@ __device__ int32_t last_true(const Pred &pred, float guess, int32_t lo, int32_t 
     return lo;
 }
 
-__global__ __launch_bounds__(kThreads) void k_gauss_limits(
-    int64_t k, const int32_t *__restrict__ gperm, const float *__restrict__ g_mr,
+// Also each chunk's box: per projection the smallest L and the largest U of its
+// 64 Gaussians, cbnd[chunk] = PP of the former, then PP of the latter (the
+// padding projections, j >= P, span everything).
+// A workgroup per chunk, its Gaussians' threshold rows staged in LDS (the gather
+// by the order then reads whole lines: one value at a time it read 268 MB of
+// lines for 17 MB at K = 262,144), a wave per projection, lane = Gaussian: the
+// bisections of the projections do not wait for each other.
+constexpr int kLimitWaves = 16;
+template <int PP>
+__global__ __launch_bounds__(kLimitWaves *kWave) void k_gauss_limits(
+    int64_t k, int P, const int32_t *__restrict__ gperm, const float *__restrict__ g_mr,
     const float *__restrict__ g_mr_s, const float *__restrict__ g_thr, float *__restrict__ g_ub,
-    float *__restrict__ g_lb)
+    float *__restrict__ g_lb, float *__restrict__ cbnd)
 {
-    const int64_t s = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (s >= k) return;
-    const int64_t j = blockIdx.y;
-    const int64_t i = gperm[s];
-    // null g_mr_s: the means are not in order yet
-    const float m = g_mr_s ? g_mr_s[j * k + s] : g_mr[j * k + i];
-    const float thr = g_thr[j * k + i];
-    float ub = __int_as_float(0x7fc00000), lb = ub;   // NaN: nothing passes
-    if (thr >= 0.0f && m - m == 0.0f) {
-        const float r = fkey_inv(last_true([thr](float x) { return x * x <= thr; }, sqrtf(thr),
-                                           fkey(0.0f), kKeyPosInf));
-        ub = fkey_inv(last_true([m, r](float x) { return x - m <= r; }, m + r, kKeyNegInf,
-                                kKeyPosInf));
-        // the smallest x with fl(m - x) <= r: one key above the largest
-        // with fl(m - x) > r (none: -inf itself passes)
-        const auto fails = [m, r](float x) { return !(m - x <= r); };
-        lb = fails(-INFINITY)
-                 ? fkey_inv(last_true(fails, m - r, kKeyNegInf, kKeyPosInf) + 1)
-                 : -INFINITY;
+    constexpr int T4 = PP / 4;
+    __shared__ float s_thr[kWave][PP + 1];
+    const int w = uniform(int(threadIdx.x) / kWave), lane = lane_id();
+    const int64_t s0 = int64_t(blockIdx.x) * kWave, s = s0 + lane;
+    const bool valid = s < k;
+    const int st = thr_stride(P);
+    for (int e = threadIdx.x; e < kWave * T4; e += kLimitWaves * kWave) {
+        const int g = e / T4, q = e % T4;
+        if (s0 + g < k && 4 * q < P) {
+            const float4 r =
+                reinterpret_cast<const float4 *>(g_thr + int64_t(gperm[s0 + g]) * st)[q];
+            s_thr[g][4 * q + 0] = r.x;
+            s_thr[g][4 * q + 1] = r.y;
+            s_thr[g][4 * q + 2] = r.z;
+            s_thr[g][4 * q + 3] = r.w;
+        }
     }
-    g_ub[j * k + s] = ub;
-    g_lb[j * k + s] = lb;
+    const int64_t i = valid && !g_mr_s ? gperm[s] : 0;
+    __syncthreads();
+    float *box = cbnd + int64_t(blockIdx.x) * 2 * PP;
+    for (int j = w; j < PP; j += kLimitWaves) {
+        if (j >= P) {   // a padding projection spans everything
+            if (lane == 0) {
+                box[j] = -INFINITY;
+                box[PP + j] = INFINITY;
+            }
+            continue;
+        }
+        float ub = __int_as_float(0x7fc00000), lb = ub;   // NaN: nothing passes
+        if (valid) {
+            // null g_mr_s: the means are not in order yet
+            const float m = g_mr_s ? g_mr_s[j * k + s] : g_mr[j * k + i];
+            const float thr = s_thr[lane][j];
+            if (thr >= 0.0f && m - m == 0.0f) {
+                const float r = fkey_inv(last_true([thr](float x) { return x * x <= thr; },
+                                                   sqrtf(thr), fkey(0.0f), kKeyPosInf));
+                ub = fkey_inv(last_true([m, r](float x) { return x - m <= r; }, m + r, kKeyNegInf,
+                                        kKeyPosInf));
+                // the smallest x with fl(m - x) <= r: one key above the
+                // largest with fl(m - x) > r (none: -inf itself passes)
+                const auto fails = [m, r](float x) { return !(m - x <= r); };
+                lb = fails(-INFINITY)
+                         ? fkey_inv(last_true(fails, m - r, kKeyNegInf, kKeyPosInf) + 1)
+                         : -INFINITY;
+            }
+            g_ub[j * k + s] = ub;
+            g_lb[j * k + s] = lb;
+        }
+        // a Gaussian without limits adds nothing to the box
+        const uint32_t lo = wave_umin_dpp(lb == lb ? orderable(lb) : 0xffffffffu);
+        const uint32_t hi = wave_umax_dpp(ub == ub ? orderable(ub) : 0u);
+        if (lane == kWave - 1) {
+            // none has limits: an empty box
+            box[j] = lo == 0xffffffffu ? INFINITY : from_orderable(lo);
+            box[PP + j] = hi == 0u ? -INFINITY : from_orderable(hi);
+        }
+    }
 }
 
 // Bounds of every super-tile: the union of its tiles' boxes.  Also clears what
@@ -490,22 +535,17 @@ __global__ __launch_bounds__(kThreads) void k_super_bounds(int64_t ntiles, int P
 // mask is read back and exec restored within the same asm block, so the
 // compiler's view of exec is untouched.  NaN limits compare false, as
 // before.
-template <int PP>
-__device__ __forceinline__ uint64_t box_test(uint64_t alive, const float (&ub)[PP],
-                                             const float (&lb)[PP],
-                                             const float *__restrict__ box_p)
+template <int PP> __device__ __forceinline__ void load_box(float (&box)[2 * PP], ConstRec box_p)
 {
-    // the whole box as two wave-uniform vector loads (one wait per box,
-    // not one per group); boxes are 2 PP floats, aligned to 2 PP * 4 bytes
-    typedef float boxv __attribute__((ext_vector_type(PP)));
-    const boxv lov = *reinterpret_cast<const boxv *>(box_p);
-    const boxv hiv = *reinterpret_cast<const boxv *>(box_p + PP);
-    float box[2 * PP];
 #pragma unroll
-    for (int j = 0; j < PP; ++j) {
-        box[j] = lov[j];
-        box[PP + j] = hiv[j];
-    }
+    for (int j = 0; j < 2 * PP; ++j) box[j] = box_p[j];
+}
+
+template <int PP>
+__device__ __forceinline__ uint64_t box_test_regs(uint64_t alive, const float (&ub)[PP],
+                                                  const float (&lb)[PP],
+                                                  const float (&box)[2 * PP])
+{
 #pragma unroll
     for (int g = 0; g < PP; g += 4) {
         uint64_t sv;
@@ -534,17 +574,98 @@ __device__ __forceinline__ uint64_t box_test(uint64_t alive, const float (&ub)[P
     return alive;
 }
 
+// A box in memory: its wave-uniform loads waited for together, not per group.
+template <int PP>
+__device__ __forceinline__ uint64_t box_test(uint64_t alive, const float (&ub)[PP],
+                                             const float (&lb)[PP], const float *box_p)
+{
+    float box[2 * PP];
+    load_box<PP>(box, const_rec(box_p));
+    return box_test_regs<PP>(alive, ub, lb, box);
+}
+
+// Ahead of it, the chunks' boxes against the tiles': lane = tile, its box in
+// registers, kPreChunks chunks in turn with theirs wave-uniform; a tile whose
+// box misses the chunk's in some projection is missed by each of its
+// Gaussians.  One bit per (64 tiles, chunk, tile), some 64 times cheaper than
+// the exact test, and 20% of the pairs are left (10-D, 2^20 queries; 12% of the
+// image's), which spares the exact kernel 40% (60%) of its tests: 382 -> 291 us
+// for this one's 26 (266 -> 151 for 38).  Bound by the vector compares and the
+// waits for the boxes, hence one box ahead; boxes loaded when needed took 51 us,
+// 16 chunks a wave instead of 64 twice that.
+constexpr int kPreChunks = 64;   // a wave's own boxes are 8 KB: enough chunks to pay for them
+constexpr int64_t kPreWords = 1024;   // (64 tiles, chunk) pairs from which it pays
+template <int PP>
+__global__ __launch_bounds__(kThreads) void k_cull_pre(int64_t nchunks, int64_t ntiles,
+                                                       const float *__restrict__ tbnd,
+                                                       const float *__restrict__ cbnd,
+                                                       uint64_t *__restrict__ nz)
+{
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t tg = int64_t(blockIdx.x) * (kThreads / kWave) + w;
+    const int64_t t = tg * kWave + lane;
+    if (tg * kWave >= ntiles) return;   // uniform over the wave
+    const bool valid = t < ntiles;
+    float lo[PP], hi[PP];
+    const float4 *tb = reinterpret_cast<const float4 *>(tbnd + (valid ? t : 0) * 2 * PP);
+#pragma unroll
+    for (int j = 0; j < PP / 4; ++j) {
+        const float4 a = tb[j], b = tb[PP / 4 + j];
+        lo[4 * j] = a.x, lo[4 * j + 1] = a.y, lo[4 * j + 2] = a.z, lo[4 * j + 3] = a.w;
+        hi[4 * j] = b.x, hi[4 * j + 1] = b.y, hi[4 * j + 2] = b.z, hi[4 * j + 3] = b.w;
+    }
+    const uint64_t alive0 = ballot(valid);
+    const int64_t c0 = int64_t(blockIdx.y) * kPreChunks;
+    const int nc = int(nchunks - c0 < kPreChunks ? nchunks - c0 : kPreChunks);
+    uint64_t mine = 0;   // lane l: word of chunk c0 + l
+    // the chunks' boxes one ahead in two register blocks (past the end the
+    // last one again)
+    ConstRec r = const_rec(cbnd) + c0 * 2 * PP;
+    float bufA[2 * PP], bufB[2 * PP];
+    load_box<PP>(bufA, r);
+    auto test = [&](const float(&box)[2 * PP], int i) {
+        const uint64_t m = box_test_regs<PP>(alive0, hi, lo, box);
+        if (lane == i) mine = m;
+    };
+    for (int i = 0; i < nc; i += 2) {
+        if (i + 1 < nc) r += 2 * PP;
+        __builtin_amdgcn_sched_barrier(0);
+        wait_scalar_then(r);
+        load_box<PP>(bufB, r);
+        __builtin_amdgcn_sched_barrier(0);
+        test(bufA, i);
+        if (i + 1 == nc) break;
+        if (i + 2 < nc) r += 2 * PP;
+        __builtin_amdgcn_sched_barrier(0);
+        wait_scalar_then(r);
+        load_box<PP>(bufA, r);
+        __builtin_amdgcn_sched_barrier(0);
+        test(bufB, i + 1);
+    }
+    if (lane < nc) nz[tg * nchunks + c0 + lane] = mine;
+}
+
+// nz: per (64 tiles, chunk) the tiles to test (pre) or, without that, space;
+// on return those with a survivor, and only their masks are written.
 template <int PP>
 __global__ __launch_bounds__(kThreads) void k_cull_test(
     int64_t k, int64_t ntiles, int64_t tpad, int P, int tiles_per_wave,
     const float *__restrict__ g_ub, const float *__restrict__ g_lb,
     const float *__restrict__ tbnd, const float *__restrict__ sbnd, uint64_t *__restrict__ masks,
-    int64_t per_seg, int32_t *__restrict__ seg_cnt)
+    int64_t per_seg, int32_t *__restrict__ seg_cnt, bool pre, uint64_t *__restrict__ nz)
 {
     const int w = threadIdx.x / kWave, lane = lane_id();
     const int64_t nchunks = (k + kWave - 1) / kWave;
     const int64_t c = int64_t(blockIdx.x) * (kThreads / kWave) + w;
     if (c >= nchunks) return;
+    if (pre) {   // nothing to test in the whole range
+        uint64_t any = 0;
+        for (int i = 0; i < tiles_per_wave / kWave; ++i) {
+            const int64_t tg = int64_t(blockIdx.y) * (tiles_per_wave / kWave) + i;
+            if (tg * kWave < ntiles) any |= nz[tg * nchunks + c];
+        }
+        if (uniform64(int64_t(any)) == 0) return;
+    }
     const int64_t s = c * kWave + lane;
     const bool valid = s < k;
     float ub[PP], lb[PP];
@@ -561,21 +682,31 @@ __global__ __launch_bounds__(kThreads) void k_cull_test(
     for (int64_t tb = t0; tb < t1; tb += kWave) {
         const int64_t te = (tb + kWave < t1) ? tb + kWave : t1;
         uint64_t mine = 0;   // lane l: mask of tile tb + l
-        for (int64_t sb = tb; sb < te; sb += kSuperTiles) {
-            const uint64_t sup =
-                box_test<PP>(alive0, ub, lb, sbnd + (sb / kSuperTiles) * 2 * PP);
-            if (sup == 0) continue;
-            const int64_t se = (sb + kSuperTiles < te) ? sb + kSuperTiles : te;
-            for (int64_t t = sb; t < se; ++t) {
-                const uint64_t m = box_test<PP>(sup, ub, lb, tbnd + t * 2 * PP);
-                if (lane == int(t - tb)) mine = m;
+        uint64_t *word = nz + tb / kWave * nchunks + c;
+        uint64_t todo = te - tb == kWave ? ~uint64_t(0) : (uint64_t(1) << (te - tb)) - 1;
+        if (pre) todo = uint64_t(uniform64(int64_t(*word)));
+        for (int sb = 0; sb < kWave; sb += kSuperTiles) {
+            uint64_t bits = (todo >> sb) & ((uint64_t(1) << kSuperTiles) - 1);
+            if (bits == 0) continue;
+            uint64_t sup = alive0;
+            // worth its own test for three tiles and more
+            if (__builtin_popcountll(bits) > 2) {
+                sup = box_test<PP>(alive0, ub, lb, sbnd + ((tb + sb) / kSuperTiles) * 2 * PP);
+                if (sup == 0) continue;
+            }
+            for (; bits != 0; bits &= bits - 1) {
+                const int i = sb + __builtin_ctzll(bits);
+                const uint64_t m = box_test<PP>(sup, ub, lb, tbnd + (tb + i) * 2 * PP);
+                if (lane == i) mine = m;
             }
         }
-        if (tb + lane < te) {
+        const uint64_t some = ballot(mine != 0);
+        if (lane == 0) *word = some;
+        if (mine) {
             masks[c * tpad + tb + lane] = mine;
             // the candidates of each (chunk segment, tile), for the lists'
             // offsets (integer atomics: the sums do not depend on order)
-            if (mine) atomicAdd(&seg_cnt[(c / per_seg) * ntiles + tb + lane], __popcll(mine));
+            atomicAdd(&seg_cnt[(c / per_seg) * ntiles + tb + lane], __popcll(mine));
         }
     }
 }
@@ -610,98 +741,79 @@ __global__ __launch_bounds__(kThreads) void k_seg_prefix(int64_t ntiles, int nse
     if (lane_id() == 0) atomicMax(maxc, static_cast<unsigned long long>(most));
 }
 
-// Candidate lists from the masks: one workgroup per (64 tiles, chunk
-// segment).  Per round of 64 chunks the masks are read row by row
-// (coalesced) into LDS, transposed; each wave then takes 16 of the tiles,
-// lane = chunk: the popcounts' exclusive scan gives each chunk's first
-// position, every lane places its chunk's set bits (ascending) in the
-// wave's LDS staging row, and the row goes out with contiguous stores.
-constexpr int kFillTiles = 64;
+// Candidate lists from the masks: a wave per (tile, chunk segment), 64 chunks
+// at a time, lane = chunk: a lane whose chunk has survivors in the tile (one bit
+// of its word; 8% of them at 10-D) reads the mask, the popcounts' exclusive scan
+// gives the chunk's first position, every lane places its set bits (ascending)
+// in the wave's LDS staging row, and the row goes out with contiguous stores.
+// A workgroup's tiles are neighbours, whose masks share lines.  Bound by the
+// chain of these loads: many waves, no barriers.
+constexpr int kFillTiles = 8;
 constexpr int kFillStage = 1024;   // staged candidates per wave and round
-__global__ __launch_bounds__(kThreads) void k_fill_cand(int64_t ntiles, int64_t tpad,
-                                                        int64_t nchunks, int64_t per_seg,
-                                                        const uint64_t *__restrict__ masks,
-                                                        const int32_t *__restrict__ seg_cnt,
-                                                        const int64_t *__restrict__ tile_off,
-                                                        int64_t cap,
-                                                        int32_t *__restrict__ cand,
-                                                        int32_t *__restrict__ ent_tile,
-                                                        const int64_t *__restrict__ item_off,
-                                                        int64_t cap_items,
-                                                        int32_t *__restrict__ item_tile)
+__global__ __launch_bounds__(kFillTiles *kWave) void k_fill_cand(
+    int64_t ntiles, int64_t tpad, int64_t nchunks, int64_t per_seg,
+    const uint64_t *__restrict__ masks, const uint64_t *__restrict__ nz,
+    const int32_t *__restrict__ seg_cnt, const int64_t *__restrict__ tile_off, int64_t cap,
+    int32_t *__restrict__ cand, int32_t *__restrict__ ent_tile,
+    const int64_t *__restrict__ item_off, int64_t cap_items, int32_t *__restrict__ item_tile)
 {
-    __shared__ uint64_t sm[kFillTiles][kWave + 1];   // [tile][chunk]
-    __shared__ int32_t stage[kThreads / kWave][kFillStage];
-    __shared__ int64_t run[kFillTiles];
-    __shared__ int64_t tend[kFillTiles];   // the tiles' list ends, loaded once
-    const int64_t t0 = int64_t(blockIdx.x) * kFillTiles;
+    __shared__ int32_t stage[kFillTiles][kFillStage];
+    const int w = uniform(int(threadIdx.x) / kWave), lane = lane_id();
+    const int64_t t = int64_t(blockIdx.x) * kFillTiles + w;
+    if (t >= ntiles) return;   // uniform over the wave
     const int64_t seg = blockIdx.y;
     const int64_t c0 = seg * per_seg;
     const int64_t c1 = (c0 + per_seg < nchunks) ? c0 + per_seg : nchunks;
-    const int w = int(threadIdx.x) / kWave, lane = lane_id();
-    int has = 0;   // this segment has candidates in this thread's tile
-    if (int(threadIdx.x) < kFillTiles) {
-        const int64_t t = t0 + threadIdx.x;
-        if (t < ntiles) {
-            // the segments' exclusive offsets within the tile's list
-            const int64_t b = seg_cnt[seg * ntiles + t];
-            const int64_t e = seg + 1 < int64_t(gridDim.y) ? seg_cnt[(seg + 1) * ntiles + t]
-                                                           : tile_off[t + 1] - tile_off[t];
-            has = e > b;
-            if (seg == 0)   // the tile's work items
-                for (int64_t i = item_off[t]; i < item_off[t + 1] && i < cap_items; ++i)
-                    item_tile[i] = int32_t(t);
-        }
-        run[threadIdx.x] = t < ntiles ? tile_off[t] + seg_cnt[seg * ntiles + t] : 0;
-        // no entry at or past `cap` is written (lists longer than the
-        // buffers are built again once the buffers have grown)
-        tend[threadIdx.x] = t < ntiles ? (tile_off[t + 1] < cap ? tile_off[t + 1] : cap) : 0;
-    }
-    // a (tiles, segment) block without candidates reads none of its masks
-    if (!__syncthreads_or(has)) return;
+    const int64_t off = uniform64(tile_off[t]), stop = uniform64(tile_off[t + 1]);
+    if (seg == 0)   // the tile's work items
+        for (int64_t i = item_off[t] + lane; i < item_off[t + 1] && i < cap_items; i += kWave)
+            item_tile[i] = int32_t(t);
+    // the segments' exclusive offsets within the tile's list
+    int64_t base = off + uniform(seg_cnt[seg * ntiles + t]);
+    const int64_t next =
+        seg + 1 < int64_t(gridDim.y) ? off + uniform(seg_cnt[(seg + 1) * ntiles + t]) : stop;
+    if (base == next) return;
+    // no entry at or past `cap` is written (lists longer than the buffers are
+    // built again once the buffers have grown)
+    const int64_t end = stop < cap ? stop : cap;
+    const uint64_t *word = nz + t / kWave * nchunks;
+    const int bit = int(t % kWave);
     int32_t *st = stage[w];
     for (int64_t cb = c0; cb < c1; cb += kWave) {
-        __syncthreads();   // run[] set; the previous round's readers done
-        for (int r = w; r < kWave; r += kThreads / kWave) {
-            const int64_t c = cb + r, t = t0 + lane;
-            sm[lane][r] = (c < c1 && t < ntiles) ? masks[c * tpad + t] : 0ull;
-        }
-        __syncthreads();
-        for (int tl = w; tl < kFillTiles; tl += kThreads / kWave) {
-            const int64_t t = t0 + tl;
-            if (t >= ntiles) break;   // uniform
-            uint64_t m = sm[tl][lane];
-            const int cnt = __popcll(m);
-            const int incl = wave_inclusive_scan(cnt);
-            const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
-            if (total == 0) continue;   // uniform
-            const int32_t gbase = int32_t((cb + lane) * kWave);
-            const int64_t base = run[tl], end = tend[tl];
-            int k = incl - cnt;
-            if (total <= kFillStage) {   // uniform
-                while (m) {
-                    st[k++] = gbase + (__ffsll(static_cast<unsigned long long>(m)) - 1);
-                    m &= m - 1;
-                }
-                for (int i = lane; i < total; i += kWave) {
-                    const int64_t pos = base + i;
-                    if (pos < end) {
-                        cand[pos] = st[i];
-                        ent_tile[pos] = int32_t(t);
-                    }
-                }
-            } else {   // a dense round: every lane writes its own bits
-                while (m) {
-                    const int64_t pos = base + k++;
-                    if (pos < end) {
-                        cand[pos] = gbase + (__ffsll(static_cast<unsigned long long>(m)) - 1);
-                        ent_tile[pos] = int32_t(t);
-                    }
-                    m &= m - 1;
+        const int64_t c = cb + lane;
+        const bool has = c < c1 && ((word[c < c1 ? c : c0] >> bit) & 1);
+        if (ballot(has) == 0) continue;   // uniform
+        uint64_t m = has ? masks[c * tpad + t] : 0ull;
+        const int cnt = __popcll(m);
+        const int incl = wave_inclusive_scan(cnt);
+        const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const int32_t gbase = int32_t(c * kWave);
+        int k = incl - cnt;
+        if (total <= kFillStage) {   // uniform
+            while (m) {
+                st[k++] = gbase + (__ffsll(static_cast<unsigned long long>(m)) - 1);
+                m &= m - 1;
+            }
+            __builtin_amdgcn_wave_barrier();
+            for (int i = lane; i < total; i += kWave) {
+                const int64_t pos = base + i;
+                if (pos < end) {
+                    cand[pos] = st[i];
+                    ent_tile[pos] = int32_t(t);
                 }
             }
-            if (lane == 0) run[tl] = base + total;   // this wave's own tile
+            __builtin_amdgcn_wave_barrier();
+        } else {   // a dense round: every lane writes its own bits
+            while (m) {
+                const int64_t pos = base + k++;
+                if (pos < end) {
+                    cand[pos] = gbase + (__ffsll(static_cast<unsigned long long>(m)) - 1);
+                    ent_tile[pos] = int32_t(t);
+                }
+                m &= m - 1;
+            }
         }
+        base += total;
     }
 }
 
@@ -810,20 +922,21 @@ hipError_t tile_offsets(ngd_cull *c, const int64_t *most, hipStream_t s)
 // limits (g_sorted: the projected means are already in that order).
 hipError_t gauss_limits(ngd_cull *c, int64_t k, int P, bool g_sorted, hipStream_t s)
 {
-    k_gauss_limits<<<dim3(nblk(k, kThreads), unsigned(P)), kThreads, 0, s>>>(
-        k, c->gperm.as<int32_t>(), c->g_mr.as<float>(), g_sorted ? c->g_mr_s.as<float>() : nullptr,
-        c->g_thr.as<float>(), c->g_ub.as<float>(), c->g_lb.as<float>());
+    auto go = [&](auto kern) {
+        kern<<<nblk(k, kWave), kLimitWaves * kWave, 0, s>>>(
+            k, P, c->gperm.as<int32_t>(), c->g_mr.as<float>(),
+            g_sorted ? c->g_mr_s.as<float>() : nullptr, c->g_thr.as<float>(),
+            c->g_ub.as<float>(), c->g_lb.as<float>(), c->cbnd.as<float>());
+    };
+    switch (pad_proj(P)) {
+    case 4: go(k_gauss_limits<4>); break;
+    case 8: go(k_gauss_limits<8>); break;
+    case 12: go(k_gauss_limits<12>); break;
+    case 16: go(k_gauss_limits<16>); break;
+    case 24: go(k_gauss_limits<24>); break;
+    default: go(k_gauss_limits<32>); break;
+    }
     return hipGetLastError();
-}
-
-// The Gaussians in their tile order, what the forward needs: records, and the
-// records of its filter.
-hipError_t gauss_records(ngd_cull *c, const ngd_mixture *mix, int64_t k, int R, hipStream_t s)
-{
-    k_rec_gather<<<nblk(k, kWave), kThreads, 0, s>>>(k, R, c->gperm.as<int32_t>(),
-                                                     mix->rec.as<float>(), c->grec.as<float>());
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? launch_mfma_coef(c->n, c, s) : e;
 }
 
 template <int N>
@@ -933,7 +1046,7 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
             if (e == hipSuccess) e = ej;
             if (e == hipSuccess) {
                 side_open = true;
-                e = gauss_records(c, mix, k, R, c->side);
+                e = launch_gauss_records(mix, c, c->side);
             }
             if (e != hipSuccess) {
                 (void)hipEventRecord(c->ev_join, c->side);
@@ -993,7 +1106,7 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
     if (side_open && (e = hipStreamWaitEvent(s, c->ev_join, 0)) != hipSuccess) return e;
     if (k > 0 && !gauss_done) {
         if ((e = gauss_limits(c, k, P, g_sorted, s)) != hipSuccess) return e;
-        if ((e = gauss_records(c, mix, k, R, s)) != hipSuccess) return e;
+        if ((e = launch_gauss_records(mix, c, s)) != hipSuccess) return e;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (k == 0 || c->ntiles == 0) {
@@ -1011,12 +1124,20 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
     // measured 356 us against 301 us here (10-D, 2^20 queries, K = 2^18)
     const int tiles_per_wave = 128;
     dim3 grid(nblk(c->nchunks, kThreads / kWave), nblk(c->ntiles, tiles_per_wave));
+    // the chunks' boxes first, unless the exact test is as short as a launch
+    const int64_t groups = c->tpad / kWave;
+    const bool pre = groups * c->nchunks >= kPreWords;
+    dim3 pgrid(nblk(groups, kThreads / kWave), nblk(c->nchunks, kPreChunks));
 #define NGD_CULL_TEST(PPV)                                                                   \
+    if (pre)                                                                                 \
+        k_cull_pre<PPV><<<pgrid, kThreads, 0, s>>>(c->nchunks, c->ntiles, c->tbnd.as<float>(), \
+                                                   c->cbnd.as<float>(), c->nz.as<uint64_t>()); \
     k_cull_test<PPV><<<grid, kThreads, 0, s>>>(k, c->ntiles, c->tpad, P, tiles_per_wave,      \
                                                c->g_ub.as<float>(), c->g_lb.as<float>(),     \
                                                c->tbnd.as<float>(), c->sbnd.as<float>(),     \
                                                c->masks.as<uint64_t>(), per_seg,              \
-                                               c->seg_cnt.as<int32_t>())
+                                               c->seg_cnt.as<int32_t>(), pre,                 \
+                                               c->nz.as<uint64_t>())
     switch (PP) {
     case 4: NGD_CULL_TEST(4); break;
     case 8: NGD_CULL_TEST(8); break;
@@ -1072,9 +1193,9 @@ hipError_t launch_cull_build_lists(ngd_cull *c, hipStream_t s, int64_t cap_ent,
     if (c->ntiles == 0 || cap_ent == 0 || c->k == 0) return hipSuccess;
     const int64_t per_seg = (c->nchunks + c->nseg - 1) / c->nseg;
     dim3 sgrid(nblk(c->ntiles, kFillTiles), unsigned(c->nseg));
-    k_fill_cand<<<sgrid, kThreads, 0, s>>>(c->ntiles, c->tpad, c->nchunks, per_seg,
-                                           c->masks.as<uint64_t>(), c->seg_cnt.as<int32_t>(),
-                                           c->tile_off.as<int64_t>(), cap_ent,
+    k_fill_cand<<<sgrid, kFillTiles * kWave, 0, s>>>(c->ntiles, c->tpad, c->nchunks, per_seg,
+                                           c->masks.as<uint64_t>(), c->nz.as<uint64_t>(),
+                                           c->seg_cnt.as<int32_t>(), c->tile_off.as<int64_t>(), cap_ent,
                                            c->cand.as<int32_t>(), c->ent_tile.as<int32_t>(),
                                            c->item_off.as<int64_t>(), cap_items,
                                            c->item_tile.as<int32_t>());
@@ -1266,7 +1387,7 @@ bool cull_reserve_front(ngd_cull *c)
     ok &= c->gext_part.ensure(sizeof(uint32_t) * 2 * P * ((kk + kThreads - 1) / kThreads));
     ok &= c->qrange.ensure(sizeof(float) * 3 * P);
     ok &= c->g_mr.ensure(sizeof(float) * P * kk);
-    ok &= c->g_thr.ensure(sizeof(float) * P * kk);
+    ok &= c->g_thr.ensure(sizeof(float) * thr_stride(P) * kk);
     ok &= c->keys0.ensure(sizeof(uint32_t) * qk);
     ok &= c->keys1.ensure(sizeof(uint32_t) * qk);
     ok &= c->vals0.ensure(sizeof(int32_t) * qk);
@@ -1290,6 +1411,9 @@ bool cull_reserve_front(ngd_cull *c)
     ok &= c->g_lb.ensure(sizeof(float) * P * kk);
     ok &= c->masks.ensure(sizeof(uint64_t) * std::max<int64_t>(c->nchunks, 1) *
                           std::max<int64_t>(c->tpad, 64));
+    ok &= c->nz.ensure(sizeof(uint64_t) * std::max<int64_t>(c->nchunks, 1) *
+                       std::max<int64_t>(c->tpad / kWave, 1));
+    ok &= c->cbnd.ensure(sizeof(float) * std::max<int64_t>(c->nchunks, 1) * 2 * pad_proj(P));
     ok &= c->seg_cnt.ensure(sizeof(int32_t) * c->nseg * T);
     ok &= c->tile_cnt.ensure(sizeof(int32_t) * T);
     ok &= c->tile_off.ensure(sizeof(int64_t) * (T + 1));

@@ -41,7 +41,8 @@
 // work and half the coefficients.
 //
 // k_filter_items: one workgroup per item (a tile's queries, up to kItemCands of
-// its candidates), 4 waves of 64 queries.  256 candidates at a time: each wave
+// its candidates; four times as many spread the work too thin: 0.30 -> 0.32 and
+// the image's 0.85 -> 1.14 ms), 4 waves of 64 queries.  256 candidates at a time: each wave
 // brings 64 records into LDS (16-byte global-to-LDS loads), lane = candidate
 // forms b, a and the bound terms beside them, then every wave contracts all
 // 256 against its queries, 32 at a time, and writes the survivors as one bit
@@ -121,17 +122,43 @@ template <int N> struct QuadTable {
 };
 template <int N> inline constexpr QuadTable<N> kQuad{};
 
-// Per ordered Gaussian: its record of the contraction.  P is formed in
-// float64 from the record's S'.
+// Per ordered Gaussian: its record in the order, and that of the contraction, P
+// formed in float64 from the record's S'.  A wave per 64 Gaussians: the records
+// come and go as float4s, consecutive lanes on consecutive ones, through LDS.
+// (Without the copy, the kernels reading the mixture's own records by the order,
+// a step took as long: they lose what it costs.)
 template <int N>
-__global__ __launch_bounds__(256) void k_mfma_coef(int64_t k, const float *__restrict__ grec,
-                                                   f16x8 *__restrict__ mrec)
+__global__ __launch_bounds__(kWave) void k_gauss_records(int64_t k, const float *__restrict__ rec,
+                                                         const int32_t *__restrict__ gperm,
+                                                         float *__restrict__ grec,
+                                                         f16x8 *__restrict__ mrec)
 {
     using Fi = Filt<N>;
-    constexpr int R = RecLayout<N>::R;
-    const int64_t g = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (g >= k) return;
-    const float *r = grec + g * R;
+    constexpr int R = RecLayout<N>::R, R4 = R / 4, kSt = R4 | 1;
+    __shared__ f32x4 s_rec[kWave * kSt];
+    const int lane = lane_id();
+    const int64_t g0 = int64_t(blockIdx.x) * kWave, g = g0 + lane;
+    const int cnt = int(k - g0 < kWave ? k - g0 : kWave);
+    const int gp = lane < cnt ? gperm[g] : 0;
+#pragma unroll
+    for (int e = 0; e < R4; ++e) {
+        const int sl = e * kWave + lane, j = sl / R4, f = sl - j * R4;
+        const int src = __shfl(gp, j, kWave);
+        if (j < cnt) {
+            const f32x4 v = reinterpret_cast<const f32x4 *>(rec)[int64_t(src) * R4 + f];
+            s_rec[j * kSt + f] = v;
+            reinterpret_cast<f32x4 *>(grec)[g0 * R4 + sl] = v;
+        }
+    }
+    __syncthreads();
+    if (lane >= cnt) return;
+    float r[R4 * 4];
+#pragma unroll
+    for (int e = 0; e < R4; ++e) {
+        const f32x4 v = s_rec[lane * kSt + e];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[4 * e + i] = v[i];
+    }
     double S[Fi::T];
 #pragma unroll
     for (int e = 0; e < Fi::T; ++e) S[e] = double(r[N + e]);
@@ -661,10 +688,11 @@ __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
     }
 }
 
-template <int N> hipError_t coef_n(ngd_cull *c, hipStream_t s)
+template <int N> hipError_t records_n(const ngd_mixture *mix, ngd_cull *c, hipStream_t s)
 {
-    k_mfma_coef<N><<<unsigned((c->k + 255) / 256), 256, 0, s>>>(c->k, c->grec.as<float>(),
-                                                               c->mrec.as<f16x8>());
+    k_gauss_records<N><<<unsigned((c->k + kWave - 1) / kWave), kWave, 0, s>>>(
+        c->k, mix->rec.as<float>(), c->gperm.as<int32_t>(), c->grec.as<float>(),
+        c->mrec.as<f16x8>());
     return hipGetLastError();
 }
 
@@ -710,12 +738,12 @@ size_t mfma_rec_bytes(int n)
     return size_t((tri(n) + 7) / 8 + (n + 2 + 3) / 4) * sizeof(f16x8);
 }
 
-hipError_t launch_mfma_coef(int n, ngd_cull *c, hipStream_t s)
+hipError_t launch_gauss_records(const ngd_mixture *mix, ngd_cull *c, hipStream_t s)
 {
     if (c->k == 0) return hipSuccess;
-    switch (n) {
+    switch (mix->n) {
 #define NGD_CASE(NN) \
-    case NN: return coef_n<NN>(c, s);
+    case NN: return records_n<NN>(mix, c, s);
         NGD_CASE(1) NGD_CASE(2) NGD_CASE(3) NGD_CASE(4) NGD_CASE(5) NGD_CASE(6)
         NGD_CASE(7) NGD_CASE(8) NGD_CASE(9) NGD_CASE(10) NGD_CASE(11) NGD_CASE(12)
 #undef NGD_CASE

@@ -147,7 +147,8 @@ struct ngd_cull {
     ngd::DevBuf range_part;    // per-block min/max partials of the queries
     ngd::DevBuf gext_part;     // per-block min/max keys of the projected means
     ngd::DevBuf qrange;        // n_proj lo | n_proj hi | n_proj scale (float)
-    ngd::DevBuf g_mr, g_thr;   // n_proj x k float (caller order)
+    ngd::DevBuf g_mr;          // n_proj x k float (caller order)
+    ngd::DevBuf g_thr;         // k x thr_stride(n_proj) float (caller order)
     ngd::DevBuf keys0, keys1, vals0, vals1;   // radix sort ping-pong
     ngd::DevBuf radix_hist;    // 256 x nblocks int32
     ngd::DevBuf radix_off;     // 256 x nblocks + 1 int64
@@ -164,7 +165,9 @@ struct ngd_cull {
     ngd::DevBuf grec;          // k x rec_stride float, sorted Gaussians
     ngd::DevBuf g_mr_s;             // n_proj x k float, sorted Gaussians
     ngd::DevBuf g_ub, g_lb;         // n_proj x k float, sorted: the interval test's limits
-    ngd::DevBuf masks;         // nchunks x tpad uint64
+    ngd::DevBuf masks;         // nchunks x tpad uint64, where nz has a bit
+    ngd::DevBuf nz;            // tpad / 64 x nchunks uint64: the tiles with a nonzero mask
+    ngd::DevBuf cbnd;          // nchunks x 2 pad_proj(n_proj) float: the chunks' boxes
     ngd::DevBuf seg_cnt;       // nseg x ntiles int32 (counts, then prefixes)
     ngd::DevBuf tile_cnt;      // ntiles int32
     ngd::DevBuf tile_off;      // ntiles + 1 int64
@@ -256,9 +259,9 @@ hipError_t launch_eval_reduce(const ngd_cull *c, float *out, hipStream_t s);
 hipError_t launch_eval_culled(const ngd_mixture *mix, const ngd_cull *c, float *out,
                               unsigned long long *stats, hipStream_t s);
 size_t mfma_rec_bytes(int n);
-// The filter's per-Gaussian records (c->mrec) from the cull's ordered records
-// c->grec, on stream s.
-hipError_t launch_mfma_coef(int n, ngd_cull *c, hipStream_t s);
+// The records in the cull's order (c->grec) and the filter's (c->mrec), on
+// stream s.
+hipError_t launch_gauss_records(const ngd_mixture *mix, ngd_cull *c, hipStream_t s);
 hipError_t launch_backward_dense(const ngd_mixture *mix, const float *queries, int64_t q,
                                  const float *grad_out, float *g_mean, float *g_factor,
                                  float *g_weight, float *g_colour, hipStream_t s);
@@ -290,6 +293,7 @@ constexpr int kRadixMaxBins = 1024;   // digits of up to 10 bits
 constexpr int kSuperTiles = 16;
 // Projections per box in the interval test: n_proj rounded up to 4 (to 8
 // above 16).
+__host__ __device__ inline int thr_stride(int p) { return (p + 3) & ~3; }
 inline int pad_proj(int p) { return p <= 16 ? (p + 3) & ~3 : (p + 7) & ~7; }
 // Every buffer's capacity is checked on the host first (hipErrorInvalidValue
 // when one is too small).

@@ -77,3 +77,12 @@ def test_tile_counts(torch_cuda, q):
     # round, in several, and by the general scans
     mix, x, proj = case(2, 70, q, seed=q)
     _check(mix, x, proj, 1)
+
+
+@pytest.mark.parametrize("n_proj", [3, 16, 20])
+@pytest.mark.parametrize("q", [64 * 960, 64 * 1024 - 36])
+def test_chunk_boxes(torch_cuda, q, n_proj):
+    # 64 chunks against 15 and 16 groups of 64 tiles: the last size tested
+    # without the chunks' boxes first and the first with them
+    mix, x, _ = case(4, 4090, q, seed=n_proj)
+    _check(mix, x, inputs.gen_projections(4, n_proj, seed=5), 64)
