@@ -347,29 +347,48 @@ __global__ __launch_bounds__(kThreads) void k_kd_count(
     }
 }
 
-// Minima over the wave of V keys per lane, scattered as wave_reduce_scatter
-// does: lane 16 r + 15 holds those of keys [r V/4, (r + 1) V/4) in v[0 .. V/4).
-template <int V> __device__ __forceinline__ void wave_umin_scatter(uint32_t (&v)[V])
+// Minima (MAX: maxima) over the wave of V keys per lane, scattered as
+// wave_reduce_scatter does: lane 16 r + 15 holds those of keys
+// [r V/4, (r + 1) V/4) in v[0 .. V/4).
+template <int V, bool MAX = false> __device__ __forceinline__ void wave_umin_scatter(uint32_t (&v)[V])
 {
     static_assert(V % 4 == 0, "keys in four equal rows");
     constexpr int H = V / 2, Q = V / 4;
+    auto pick = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         const auto r = __builtin_amdgcn_permlane32_swap(v[i], v[i + H], false, false);
-        v[i] = min(uint32_t(r[0]), uint32_t(r[1]));
+        v[i] = pick(uint32_t(r[0]), uint32_t(r[1]));
     }
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         const auto r = __builtin_amdgcn_permlane16_swap(v[i], v[i + Q], false, false);
-        v[i] = min(uint32_t(r[0]), uint32_t(r[1]));
+        v[i] = pick(uint32_t(r[0]), uint32_t(r[1]));
     }
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        v[i] = dpp_umin<kDppRowShr1>(v[i]);
-        v[i] = dpp_umin<kDppRowShr2>(v[i]);
-        v[i] = dpp_umin<kDppRowShr4>(v[i]);
-        v[i] = dpp_umin<kDppRowShr8>(v[i]);
+        if constexpr (MAX) {
+            v[i] = dpp_umax_row<kDppRowShr1>(v[i]);
+            v[i] = dpp_umax_row<kDppRowShr2>(v[i]);
+            v[i] = dpp_umax_row<kDppRowShr4>(v[i]);
+            v[i] = dpp_umax_row<kDppRowShr8>(v[i]);
+        } else {
+            v[i] = dpp_umin<kDppRowShr1>(v[i]);
+            v[i] = dpp_umin<kDppRowShr2>(v[i]);
+            v[i] = dpp_umin<kDppRowShr4>(v[i]);
+            v[i] = dpp_umin<kDppRowShr8>(v[i]);
+        }
     }
+}
+
+// Each lane's minimum (maximum) with the lanes 16, 32 and 48 apart.
+template <bool MAX> __device__ __forceinline__ uint32_t rows_pick(uint32_t v)
+{
+    auto pick = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = pick(uint32_t(r[0]), uint32_t(r[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return pick(uint32_t(q[0]), uint32_t(q[1]));
 }
 
 // Moves a slice's points to their node's children: ranks inside the slice by
@@ -1073,11 +1092,14 @@ __global__ __launch_bounds__(kLocalThreads) void k_kd_local(
 // projection from them; a histogram of 256 equal steps over the run's range on
 // it, in floats (a monotone map, so that any rounding only moves points
 // between bins the same way for all), whose bin holding the pivot's rank
-// leaves a handful of points that one wave ranks; more than 64 of them
-// (ties, infinite ranges) are resolved by a radix descent instead.  Stable
-// partition by (key, position) against the pivot's.  Bound by its vector
-// operations and the chain of these steps: 36 us for one subtree, 107 for 512
-// (two rounds of the CUs; 10-D, 2^20 queries), where the sorts of k_kd_local
+// leaves a handful of points that one wave ranks; more than 64 of them take a
+// second histogram over the bin, and if they remain (ties, infinite ranges) a
+// radix descent (the Gaussians of an 800 x 800 10-D image, where far ones
+// squeeze the rest into a few bins: 206 -> 66 us by the second histogram).
+// Stable partition by (key, position) against the pivot's.  Bound by its
+// vector operations and the chain of these steps: 36 us for one subtree, 100
+// for 512 (two rounds of the CUs; 10-D, 2^20 queries; 107 with a reduction per
+// chunk instead of one for a wave's two), where the sorts of k_kd_local
 // took 58 to 100 and, with the level above that they left, 300.
 __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
     const int64_t *__restrict__ nodes, int64_t n, int P, int leaf,
@@ -1091,12 +1113,14 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
     __shared__ uint16_t ord[2][kSubMax];
     // histograms of the splitting runs; then the pivot bin's points of each
     __shared__ __attribute__((aligned(16))) uint32_t hist[kSplits][kHBins];
-    __shared__ uint32_t cext[kSubChunks][2 * kSubProj];   // minima, ~maxima
+    __shared__ uint32_t cext[kSubChunks][2 * kSubProj];   // minima, maxima
     __shared__ int rs[2][kRuns], rl[2][kRuns], rn[2][kRuns], rsi[2][kRuns];
     __shared__ int nruns[2], nsplit[2];
     __shared__ int srun[2][kSplits];                      // a splitting run's index
     __shared__ int sbin[kSplits], srank[kSplits], scnt[kSplits], lcnt[kSplits];
-    __shared__ int sdim[kSplits];
+    __shared__ int sdim[kSplits], sbin2[kSplits];   // sbin2: -1 without a second histogram
+    __shared__ int s_again;
+    __shared__ uint32_t s_starts;
     __shared__ uint64_t spiv[kSplits];
     __shared__ int ccnt[kSubChunks];
     __shared__ int crun[2][kSubChunks];
@@ -1140,69 +1164,84 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
         if (ns == 0) break;   // uniform
         int o[kPer], run[kPer], si[kPer];
         bool in[kPer];
-        // the chunks' extents
+        // the chunks' extents (lanes past the end repeat the last point, which
+        // is in the same run; keys of projections past P are not looked at)
+        bool have[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int c = kPer * w + u, pos = c * kWave + lane;
+            run[u] = uniform(crun[cur][c]);
+            si[u] = uniform(rsi[cur][run[u]]);
+            in[u] = pos < m;
+            o[u] = ord[cur][in[u] ? pos : m - 1];
+            have[u] = si[u] >= 0 && c * kWave < m;   // uniform
+        }
         {
-            uint32_t mm[2][2 * kSubProj];
-#pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const int c = kPer * w + u, pos = c * kWave + lane;
-                run[u] = uniform(crun[cur][c]);
-                si[u] = uniform(rsi[cur][run[u]]);
-                in[u] = pos < m;
-                o[u] = in[u] ? ord[cur][pos] : 0;
-#pragma unroll
-                for (int j = 0; j < kSubProj; ++j) {
-                    const bool ok = in[u] && j < P && si[u] >= 0;
-                    const uint32_t k = ok ? val[j][o[u]] : 0u;
-                    mm[u][j] = ok ? k : 0xffffffffu;
-                    mm[u][kSubProj + j] = ok ? ~k : 0xffffffffu;
-                }
-            }
-            auto put = [&](uint32_t (&v)[2 * kSubProj], int c) {
-                wave_umin_scatter<2 * kSubProj>(v);
+            auto put = [&](uint32_t (&lo)[kSubProj], uint32_t (&hi)[kSubProj], int c) {
+                wave_umin_scatter<kSubProj>(lo);
+                wave_umin_scatter<kSubProj, true>(hi);
                 if ((lane & 15) == 15)
 #pragma unroll
-                    for (int e = 0; e < kSubProj / 2; ++e)
-                        cext[c][(lane >> 4) * (kSubProj / 2) + e] = v[e];
+                    for (int e = 0; e < kSubProj / 4; ++e) {
+                        cext[c][(lane >> 4) * (kSubProj / 4) + e] = lo[e];
+                        cext[c][kSubProj + (lane >> 4) * (kSubProj / 4) + e] = hi[e];
+                    }
             };
-            if (run[0] == run[1]) {   // one reduction for both
+            uint32_t lo[kSubProj], hi[kSubProj];
+            if (have[0] && have[1] && run[0] == run[1]) {   // one reduction for both
 #pragma unroll
-                for (int e = 0; e < 2 * kSubProj; ++e) mm[0][e] = min(mm[0][e], mm[1][e]);
-                if (lane < 2 * kSubProj) cext[kPer * w + 1][lane] = 0xffffffffu;
-                put(mm[0], kPer * w);
+                for (int j = 0; j < kSubProj; ++j) {
+                    const uint32_t a = val[j][o[0]], b = val[j][o[1]];
+                    lo[j] = min(a, b);
+                    hi[j] = max(a, b);
+                }
+                if (lane < 2 * kSubProj)
+                    cext[kPer * w + 1][lane] = lane < kSubProj ? 0xffffffffu : 0u;
+                put(lo, hi, kPer * w);
             } else {
-                put(mm[0], kPer * w);
-                put(mm[1], kPer * w + 1);
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    if (!have[u]) continue;
+#pragma unroll
+                    for (int j = 0; j < kSubProj; ++j) lo[j] = hi[j] = val[j][o[u]];
+                    put(lo, hi, kPer * w + u);
+                }
             }
         }
+        if (tid == 0) s_again = 0;
         __syncthreads();
         // split projections; histograms over the runs' ranges on them
         uint32_t key[kPer];
-        int bin[kPer];
+        int bin[kPer], bin2[kPer];
+        float t[kPer];
         int dim = 0;
         float vlo = 0.0f, scale = 0.0f;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             key[u] = 0;
-            bin[u] = -1;
-            if (si[u] < 0) continue;   // uniform
-            if (u == 0 || run[u] != run[0]) {
+            bin[u] = bin2[u] = -1;
+            if (!have[u]) continue;   // uniform
+            if (u == 0 || !have[0] || run[u] != run[0]) {
                 const int c0 = rs[cur][run[u]] / kWave;
                 const int c1 = (rs[cur][run[u]] + rl[cur][run[u]] + kWave - 1) / kWave;
+                // lane: projection lane mod 16, every fourth chunk (past the
+                // last, it again)
                 const int j = lane & 15;
-                uint32_t lo = 0xffffffffu, nhi = 0xffffffffu;
-                for (int c = c0 + (lane >> 4); c < c1; c += 4) {
-                    lo = min(lo, cext[c][j]);
-                    nhi = min(nhi, cext[c][kSubProj + j]);
+                uint32_t lo = 0xffffffffu, hi = 0u;
+                for (int b = c0 + (lane >> 4); b < c1 + (lane >> 4); b += 16) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int c = min(b + 4 * e, c1 - 1);
+                        lo = min(lo, cext[c][j]);
+                        hi = max(hi, cext[c][kSubProj + j]);
+                    }
                 }
-                lo = min(lo, uint32_t(__shfl_xor(int(lo), 16, kWave)));
-                lo = min(lo, uint32_t(__shfl_xor(int(lo), 32, kWave)));
-                nhi = min(nhi, uint32_t(__shfl_xor(int(nhi), 16, kWave)));
-                nhi = min(nhi, uint32_t(__shfl_xor(int(nhi), 32, kWave)));
+                lo = rows_pick<false>(lo);
+                hi = rows_pick<true>(hi);
                 // the largest extent, the first on ties; one that is not a
                 // number counts only in the first place
-                const float flo = from_orderable(lo), fhi = from_orderable(~nhi);
-                const float e = fhi - flo;
+                const float flo = from_orderable(lo);
+                const float e = from_orderable(hi) - flo;
                 uint32_t ek = e == e ? orderable(e) : (j == 0 ? 0xffffffffu : 0u);
                 if (j >= P) ek = 0u;
                 const uint32_t best = __builtin_amdgcn_readlane(wave_umax_dpp(ek), kWave - 1);
@@ -1215,19 +1254,16 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
                 if (!(scale < INFINITY)) scale = 0.0f;
                 if (lane == 0) sdim[si[u]] = dim;
             }
+            key[u] = val[dim][o[u]];
+            t[u] = (from_orderable(key[u]) - vlo) * scale;
             if (in[u]) {
-                key[u] = val[dim][o[u]];
-                const float t = (from_orderable(key[u]) - vlo) * scale;
-                bin[u] = t > 0.0f ? min(int(t), kHBins - 1) : 0;   // not a number: 0
+                bin[u] = t[u] > 0.0f ? min(int(t[u]), kHBins - 1) : 0;   // not a number: 0
                 atomicAdd(&hist[si[u]][bin[u]], 1u);
             }
         }
         __syncthreads();
-        // the bin of each splitting run's pivot, a wave per run; the run
-        // tables of the next level, wave 15 (runs in order of their starts)
-        if (w < ns) {
-            const int r = srun[cur][w];
-            const int want = rn[cur][r];
+        // the bin of run w's histogram that holds rank `want`
+        auto pick_bin = [&](int want, int *out) {
             const uint4 c4 = *reinterpret_cast<const uint4 *>(&hist[w][4 * lane]);
             const int c[4] = {int(c4.x), int(c4.y), int(c4.z), int(c4.w)};
             const int sum = c[0] + c[1] + c[2] + c[3];
@@ -1235,13 +1271,22 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (want >= cum && want < cum + c[i]) {
-                    sbin[w] = 4 * lane + i;
+                    out[w] = 4 * lane + i;
                     srank[w] = want - cum;
                     scnt[w] = c[i];
+                    if (out == sbin && c[i] > kWave) s_again = 1;
                 }
                 cum += c[i];
             }
-            if (lane == 0) lcnt[w] = 0;
+        };
+        // the bin of each splitting run's pivot, a wave per run; the run
+        // tables of the next level, wave 15 (runs in order of their starts)
+        if (w < ns) {
+            pick_bin(rn[cur][srun[cur][w]], sbin);
+            if (lane == 0) {
+                lcnt[w] = 0;
+                sbin2[w] = -1;
+            }
         }
         if (w == kSubThreads / kWave - 1) {
             const int nr = nruns[cur];
@@ -1269,19 +1314,48 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
                     rsi[nx][at + 1] = n1 >= 0 ? k1 : -1;
                     if (n1 >= 0) srun[nx][k1] = at + 1;
                 }
-                for (int c = s0 / kWave; c * kWave < s0 + len; ++c)
-                    crun[nx][c] = at + (nl >= 0 && c * kWave >= s0 + l0 ? 1 : 0);
             }
+            // a chunk's run: the runs that start at or before it
+            if (lane == 0) s_starts = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (has)
+                atomicOr(&s_starts, 1u << (s0 / kWave) | (nl >= 0 ? 1u << ((s0 + l0) / kWave) : 0u));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t starts = s_starts;
+            if (lane < kSubChunks)
+                crun[nx][lane] = __popc(starts & (0xffffffffu >> (31 - lane))) - 1;
             if (lane == 0) {
                 nruns[nx] = nr + __popcll(sp);
                 nsplit[nx] = __popcll(b0) + __popcll(b1);
             }
         }
         __syncthreads();
+        // bins of more points than a wave ranks: a second histogram over the
+        // bin's own range (the same map, of what it left)
+        if (s_again) {   // uniform
+            if (w < ns && scnt[w] > kWave) {
+                *reinterpret_cast<uint4 *>(&hist[w][4 * lane]) = make_uint4(0, 0, 0, 0);
+                if (lane == 0) sbin2[w] = 0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                if (bin[u] >= 0 && sbin2[si[u]] >= 0 && bin[u] == sbin[si[u]]) {
+                    const float f = (t[u] - float(bin[u])) * float(kHBins);
+                    bin2[u] = f > 0.0f ? min(int(f), kHBins - 1) : 0;
+                    atomicAdd(&hist[si[u]][bin2[u]], 1u);
+                }
+            }
+            __syncthreads();
+            if (w < ns && sbin2[w] >= 0) pick_bin(srank[w], sbin2);
+            __syncthreads();
+        }
         // that bin's points, listed over the run's histogram
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
-            if (bin[u] >= 0 && bin[u] == sbin[si[u]]) {
+            if (bin[u] >= 0 && bin[u] == sbin[si[u]] && bin2[u] == sbin2[si[u]]) {
                 const int slot = atomicAdd(&lcnt[si[u]], 1);
                 if (slot < kWave)
                     reinterpret_cast<uint64_t *>(hist[si[u]])[slot] =
@@ -1352,7 +1426,7 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
         for (int u = 0; u < kPer; ++u) {
             const int c = kPer * w + u;
             const uint64_t mine = uint64_t(key[u]) << 16 | uint32_t(c * kWave + lane);
-            bl[u] = si[u] >= 0 ? ballot(in[u] && mine < spiv[si[u]]) : 0;
+            bl[u] = have[u] ? ballot(in[u] && mine < spiv[si[u]]) : 0;
             if (lane == 0) ccnt[c] = __popcll(bl[u]);
         }
         __syncthreads();
@@ -1360,7 +1434,7 @@ __global__ __launch_bounds__(kSubThreads) void k_kd_subtree(
         for (int u = 0; u < kPer; ++u) {
             const int c = kPer * w + u, pos = c * kWave + lane;
             int np = pos;
-            if (si[u] >= 0) {   // uniform
+            if (have[u]) {   // uniform
                 const int s0 = rs[cur][run[u]];
                 const int v = lane >= s0 / kWave && lane < c ? ccnt[lane & (kSubChunks - 1)] : 0;
                 const int before = wave_last(wave_inclusive_scan(v));

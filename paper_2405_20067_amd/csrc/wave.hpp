@@ -193,6 +193,12 @@ __device__ __forceinline__ uint32_t wave_umin_dpp(uint32_t v)
     return v;
 }
 
+// One step of such a running maximum.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_umax_row(uint32_t v)
+{
+    return max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, false)));
+}
+
 // One step of such a running minimum.
 template <int CTRL> __device__ __forceinline__ uint32_t dpp_umin(uint32_t v)
 {

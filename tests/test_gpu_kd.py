@@ -22,7 +22,7 @@ def torch_cuda():
     return torch
 
 
-def _check(mix, x, proj, tile):
+def _check(mix, x, proj, tile, fields=("perm", "gperm", "tile_off", "cand")):
     from paper_2405_20067_amd import ngd
     k, n = mix["mean"].shape
     m = ngd.Mixture(n, k)
@@ -36,7 +36,7 @@ def _check(mix, x, proj, tile):
         got = c.build(m, xd, proj, p).export()
         want = oracle.cull(mix["mean"], mix["factor"], x, proj, tau=p.tau, tile=tile,
                            key_proj=p.key_proj)
-        for f in ("perm", "gperm", "tile_off", "cand"):
+        for f in fields:
             np.testing.assert_array_equal(got[f], want[f], err_msg=f)
 
 
@@ -86,3 +86,17 @@ def test_chunk_boxes(torch_cuda, q, n_proj):
     # without the chunks' boxes first and the first with them
     mix, x, _ = case(4, 4090, q, seed=n_proj)
     _check(mix, x, inputs.gen_projections(4, n_proj, seed=5), 64)
+
+
+@pytest.mark.parametrize("q", [1500, 2048, 5000])
+@pytest.mark.parametrize("far", [30.0, 3e3, 3e38])
+def test_heavy_bins(torch_cuda, q, far):
+    # bins of more than 64 points that a second histogram over the bin
+    # separates wholly, in part, and not at all (the range is infinite)
+    mix, x, proj = case(3, 3000, q, seed=q)
+    x[q // 2] = far
+    x[q // 3] = -far
+    mix["mean"][:] = x[np.random.default_rng(q).integers(0, q, 3000)]
+    # the orders alone: the lists of means whose projections overflow are not
+    # the re-implementation's
+    _check(mix, x, proj, 256, fields=("perm", "gperm"))
