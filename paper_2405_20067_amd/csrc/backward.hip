@@ -11,8 +11,11 @@
 // Atomics-free and Gaussian-major.  Culled: the forward pass records, for
 // every candidate entry (tile, Gaussian) and every 64-query group of the
 // tile, whether it kept the pair group (one byte); the backward visits only
-// the kept groups, so it sums over exactly the pairs the forward summed,
-// recomputing y, G and the exp rather than storing them.  A work item is one
+// the kept groups, recomputing y, G and the exp rather than storing them.  In
+// mixtures of more than kOneScanItems Gaussians, one with a handful of queries
+// above the skip threshold takes those alone (k_light_moments,
+// k_light_gradients); the others, and all of a smaller mixture, sum over
+// exactly the pairs the forward summed, by work items.  A work item is one
 // Gaussian and at most kItemTiles of its candidate entries (the transposed
 // lists); one wave evaluates the item's kept groups 64 queries at a time,
 // keeps per-lane partial moments in registers (B1: n, B2: n(n+1)/2, H: 3),
@@ -20,7 +23,10 @@
 // k_backward_finalize then adds each Gaussian's items in item order and
 // applies S^T.  Dense: one workgroup per Gaussian over all queries.
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
 
+#include "eval_common.hpp"
 #include "ngd_internal.hpp"
 #include "wave.hpp"
 
@@ -228,21 +234,22 @@ __device__ __forceinline__ void backward_item(
         {
             const int64_t tt = __builtin_amdgcn_readlane(tl, l);
             const int sidx = gq * kWave + lane;
-            const int64_t p = tt * tile + sidx;
-            const bool valid = (sidx < tile) && (p < q);
+            const bool valid = (sidx < tile) && (tt * tile + sidx < q);
             // every lane loads (a lane past the tile's end from the tile's
-            // first query) and the invalid ones are zeroed: no branches
-            const int64_t pc = valid ? p : tt * tile;
+            // first query) and the invalid ones are zeroed: no branches;
+            // scalar bases and one offset, no 64-bit sums a lane
+            const uint32_t at = valid ? uint32_t(sidx) : 0u;
             float x[N], d[N], y[N];
 #pragma unroll
-            for (int a = 0; a < N; ++a) x[a] = qs[a * q + pc];
+            for (int a = 0; a < N; ++a) x[a] = (qs + a * q + tt * tile)[at];
             float msq = 0.0f;
             brows<N, 0, N>(r, x, d, y, msq);
             any = true;
             const float G = valid ? __builtin_amdgcn_exp2f(-msq) : 0.0f;
-            const float g0v = valid ? gs[pc] : 0.0f;
-            const float g1v = valid ? gs[q + pc] : 0.0f;
-            const float g2v = valid ? gs[2 * q + pc] : 0.0f;
+            const float *gt = gs + tt * tile;
+            const float g0v = valid ? gt[at] : 0.0f;
+            const float g1v = valid ? (gt + q)[at] : 0.0f;
+            const float g2v = valid ? (gt + 2 * q)[at] : 0.0f;
             const float sdot = fmaf(g2v, c2, fmaf(g1v, c1, g0v * c0));
             const float w = alpha * G * sdot;
             h0 = fmaf(G, g0v, h0);
@@ -304,11 +311,310 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_items(
                          gitem_g, gpart, gflag);
 }
 
+// ---- culled: Gaussians with a handful of queries --------------------------
+// Where a Gaussian is small against the queries' spacing (10-D, 2^20 queries:
+// 1.4 kept groups a Gaussian with 1.5 queries each above the skip threshold),
+// an item's wave adds moments that are zero in nearly all lanes, and its sum
+// over the lanes takes longer than its pairs.  Here a lane is a query for the
+// distances only; the few that count leave their factors in LDS, and the lanes
+// then take a moment each.
+//
+// A query counts unless its Gaussian value is below tau 2^-kLightLog2Margin,
+// half a float32 rounding step of the least weight the cull keeps.  One that
+// is infinite or not a number counts wherever its group is kept, as in an item.
+constexpr double kLightLog2Margin = 24.0;
+constexpr int kLightGaussians = 8;    // of a wave (4: 177 us and 385 at 2^22 queries, 16: 177 and 403)
+constexpr int kLightRows = 32;        // queries of a pair that can count
+constexpr int kLightQueries = 64;     // queries of a Gaussian
+constexpr int kLightEntries = 32;     // kept entries of a Gaussian
+
+// ncount: the Gaussian's queries, its moments then in row g of mom (if any), or
+// -1 where there are more than the above: it goes to items (their number in
+// item_cnt).  Bound by the loads of the pairs' queries, 13 separate rows of 256
+// bytes at n = 10: 169 us at 10-D, 2^20 queries (379 at 2^22), with an L2 miss
+// for 43% of the lines.  Loading a pair ahead, or the records' lines beforehand,
+// changed nothing, and neither did a sixth fewer vector operations.
+template <int N>
+__global__ __launch_bounds__(kBwdThreads) void k_light_moments(
+    int64_t k, int64_t q, int tile, float lim, const float *__restrict__ grec,
+    const float *__restrict__ qs, const float *__restrict__ gs,
+    const int64_t *__restrict__ a_off, const uint32_t *__restrict__ a_key,
+    const int32_t *__restrict__ a_ent, const int32_t *__restrict__ ent_tile,
+    const uint8_t *__restrict__ act, float *__restrict__ mom, int32_t *__restrict__ ncount,
+    int32_t *__restrict__ item_cnt)
+{
+    using Lay = BwdLayout<N>;
+    constexpr int T = Lay::T, R = Lay::R, NM = Lay::NM;
+    constexpr int AL = N + T + 3, CO = N + T + 4;
+    // a row: y (N) | w y (N) | 1 | G g (3); every moment is a product of two
+    constexpr int ONE = 2 * N, RS = (2 * N + 4) | 1;
+    constexpr int NE = (NM + kWave - 1) / kWave;
+    __shared__ float s_row[kWavesPerBlock][kLightRows * RS];
+    const int lane = lane_id(), w = uniform(int(threadIdx.x) / kWave);
+    // neighbouring Gaussians, which share tiles, share an L2
+    const int64_t g0 =
+        (xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + w) * kLightGaussians;
+    if (g0 >= k) return;
+    const int ng = int(k - g0 < kLightGaussians ? k - g0 : kLightGaussians);
+    const int64_t off = a_off[g0 + (lane < ng ? lane : ng)];
+    const int64_t b = uniform64(off);
+    const int rel = int(off - b);   // this wave's entries: below 2^31
+    const int ne = __builtin_amdgcn_readlane(rel, ng);
+    const int mine = __shfl_down(rel, 1, kWave) - rel;   // lane < ng: its Gaussian's entries
+    // lane < ng: its Gaussian's queries so far
+    int cnt = lane < ng && mine > kLightEntries ? kLightQueries + 1 : 0;
+    // this lane's moments: lane, lane + 64
+    int fa[NE], fb[NE];
+    float acc[NE];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int e = lane + i * kWave;
+        fa[i] = fb[i] = ONE;
+        acc[i] = 0.0f;
+        if (e < N) {
+            fa[i] = N + e;
+        } else if (e < N + T) {
+            int a = 0;
+            while ((a + 1) * (a + 2) / 2 <= e - N) ++a;
+            fa[i] = N + a;
+            fb[i] = e - N - a * (a + 1) / 2;
+        } else if (e < NM) {
+            fa[i] = ONE + 1 + e - N - T;
+        }
+    }
+    const ConstRec rec0 = const_rec(grec) + g0 * R;
+    float *row = s_row[w];
+    int cur = -1;
+    auto flush = [&](int next) {   // the moments of Gaussian cur
+        if (cur >= 0) {
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = lane + i * kWave;
+                if (e < NM) mom[(g0 + cur) * NM + e] = acc[i];
+                acc[i] = 0.0f;
+            }
+        }
+        cur = next;
+    };
+    const int ngroups = (tile + kWave - 1) / kWave;
+    for (int base = 0; base < ne; base += kWave) {
+        int tl = 0, gl = 0;
+        uint32_t fl = 0;   // bit g: group g kept
+        if (base + lane < ne) {
+            const int64_t e = b + base + lane;
+            gl = int(a_key[e] - uint32_t(g0));
+            const int64_t ent = a_ent[e];
+            tl = ent_tile[ent];
+            const uint8_t *af = act + ent * ngroups;
+            if (ngroups == 4) {
+                const uint32_t v = *reinterpret_cast<const uint32_t *>(af);
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) fl |= uint32_t(((v >> (8 * gq)) & 0xffu) != 0) << gq;
+            } else {
+                for (int gq = 0; gq < ngroups; ++gq) fl |= uint32_t(af[gq] != 0) << gq;
+            }
+        }
+        if (__shfl(cnt, gl, kWave) > kLightQueries) fl = 0;
+        for (uint64_t m = ballot(fl != 0); m != 0; m = ballot(fl != 0)) {
+            const int l = __builtin_ctzll(m);
+            const uint32_t bits = __builtin_amdgcn_readlane(fl, l);
+            const int gq = __builtin_ctz(bits);
+            if (lane == l) fl = bits & (bits - 1);
+            const int gg = __builtin_amdgcn_readlane(gl, l);
+            const int64_t t0 = int64_t(__builtin_amdgcn_readlane(tl, l)) * tile;
+            const int sidx = gq * kWave + lane;
+            const bool valid = (sidx < tile) && (t0 + sidx < q);
+            // scalar bases and one offset, no 64-bit sums a lane
+            const uint32_t at = valid ? uint32_t(sidx) : 0u;
+            const ConstRec r = rec0 + gg * R;
+            float x[N], d[N], y[N];
+            const float *col = qs + t0;
+#pragma unroll
+            for (int a = 0; a < N; ++a, col += q) x[a] = col[at];
+            float msq = 0.0f;
+#pragma unroll
+            for (int a = 0; a < N; ++a) {
+                d[a] = x[a] - r[a];
+                float t = r[N + a * (a + 1) / 2] * d[0];
+#pragma unroll
+                for (int j = 1; j <= a; ++j) t = fmaf(r[N + a * (a + 1) / 2 + j], d[j], t);
+                y[a] = t;
+                msq = fmaf(t, t, msq);
+            }
+            const bool counts = valid && !(msq > lim && msq < INFINITY);
+            const uint64_t hit = ballot(counts);
+            const int nh = __popcll(hit);
+            int c = __builtin_amdgcn_readlane(cnt, gg) + nh;
+            if (nh > kLightRows) c = kLightQueries + 1;
+            if (lane == gg) cnt = c;
+            if (c > kLightQueries) {
+                if (gl == gg) fl = 0;
+                continue;
+            }
+            if (nh == 0) continue;
+            if (gg != cur) flush(gg);
+            if (counts) {
+                float *o = row + __popcll(hit & lanemask_lt()) * RS;
+                const float *gt = gs + t0;
+                const float gv[3] = {gt[at], (gt + q)[at], (gt + 2 * q)[at]};
+                const float G = __builtin_amdgcn_exp2f(-msq);
+                const float wgt = r[AL] * G *
+                                  fmaf(gv[2], r[CO + 2], fmaf(gv[1], r[CO + 1], gv[0] * r[CO]));
+#pragma unroll
+                for (int a = 0; a < N; ++a) {
+                    o[a] = y[a];
+                    o[N + a] = wgt * y[a];
+                }
+                o[ONE] = 1.0f;
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) o[ONE + 1 + ch] = G * gv[ch];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int h = 0; h < nh; ++h) {
+#pragma unroll
+                for (int i = 0; i < NE; ++i)
+                    acc[i] = fmaf(row[h * RS + fa[i]], row[h * RS + fb[i]], acc[i]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    flush(-1);
+    if (lane < ng) {
+        const bool heavy = cnt > kLightQueries;
+        ncount[g0 + lane] = heavy ? -1 : cnt;
+        item_cnt[g0 + lane] = heavy ? (mine + kItemTiles - 1) / kItemTiles : 0;
+    }
+}
+
+// The gradients of the Gaussians whose moments k_light_moments left: a lane
+// applies S^T to its Gaussian's, a wave per 64 Gaussians.  Records and moments
+// come, and gradients go, through LDS, consecutive lanes on consecutive words:
+// written from the lanes, every store would touch 64 lines.  62 us at K =
+// 262,144, n = 10, 3.5 TB/s (the pass of k_backward_finalize, which stores from
+// its lanes, took 81).
+template <int N>
+__global__ __launch_bounds__(kWave, 2) void k_light_gradients(
+    int64_t k, const float *__restrict__ grec, const float *__restrict__ mom,
+    const int32_t *__restrict__ ncount, const int32_t *__restrict__ gperm,
+    float *__restrict__ g_mean, float *__restrict__ g_factor, float *__restrict__ g_weight,
+    float *__restrict__ g_colour)
+{
+    using Lay = BwdLayout<N>;
+    constexpr int T = Lay::T, R = Lay::R, NM = Lay::NM;
+    constexpr int F = N + T + 7;        // fields used of a record
+    constexpr int ST = R + 1;           // odd: no bank conflicts
+    static_assert(R % 4 == 0 && N + T + 4 <= R, "a lane's row");
+    __shared__ float st[kWave * ST];
+    __shared__ int32_t s_gi[kWave];
+    const int lane = lane_id();
+    const int64_t g0 = int64_t(blockIdx.x) * kWave, g = g0 + lane;
+    const int n = g < k ? ncount[g] : -1;
+    if (ballot(n >= 0) == 0) return;
+    s_gi[lane] = n >= 0 ? gperm[g] : -1;
+    const int rows = int(k - g0 < kWave ? k - g0 : kWave);
+    {
+        const float4 *src = reinterpret_cast<const float4 *>(grec + g0 * R);
+#pragma unroll
+        for (int i = 0; i < R / 4; ++i) {
+            const int e = i * kWave + lane, j = e / (R / 4), u = e - j * (R / 4);
+            if (j < rows) {
+                const float4 v = src[e];
+                float *o = st + j * ST + 4 * u;
+                o[0] = v.x;
+                o[1] = v.y;
+                o[2] = v.z;
+                o[3] = v.w;
+            }
+        }
+    }
+    __syncthreads();
+    float r[F], mo[NM];
+#pragma unroll
+    for (int e = 0; e < F; ++e) r[e] = st[lane * ST + e];
+    __syncthreads();
+    {
+        constexpr int V = (NM + 3) / 4;
+        // (rows nobody wrote are read, below the buffer's end, and not used)
+        const float4 *src = reinterpret_cast<const float4 *>(mom + g0 * NM);
+        const int words = rows * NM;
+        float4 v[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int e = 4 * (i * kWave + lane);
+            if (e + 3 < words) {
+                v[i] = src[i * kWave + lane];
+            } else {
+                v[i].x = e < words ? mom[g0 * NM + e] : 0.0f;
+                v[i].y = e + 1 < words ? mom[g0 * NM + e + 1] : 0.0f;
+                v[i].z = e + 2 < words ? mom[g0 * NM + e + 2] : 0.0f;
+                v[i].w = 0.0f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const float c[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = 4 * (i * kWave + lane) + u, j = e / NM;
+                if (e < words) st[j * ST + e - j * NM] = c[u];
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NM; ++e) mo[e] = n > 0 ? st[lane * ST + e] : 0.0f;
+    __syncthreads();
+    constexpr int AL = N + T + 3, CO = N + T + 4;
+    const float *b1 = mo, *b2 = mo + N;
+    // dm | dL | dc | dalpha
+    const float inv_c = float(1.0 / kHalfLog2e);
+    const float inv_c15 = float(1.0 / (kHalfLog2e * kSqrtHalfLog2e));
+    float *o = st + lane * ST;
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int kk = a; kk < N; ++kk) sum = fmaf(r[N + kk * (kk + 1) / 2 + a], b1[kk], sum);
+        o[a] = sum * inv_c;
+#pragma unroll
+        for (int c = 0; c <= a; ++c) {
+            float t = 0.0f;
+#pragma unroll
+            for (int kk = a; kk < N; ++kk)
+                t = fmaf(r[N + kk * (kk + 1) / 2 + a], b2[kk * (kk + 1) / 2 + c], t);
+            o[N + a * (a + 1) / 2 + c] = t * inv_c15;
+        }
+    }
+    const float h0 = mo[N + T], h1 = mo[N + T + 1], h2 = mo[N + T + 2];
+    o[N + T + 0] = r[AL] * h0;
+    o[N + T + 1] = r[AL] * h1;
+    o[N + T + 2] = r[AL] * h2;
+    o[N + T + 3] = fmaf(r[CO + 2], h2, fmaf(r[CO + 1], h1, r[CO] * h0));
+    __syncthreads();
+    auto put = [&](float *dst, auto width, int from) {
+        constexpr int W = decltype(width)::value;
+#pragma unroll 11
+        for (int i = 0; i < W; ++i) {
+            const int e = i * kWave + lane, j = e / W, c = e - j * W;
+            const int64_t gi = s_gi[j];
+            if (gi >= 0) dst[gi * W + c] = st[j * ST + from + c];
+        }
+    };
+    put(g_mean, std::integral_constant<int, N>{}, 0);
+    put(g_factor, std::integral_constant<int, T>{}, N);
+    put(g_colour, std::integral_constant<int, 3>{}, N + T);
+    put(g_weight, std::integral_constant<int, 1>{}, N + T + 3);
+}
+
 // Per sorted Gaussian: sum its items' moments in item order, then
 //   dm = S'^T B1 / c, dL = tril(S'^T B2) / c^1.5, dalpha = c . H, dc = alpha H.
+// light: those without items have their gradients already.
 template <int N>
 __global__ __launch_bounds__(kBwdThreads) void k_backward_finalize(
-    int64_t k, const float *__restrict__ grec, const int64_t *__restrict__ gitem_off,
+    int64_t k, bool light, const float *__restrict__ grec, const int64_t *__restrict__ gitem_off,
     const float *__restrict__ gpart, const int32_t *__restrict__ gflag,
     const int32_t *__restrict__ gperm, float *__restrict__ g_mean,
     float *__restrict__ g_factor, float *__restrict__ g_weight, float *__restrict__ g_colour)
@@ -317,10 +623,12 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_finalize(
     constexpr int T = Lay::T, NM = Lay::NM;
     const int64_t g = int64_t(blockIdx.x) * kBwdThreads + threadIdx.x;
     if (g >= k) return;
+    const int64_t i0 = gitem_off[g], i1 = gitem_off[g + 1];
+    if (light && i0 == i1) return;
     float acc[NM];
 #pragma unroll
     for (int e = 0; e < NM; ++e) acc[e] = 0.0f;
-    for (int64_t i = gitem_off[g]; i < gitem_off[g + 1]; ++i) {
+    for (int64_t i = i0; i < i1; ++i) {
         if (!gflag[i]) continue;
         const float *pp = gpart + i * NM;
 #pragma unroll
@@ -403,6 +711,27 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
         c->q, c->perm.as<int32_t>(), grad_out, c->gs.as<float>(), c->k, c->a_cnt.as<int32_t>());
     hipError_t err = launch_backward_prepare(c, s);
     if (err != hipSuccess) return err;
+    const int32_t *a_ent = c->a_ent_buf ? c->vals1.as<int32_t>() : c->vals0.as<int32_t>();
+    // The Gaussians with a handful of queries first, by lanes: 10-D, K =
+    // 262,144, 2^20 queries: items and their sums 370 us, now 231 + 9; 2^22
+    // queries 560, now 441 + 49.  Up to kOneScanItems Gaussians, whose items'
+    // offsets come with the lists' in one launch, the four launches more cost
+    // what it saves.
+    const bool light = mix->k > kOneScanItems;
+    if (light) {
+        const float lim = float(-std::log2(double(c->params.tau)) + kLightLog2Margin);
+        const int64_t per = int64_t(kWavesPerBlock) * kLightGaussians;
+        k_light_moments<N><<<unsigned((mix->k + per - 1) / per), kBwdThreads, 0, s>>>(
+            mix->k, c->q, c->params.tile, lim, c->grec.as<float>(), c->qs.as<float>(),
+            c->gs.as<float>(), c->a_off.as<int64_t>(),
+            c->a_ent_buf ? c->keys1.as<uint32_t>() : c->keys0.as<uint32_t>(), a_ent,
+            c->ent_tile.as<int32_t>(), c->act.as<uint8_t>(), c->gpart.as<float>(),
+            c->gflag.as<int32_t>(), c->gitem_cnt.as<int32_t>());
+        k_light_gradients<N><<<unsigned((mix->k + kWave - 1) / kWave), kWave, 0, s>>>(
+            mix->k, c->grec.as<float>(), c->gpart.as<float>(), c->gflag.as<int32_t>(),
+            c->gperm.as<int32_t>(), gm, gf, gw, gc);
+        if ((err = launch_backward_items(c, s)) != hipSuccess) return err;
+    }
     if (c->gitems_cap > 0) {
         // about four rounds of resident waves (4 per SIMD at this kernel's
         // register count), each taking items a grid apart: 1,024 / 2,048 /
@@ -411,7 +740,6 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
         // one wave per item
         const unsigned blocks = unsigned(std::min<int64_t>(
             (c->gitems_cap + kWavesPerBlock - 1) / kWavesPerBlock, kBwdItemBlocks));
-        const int32_t *a_ent = c->a_ent_buf ? c->vals1.as<int32_t>() : c->vals0.as<int32_t>();
         k_backward_items<N><<<blocks, kBwdThreads, 0, s>>>(
             mix->k, c->q, c->params.tile, c->grec.as<float>(), c->qs.as<float>(),
             c->gs.as<float>(), c->a_off.as<int64_t>(), a_ent,
@@ -420,7 +748,7 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     }
     const unsigned fb = unsigned((mix->k + kBwdThreads - 1) / kBwdThreads);
     k_backward_finalize<N><<<fb, kBwdThreads, 0, s>>>(
-        mix->k, c->grec.as<float>(), c->gitem_off.as<int64_t>(), c->gpart.as<float>(),
+        mix->k, light, c->grec.as<float>(), c->gitem_off.as<int64_t>(), c->gpart.as<float>(),
         c->gflag.as<int32_t>(), c->gperm.as<int32_t>(), gm, gf, gw, gc);
     return hipGetLastError();
 }

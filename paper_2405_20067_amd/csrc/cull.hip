@@ -1290,6 +1290,16 @@ __global__ __launch_bounds__(kThreads) void k_ecompact(int64_t total, int groups
 
 }  // namespace
 
+namespace {
+hipError_t item_fill(ngd_cull *c, hipStream_t s)
+{
+    if (c->k > 0 && c->gitems_cap > 0)
+        k_item_fill<<<nblk(c->k, kThreads), kThreads, 0, s>>>(
+            c->k, c->gitem_off.as<int64_t>(), c->gitems_cap, c->gitem_g.as<int32_t>());
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
 {
     const int64_t k = c->k, total = c->total;
@@ -1319,20 +1329,15 @@ hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
     } else {
         c->a_ent_buf = 0;
     }
-    if (k <= kOneScanItems) {
-        e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, nullptr, s);
-    } else {
-        e = scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
-        if (e == hipSuccess)
-            e = launch_items(k, c->a_off.as<int64_t>(), kItemTiles, c->gitem_cnt, c->gitem_off,
-                             c->scan_tmp, s);
-    }
-    if (e != hipSuccess) return e;
-    if (k > 0 && c->gitems_cap > 0)
-        k_item_fill<<<nblk(k, kThreads), kThreads, 0, s>>>(k, c->gitem_off.as<int64_t>(),
-                                                           c->gitems_cap,
-                                                           c->gitem_g.as<int32_t>());
-    return hipGetLastError();
+    if (k > kOneScanItems) return scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
+    e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, nullptr, s);
+    return e == hipSuccess ? item_fill(c, s) : e;
+}
+
+hipError_t launch_backward_items(ngd_cull *c, hipStream_t s)
+{
+    const hipError_t e = scan_counts(c->gitem_cnt, c->gitem_off, c->k, c->scan_tmp, s);
+    return e == hipSuccess ? item_fill(c, s) : e;
 }
 
 bool cull_reserve_lists(ngd_cull *c)

@@ -270,9 +270,12 @@ hipError_t launch_backward_culled(const ngd_mixture *mix, ngd_cull *c,
                                   float *g_weight, float *g_colour, hipStream_t s);
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 // Groups the entries with a kept query group by Gaussian (a_cnt, a_off, the
-// sorted entries in vals0/vals1) and builds the backward work items; a_cnt
-// is zero on entry.
+// sorted entries with their Gaussians in vals0/vals1 and keys0/keys1) and, for
+// at most kOneScanItems Gaussians, builds the backward work items; a_cnt is
+// zero on entry.
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s);
+// The work items from the Gaussians' item counts (gitem_cnt).
+hipError_t launch_backward_items(ngd_cull *c, hipStream_t s);
 // Mean squared error over q x 3 and its gradient; rel_eps > 0: each error
 // weighted by 1 / (|f| + rel_eps)^2, the weight held constant.
 hipError_t launch_l2_loss(const float *f, const float *target, int64_t q, float *loss,
