@@ -1,19 +1,21 @@
 // Tile cull (Sec. 3.2, Eq. 3-5) on the device.
 //
-// Steps, all on the caller's stream:
+// Steps, the Gaussians' (1, their part of 3 and 4, the limits and records) on a
+// second stream that the caller's waits for:
 //   1. Gaussian projections m_r = m . r (float32 fma chain) and thresholds
 //      kappa^2 sigma_r^2 with sigma_r^2 = |L^T r|^2 in float64 (Eq. 3, 4).
 //   2. Query projections q_r (Eq. 3) and their range per projection.
-//   3. Locality keys: key_proj projections quantised to key_bits each over
-//      the queries' range, bits interleaved (a Morton code); the same key for
-//      the projected means.
-//   4. Stable LSD radix sorts (8-bit digits, wavefront ballot ranking) of the
-//      queries and of the Gaussians by key.
+//   3. The k-d order of the queries and of the Gaussians in projection space
+//      (kd.hip); in the Morton tiling, locality keys instead: key_proj
+//      projections quantised to key_bits each over the queries' range, bits
+//      interleaved, the same key for the projected means.
+//   4. (Morton) stable LSD radix sorts of both by key.
 //   5. Tiles of `tile` consecutive sorted queries; per tile and projection
 //      the extent [lo, hi] of its projected queries; sorted SoA query copy.
-//   6. The (tile, Gaussian) interval test: one wave per 64 sorted Gaussians
-//      walks a range of tiles, tile bounds wave-uniform, leaving each tile as
-//      soon as no lane survives; one 64-bit ballot mask per (chunk, tile).
+//   6. The (tile, Gaussian) interval test: the boxes of 64 sorted Gaussians
+//      against the tiles' first, then one wave per 64 Gaussians walks the
+//      tiles left of a range, tile bounds wave-uniform, leaving each as soon as
+//      no lane survives; one 64-bit ballot mask per (chunk, tile) left.
 //   7. Per-tile counts, an exclusive scan into CSR offsets, and the
 //      candidate lists (ascending sorted positions); then the transposed
 //      Gaussian -> tile lists for the backward pass.

@@ -71,7 +71,7 @@ def test_ties(torch_cuda, q, what):
     _check(mix, np.ascontiguousarray(x, dtype=np.float32), proj, 256)
 
 
-@pytest.mark.parametrize("q", [4096, 4097, 65536, 65537])
+@pytest.mark.parametrize("q", [4096, 4097, 16384, 16385, 65536, 65537])
 def test_tile_counts(torch_cuda, q):
     # as many tiles as queries: the lists' offsets by one workgroup, in one
     # round, in several, and by the general scans
@@ -100,3 +100,11 @@ def test_heavy_bins(torch_cuda, q, far):
     # the orders alone: the lists of means whose projections overflow are not
     # the re-implementation's
     _check(mix, x, proj, 256, fields=("perm", "gperm"))
+
+
+@pytest.mark.parametrize("q", [1 << 20, (1 << 20) + 1])
+def test_scan_blocks(torch_cuda, q):
+    # tiles of one query: as many counts as 256 blocks of a scan hold, the last
+    # size whose blocks add up the sums before them, and one more
+    mix, x, proj = case(1, 5, q, seed=1)
+    _check(mix, x, proj, 1)
