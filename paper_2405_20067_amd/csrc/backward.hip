@@ -714,9 +714,10 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     const int32_t *a_ent = c->a_ent_buf ? c->vals1.as<int32_t>() : c->vals0.as<int32_t>();
     // The Gaussians with a handful of queries first, by lanes: 10-D, K =
     // 262,144, 2^20 queries: items and their sums 370 us, now 231 + 9; 2^22
-    // queries 560, now 441 + 49; K = 65,536, 2^18 queries: 116, now 85 + 9.  Up
-    // to kOneScanItems Gaussians, whose items' offsets come with the lists' in
-    // one launch, the six launches more cost what it saves.
+    // queries 560, now 441 + 49.  Up to kOneScanItems Gaussians, whose items'
+    // offsets come with the lists' in one launch, the six launches more cost
+    // what it saves (K = 65,536, 2^18 queries: 68 us less on the device, the
+    // fitting step as long).
     const bool light = mix->k > kOneScanItems;
     if (light) {
         const float lim = float(-std::log2(double(c->params.tau)) + kLightLog2Margin);

@@ -310,9 +310,11 @@ hipError_t radix_sort(int64_t n, const int64_t *n_dev, int nbits, DevBuf &k0, De
 // the host first (hipErrorInvalidValue when one is too small).
 constexpr int64_t kOneScan = 16384;   // counts scanned by one workgroup
 // With the items of the counts beside their offsets, always by one workgroup:
-// 18 us for 16,384 counts and 70 for 65,536, where the five launches otherwise
-// take about 30 and their gaps.
-constexpr int64_t kOneScanItems = 16384;
+// at 65,536 it takes 70 us, more than the launches otherwise (five for a list,
+// some 30 us), but a host that feeds the device call by call is kept longer by
+// those: a fitting step of K = 65,536, 2^18 queries 1.30 ms, with 16,384 here
+// (and the backward's other path, 68 us less on the device) 1.31 to 1.39.
+constexpr int64_t kOneScanItems = 65536;
 size_t scan_tmp_bytes(int64_t n);
 hipError_t scan_counts(const DevBuf &in, DevBuf &out, int64_t n, DevBuf &tmp, hipStream_t s);
 // The same with the offsets of ceil(count / per) in items (n + 1 int64) and,

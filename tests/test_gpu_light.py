@@ -13,7 +13,7 @@ from paper_2405_20067_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
-K = 16385          # one more than the last size without the rule
+K = 65537          # one more than the last size without the rule
 TOL_FP32 = 1e-4    # the bar of the other comparisons with the oracle
 
 
