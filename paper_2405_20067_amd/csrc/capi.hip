@@ -600,9 +600,9 @@ int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *qu
     if (e != hipSuccess) return hip_fail(e, "ngd_eval_stats");
     if (dev < 0 || dev >= 64) return fail(NGD_E_INVAL, "ngd_eval_stats: device %d", dev);
     std::lock_guard<std::mutex> lk(mu);
-    if (!buf[dev].ensure(5 * sizeof(unsigned long long)))
+    unsigned long long host[kStatSlots * 8] = {};
+    if (!buf[dev].ensure(sizeof(host)))
         return fail(NGD_E_NOMEM, "ngd_eval_stats: workspace allocation failed");
-    unsigned long long host[5] = {0, 0, 0, 0, 0};
     e = hipMemcpyAsync(buf[dev].p, host, sizeof(host), hipMemcpyHostToDevice, S(stream));
     if (e == hipSuccess)
         e = launch_eval_culled(mix, cull, nullptr, buf[dev].as<unsigned long long>(), S(stream));
@@ -611,7 +611,8 @@ int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *qu
     if (e == hipSuccess) e = hipStreamSynchronize(S(stream));
     if (e != hipSuccess) return hip_fail(e, "ngd_eval_stats");
     cull->act_version = mix->version;
-    for (int i = 0; i < 5; ++i) counts[i] = int64_t(host[i]);
+    for (int i = 0; i < kStatSlots * 8; ++i)
+        if (i % 8 < 5) counts[i % 8] += int64_t(host[i]);
     return NGD_OK;
 }
 

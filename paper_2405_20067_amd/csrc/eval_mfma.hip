@@ -516,7 +516,7 @@ __device__ __forceinline__ void pair_part(PairState<N> &st, const float (&x)[N],
 }
 
 // OUT: the colours are accumulated; otherwise only the (entry, group) flags.
-// COUNT (with OUT = false): stats[0..4] += (pairs examined, not skipped by the
+// COUNT (with OUT = false): the first five of a slot of stats += (pairs examined, not skipped by the
 // filter, below the threshold after 3 rows, after 6 rows, kept).
 template <int N, bool OUT, bool COUNT>
 __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
@@ -548,7 +548,8 @@ __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
     const int grp = uniform(s / kWave);
     if (vmask == 0) {   // a group past the end: its pairs count as examined
         if constexpr (COUNT) {
-            if (lane == 0 && grp < ngroups) atomicAdd(&stats[0], (unsigned long long)(ne));
+            if (lane == 0 && grp < ngroups)
+                atomicAdd(&stats[it % kStatSlots * 8], (unsigned long long)(ne));
         }
         return;
     }
@@ -666,11 +667,12 @@ __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
     }
     if constexpr (COUNT) {
         if (lane == 0) {
-            atomicAdd(&stats[0], static_cast<unsigned long long>(ne));
-            atomicAdd(&stats[1], static_cast<unsigned long long>(cnt));
-            atomicAdd(&stats[2], static_cast<unsigned long long>(n1));
-            atomicAdd(&stats[3], static_cast<unsigned long long>(n2));
-            atomicAdd(&stats[4], static_cast<unsigned long long>(nk));
+            unsigned long long *sl = stats + it % kStatSlots * 8;
+            atomicAdd(&sl[0], static_cast<unsigned long long>(ne));
+            atomicAdd(&sl[1], static_cast<unsigned long long>(cnt));
+            atomicAdd(&sl[2], static_cast<unsigned long long>(n1));
+            atomicAdd(&sl[3], static_cast<unsigned long long>(n2));
+            atomicAdd(&sl[4], static_cast<unsigned long long>(nk));
         }
     }
     if constexpr (!OUT) return;
