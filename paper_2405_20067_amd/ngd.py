@@ -310,8 +310,8 @@ def eval_mixture(mix: Mixture, cull: Cull | None, queries, out=None, precision=F
 
 
 def eval_prepare(mix: Mixture, cull: Cull, queries, precision=FP32, stream=None):
-    """Builds what a forward of `precision` derives once per cull build
-    (ngd_eval does it itself when it is missing)."""
+    """Checks the arguments of a forward of `precision`; the cull build has
+    already formed all that it derives once per build."""
     q = queries.numel() // mix.n
     _check(lib().ngd_eval_prepare(mix.handle, cull.handle, _ptr(queries, "queries", q * mix.n),
                                   q, int(precision), _stream(stream)))
@@ -320,8 +320,7 @@ def eval_prepare(mix: Mixture, cull: Cull, queries, precision=FP32, stream=None)
 def eval_stats(mix: Mixture, cull: Cull, queries, precision=FP32, stream=None):
     """Work counters of the culled forward of `precision`: dict(examined,
     filtered, pass1, pass2, kept), counted in (64-query group, candidate)
-    pairs; `filtered` are those the first filter did not skip (the
-    matrix-core one with BF16_MFMA, the per-coordinate box test with FP32)."""
+    pairs; `filtered` are those the matrix-core filter did not skip."""
     q = queries.numel() // mix.n
     counts = (ctypes.c_int64 * 5)()
     _check(lib().ngd_eval_stats(mix.handle, cull.handle, _ptr(queries, "queries", q * mix.n),
