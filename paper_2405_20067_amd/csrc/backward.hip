@@ -321,7 +321,8 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_items(
 //
 // A query counts unless its Gaussian value is below tau 2^-kLightLog2Margin,
 // half a float32 rounding step of the least weight the cull keeps.  One that
-// is infinite or not a number counts wherever its group is kept, as in an item.
+// is infinite or not a number, or whose upstream gradient is, counts wherever
+// its group is kept, as in an item.
 constexpr double kLightLog2Margin = 24.0;
 constexpr int kLightGaussians = 8;    // of a wave (4: 177 us and 385 at 2^22 queries, 16: 177 and 403)
 constexpr int kLightRows = 32;        // queries of a pair that can count
@@ -431,6 +432,8 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
             const float *col = qs + t0;
 #pragma unroll
             for (int a = 0; a < N; ++a, col += q) x[a] = col[at];
+            const float *gt = gs + t0;
+            const float gv[3] = {gt[at], (gt + q)[at], (gt + 2 * q)[at]};
             float msq = 0.0f;
 #pragma unroll
             for (int a = 0; a < N; ++a) {
@@ -441,7 +444,9 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
                 y[a] = t;
                 msq = fmaf(t, t, msq);
             }
-            const bool counts = valid && !(msq > lim && msq < INFINITY);
+            const bool finite = msq < INFINITY &&
+                                fabsf(gv[0]) + fabsf(gv[1]) + fabsf(gv[2]) < INFINITY;
+            const bool counts = valid && !(msq > lim && finite);
             const uint64_t hit = ballot(counts);
             const int nh = __popcll(hit);
             int c = __builtin_amdgcn_readlane(cnt, gg) + nh;
@@ -455,8 +460,6 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
             if (gg != cur) flush(gg);
             if (counts) {
                 float *o = row + __popcll(hit & lanemask_lt()) * RS;
-                const float *gt = gs + t0;
-                const float gv[3] = {gt[at], (gt + q)[at], (gt + 2 * q)[at]};
                 const float G = __builtin_amdgcn_exp2f(-msq);
                 const float wgt = r[AL] * G *
                                   fmaf(gv[2], r[CO + 2], fmaf(gv[1], r[CO + 1], gv[0] * r[CO]));
