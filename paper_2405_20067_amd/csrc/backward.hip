@@ -235,10 +235,10 @@ __device__ __forceinline__ void backward_item(
             const int64_t tt = __builtin_amdgcn_readlane(tl, l);
             const int sidx = gq * kWave + lane;
             const bool valid = (sidx < tile) && (tt * tile + sidx < q);
-            // every lane loads (a lane past the tile's end from the tile's
-            // first query) and the invalid ones are zeroed: no branches;
-            // scalar bases and one offset, no 64-bit sums a lane
-            const uint32_t at = valid ? uint32_t(sidx) : 0u;
+            // every lane loads (a lane past the end from the group's first
+            // query, which a kept group has) and the invalid ones are zeroed:
+            // no branches; scalar bases and one offset, no 64-bit sums a lane
+            const uint32_t at = valid ? uint32_t(sidx) : uint32_t(gq * kWave);
             float x[N], d[N], y[N];
 #pragma unroll
             for (int a = 0; a < N; ++a) x[a] = (qs + a * q + tt * tile)[at];
@@ -425,8 +425,9 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
             const int64_t t0 = int64_t(__builtin_amdgcn_readlane(tl, l)) * tile;
             const int sidx = gq * kWave + lane;
             const bool valid = (sidx < tile) && (t0 + sidx < q);
-            // scalar bases and one offset, no 64-bit sums a lane
-            const uint32_t at = valid ? uint32_t(sidx) : 0u;
+            // scalar bases and one offset, no 64-bit sums a lane (past the
+            // end the group's first query)
+            const uint32_t at = valid ? uint32_t(sidx) : uint32_t(gq * kWave);
             const ConstRec r = rec0 + gg * R;
             float x[N], d[N], y[N];
             const float *col = qs + t0;

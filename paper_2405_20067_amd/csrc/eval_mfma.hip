@@ -546,10 +546,12 @@ __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
     const uint64_t vmask = ballot(valid);
     const int ngroups = (tile + kWave - 1) / kWave;
     const int grp = uniform(s / kWave);
-    if (vmask == 0) {   // a group past the end: its pairs count as examined
-        if constexpr (COUNT) {
-            if (lane == 0 && grp < ngroups)
-                atomicAdd(&stats[it % kStatSlots * 8], (unsigned long long)(ne));
+    if (vmask == 0) {   // a group past the end keeps nothing; its pairs count as examined
+        if (grp < ngroups) {
+            for (int o = lane; o < ne; o += kWave) act[(e0 + o) * ngroups + grp] = 0;
+            if constexpr (COUNT) {
+                if (lane == 0) atomicAdd(&stats[it % kStatSlots * 8], (unsigned long long)(ne));
+            }
         }
         return;
     }
