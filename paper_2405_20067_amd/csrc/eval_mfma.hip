@@ -266,6 +266,7 @@ __global__ __launch_bounds__(kMThreads, 3) void k_filter_items(
     f16x8 fa[2][KS];
     float hq, hm;
     float sig;
+    bool far;
     {
         float xr[2][N];
         float m1 = 0.0f, m2 = 0.0f;
@@ -295,9 +296,11 @@ __global__ __launch_bounds__(kMThreads, 3) void k_filter_items(
         // of that distance, so that b stays in range
 #pragma unroll
         for (int a = 0; a < N; ++a) ht = fmaxf(ht, fabsf(cen[a]) * (1.0f / 1024.0f));
-        // ht sigma in (8, 16]
+        // ht sigma in (8, 16]; beyond 2^60 the features would not be finite
+        // and nothing is skipped
         const int e = int(__float_as_uint(ht) >> 23) - 127;
-        sig = (e > -60 && e < 60) ? __uint_as_float(uint32_t(3 - e + 127) << 23) : 1.0f;
+        far = e >= 60;
+        sig = (e > -60 && !far) ? __uint_as_float(uint32_t(3 - e + 127) << 23) : 1.0f;
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
@@ -401,7 +404,7 @@ __global__ __launch_bounds__(kMThreads, 3) void k_filter_items(
             // covers float16's least steps (values below 2^-14)
             const float K = sig2 * sc, rk = kGamma * Rs * sig2;
             float t0 = fmaf(rk, mm, fmaf(skip, K, 1.0f));
-            if (!(bmax < 65000.0f) || !(K > 0x1p-60f && K < 0x1p60f)) t0 = INFINITY;
+            if (far || !(bmax < 65000.0f) || !(K > 0x1p-60f && K < 0x1p60f)) t0 = INFINITY;
             mine[Fi::META] = __builtin_bit_cast(
                 f16x8, f32x4{t0, 2.0f * rk * sqrtf(mm), 2.0f * rk,
                              (Fi::LO ? 1.0f : 2.0f) * kGamma * b1 * sig2});
