@@ -259,9 +259,7 @@ int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *qu
  *   dl/dalpha_i = sum_x G_i s,  dl/dc_i = alpha_i sum_x G_i g,
  *   dl/dm_i = sum_x w z,        dl/dL_i = tril(sum_x w z y^T),
  * with g = grad_out(x), s = g . c_i, w = alpha_i G_i s, y = L_i^-1 (x - m_i),
- * z = L_i^-T y.  With a cull the sums run over the same pairs as ngd_eval's;
- * in mixtures of more than 65,536 Gaussians, one with few queries leaves out
- * those of a kept pair whose Gaussian value is below tau 2^-24.
+ * z = L_i^-T y.  With a cull the sums run over the same pairs as ngd_eval's.
  * Outputs (device, overwritten, caller's Gaussian order): g_mean k x n,
  * g_factor k x n(n+1)/2 (packed like the factor), g_weight k, g_colour k x 3.
  * Each Gaussian's sums are formed by one wave in a fixed order: no atomics,

@@ -11,11 +11,11 @@
 // Atomics-free and Gaussian-major.  Culled: the forward pass records, for
 // every candidate entry (tile, Gaussian) and every 64-query group of the
 // tile, whether it kept the pair group (one byte); the backward visits only
-// the kept groups, recomputing y, G and the exp rather than storing them.  In
-// mixtures of more than kOneScanItems Gaussians, one with a handful of queries
-// above the skip threshold takes those alone (k_light_moments,
-// k_light_gradients); the others, and all of a smaller mixture, sum over
-// exactly the pairs the forward summed, by work items.  A work item is one
+// the kept groups, so it sums over exactly the pairs the forward summed,
+// recomputing y, G and the exp rather than storing them.  In mixtures of more
+// than kOneScanItems Gaussians, one to which a handful of queries add anything
+// takes those alone (k_light_moments, k_light_gradients); the others, and all of
+// a smaller mixture, go to work items.  A work item is one
 // Gaussian and at most kItemTiles of its candidate entries (the transposed
 // lists); one wave evaluates the item's kept groups 64 queries at a time,
 // keeps per-lane partial moments in registers (B1: n, B2: n(n+1)/2, H: 3),
@@ -313,17 +313,18 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_items(
 
 // ---- culled: Gaussians with a handful of queries --------------------------
 // Where a Gaussian is small against the queries' spacing (10-D, 2^20 queries:
-// 1.4 kept groups a Gaussian with 1.5 queries each above the skip threshold),
+// 1.4 kept groups a Gaussian, 1.5 queries of each above the skip threshold),
 // an item's wave adds moments that are zero in nearly all lanes, and its sum
 // over the lanes takes longer than its pairs.  Here a lane is a query for the
 // distances only; the few that count leave their factors in LDS, and the lanes
 // then take a moment each.
 //
-// A query counts unless its Gaussian value is below tau 2^-kLightLog2Margin,
-// half a float32 rounding step of the least weight the cull keeps.  One that
-// is infinite or not a number, or whose upstream gradient is, counts wherever
-// its group is kept, as in an item.
-constexpr double kLightLog2Margin = 24.0;
+// A query counts unless every term it would add is zero, its value having
+// underflowed (below 2^-126: some 3.7 times the threshold's distance) or nothing
+// coming from upstream, so that the sums are those of the items over every query
+// of the kept groups.  (Counting those above tau 2^-24 only, the step of 2^20
+// queries took 16 us less of 2,271, that of 2^22 as long, but an upstream
+// gradient large enough makes any of the others matter.)
 constexpr int kLightGaussians = 8;    // of a wave (4: 177 us and 385 at 2^22 queries, 16: 177 and 403)
 constexpr int kLightRows = 32;        // queries of a pair that can count
 constexpr int kLightQueries = 64;     // queries of a Gaussian
@@ -337,7 +338,7 @@ constexpr int kLightEntries = 32;     // kept entries of a Gaussian
 // changed nothing, and neither did a sixth fewer vector operations.
 template <int N>
 __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
-    int64_t k, int64_t q, int tile, float lim, const float *__restrict__ grec,
+    int64_t k, int64_t q, int tile, const float *__restrict__ grec,
     const float *__restrict__ qs, const float *__restrict__ gs,
     const int64_t *__restrict__ a_off, const uint32_t *__restrict__ a_key,
     const int32_t *__restrict__ a_ent, const int32_t *__restrict__ ent_tile,
@@ -445,9 +446,17 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
                 y[a] = t;
                 msq = fmaf(t, t, msq);
             }
-            const bool finite = msq < INFINITY &&
-                                fabsf(gv[0]) + fabsf(gv[1]) + fabsf(gv[2]) < INFINITY;
-            const bool counts = valid && !(msq > lim && finite);
+            const float G = __builtin_amdgcn_exp2f(-msq);
+            const float wgt = r[AL] * G *
+                              fmaf(gv[2], r[CO + 2], fmaf(gv[1], r[CO + 1], gv[0] * r[CO]));
+            float h[3];
+            bool none = wgt == 0.0f && msq < INFINITY;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                h[ch] = G * gv[ch];
+                none &= h[ch] == 0.0f;
+            }
+            const bool counts = valid && !none;
             const uint64_t hit = ballot(counts);
             const int nh = __popcll(hit);
             int c = __builtin_amdgcn_readlane(cnt, gg) + nh;
@@ -461,9 +470,6 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
             if (gg != cur) flush(gg);
             if (counts) {
                 float *o = row + __popcll(hit & lanemask_lt()) * RS;
-                const float G = __builtin_amdgcn_exp2f(-msq);
-                const float wgt = r[AL] * G *
-                                  fmaf(gv[2], r[CO + 2], fmaf(gv[1], r[CO + 1], gv[0] * r[CO]));
 #pragma unroll
                 for (int a = 0; a < N; ++a) {
                     o[a] = y[a];
@@ -471,7 +477,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
                 }
                 o[ONE] = 1.0f;
 #pragma unroll
-                for (int ch = 0; ch < 3; ++ch) o[ONE + 1 + ch] = G * gv[ch];
+                for (int ch = 0; ch < 3; ++ch) o[ONE + 1 + ch] = h[ch];
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -724,10 +730,9 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     // fitting step as long).
     const bool light = mix->k > kOneScanItems;
     if (light) {
-        const float lim = float(-std::log2(double(c->params.tau)) + kLightLog2Margin);
         const int64_t per = int64_t(kWavesPerBlock) * kLightGaussians;
         k_light_moments<N><<<unsigned((mix->k + per - 1) / per), kBwdThreads, 0, s>>>(
-            mix->k, c->q, c->params.tile, lim, c->grec.as<float>(), c->qs.as<float>(),
+            mix->k, c->q, c->params.tile, c->grec.as<float>(), c->qs.as<float>(),
             c->gs.as<float>(), c->a_off.as<int64_t>(),
             c->a_ent_buf ? c->keys1.as<uint32_t>() : c->keys0.as<uint32_t>(), a_ent,
             c->ent_tile.as<int32_t>(), c->act.as<uint8_t>(), c->gpart.as<float>(),
