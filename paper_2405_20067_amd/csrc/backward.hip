@@ -50,7 +50,7 @@ static_assert(kItemTiles <= kWave, "an item's tile list must fit one wave");
 // independent.
 template <int N, int W>
 __global__ __launch_bounds__(W *kWave) void k_backward_dense(
-    int64_t q, const float *__restrict__ rec, const float *__restrict__ xq,
+    int64_t first, int64_t q, const float *__restrict__ rec, const float *__restrict__ xq,
     const float *__restrict__ gq, float *__restrict__ g_mean, float *__restrict__ g_factor,
     float *__restrict__ g_weight, float *__restrict__ g_colour)
 {
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(W *kWave) void k_backward_dense(
     constexpr int AL = N + T + 3, CO = N + T + 4;
     __shared__ float part[W][VP];
     const int lane = lane_id(), w = int(threadIdx.x) / kWave;
-    const int64_t g = blockIdx.x;
+    const int64_t g = first + blockIdx.x;
     const float *__restrict__ r = rec + g * R;
     const float alpha = r[AL], c0 = r[CO], c1 = r[CO + 1], c2 = r[CO + 2];
 
@@ -338,7 +338,7 @@ constexpr int kLightEntries = 32;     // kept entries of a Gaussian
 // changed nothing, and neither did a sixth fewer vector operations.
 template <int N>
 __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
-    int64_t k, int64_t q, int tile, const float *__restrict__ grec,
+    int64_t first, int64_t k, int64_t q, int tile, const float *__restrict__ grec,
     const float *__restrict__ qs, const float *__restrict__ gs,
     const int64_t *__restrict__ a_off, const uint32_t *__restrict__ a_key,
     const int32_t *__restrict__ a_ent, const int32_t *__restrict__ ent_tile,
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
     const int lane = lane_id(), w = uniform(int(threadIdx.x) / kWave);
     // neighbouring Gaussians, which share tiles, share an L2
     const int64_t g0 =
-        (xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + w) * kLightGaussians;
+        ((first + xcd_block(blockIdx.x, gridDim.x)) * kWavesPerBlock + w) * kLightGaussians;
     if (g0 >= k) return;
     const int ng = int(k - g0 < kLightGaussians ? k - g0 : kLightGaussians);
     const int64_t off = a_off[g0 + (lane < ng ? lane : ng)];
@@ -698,8 +698,10 @@ hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q,
     // 128 registers a lane of a 16-wave workgroup has) while that is what it
     // takes to fill the chip; with 4,096 Gaussians and more, 4
     auto go = [&](auto kern, int waves) {
-        kern<<<unsigned(mix->k), waves * kWave, 0, s>>>(q, mix->rec.as<float>(), queries,
-                                                        grad_out, gm, gf, gw, gc);
+        const int64_t most = max_grid(waves * kWave);
+        for (int64_t b = 0; b < mix->k; b += most)
+            kern<<<unsigned(std::min(mix->k - b, most)), waves * kWave, 0, s>>>(
+                b, q, mix->rec.as<float>(), queries, grad_out, gm, gf, gw, gc);
         return hipGetLastError();
     };
     if (q == 0) {   // no queries: zero gradients whatever the parameters
@@ -731,12 +733,14 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     const bool light = mix->k > kOneScanItems;
     if (light) {
         const int64_t per = int64_t(kWavesPerBlock) * kLightGaussians;
-        k_light_moments<N><<<unsigned((mix->k + per - 1) / per), kBwdThreads, 0, s>>>(
-            mix->k, c->q, c->params.tile, c->grec.as<float>(), c->qs.as<float>(),
-            c->gs.as<float>(), c->a_off.as<int64_t>(),
-            c->a_ent_buf ? c->keys1.as<uint32_t>() : c->keys0.as<uint32_t>(), a_ent,
-            c->ent_tile.as<int32_t>(), c->act.as<uint8_t>(), c->gpart.as<float>(),
-            c->gflag.as<int32_t>(), c->gitem_cnt.as<int32_t>());
+        const int64_t blocks = (mix->k + per - 1) / per, most = max_grid(kBwdThreads);
+        for (int64_t b = 0; b < blocks; b += most)
+            k_light_moments<N><<<unsigned(std::min(blocks - b, most)), kBwdThreads, 0, s>>>(
+                b, mix->k, c->q, c->params.tile, c->grec.as<float>(), c->qs.as<float>(),
+                c->gs.as<float>(), c->a_off.as<int64_t>(),
+                c->a_ent_buf ? c->keys1.as<uint32_t>() : c->keys0.as<uint32_t>(), a_ent,
+                c->ent_tile.as<int32_t>(), c->act.as<uint8_t>(), c->gpart.as<float>(),
+                c->gflag.as<int32_t>(), c->gitem_cnt.as<int32_t>());
         k_light_gradients<N><<<unsigned((mix->k + kWave - 1) / kWave), kWave, 0, s>>>(
             mix->k, c->grec.as<float>(), c->gpart.as<float>(), c->gflag.as<int32_t>(),
             c->gperm.as<int32_t>(), gm, gf, gw, gc);

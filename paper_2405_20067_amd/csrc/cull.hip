@@ -436,14 +436,16 @@ __device__ int32_t last_true(const Pred &pred, float guess, int32_t lo, int32_t 
 constexpr int kLimitWaves = 16;
 template <int PP>
 __global__ __launch_bounds__(kLimitWaves *kWave) void k_gauss_limits(
-    int64_t k, int P, const int32_t *__restrict__ gperm, const float *__restrict__ g_mr,
-    const float *__restrict__ g_mr_s, const float *__restrict__ g_thr, float *__restrict__ g_ub,
-    float *__restrict__ g_lb, float *__restrict__ cbnd)
+    int64_t chunk0, int64_t k, int P, const int32_t *__restrict__ gperm,
+    const float *__restrict__ g_mr, const float *__restrict__ g_mr_s,
+    const float *__restrict__ g_thr, float *__restrict__ g_ub, float *__restrict__ g_lb,
+    float *__restrict__ cbnd)
 {
     constexpr int T4 = PP / 4;
     __shared__ float s_thr[kWave][PP + 1];
     const int w = uniform(int(threadIdx.x) / kWave), lane = lane_id();
-    const int64_t s0 = int64_t(blockIdx.x) * kWave, s = s0 + lane;
+    const int64_t chunk = chunk0 + blockIdx.x;
+    const int64_t s0 = chunk * kWave, s = s0 + lane;
     const bool valid = s < k;
     const int st = thr_stride(P);
     for (int e = threadIdx.x; e < kWave * T4; e += kLimitWaves * kWave) {
@@ -459,7 +461,7 @@ __global__ __launch_bounds__(kLimitWaves *kWave) void k_gauss_limits(
     }
     const int64_t i = valid && !g_mr_s ? gperm[s] : 0;
     __syncthreads();
-    float *box = cbnd + int64_t(blockIdx.x) * 2 * PP;
+    float *box = cbnd + chunk * 2 * PP;
     for (int j = w; j < PP; j += kLimitWaves) {
         if (j >= P) {   // a padding projection spans everything
             if (lane == 0) {
@@ -925,10 +927,12 @@ hipError_t tile_offsets(ngd_cull *c, const int64_t *most, hipStream_t s)
 hipError_t gauss_limits(ngd_cull *c, int64_t k, int P, bool g_sorted, hipStream_t s)
 {
     auto go = [&](auto kern) {
-        kern<<<nblk(k, kWave), kLimitWaves * kWave, 0, s>>>(
-            k, P, c->gperm.as<int32_t>(), c->g_mr.as<float>(),
-            g_sorted ? c->g_mr_s.as<float>() : nullptr, c->g_thr.as<float>(),
-            c->g_ub.as<float>(), c->g_lb.as<float>(), c->cbnd.as<float>());
+        const int64_t most = max_grid(kLimitWaves * kWave);
+        for (int64_t b = 0; b < c->nchunks; b += most)
+            kern<<<unsigned(std::min(c->nchunks - b, most)), kLimitWaves * kWave, 0, s>>>(
+                b, k, P, c->gperm.as<int32_t>(), c->g_mr.as<float>(),
+                g_sorted ? c->g_mr_s.as<float>() : nullptr, c->g_thr.as<float>(),
+                c->g_ub.as<float>(), c->g_lb.as<float>(), c->cbnd.as<float>());
     };
     switch (pad_proj(P)) {
     case 4: go(k_gauss_limits<4>); break;

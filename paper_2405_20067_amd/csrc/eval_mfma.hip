@@ -61,6 +61,7 @@
 // bound by the gathers of its records (160 B a candidate and tile at 10-D),
 // the evaluation of the image by its vector operations (80 of about 114 issue
 // slots a pair).
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -236,7 +237,7 @@ template <int N, int SLOT> __device__ __forceinline__ float feature(const float 
 // masks: per (item, group) kItemChunks words, bit = candidate not skipped.
 template <int N>
 __global__ __launch_bounds__(kMThreads, 3) void k_filter_items(
-    int64_t q, int tile, const f16x8 *__restrict__ mrec, const float *__restrict__ tcen,
+    int64_t item0, int64_t q, int tile, const f16x8 *__restrict__ mrec, const float *__restrict__ tcen,
     const float *__restrict__ qs, const int64_t *__restrict__ tile_off,
     const int32_t *__restrict__ cand, const int32_t *__restrict__ item_tile,
     const int64_t *__restrict__ item_off, float skip, uint64_t *__restrict__ masks)
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(kMThreads, 3) void k_filter_items(
     __shared__ f16x8 s_col[kMThreads * ST];
     __shared__ float s_hm[kWaves];
 
-    const int64_t it = xcd_block(blockIdx.x, gridDim.x);   // neighbouring tiles share an L2
+    const int64_t it = item0 + xcd_block(blockIdx.x, gridDim.x);   // neighbouring tiles share an L2
     const int64_t t = uniform(item_tile[it]);
     const int64_t c1 = uniform64(tile_off[t + 1]);
     const int64_t e0 = uniform64(tile_off[t]) + (it - uniform64(item_off[t])) * kItemCands;
@@ -523,7 +524,7 @@ __device__ __forceinline__ void pair_part(PairState<N> &st, const float (&x)[N],
 // filter, below the threshold after 3 rows, after 6 rows, kept).
 template <int N, bool OUT, bool COUNT>
 __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
-    int64_t q, int tile, const uint64_t *__restrict__ masks, const float *__restrict__ qs,
+    int64_t item0, int64_t q, int tile, const uint64_t *__restrict__ masks, const float *__restrict__ qs,
     const float *__restrict__ grec, const int64_t *__restrict__ tile_off,
     const int32_t *__restrict__ cand, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ item_tile, const int64_t *__restrict__ item_off, float skip,
@@ -535,7 +536,7 @@ __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
     __shared__ int32_t s_idx[kWaves][kItemCands];    // the survivors' Gaussians
     __shared__ uint16_t s_pos[kWaves][kItemCands];   // their places in the item
     __shared__ uint32_t s_kept[kWaves][kItemCands / 32];
-    const int64_t it = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t it = item0 + xcd_block(blockIdx.x, gridDim.x);
     const int64_t t = uniform(item_tile[it]);
     const int64_t i0 = uniform64(item_off[t]);
     const int64_t nit = uniform64(item_off[t + 1]) - i0;
@@ -709,17 +710,17 @@ hipError_t culled_n(const ngd_cull *c, float *out, unsigned long long *stats, hi
     const int tile = c->params.tile;
     const unsigned gy = unsigned((tile + kMThreads - 1) / kMThreads);
     const float skip = float(-std::log2(double(c->params.tau)) + kSkipLog2Margin);
-    if (c->nitems > 0) {
-        const dim3 grid(unsigned(c->nitems), gy);
+    // no idle waves for tiles of fewer than 256 queries
+    const int threads = tile < kMThreads ? (tile + kWave - 1) / kWave * kWave : kMThreads;
+    for (int64_t i0 = 0; i0 < c->nitems; i0 += max_grid(kMThreads)) {
+        const dim3 grid(unsigned(std::min(c->nitems - i0, max_grid(kMThreads))), gy);
         k_filter_items<N><<<grid, kMThreads, 0, s>>>(
-            c->q, tile, c->mrec.as<f16x8>(), c->tcen.as<float>(), c->qs.as<float>(),
+            i0, c->q, tile, c->mrec.as<f16x8>(), c->tcen.as<float>(), c->qs.as<float>(),
             c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->item_tile.as<int32_t>(),
             c->item_off.as<int64_t>(), skip, c->fmask.as<uint64_t>());
-        // no idle waves for tiles of fewer than 256 queries
-        const int threads = tile < kMThreads ? (tile + kWave - 1) / kWave * kWave : kMThreads;
         auto go = [&](auto kern) {
             kern<<<grid, threads, 0, s>>>(
-                c->q, tile, c->fmask.as<uint64_t>(), c->qs.as<float>(), c->grec.as<float>(),
+                i0, c->q, tile, c->fmask.as<uint64_t>(), c->qs.as<float>(), c->grec.as<float>(),
                 c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->perm.as<int32_t>(),
                 c->item_tile.as<int32_t>(), c->item_off.as<int64_t>(), skip,
                 c->act.as<uint8_t>(), out, c->fpart.as<float>(), stats);

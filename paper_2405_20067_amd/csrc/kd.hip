@@ -548,7 +548,7 @@ __global__ __launch_bounds__(kThreads) void k_kd_scatter(
 constexpr int kListMax = 256;
 template <int S>
 __global__ __launch_bounds__(kNodeThreads) void k_kd_select(
-    const int64_t *__restrict__ nodes, int64_t slice0, int64_t n, int P,
+    int64_t node_first, const int64_t *__restrict__ nodes, int64_t slice0, int64_t n, int P,
     const float *__restrict__ vin, const uint32_t *__restrict__ ext, int64_t max_nodes,
     uint32_t *__restrict__ ext_next, int32_t *__restrict__ dim, uint32_t *__restrict__ pre_out,
     int64_t *__restrict__ rank_out, int64_t *__restrict__ cnt)
@@ -561,7 +561,7 @@ __global__ __launch_bounds__(kNodeThreads) void k_kd_select(
     __shared__ uint64_t s_list[kListMax];
     __shared__ int s_num, s_need;
     __shared__ uint32_t s_pivot;
-    const int64_t nd = blockIdx.x;
+    const int64_t nd = node_first + blockIdx.x;
     const int64_t *row = nodes + nd * kNodeCols;
     const int64_t start = row[0];
     const int size = int(row[1]), nleft = int(row[2]);
@@ -1688,9 +1688,11 @@ hipError_t kd_step(KdRun &r)
         const bool one = lv.biggest <= kNodeMax;   // the selection in one launch
         if (one) {
             auto go = [&](auto kern) {
-                kern<<<unsigned(lv.node1 - lv.node0), kNodeThreads, 0, s>>>(
-                    nt, lv.slice0, n, P, r.vin, ext, mn, ext_next, dim, prefix + 2 * mn,
-                    rank + 2 * mn, cnt);
+                const int64_t nn = lv.node1 - lv.node0, most = max_grid(kNodeThreads);
+                for (int64_t b = 0; b < nn; b += most)
+                    kern<<<unsigned(std::min(nn - b, most)), kNodeThreads, 0, s>>>(
+                        b, nt, lv.slice0, n, P, r.vin, ext, mn, ext_next, dim, prefix + 2 * mn,
+                        rank + 2 * mn, cnt);
             };
             if (lv.biggest <= 4 * kNodeThreads) go(k_kd_select<4>);
             else go(k_kd_select<16>);

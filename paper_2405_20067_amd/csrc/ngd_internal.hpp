@@ -29,6 +29,11 @@ constexpr int kItemTiles = 32;
 
 inline int tri(int n) { return n * (n + 1) / 2; }
 
+// Workgroups that one launch can have: its threads along x are counted in 32
+// bits, and a grid of 2^32 threads or more wraps around without an error.
+// Kernels with more threads than elements are launched again for the rest.
+inline int64_t max_grid(int threads) { return ((int64_t(1) << 32) - 1) / threads; }
+
 // Per-Gaussian record read by the evaluation kernels, one row of `stride`
 // floats: m (n) | S' = sqrt(kHalfLog2e) L^-1 packed lower by rows (tri) |
 // alpha*c (3) | alpha (1) | c (3) | padding to a multiple of 4.
