@@ -13,7 +13,7 @@
 // tile, whether it kept the pair group (one byte); the backward visits only
 // the kept groups, so it sums over exactly the pairs the forward summed,
 // recomputing y, G and the exp rather than storing them.  In mixtures of more
-// than kOneScanItems Gaussians, one to which a handful of queries add anything
+// than kLightMin Gaussians, one to which a handful of queries add anything
 // takes those alone (k_light_moments, k_light_gradients); the others, and all of
 // a smaller mixture, go to work items.  A work item is one
 // Gaussian and at most kItemTiles of its candidate entries (the transposed
@@ -726,11 +726,11 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     const int32_t *a_ent = c->a_ent_buf ? c->vals1.as<int32_t>() : c->vals0.as<int32_t>();
     // The Gaussians with a handful of queries first, by lanes: 10-D, K =
     // 262,144, 2^20 queries: items and their sums 370 us, now 231 + 9; 2^22
-    // queries 560, now 441 + 49.  Up to kOneScanItems Gaussians, whose items'
+    // queries 560, now 441 + 49.  Up to kLightMin Gaussians, whose items'
     // offsets come with the lists' in one launch, the six launches more cost
     // what it saves (K = 65,536, 2^18 queries: 68 us less on the device, the
     // fitting step as long).
-    const bool light = mix->k > kOneScanItems;
+    const bool light = mix->k > kLightMin;
     if (light) {
         const int64_t per = int64_t(kWavesPerBlock) * kLightGaussians;
         const int64_t blocks = (mix->k + per - 1) / per, most = max_grid(kBwdThreads);

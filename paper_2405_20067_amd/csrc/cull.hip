@@ -905,13 +905,13 @@ hipError_t launch_items(int64_t n, const int64_t *off, int per, DevBuf &cnt, Dev
     return scan_counts(cnt, ioff, n, scan_tmp, s);
 }
 
-// Offsets of the tiles' lists and items, and the sizes for the host: up to
-// kOneScanItems tiles in one launch, else in seven.
+// Offsets of the tiles' lists and items, and the sizes for the host: one or two
+// launches up to kTwoScan tiles, eight above.
 hipError_t tile_offsets(ngd_cull *c, const int64_t *most, hipStream_t s)
 {
-    if (c->ntiles <= kOneScanItems)
+    if (c->ntiles <= kTwoScan)
         return scan_items(c->tile_cnt, c->tile_off, kItemCands, c->item_off, c->ntiles,
-                          c->stats_host, s);
+                          c->scan_tmp, c->stats_host, s);
     hipError_t e = scan_counts(c->tile_cnt, c->tile_off, c->ntiles, c->scan_tmp, s);
     if (e == hipSuccess)
         e = launch_items(c->ntiles, c->tile_off.as<int64_t>(), kItemCands, c->item_cnt,
@@ -1156,7 +1156,7 @@ hipError_t front_body_n(ngd_cull *c, const ngd_mixture *mix, const float *querie
     // per-tile counts -> offsets
     k_seg_prefix<<<nblk(c->ntiles, kThreads), kThreads, 0, s>>>(
         c->ntiles, c->nseg, c->seg_cnt.as<int32_t>(), c->tile_cnt.as<int32_t>(),
-        c->ntiles <= kOneScanItems ? nullptr : c->stats.as<unsigned long long>());
+        c->ntiles <= kTwoScan ? nullptr : c->stats.as<unsigned long long>());
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return tile_offsets(c, c->stats.as<int64_t>(), s);
 }
@@ -1335,8 +1335,8 @@ hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
     } else {
         c->a_ent_buf = 0;
     }
-    if (k > kOneScanItems) return scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
-    e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, nullptr, s);
+    if (k > kLightMin) return scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
+    e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, c->scan_tmp, nullptr, s);
     return e == hipSuccess ? item_fill(c, s) : e;
 }
 

@@ -26,6 +26,9 @@ constexpr double kSkipLog2Margin = 20.0;
 // workgroups / waves; their partial sums are combined in a fixed order.
 constexpr int kItemCands = 512;
 constexpr int kItemTiles = 32;
+// Mixtures of more Gaussians than this have a pass for those with a handful of
+// queries ahead of the backward's items (backward.hip).
+constexpr int64_t kLightMin = 65536;
 
 inline int tri(int n) { return n * (n + 1) / 2; }
 
@@ -280,7 +283,7 @@ hipError_t launch_backward_culled(const ngd_mixture *mix, ngd_cull *c,
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 // Groups the entries with a kept query group by Gaussian (a_cnt, a_off, the
 // sorted entries with their Gaussians in vals0/vals1 and keys0/keys1) and, for
-// at most kOneScanItems Gaussians, builds the backward work items; a_cnt is
+// at most kLightMin Gaussians, builds the backward work items; a_cnt is
 // zero on entry.
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s);
 // The work items from the Gaussians' item counts (gitem_cnt).
@@ -317,29 +320,30 @@ hipError_t radix_sort(int64_t n, const int64_t *n_dev, int nbits, DevBuf &k0, De
 // the total).  `tmp` must hold scan_tmp_bytes(n) bytes.
 // The capacities of in (n int32), out (n + 1 int64) and tmp are checked on
 // the host first (hipErrorInvalidValue when one is too small).
-constexpr int64_t kOneScan = 16384;   // counts scanned by one workgroup
-// With the items of the counts beside their offsets, always by one workgroup:
-// at 65,536 it takes 70 us, more than the launches otherwise (five for a list,
-// some 30 us), but a host that feeds the device call by call is kept longer by
-// those: a fitting step of K = 65,536, 2^18 queries 1.30 ms, with 16,384 here
-// (and the backward's other path, 68 us less on the device) 1.31 to 1.39.
-constexpr int64_t kOneScanItems = 65536;
+constexpr int64_t kOneScan = 16384;         // counts scanned by one workgroup
+constexpr int64_t kTwoScan = 1 << 20;       // by two launches
 size_t scan_tmp_bytes(int64_t n);
 hipError_t scan_counts(const DevBuf &in, DevBuf &out, int64_t n, DevBuf &tmp, hipStream_t s);
-// The same with the offsets of ceil(count / per) in items (n + 1 int64) and,
-// when sizes is not null, (largest count, total, items) stored there; sizes is
-// memory the host reads after the stream has passed.
+// The same, for n <= kTwoScan, with the offsets of ceil(count / per) in items
+// (n + 1 int64) and, when sizes is not null, (largest count, total, items)
+// stored there; sizes is memory the host reads after the stream has passed.
+// One workgroup up to kOneScan counts, two launches above: 65,536 counts and
+// their items take one workgroup 70 us, the two launches 14.
 hipError_t scan_items(const DevBuf &in, DevBuf &out, int per, DevBuf &items, int64_t n,
-                      int64_t *sizes, hipStream_t s);
+                      DevBuf &tmp, int64_t *sizes, hipStream_t s);
 
 #if defined(__HIPCC__)
 // Stores that the host sees once the kernel is done.
+__device__ __forceinline__ void store_size(int64_t *p, int64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 __device__ __forceinline__ void store_sizes(int64_t *sizes, int64_t most, int64_t total,
                                             int64_t items)
 {
-    __hip_atomic_store(&sizes[0], most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&sizes[1], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&sizes[2], items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    store_size(&sizes[0], most);
+    store_size(&sizes[1], total);
+    store_size(&sizes[2], items);
     __threadfence_system();
 }
 #endif

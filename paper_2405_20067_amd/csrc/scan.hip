@@ -1,9 +1,9 @@
 // Device-wide exclusive scan of counts into offsets, and the L2 loss.
 //
 // The scan is three launches: per-block totals, one block scanning those,
-// then every block scanning its own items with its carry.  Up to kOneScan
-// counts one workgroup takes them all in one launch, 4,096 at a time: about
-// 2 us a round against three dependent launches of 4 us.
+// then every block scanning its own counts with its carry; up to kTwoScan
+// counts the last adds up the totals before its own, without the second.  Up to
+// kOneScan counts one workgroup takes them all in one launch, 4,096 at a time.
 #include "ngd_internal.hpp"
 #include "wave.hpp"
 
@@ -13,6 +13,7 @@ namespace {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanBlock = kScanThreads * kScanItems;
+static_assert(kTwoScan == int64_t(kScanBlock) * kScanThreads, "a thread per block sum");
 
 __device__ __forceinline__ int64_t wave_inclusive_scan64(int64_t x)
 {
@@ -45,21 +46,41 @@ __device__ int64_t block_exclusive_scan64(int64_t v, int64_t *total)
     return before + inc - v;
 }
 
+// What row y of a scan's blocks adds up: the counts, or (y = 1) their items.
+__device__ __forceinline__ int scan_value(int v, int per)
+{
+    return blockIdx.y == 0 ? v : int((unsigned(v) + unsigned(per) - 1u) / unsigned(per));
+}
+
+// bsum: a row of block sums per y; with bmax, also the largest count per block.
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const int32_t *__restrict__ in,
-                                                              int64_t n,
-                                                              int64_t *__restrict__ bsum)
+                                                              int64_t n, int per,
+                                                              int64_t *__restrict__ bsum,
+                                                              int64_t *__restrict__ bmax)
 {
     // a sum: the block's items are read coalesced, in any order
     const int64_t b0 = int64_t(blockIdx.x) * kScanBlock + threadIdx.x;
     int64_t acc = 0;
+    int most = 0;
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         const int64_t g = b0 + int64_t(j) * kScanThreads;
-        if (g < n) acc += in[g];
+        const int v = g < n ? in[g] : 0;
+        acc += scan_value(v, per);
+        most = v > most ? v : most;
     }
     int64_t tot;
     block_exclusive_scan64(acc, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+    if (threadIdx.x == 0) bsum[int64_t(blockIdx.y) * gridDim.x + blockIdx.x] = tot;
+    if (!bmax || blockIdx.y != 0) return;   // uniform
+    __shared__ int wmax[kScanThreads / kWave];
+    most = __float_as_int(wave_max_nonneg(__int_as_float(most)));   // counts >= 0
+    if (lane_id() == 0) wmax[threadIdx.x / kWave] = most;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / kWave; ++w) most = wmax[w] > most ? wmax[w] : most;
+    bmax[blockIdx.x] = most;
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_top(int64_t *__restrict__ bsum,
@@ -81,13 +102,17 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_top(int64_t *__restrict__
 __device__ __forceinline__ int scan_slot(int i) { return i + i / kScanItems; }
 
 // SUM: boff holds the blocks' sums, a thread's at most one, and a block adds up
-// those before it; otherwise their offsets.
+// those before it; otherwise their offsets.  Row y = 1 scans the counts' items
+// into iout.  With sizes (SUM), the last block of each row stores its total
+// there, that of the first row also the largest count, from bmax.
 template <bool SUM>
-__global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t *__restrict__ in,
-                                                            int64_t n,
-                                                            const int64_t *__restrict__ boff,
-                                                            int64_t *__restrict__ out)
+__global__ __launch_bounds__(kScanThreads) void k_scan_down(
+    const int32_t *__restrict__ in, int64_t n, int per, const int64_t *__restrict__ boff,
+    int64_t *__restrict__ out, int64_t *__restrict__ iout, const int64_t *__restrict__ bmax,
+    int64_t *__restrict__ sizes)
 {
+    boff += int64_t(blockIdx.y) * gridDim.x;
+    if (blockIdx.y != 0) out = iout;
     // Coalesced in and out through LDS; in between each thread scans its
     // run of kScanItems consecutive items.
     __shared__ int64_t sb[kScanBlock + kScanBlock / kScanItems];
@@ -95,7 +120,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t *__res
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         const int i = threadIdx.x + j * kScanThreads;
-        sb[scan_slot(i)] = (b0 + i < n) ? in[b0 + i] : 0;
+        sb[scan_slot(i)] = (b0 + i < n) ? scan_value(in[b0 + i], per) : 0;
     }
     int64_t before = 0;
     if constexpr (SUM)   // syncs
@@ -119,7 +144,17 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t *__res
         run += v[j];
     }
     const int64_t base = b0 + t0;
-    if (base < n && base + kScanItems >= n) out[n] = run;   // thread holding the last item
+    if (base < n && base + kScanItems >= n) {   // the thread holding the last count
+        out[n] = run;
+        if (sizes) {
+            int64_t most = 0;
+            if (blockIdx.y == 0)
+                for (unsigned b = 0; b < gridDim.x; ++b) most = bmax[b] > most ? bmax[b] : most;
+            if (blockIdx.y == 0) store_size(&sizes[0], most);
+            store_size(&sizes[1 + blockIdx.y], run);
+            __threadfence_system();
+        }
+    }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
@@ -269,8 +304,9 @@ __global__ __launch_bounds__(kLossThreads) void k_l2_final(const double *__restr
 
 size_t scan_tmp_bytes(int64_t n)
 {
+    // two rows of block sums and one of maxima
     const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-    return size_t(nb > 0 ? nb : 1) * sizeof(int64_t);
+    return 3 * size_t(nb > 0 ? nb : 1) * sizeof(int64_t);
 }
 
 hipError_t scan_counts(const DevBuf &in_buf, DevBuf &out_buf, int64_t n, DevBuf &tmp_buf,
@@ -293,28 +329,40 @@ hipError_t scan_counts(const DevBuf &in_buf, DevBuf &out_buf, int64_t n, DevBuf 
     }
     const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
     int64_t *bsum = static_cast<int64_t *>(tmp);
-    k_scan_reduce<<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(in, n, bsum);
+    const dim3 grid{unsigned(nb)};
+    k_scan_reduce<<<grid, kScanThreads, 0, s>>>(in, n, 1, bsum, nullptr);
     // a launch less while a block's threads can read all the sums before it
     // (the five scans of a 10-D training step of 2^20 queries: 80 -> 62 us, and
     // their gaps)
-    if (nb <= kScanThreads) {
-        k_scan_down<true><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(in, n, bsum, out);
+    if (n <= kTwoScan) {
+        k_scan_down<true><<<grid, kScanThreads, 0, s>>>(in, n, 1, bsum, out, nullptr, nullptr,
+                                                        nullptr);
         return hipGetLastError();
     }
     k_scan_top<<<1, kScanThreads, 0, s>>>(bsum, nb);
-    k_scan_down<false><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(in, n, bsum, out);
+    k_scan_down<false><<<grid, kScanThreads, 0, s>>>(in, n, 1, bsum, out, nullptr, nullptr,
+                                                     nullptr);
     return hipGetLastError();
 }
 
 hipError_t scan_items(const DevBuf &in_buf, DevBuf &out_buf, int per, DevBuf &item_buf, int64_t n,
-                      int64_t *sizes, hipStream_t s)
+                      DevBuf &tmp_buf, int64_t *sizes, hipStream_t s)
 {
-    if (n < 0 || out_buf.cap < sizeof(int64_t) * size_t(n + 1) ||
+    if (n < 0 || n > kTwoScan || out_buf.cap < sizeof(int64_t) * size_t(n + 1) ||
         item_buf.cap < sizeof(int64_t) * size_t(n + 1) ||
-        in_buf.cap < sizeof(int32_t) * size_t(n))
+        in_buf.cap < sizeof(int32_t) * size_t(n) || tmp_buf.cap < scan_tmp_bytes(n))
         return hipErrorInvalidValue;
-    k_scan_one<<<1, kOneThreads, 0, s>>>(n, in_buf.as<int32_t>(), out_buf.as<int64_t>(), per,
-                                         item_buf.as<int64_t>(), sizes);
+    const int32_t *in = in_buf.as<int32_t>();
+    int64_t *out = out_buf.as<int64_t>(), *items = item_buf.as<int64_t>();
+    if (n <= kOneScan) {
+        k_scan_one<<<1, kOneThreads, 0, s>>>(n, in, out, per, items, sizes);
+        return hipGetLastError();
+    }
+    const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
+    int64_t *bsum = tmp_buf.as<int64_t>(), *bmax = sizes ? bsum + 2 * nb : nullptr;
+    const dim3 grid(unsigned(nb), 2);
+    k_scan_reduce<<<grid, kScanThreads, 0, s>>>(in, n, per, bsum, bmax);
+    k_scan_down<true><<<grid, kScanThreads, 0, s>>>(in, n, per, bsum, out, items, bmax, sizes);
     return hipGetLastError();
 }
 
