@@ -12,10 +12,10 @@
 // every candidate entry (tile, Gaussian) and every 64-query group of the
 // tile, whether it kept the pair group (one byte); the backward visits only
 // the kept groups, so it sums over exactly the pairs the forward summed,
-// recomputing y, G and the exp rather than storing them.  In mixtures of more
-// than kLightMin Gaussians, one to which a handful of queries add anything
-// takes those alone (k_light_moments, k_light_gradients); the others, and all of
-// a smaller mixture, go to work items.  A work item is one
+// recomputing y, G and the exp rather than storing them.  In large mixtures
+// (backward_light) a Gaussian to which a handful of queries add anything takes
+// those alone (k_light_moments, k_light_gradients); the others go to work items,
+// as all do elsewhere.  A work item is one
 // Gaussian and at most kItemTiles of its candidate entries (the transposed
 // lists); one wave evaluates the item's kept groups 64 queries at a time,
 // keeps per-lane partial moments in registers (B1: n, B2: n(n+1)/2, H: 3),
@@ -232,24 +232,23 @@ __device__ __forceinline__ void backward_item(
         const int gq = __builtin_ctz(fb);
         if (lane == l) fl = fb & (fb - 1);
         {
-            const int64_t tt = __builtin_amdgcn_readlane(tl, l);
-            const int sidx = gq * kWave + lane;
-            const bool valid = (sidx < tile) && (tt * tile + sidx < q);
+            const int64_t p0 = int64_t(__builtin_amdgcn_readlane(tl, l)) * tile + gq * kWave;
+            const int64_t p = p0 + lane;
+            const bool valid = (gq * kWave + lane < tile) && (p < q);
             // every lane loads (a lane past the end from the group's first
             // query, which a kept group has) and the invalid ones are zeroed:
-            // no branches; scalar bases and one offset, no 64-bit sums a lane
-            const uint32_t at = valid ? uint32_t(sidx) : uint32_t(gq * kWave);
+            // no branches
+            const int64_t pc = valid ? p : p0;
             float x[N], d[N], y[N];
 #pragma unroll
-            for (int a = 0; a < N; ++a) x[a] = (qs + a * q + tt * tile)[at];
+            for (int a = 0; a < N; ++a) x[a] = qs[a * q + pc];
             float msq = 0.0f;
             brows<N, 0, N>(r, x, d, y, msq);
             any = true;
             const float G = valid ? __builtin_amdgcn_exp2f(-msq) : 0.0f;
-            const float *gt = gs + tt * tile;
-            const float g0v = valid ? gt[at] : 0.0f;
-            const float g1v = valid ? (gt + q)[at] : 0.0f;
-            const float g2v = valid ? (gt + 2 * q)[at] : 0.0f;
+            const float g0v = valid ? gs[pc] : 0.0f;
+            const float g1v = valid ? gs[q + pc] : 0.0f;
+            const float g2v = valid ? gs[2 * q + pc] : 0.0f;
             const float sdot = fmaf(g2v, c2, fmaf(g1v, c1, g0v * c0));
             const float w = alpha * G * sdot;
             h0 = fmaf(G, g0v, h0);
@@ -328,7 +327,8 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_items(
 constexpr int kLightGaussians = 8;    // of a wave (4: 177 us and 385 at 2^22 queries, 16: 177 and 403)
 constexpr int kLightRows = 32;        // queries of a pair that can count
 constexpr int kLightQueries = 64;     // queries of a Gaussian
-constexpr int kLightEntries = 32;     // kept entries of a Gaussian
+constexpr int kLightEntries = 8;      // kept entries of a Gaussian (4: 1,527 us at 2^22 queries,
+                                      // 8: 1,431, 16: 1,436, 32: 1,439)
 
 // ncount: the Gaussian's queries, its moments then in row g of mom (if any), or
 // -1 where there are more than the above: it goes to items (their number in
@@ -363,8 +363,12 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
     const int rel = int(off - b);   // this wave's entries: below 2^31
     const int ne = __builtin_amdgcn_readlane(rel, ng);
     const int mine = __shfl_down(rel, 1, kWave) - rel;   // lane < ng: its Gaussian's entries
-    // lane < ng: its Gaussian's queries so far
-    int cnt = lane < ng && mine > kLightEntries ? kLightQueries + 1 : 0;
+    // lane < ng: its Gaussian's queries so far.  Where the Gaussians have more
+    // entries than that on average all of them go to items: an image's backward
+    // (K = 131,072, 512 x 512, 40 kept groups a Gaussian) 2,139 us without this
+    // pass, 2,221 with it, 2,155 so.
+    const bool none = uniform64(a_off[k]) > kLightEntries * k;
+    int cnt = lane < ng && (none || mine > kLightEntries) ? kLightQueries + 1 : 0;
     // this lane's moments: lane, lane + 64
     int fa[NE], fb[NE];
     float acc[NE];
@@ -400,6 +404,11 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
     };
     const int ngroups = (tile + kWave - 1) / kWave;
     for (int base = 0; base < ne; base += kWave) {
+        // past the entries of Gaussians that go to items
+        const uint64_t ahead =
+            ballot(lane < ng && cnt <= kLightQueries && mine > 0 && rel + mine > base);
+        if (ahead == 0) break;
+        base = max(base, __builtin_amdgcn_readlane(rel, __builtin_ctzll(ahead)));
         int tl = 0, gl = 0;
         uint32_t fl = 0;   // bit g: group g kept
         if (base + lane < ne) {
@@ -724,13 +733,8 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     hipError_t err = launch_backward_prepare(c, s);
     if (err != hipSuccess) return err;
     const int32_t *a_ent = c->a_ent_buf ? c->vals1.as<int32_t>() : c->vals0.as<int32_t>();
-    // The Gaussians with a handful of queries first, by lanes: 10-D, K =
-    // 262,144, 2^20 queries: items and their sums 370 us, now 231 + 9; 2^22
-    // queries 560, now 441 + 49.  Up to kLightMin Gaussians, whose items'
-    // offsets come with the lists' in one launch, the six launches more cost
-    // what it saves (K = 65,536, 2^18 queries: 68 us less on the device, the
-    // fitting step as long).
-    const bool light = mix->k > kLightMin;
+    // the Gaussians with a handful of queries first, by lanes
+    const bool light = backward_light(c);
     if (light) {
         const int64_t per = int64_t(kWavesPerBlock) * kLightGaussians;
         const int64_t blocks = (mix->k + per - 1) / per, most = max_grid(kBwdThreads);

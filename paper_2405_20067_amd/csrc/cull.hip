@@ -1335,8 +1335,15 @@ hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
     } else {
         c->a_ent_buf = 0;
     }
-    if (k > kLightMin) return scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
-    e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, c->scan_tmp, nullptr, s);
+    if (backward_light(c)) return scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
+    if (k <= kTwoScan) {
+        e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, c->scan_tmp, nullptr, s);
+    } else {
+        e = scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
+        if (e == hipSuccess)
+            e = launch_items(k, c->a_off.as<int64_t>(), kItemTiles, c->gitem_cnt, c->gitem_off,
+                             c->scan_tmp, s);
+    }
     return e == hipSuccess ? item_fill(c, s) : e;
 }
 

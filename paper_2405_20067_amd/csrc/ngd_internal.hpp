@@ -26,9 +26,6 @@ constexpr double kSkipLog2Margin = 20.0;
 // workgroups / waves; their partial sums are combined in a fixed order.
 constexpr int kItemCands = 512;
 constexpr int kItemTiles = 32;
-// Mixtures of more Gaussians than this have a pass for those with a handful of
-// queries ahead of the backward's items (backward.hip).
-constexpr int64_t kLightMin = 65536;
 
 inline int tri(int n) { return n * (n + 1) / 2; }
 
@@ -283,9 +280,23 @@ hipError_t launch_backward_culled(const ngd_mixture *mix, ngd_cull *c,
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 // Groups the entries with a kept query group by Gaussian (a_cnt, a_off, the
 // sorted entries with their Gaussians in vals0/vals1 and keys0/keys1) and, for
-// at most kLightMin Gaussians, builds the backward work items; a_cnt is
+// builds the backward work items unless backward_light; a_cnt is
 // zero on entry.
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s);
+// Whether the backward has a pass for the Gaussians with a handful of queries
+// ahead of its items (backward.hip).  The pass saves the items of these their
+// sums over the lanes and costs two launches, so it takes many candidates, many
+// Gaussians and many moments to pay.  Backward without it and with it, 10-D:
+// K = 262,144, 2^22 queries (281 candidates a Gaussian) 1,553 and 1,426 us, 2^20
+// (100) 726 and 621, 2^18 (43) 384 and 374, 2^17 (31) 308 and 315, 2^16 (22) 228
+// and 257; 2^18 queries, K = 131,072 (47) 279 and 268, 100,000 (45) 258 and 253,
+// 65,537 (44) 217 and 230.  8-D, 2^18, K = 131,072 (41) 335 and 314, 100,000 (42)
+// 291 and 302; 7-D, 2^20, K = 200,000 (88) 1,650 and 1,670; 6-D, 2^18, K = 262,144
+// (35) 1,269 and 1,296.
+inline bool backward_light(const ngd_cull *c)
+{
+    return c->n >= 8 && c->k >= 131072 && c->total >= 32 * c->k;
+}
 // The work items from the Gaussians' item counts (gitem_cnt).
 hipError_t launch_backward_items(ngd_cull *c, hipStream_t s);
 // Mean squared error over q x 3 and its gradient; rel_eps > 0: each error
