@@ -21,7 +21,7 @@
 // keeps per-lane partial moments in registers (B1: n, B2: n(n+1)/2, H: 3),
 // reduces them across lanes once and writes them to the item's slot.
 // k_backward_finalize then adds each Gaussian's items in item order and
-// applies S^T.  Dense: one workgroup per Gaussian over all queries.
+// applies S^T.  Dense: one to sixteen waves per Gaussian over all queries.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -40,43 +40,50 @@ constexpr int kWavesPerBlock = kBwdThreads / kWave;
 static_assert(kItemTiles <= kWave, "an item's tile list must fit one wave");
 
 // ---- dense: every Gaussian over all queries --------------------------------
-// One workgroup per Gaussian; its waves take the 64-query blocks in turn
-// (lane = query), keep per-lane moments and reduce them over the lanes, then
-// over the waves in order through LDS, and the first threads form the outputs.
-// With W waves per Gaussian a mixture of a few hundred Gaussians fills the
-// chip: with one wave per Gaussian the loads of each block waited in a single
-// chain (K = 256, Q = 65,536, n = 4: 375 us, now 38 us, against 17 us of
-// vector operations).  No workspace, so calls on several streams stay
-// independent.
-template <int N, int W>
-__global__ __launch_bounds__(W *kWave) void k_backward_dense(
-    int64_t first, int64_t q, const float *__restrict__ rec, const float *__restrict__ xq,
-    const float *__restrict__ gq, float *__restrict__ g_mean, float *__restrict__ g_factor,
-    float *__restrict__ g_weight, float *__restrict__ g_colour)
+// W waves per Gaussian, PER Gaussians per workgroup; a Gaussian's waves take
+// the 64-query blocks in turn (lane = query), keep per-lane moments and reduce
+// them over the lanes, then over the waves in order through LDS, and its first
+// threads form the outputs.  With W waves per Gaussian a mixture of a few
+// hundred Gaussians fills the chip: with one wave per Gaussian the loads of each
+// block waited in a single chain (K = 256, Q = 65,536, n = 4: 375 us, now 27 us
+// with its launch, against 17 us of vector operations).  No workspace, so calls
+// on several streams stay independent.
+template <int N, int W, int PER>
+__global__ __launch_bounds__(PER *W *kWave) void k_backward_dense(
+    int64_t first, int64_t k, int64_t q, const float *__restrict__ rec,
+    const float *__restrict__ xq, const float *__restrict__ gq, float *__restrict__ g_mean,
+    float *__restrict__ g_factor, float *__restrict__ g_weight, float *__restrict__ g_colour)
 {
     constexpr int T = N * (N + 1) / 2;
     constexpr int R = (N + T + 7 + 3) / 4 * 4;
     constexpr int NM = N + T + 3;   // B1 | B2 | H
     constexpr int VP = (NM + 3) & ~3, Q4 = VP / 4;
     constexpr int AL = N + T + 3, CO = N + T + 4;
-    __shared__ float part[W][VP];
-    const int lane = lane_id(), w = int(threadIdx.x) / kWave;
-    const int64_t g = first + blockIdx.x;
+    __shared__ float s_part[PER][W][VP];
+    const int lane = lane_id(), w = int(threadIdx.x) / kWave % W;
+    const int own = uniform(int(threadIdx.x) / (W * kWave));
+    const int64_t gi = (first + blockIdx.x) * PER + own;
+    const int64_t g = gi < k ? gi : k - 1;   // past the end the last one, not stored
+    auto &part = s_part[own];
     const float *__restrict__ r = rec + g * R;
     const float alpha = r[AL], c0 = r[CO], c1 = r[CO + 1], c2 = r[CO + 2];
 
     float mv[VP];
 #pragma unroll
     for (int e = 0; e < VP; ++e) mv[e] = 0.0f;
-    for (int64_t b = int64_t(uniform(w)) * kWave; b < q; b += W * kWave) {
-        const bool valid = b + lane < q;
+    // 64 queries from b; FULL: all of them there, otherwise a lane past the end
+    // repeats the last with nothing upstream
+    auto block = [&]<bool FULL>(int64_t b) {
+        const bool valid = FULL || b + lane < q;
+        // (loaded from 64-bit addresses and without a condition, the three values
+        // by one load: three took twice the time in few dimensions)
         const int64_t p = valid ? b + lane : q - 1;
+        const float *__restrict__ xp = xq + p * N, *__restrict__ gp = gq + p * 3;
         float d[N], y[N];
 #pragma unroll
-        for (int a = 0; a < N; ++a) d[a] = xq[p * N + a];
-        // a lane past the end repeats the last query with nothing upstream
-        const float g0 = valid ? gq[p * 3 + 0] : 0.0f, g1 = valid ? gq[p * 3 + 1] : 0.0f,
-                    g2 = valid ? gq[p * 3 + 2] : 0.0f;
+        for (int a = 0; a < N; ++a) d[a] = xp[a];
+        const float u0 = gp[0], u1 = gp[1], u2 = gp[2];
+        const float g0 = valid ? u0 : 0.0f, g1 = valid ? u1 : 0.0f, g2 = valid ? u2 : 0.0f;
         float msq = 0.0f;
 #pragma unroll
         for (int row = 0; row < N; ++row) {
@@ -102,7 +109,10 @@ __global__ __launch_bounds__(W *kWave) void k_backward_dense(
             for (int c = 0; c <= a; ++c)
                 mv[N + a * (a + 1) / 2 + c] = fmaf(wy, y[c], mv[N + a * (a + 1) / 2 + c]);
         }
-    }
+    };
+    int64_t b = int64_t(uniform(w)) * kWave;
+    for (; b + kWave <= q; b += W * kWave) block.template operator()<true>(b);
+    if (b < q) block.template operator()<false>(b);
     // lane 16 i + 15 holds the totals of the i-th quarter
     wave_reduce_scatter<VP>(mv);
     if ((lane & 15) == 15) {
@@ -111,8 +121,8 @@ __global__ __launch_bounds__(W *kWave) void k_backward_dense(
         for (int i = 0; i < Q4; ++i) part[w][r0 + i] = mv[i];
     }
     __syncthreads();
-    const int t = int(threadIdx.x);
-    for (int e = t; e < NM; e += W * kWave) {
+    const int t = int(threadIdx.x) % (W * kWave);
+    for (int e = t; W > 1 && e < NM; e += W * kWave) {
         float acc = part[0][e];
 #pragma unroll
         for (int i = 1; i < W; ++i) acc += part[i][e];
@@ -124,7 +134,7 @@ __global__ __launch_bounds__(W *kWave) void k_backward_dense(
     const float inv_c = float(1.0 / kHalfLog2e);
     const float inv_c15 = float(1.0 / (kHalfLog2e * kSqrtHalfLog2e));
     const float *tot = part[0];
-    for (int e = t; e < NM + 1; e += W * kWave) {
+    for (int e = t; e < NM + 1 && gi < k; e += W * kWave) {
         if (e < N) {
             float acc = 0.0f;
             for (int kk = e; kk < N; ++kk) acc = fmaf(r[N + kk * (kk + 1) / 2 + e], tot[kk], acc);
@@ -705,12 +715,17 @@ hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q,
 {
     // 16 waves per Gaussian (8 from n = 11, whose moments take more than the
     // 128 registers a lane of a 16-wave workgroup has) while that is what it
-    // takes to fill the chip; with 4,096 Gaussians and more, 4
-    auto go = [&](auto kern, int waves) {
-        const int64_t most = max_grid(waves * kWave);
-        for (int64_t b = 0; b < mix->k; b += most)
-            kern<<<unsigned(std::min(mix->k - b, most)), waves * kWave, 0, s>>>(
-                b, q, mix->rec.as<float>(), queries, grad_out, gm, gf, gw, gc);
+    // takes to fill the chip, then 4, and one where the Gaussians fill it by
+    // themselves and a wave's sum over its lanes costs as much as its few
+    // queries.  n = 10, 16 / 4 / 1 waves: K = 256, Q = 65,536 65 / 120 / 454 us;
+    // K = 1,000, Q = 4,096 30 / 22 / 37; K = 4,096, Q = 8,192 - / 116 / 117 and
+    // Q = 300 - / 23 / 17; K = 131,072, Q = 64 - / 418 / 186.
+    auto go = [&](auto kern, int waves, int per = 1) {
+        const int threads = waves * per * kWave;
+        const int64_t blocks = (mix->k + per - 1) / per, most = max_grid(threads);
+        for (int64_t b = 0; b < blocks; b += most)
+            kern<<<unsigned(std::min(blocks - b, most)), threads, 0, s>>>(
+                b, mix->k, q, mix->rec.as<float>(), queries, grad_out, gm, gf, gw, gc);
         return hipGetLastError();
     };
     if (q == 0) {   // no queries: zero gradients whatever the parameters
@@ -719,9 +734,12 @@ hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q,
         if (e == hipSuccess) e = launch_zero_f32(gw, mix->k, s);
         return e == hipSuccess ? launch_zero_f32(gc, mix->k * 3, s) : e;
     }
-    if (mix->k >= 4096) return go(k_backward_dense<N, 4>, 4);
-    constexpr int W = N <= 10 ? 16 : 8;
-    return go(k_backward_dense<N, W>, W);
+    if (mix->k < 512) {
+        constexpr int W = N <= 10 ? 16 : 8;
+        return go(k_backward_dense<N, W, 1>, W);
+    }
+    if (mix->k < 2048 || (mix->k < 32768 && q >= 4096)) return go(k_backward_dense<N, 4, 1>, 4);
+    return go(k_backward_dense<N, 1, 4>, 1, 4);
 }
 
 template <int N>
