@@ -45,8 +45,8 @@ static_assert(kItemTiles <= kWave, "an item's tile list must fit one wave");
 // them over the lanes, then over the waves in order through LDS, and its first
 // threads form the outputs.  With W waves per Gaussian a mixture of a few
 // hundred Gaussians fills the chip: with one wave per Gaussian the loads of each
-// block waited in a single chain (K = 256, Q = 65,536, n = 4: 375 us, now 27 us
-// with its launch, against 17 us of vector operations).  No workspace, so calls
+// block waited in a single chain (K = 256, Q = 65,536, n = 4: 327 us, now 28,
+// against 17 us of vector operations).  No workspace, so calls
 // on several streams stay independent.
 template <int N, int W, int PER>
 __global__ __launch_bounds__(PER *W *kWave) void k_backward_dense(

@@ -21,8 +21,9 @@ constexpr int kEvalThreads = 256;
 // order through LDS, so the result does not depend on scheduling.  Otherwise
 // each wave has its own queries and sums all Gaussians.
 // Bound by the vector operations (N = 4: 25 issue slots a pair with the exp).
-// K = 256, Q = 65,536, n = 4: 16.6 us, 10 of them vector issue; with one
-// query a lane and 4 waves (whose records came through vector loads) 41.9 us.
+// K = 256, Q = 65,536, n = 4, one query a lane, 16 waves: 13.5 us, 10 of them
+// vector issue (15.2 with four queries a lane); with 4 waves whose records came
+// through vector loads 41.9 us.
 template <int N, int NQ, int W, bool SPLIT>
 __global__ __launch_bounds__(W *kWave) void k_eval_dense(int64_t k, int64_t q,
                                                          const float *__restrict__ rec,
@@ -125,18 +126,31 @@ template <int N>
 hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q, float *out,
                    hipStream_t s)
 {
-    // Four queries a lane while that still gives every SIMD about four waves
-    // (the Gaussians split over 4, then 16 waves as the batch shrinks), two
-    // and one below that.
     auto go = [&](auto kern, int per_block, int waves) {
         kern<<<unsigned((q + per_block - 1) / per_block), waves * kWave, 0, s>>>(
             mix->k, q, mix->rec.as<float>(), queries, out);
         return hipGetLastError();
     };
-    if (q >= (int64_t(1) << 20)) return go(k_eval_dense<N, 4, 4, false>, 16 * kWave, 4);
-    if (q >= (int64_t(1) << 18)) return go(k_eval_dense<N, 4, 4, true>, 4 * kWave, 4);
-    if (q >= (int64_t(1) << 16)) return go(k_eval_dense<N, 4, 16, true>, 4 * kWave, 16);
-    if (q >= (int64_t(1) << 15)) return go(k_eval_dense<N, 2, 16, true>, 2 * kWave, 16);
+    // Too few Gaussians to share, or few and many queries: a wave per 64 queries.
+    // Otherwise four waves share the Gaussians, sixteen where the queries alone
+    // leave the chip idle.  n = 8, 4 / 16 waves: K = 1,000, Q = 2,000 67 / 34 us,
+    // 70,000 137 / 118, 2^18 367 / 353; K = 64, Q = 2^17 18 / 32; n = 10: K = 1,000,
+    // Q = 70,000 186 / 198, 2^18 516 / 632.  n = 8, K = 16, Q = 2^20: one wave 34,
+    // four 61; n = 4, K = 15, Q = 2^18 - 1: one 11.3 with its launch, sixteen 18.8.
+    // Four queries a lane pay in one dimension only, whose pairs are cheaper than
+    // the waits for their records (K = 1,000: Q = 2^20 268 us against 292, 2^18 67
+    // against 82; n = 10, 2^20 2,204 against 1,966).
+    if constexpr (N == 1) {
+        if (mix->k >= 64 && q >= (int64_t(1) << 16)) {
+            if (q >= (int64_t(1) << 20)) return go(k_eval_dense<N, 4, 4, false>, 16 * kWave, 4);
+            if (q >= (int64_t(1) << 18)) return go(k_eval_dense<N, 4, 4, true>, 4 * kWave, 4);
+            return go(k_eval_dense<N, 4, 16, true>, 4 * kWave, 16);
+        }
+    }
+    if (mix->k < 16 || (mix->k < 64 && q >= (int64_t(1) << 19)))
+        return go(k_eval_dense<N, 1, 4, false>, 4 * kWave, 4);
+    const int64_t few = N < 10 ? int64_t(1) << 17 : int64_t(1) << 16;
+    if (mix->k < 256 || q >= few) return go(k_eval_dense<N, 1, 4, true>, kWave, 4);
     return go(k_eval_dense<N, 1, 16, true>, kWave, 16);
 }
 

@@ -1,0 +1,44 @@
+"""The forward without a cull at the sizes where its launches change, against the
+oracle."""
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import case, dev, host, normwise
+
+pytestmark = pytest.mark.gpu
+
+TOL_FP32 = 1e-4    # the bar of the other comparisons with the oracle
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.mark.parametrize("k", [1, 15, 16, 17])
+@pytest.mark.parametrize("n,q", [(1, 1), (4, 255), (4, 257), (10, 70001), (12, 1023)])
+def test_few_gaussians(torch_cuda, n, q, k):
+    from paper_2405_20067_amd import ngd
+    mix, x, _ = case(n, k, q, seed=n + k, sdiag=(2.0, 8.0), soff=0.5)
+    m = ngd.Mixture(n, k)
+    m.update(*(dev(mix[f]) for f in ("mean", "factor", "weight", "colour")))
+    got = host(ngd.eval_mixture(m, None, dev(x)))
+    want = oracle.eval_mixture(mix["mean"], mix["factor"], mix["weight"], mix["colour"], x)
+    assert normwise(got, want) <= TOL_FP32
+
+
+# a wave per 64 queries, 4 and 16 waves sharing the Gaussians; in one dimension
+# four queries a lane
+@pytest.mark.parametrize("n,q,k", [(2, (1 << 19) - 1, 63), (2, 1 << 19, 63), (2, 1 << 19, 64),
+                                   (9, (1 << 17) - 1, 256), (9, 1 << 17, 256),
+                                   (10, (1 << 16) - 1, 256), (10, 1 << 16, 256),
+                                   (10, 1000, 255), (10, 1000, 256), (1, (1 << 16) - 1, 257),
+                                   (1, 1 << 16, 257), (1, (1 << 18) + 5, 64),
+                                   (1, (1 << 20) + 300, 65), (1, (1 << 20) + 300, 63)])
+def test_launches(torch_cuda, n, q, k):
+    test_few_gaussians(torch_cuda, n, q, k)
