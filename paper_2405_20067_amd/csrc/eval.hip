@@ -17,8 +17,10 @@ constexpr int kEvalThreads = 256;
 // loads and their waits serve NQ distances; records alternate between two
 // register blocks, the next one's load issued after the wait for the current.
 // SPLIT: the workgroup's W waves take the same 64 NQ queries and split the
-// Gaussians into W consecutive ranges; the partial sums are added in range
-// order through LDS, so the result does not depend on scheduling.  Otherwise
+// Gaussians into W consecutive ranges; the partial sums are added in float64 and
+// range order through LDS, so the result does not depend on scheduling (in
+// float32 sixteen of them had a larger error than four: K = 256, n = 4 8.9e-8
+// root mean square against 8.2e-8, now 7.0e-8).  Otherwise
 // each wave has its own queries and sums all Gaussians.
 // Bound by the vector operations (N = 4: 25 issue slots a pair with the exp).
 // K = 256, Q = 65,536, n = 4, one query a lane, 16 waves: 13.5 us, 10 of them
@@ -81,10 +83,10 @@ __global__ __launch_bounds__(W *kWave) void k_eval_dense(int64_t k, int64_t q,
         for (int e = int(threadIdx.x); e < 3 * kQ; e += W * kWave) {
             const int s = e / 3, ch = e - 3 * s;
             if (p0 + s >= q) break;
-            float acc = part[0][ch][s];
+            double acc = part[0][ch][s];
 #pragma unroll
-            for (int v = 1; v < W; ++v) acc += part[v][ch][s];
-            out[p0 * 3 + e] = acc;
+            for (int v = 1; v < W; ++v) acc += double(part[v][ch][s]);
+            out[p0 * 3 + e] = float(acc);
         }
     } else {
 #pragma unroll

@@ -42,3 +42,21 @@ def test_few_gaussians(torch_cuda, n, q, k):
                                    (1, (1 << 20) + 300, 65), (1, (1 << 20) + 300, 63)])
 def test_launches(torch_cuda, n, q, k):
     test_few_gaussians(torch_cuda, n, q, k)
+
+
+@pytest.mark.parametrize("q", [100, 1 << 17])
+def test_partial_sums(torch_cuda, q):
+    # Gaussians of value 1 at every query, whose colours add up without rounding
+    # within each wave's range but not over the ranges: the sum of the partial
+    # sums is rounded once
+    from paper_2405_20067_amd import ngd
+    n, k = 2, 256
+    waves = 16 if q < 1 << 17 else 4
+    zero = np.zeros((k, n), np.float32)
+    factor = np.tile(np.array([1.0, 0.0, 1.0], np.float32), (k, 1))
+    colour = np.ones((k, 3), np.float32) * np.float32(waves / k)   # a partial sum of 1 ...
+    colour[:k // waves] *= np.float32(2.0**24)                     # ... the first one 2^24
+    m = ngd.Mixture(n, k)
+    m.update(dev(zero), dev(factor), dev(np.ones(k, np.float32)), dev(colour))
+    got = host(ngd.eval_mixture(m, None, dev(np.zeros((q, n), np.float32))))
+    assert np.all(got == np.float32(2.0**24 + waves - 1))
