@@ -165,11 +165,11 @@ __global__ __launch_bounds__(kWave) void k_gauss_records(int64_t k, const float 
     for (int e = 0; e < Fi::T; ++e) S[e] = double(r[N + e]);
     auto sidx = [](int row, int col) { return row * (row + 1) / 2 + col; };
     float cf[Fi::QU * 8];
-    float rs[N];
+    double rs[N];
     float cmax = 0.0f;
     bool ok = true;
 #pragma unroll
-    for (int a = 0; a < N; ++a) rs[a] = 0.0f;
+    for (int a = 0; a < N; ++a) rs[a] = 0.0;
 #pragma unroll
     for (int q = 0; q < Fi::QU * 8; ++q) {
         cf[q] = 0.0f;
@@ -180,15 +180,15 @@ __global__ __launch_bounds__(kWave) void k_gauss_records(int64_t k, const float 
             for (int row = 0; row < N; ++row)
                 if (row >= b) p += S[sidx(row, a)] * S[sidx(row, b)];
             cf[q] = float(a == b ? p : 2.0 * p);
-            rs[a] += fabsf(float(p));
-            if (a != b) rs[b] += fabsf(float(p));
+            rs[a] += fabs(p);
+            if (a != b) rs[b] += fabs(p);
             cmax = fmaxf(cmax, fabsf(cf[q]));
             ok = ok && fabsf(cf[q]) < INFINITY;
         }
     }
-    float best = 0.0f;
+    double best = 0.0;
 #pragma unroll
-    for (int a = 0; a < N; ++a) best = fmaxf(best, rs[a]);
+    for (int a = 0; a < N; ++a) best = fmax(best, rs[a]);
     // s: the power of two that puts cmax s into [2^7, 2^8)
     const int e = int(__float_as_uint(cmax) >> 23) - 127;
     ok = ok && e > -90 && e < 90;
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kWave) void k_gauss_records(int64_t k, const float 
     for (int i = 0; i < Fi::MU * 4; ++i) mt[i] = 0.0f;
 #pragma unroll
     for (int a = 0; a < N; ++a) mt[a] = r[a];
-    mt[N] = ok ? best * s * (1.0f + 1.0f / 1048576.0f) : INFINITY;
+    mt[N] = ok ? float(best * s * (1.0 + 1.0 / 1048576.0)) : INFINITY;   // rounded up
     mt[N + 1] = s;
 #pragma unroll
     for (int u = 0; u < Fi::MU; ++u)
