@@ -519,9 +519,10 @@ __device__ __forceinline__ void pair_part(PairState<N> &st, const float (&x)[N],
     }(std::make_integer_sequence<int, Parts<N>::PS>{});
 }
 
+// masks: the filter's; null: every candidate is evaluated.
 // OUT: the colours are accumulated; otherwise only the (entry, group) flags.
-// COUNT (with OUT = false): the first five of a slot of stats += (pairs examined, not skipped by the
-// filter, below the threshold after 3 rows, after 6 rows, kept).
+// COUNT (with OUT = false): the first five of a slot of stats += (pairs examined,
+// not skipped by the filter, below the threshold after 3 rows, after 6 rows, kept).
 template <int N, bool OUT, bool COUNT>
 __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
     int64_t item0, int64_t q, int tile, const uint64_t *__restrict__ masks, const float *__restrict__ qs,
@@ -576,8 +577,10 @@ __global__ __launch_bounds__(kMThreads, 7) void k_eval_items(
 #pragma unroll
         for (int c = 0; c < kItemChunks; ++c) {
             if (c * kWave < ne) {
-                const uint64_t m = uint64_t(
-                    uniform64(int64_t(masks[(it * ngroups + grp) * kItemChunks + c])));
+                const uint64_t m =
+                    masks ? uint64_t(uniform64(
+                                int64_t(masks[(it * ngroups + grp) * kItemChunks + c])))
+                          : ballot(c * kWave + lane < ne);
                 if ((m >> lane) & 1) {
                     const int o = cnt + __popcll(m & lanemask_lt());
                     s_idx[w][o] = cv[c];
@@ -710,20 +713,30 @@ hipError_t culled_n(const ngd_cull *c, float *out, unsigned long long *stats, hi
     const int tile = c->params.tile;
     const unsigned gy = unsigned((tile + kMThreads - 1) / kMThreads);
     const float skip = float(-std::log2(double(c->params.tau)) + kSkipLog2Margin);
+    // A handful of candidates an item are evaluated at once, and so are all in
+    // one dimension, whose tiles keep nearly every candidate.  Without the filter
+    // and with it: n = 10, Q = 2^20, K = 200 (4.9 candidates an item) 31 and 54 us,
+    // K = 1,000 (24) 73 and 53; Q = 2^18, K = 500 (20) 28 and 19; K = 4,096, Q =
+    // 32,768 in tiles of one (1.3) 32 and 137, of 4 (11) 36 and 60, of 16 (70) 55
+    // and 26; n = 12, Q = 2^20, K = 300 (8.2) 45 and 65; n = 4, Q = 2^18, K = 300
+    // (7.8) 13 and 17; n = 3, Q = 2^20, K = 60 (60) 42 and 47, Q = 30,000, K = 2,000
+    // (160) 41 and 29; n = 1, K = 500, Q = 30,000 (121) 23 and 27.
+    const bool filter = N > 1 && c->total > (N <= 3 ? 64 : 12) * c->nitems;
     // no idle waves for tiles of fewer than 256 queries
     const int threads = tile < kMThreads ? (tile + kWave - 1) / kWave * kWave : kMThreads;
     for (int64_t i0 = 0; i0 < c->nitems; i0 += max_grid(kMThreads)) {
         const dim3 grid(unsigned(std::min(c->nitems - i0, max_grid(kMThreads))), gy);
-        k_filter_items<N><<<grid, kMThreads, 0, s>>>(
-            i0, c->q, tile, c->mrec.as<f16x8>(), c->tcen.as<float>(), c->qs.as<float>(),
-            c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->item_tile.as<int32_t>(),
-            c->item_off.as<int64_t>(), skip, c->fmask.as<uint64_t>());
+        if (filter)
+            k_filter_items<N><<<grid, kMThreads, 0, s>>>(
+                i0, c->q, tile, c->mrec.as<f16x8>(), c->tcen.as<float>(), c->qs.as<float>(),
+                c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->item_tile.as<int32_t>(),
+                c->item_off.as<int64_t>(), skip, c->fmask.as<uint64_t>());
         auto go = [&](auto kern) {
             kern<<<grid, threads, 0, s>>>(
-                i0, c->q, tile, c->fmask.as<uint64_t>(), c->qs.as<float>(), c->grec.as<float>(),
-                c->tile_off.as<int64_t>(), c->cand.as<int32_t>(), c->perm.as<int32_t>(),
-                c->item_tile.as<int32_t>(), c->item_off.as<int64_t>(), skip,
-                c->act.as<uint8_t>(), out, c->fpart.as<float>(), stats);
+                i0, c->q, tile, filter ? c->fmask.as<uint64_t>() : nullptr, c->qs.as<float>(),
+                c->grec.as<float>(), c->tile_off.as<int64_t>(), c->cand.as<int32_t>(),
+                c->perm.as<int32_t>(), c->item_tile.as<int32_t>(), c->item_off.as<int64_t>(),
+                skip, c->act.as<uint8_t>(), out, c->fpart.as<float>(), stats);
         };
         if (stats)
             go(k_eval_items<N, false, true>);
