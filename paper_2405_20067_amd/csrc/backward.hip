@@ -161,17 +161,15 @@ template <int N> struct BwdLayout {
     static constexpr int T = N * (N + 1) / 2;
     static constexpr int R = (N + T + 7 + 3) / 4 * 4;
     static constexpr int NM = N + T + 3;             // B1 | B2 | H
-    static constexpr int K1 = N < 3 ? N : 3;        // stage boundaries
-    static constexpr int K2 = N < 6 ? N : 6;
 };
 
-// y rows [R0, R1) and msq for one lane; d[a] = x[a] - m[a].
-template <int N, int R0, int R1>
+// y and msq for one lane; d[a] = x[a] - m[a].
+template <int N>
 __device__ __forceinline__ void brows(const float *__restrict__ r, const float (&x)[N],
                                       float (&d)[N], float (&y)[N], float &msq)
 {
 #pragma unroll
-    for (int row = R0; row < R1; ++row) {
+    for (int row = 0; row < N; ++row) {
         d[row] = x[row] - r[row];
         const float *srow = r + N + row * (row + 1) / 2;
         float acc = srow[0] * d[0];
@@ -253,7 +251,7 @@ __device__ __forceinline__ void backward_item(
 #pragma unroll
             for (int a = 0; a < N; ++a) x[a] = qs[a * q + pc];
             float msq = 0.0f;
-            brows<N, 0, N>(r, x, d, y, msq);
+            brows<N>(r, x, d, y, msq);
             any = true;
             const float G = valid ? __builtin_amdgcn_exp2f(-msq) : 0.0f;
             const float g0v = valid ? gs[pc] : 0.0f;

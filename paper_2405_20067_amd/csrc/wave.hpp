@@ -67,15 +67,6 @@ __device__ __forceinline__ int wave_last(int x)
     return __builtin_amdgcn_readlane(x, 63);
 }
 
-// Sum over the wave, identical in every lane (xor butterfly: each step adds
-// the same two operands in every lane pair, so the result is one value).
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
-    return v;
-}
-
 // Maximum over the wave of non-negative floats by DPP, the same in every
 // lane: the bit patterns of non-negative floats order as unsigned integers
 // as the floats do; a running max over row_shr 1, 2, 4, 8 and row_bcast 15,
@@ -98,24 +89,12 @@ __device__ __forceinline__ float wave_max_nonneg(float v)
     return __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(x), 63)));
 }
 
-// Sum over the wave by DPP (no LDS traffic), valid in lane 63 only: the
-// inclusive-scan steps of wave_inclusive_scan on floats.  A fixed order, so
-// bitwise reproducible.
+// One step of a running sum over lanes (lanes shifted in from outside the row
+// add 0).
 template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_add(float x)
 {
     const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, false);
     return x + __int_as_float(y);
-}
-
-__device__ __forceinline__ float wave_sum_last(float v)
-{
-    v = dpp_add<kDppRowShr1, 0xf>(v);
-    v = dpp_add<kDppRowShr2, 0xf>(v);
-    v = dpp_add<kDppRowShr4, 0xf>(v);
-    v = dpp_add<kDppRowShr8, 0xf>(v);
-    v = dpp_add<kDppRowBcast15, 0xa>(v);
-    v = dpp_add<kDppRowBcast31, 0xc>(v);
-    return v;
 }
 
 // Sums over the wave of V values per lane (V a multiple of 4), scattered:
