@@ -23,7 +23,6 @@
 // k_backward_finalize then adds each Gaussian's items in item order and
 // applies S^T.  Dense: one to sixteen waves per Gaussian over all queries.
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "eval_common.hpp"
@@ -183,17 +182,16 @@ __device__ __forceinline__ void brows(const float *__restrict__ r, const float (
 // One work item (wave-uniform `it`).
 template <int N>
 __device__ __forceinline__ void backward_item(
-    int64_t it, int64_t q, int tile, const float *__restrict__ grec,
+    int64_t it, int64_t g, int64_t q, int tile, const float *__restrict__ grec,
     const float *__restrict__ qs, const float *__restrict__ gs,
     const int64_t *__restrict__ a_off, const int32_t *__restrict__ a_ent,
     const int32_t *__restrict__ ent_tile, const uint8_t *__restrict__ act,
-    const int64_t *__restrict__ gitem_off, const int32_t *__restrict__ gitem_g,
-    float *__restrict__ gpart, int32_t *__restrict__ gflag)
+    const int64_t *__restrict__ gitem_off, float *__restrict__ gpart,
+    int32_t *__restrict__ gflag)
 {
     using Lay = BwdLayout<N>;
     constexpr int T = Lay::T;
     const int lane = lane_id();
-    const int64_t g = uniform(gitem_g[it]);
     const int64_t j0 = uniform64(gitem_off[g]);
     const int64_t t0 = uniform64(a_off[g]), t1 = uniform64(a_off[g + 1]);
     const int64_t e0 = t0 + (it - j0) * kItemTiles;
@@ -312,10 +310,17 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_items(
 {
     const int64_t nit = uniform64(gitem_off[k]);
     const int64_t stride = int64_t(gridDim.x) * kWavesPerBlock;
-    for (int64_t it = int64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave; it < nit;
-         it += stride)
-        backward_item<N>(it, q, tile, grec, qs, gs, a_off, a_ent, ent_tile, act, gitem_off,
-                         gitem_g, gpart, gflag);
+    // a lane looks up each of the next 64, so that those left out cost nothing
+    for (int64_t base = int64_t(blockIdx.x) * kWavesPerBlock + uniform(int(threadIdx.x) / kWave);
+         base < nit; base += stride * kWave) {
+        const int64_t mine = base + lane_id() * stride;
+        const int g = mine < nit ? gitem_g[mine] : -1;
+        for (uint64_t m = ballot(g >= 0); m != 0; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            backward_item<N>(base + l * stride, __builtin_amdgcn_readlane(g, l), q, tile, grec, qs,
+                             gs, a_off, a_ent, ent_tile, act, gitem_off, gpart, gflag);
+        }
+    }
 }
 
 // ---- culled: Gaussians with a handful of queries --------------------------
@@ -338,9 +343,19 @@ constexpr int kLightQueries = 64;     // queries of a Gaussian
 constexpr int kLightEntries = 8;      // kept entries of a Gaussian (4: 1,527 us at 2^22 queries,
                                       // 8: 1,431, 16: 1,436, 32: 1,439)
 
+// Whether the pass leaves every Gaussian to the items: where they have more
+// entries on average than one of its own may have, or at most one in four has any
+// (a_off: their entries' offsets).  K = 262,144, n = 10: uniform queries, Q =
+// 2^20, 223 us without the pass, 277 with it, 242 so; an image's (66 kept groups a
+// Gaussian) 6.93, 7.11 and 6.93 ms.
+__device__ __forceinline__ bool light_none(int64_t k, const int64_t *__restrict__ a_off)
+{
+    const int64_t all = uniform64(a_off[k]);
+    return all > kLightEntries * k || 4 * all < k;
+}
+
 // ncount: the Gaussian's queries, its moments then in row g of mom (if any), or
-// -1 where there are more than the above: it goes to items (their number in
-// item_cnt).  Bound by the loads of the pairs' queries, 13 separate rows of 256
+// -1 where there are more than the above: it goes to items.  Bound by the loads of the pairs' queries, 13 separate rows of 256
 // bytes at n = 10: 169 us at 10-D, 2^20 queries (379 at 2^22), with an L2 miss
 // for 43% of the lines.  Loading a pair ahead, or the records' lines beforehand,
 // changed nothing, and neither did a sixth fewer vector operations.
@@ -350,8 +365,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
     const float *__restrict__ qs, const float *__restrict__ gs,
     const int64_t *__restrict__ a_off, const uint32_t *__restrict__ a_key,
     const int32_t *__restrict__ a_ent, const int32_t *__restrict__ ent_tile,
-    const uint8_t *__restrict__ act, float *__restrict__ mom, int32_t *__restrict__ ncount,
-    int32_t *__restrict__ item_cnt)
+    const uint8_t *__restrict__ act, float *__restrict__ mom, int32_t *__restrict__ ncount)
 {
     using Lay = BwdLayout<N>;
     constexpr int T = Lay::T, R = Lay::R, NM = Lay::NM;
@@ -371,11 +385,8 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
     const int rel = int(off - b);   // this wave's entries: below 2^31
     const int ne = __builtin_amdgcn_readlane(rel, ng);
     const int mine = __shfl_down(rel, 1, kWave) - rel;   // lane < ng: its Gaussian's entries
-    // lane < ng: its Gaussian's queries so far.  Where the Gaussians have more
-    // entries than that on average all of them go to items: an image's backward
-    // (K = 131,072, 512 x 512, 40 kept groups a Gaussian) 2,139 us without this
-    // pass, 2,221 with it, 2,155 so.
-    const bool none = uniform64(a_off[k]) > kLightEntries * k;
+    // lane < ng: its Gaussian's queries so far
+    const bool none = light_none(k, a_off);
     int cnt = lane < ng && (none || mine > kLightEntries) ? kLightQueries + 1 : 0;
     // this lane's moments: lane, lane + 64
     int fa[NE], fb[NE];
@@ -509,11 +520,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_light_moments(
         }
     }
     flush(-1);
-    if (lane < ng) {
-        const bool heavy = cnt > kLightQueries;
-        ncount[g0 + lane] = heavy ? -1 : cnt;
-        item_cnt[g0 + lane] = heavy ? (mine + kItemTiles - 1) / kItemTiles : 0;
-    }
+    if (lane < ng) ncount[g0 + lane] = cnt > kLightQueries ? -1 : cnt;
 }
 
 // The gradients of the Gaussians whose moments k_light_moments left: a lane
@@ -638,20 +645,20 @@ __global__ __launch_bounds__(kWave, 2) void k_light_gradients(
 
 // Per sorted Gaussian: sum its items' moments in item order, then
 //   dm = S'^T B1 / c, dL = tril(S'^T B2) / c^1.5, dalpha = c . H, dc = alpha H.
-// light: those without items have their gradients already.
+// light: not negative where a Gaussian has its gradients already (null: nowhere).
 template <int N>
 __global__ __launch_bounds__(kBwdThreads) void k_backward_finalize(
-    int64_t k, bool light, const float *__restrict__ grec, const int64_t *__restrict__ gitem_off,
-    const float *__restrict__ gpart, const int32_t *__restrict__ gflag,
+    int64_t k, const int32_t *__restrict__ light, const float *__restrict__ grec,
+    const int64_t *__restrict__ gitem_off, const float *__restrict__ gpart,
+    const int32_t *__restrict__ gflag,
     const int32_t *__restrict__ gperm, float *__restrict__ g_mean,
     float *__restrict__ g_factor, float *__restrict__ g_weight, float *__restrict__ g_colour)
 {
     using Lay = BwdLayout<N>;
     constexpr int T = Lay::T, NM = Lay::NM;
     const int64_t g = int64_t(blockIdx.x) * kBwdThreads + threadIdx.x;
-    if (g >= k) return;
+    if (g >= k || (light && light[g] >= 0)) return;
     const int64_t i0 = gitem_off[g], i1 = gitem_off[g + 1];
-    if (light && i0 == i1) return;
     float acc[NM];
 #pragma unroll
     for (int e = 0; e < NM; ++e) acc[e] = 0.0f;
@@ -750,8 +757,10 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
     if (err != hipSuccess) return err;
     const int32_t *a_ent = c->a_ent_buf ? c->vals1.as<int32_t>() : c->vals0.as<int32_t>();
     // the Gaussians with a handful of queries first, by lanes
-    const bool light = backward_light(c);
-    if (light) {
+    const int32_t *light = nullptr;
+    if (backward_light(c)) {
+        // (their queries in gitem_cnt, which the items' offsets no longer need)
+        int32_t *ncount = c->gitem_cnt.as<int32_t>();
         const int64_t per = int64_t(kWavesPerBlock) * kLightGaussians;
         const int64_t blocks = (mix->k + per - 1) / per, most = max_grid(kBwdThreads);
         for (int64_t b = 0; b < blocks; b += most)
@@ -759,13 +768,13 @@ hipError_t culled_n(const ngd_mixture *mix, ngd_cull *c, const float *grad_out, 
                 b, mix->k, c->q, c->params.tile, c->grec.as<float>(), c->qs.as<float>(),
                 c->gs.as<float>(), c->a_off.as<int64_t>(),
                 c->a_ent_buf ? c->keys1.as<uint32_t>() : c->keys0.as<uint32_t>(), a_ent,
-                c->ent_tile.as<int32_t>(), c->act.as<uint8_t>(), c->gpart.as<float>(),
-                c->gflag.as<int32_t>(), c->gitem_cnt.as<int32_t>());
+                c->ent_tile.as<int32_t>(), c->act.as<uint8_t>(), c->gpart.as<float>(), ncount);
         k_light_gradients<N><<<unsigned((mix->k + kWave - 1) / kWave), kWave, 0, s>>>(
-            mix->k, c->grec.as<float>(), c->gpart.as<float>(), c->gflag.as<int32_t>(),
-            c->gperm.as<int32_t>(), gm, gf, gw, gc);
-        if ((err = launch_backward_items(c, s)) != hipSuccess) return err;
+            mix->k, c->grec.as<float>(), c->gpart.as<float>(), ncount, c->gperm.as<int32_t>(), gm,
+            gf, gw, gc);
+        light = ncount;
     }
+    if ((err = launch_backward_items(c, light, s)) != hipSuccess) return err;
     if (c->gitems_cap > 0) {
         // about four rounds of resident waves (4 per SIMD at this kernel's
         // register count), each taking items a grid apart: 1,024 / 2,048 /

@@ -862,12 +862,16 @@ __global__ __launch_bounds__(kThreads) void k_item_count(int64_t n, const int64_
     cnt[i] = int32_t((len + per - 1) / per);
 }
 
+// skip: rows whose items are not wanted (>= 0; null: none) get -1.
 __global__ __launch_bounds__(kThreads) void k_item_fill(int64_t n, const int64_t *__restrict__ ioff,
-                                                        int64_t cap, int32_t *__restrict__ owner)
+                                                        int64_t cap,
+                                                        const int32_t *__restrict__ skip,
+                                                        int32_t *__restrict__ owner)
 {
     const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
     if (i >= n) return;
-    for (int64_t j = ioff[i]; j < ioff[i + 1] && j < cap; ++j) owner[j] = int32_t(i);
+    const int32_t v = skip && skip[i] >= 0 ? -1 : int32_t(i);
+    for (int64_t j = ioff[i]; j < ioff[i + 1] && j < cap; ++j) owner[j] = v;
 }
 
 // The list sizes, stored for the host (null most: no lists).
@@ -1296,16 +1300,6 @@ __global__ __launch_bounds__(kThreads) void k_ecompact(int64_t total, int groups
 
 }  // namespace
 
-namespace {
-hipError_t item_fill(ngd_cull *c, hipStream_t s)
-{
-    if (c->k > 0 && c->gitems_cap > 0)
-        k_item_fill<<<nblk(c->k, kThreads), kThreads, 0, s>>>(
-            c->k, c->gitem_off.as<int64_t>(), c->gitems_cap, c->gitem_g.as<int32_t>());
-    return hipGetLastError();
-}
-}  // namespace
-
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
 {
     const int64_t k = c->k, total = c->total;
@@ -1335,22 +1329,20 @@ hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s)
     } else {
         c->a_ent_buf = 0;
     }
-    if (backward_light(c)) return scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
-    if (k <= kTwoScan) {
-        e = scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, c->scan_tmp, nullptr, s);
-    } else {
-        e = scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
-        if (e == hipSuccess)
-            e = launch_items(k, c->a_off.as<int64_t>(), kItemTiles, c->gitem_cnt, c->gitem_off,
-                             c->scan_tmp, s);
-    }
-    return e == hipSuccess ? item_fill(c, s) : e;
+    if (k <= kTwoScan)
+        return scan_items(c->a_cnt, c->a_off, kItemTiles, c->gitem_off, k, c->scan_tmp, nullptr, s);
+    e = scan_counts(c->a_cnt, c->a_off, k, c->scan_tmp, s);
+    if (e != hipSuccess) return e;
+    return launch_items(k, c->a_off.as<int64_t>(), kItemTiles, c->gitem_cnt, c->gitem_off,
+                        c->scan_tmp, s);
 }
 
-hipError_t launch_backward_items(ngd_cull *c, hipStream_t s)
+hipError_t launch_backward_items(ngd_cull *c, const int32_t *skip, hipStream_t s)
 {
-    const hipError_t e = scan_counts(c->gitem_cnt, c->gitem_off, c->k, c->scan_tmp, s);
-    return e == hipSuccess ? item_fill(c, s) : e;
+    if (c->k > 0 && c->gitems_cap > 0)
+        k_item_fill<<<nblk(c->k, kThreads), kThreads, 0, s>>>(
+            c->k, c->gitem_off.as<int64_t>(), c->gitems_cap, skip, c->gitem_g.as<int32_t>());
+    return hipGetLastError();
 }
 
 bool cull_reserve_lists(ngd_cull *c)

@@ -195,7 +195,7 @@ struct ngd_cull {
     ngd::DevBuf item_off;      // ntiles + 1 int64
     ngd::DevBuf item_tile;     // nitems int32
     ngd::DevBuf fpart;         // nitems x 3 x tile float: forward partial sums
-    ngd::DevBuf gitem_cnt;     // k int32: backward items per Gaussian
+    ngd::DevBuf gitem_cnt;     // k int32: backward items per Gaussian (or light queries)
     ngd::DevBuf gitem_off;     // k + 1 int64
     ngd::DevBuf gitem_g;       // gitems_cap int32: sorted Gaussian of each item
     ngd::DevBuf gpart;         // gitems_cap x (n + tri + 3) float: moments
@@ -279,26 +279,24 @@ hipError_t launch_backward_culled(const ngd_mixture *mix, ngd_cull *c,
                                   float *g_weight, float *g_colour, hipStream_t s);
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 // Groups the entries with a kept query group by Gaussian (a_cnt, a_off, the
-// sorted entries with their Gaussians in vals0/vals1 and keys0/keys1) and, for
-// builds the backward work items unless backward_light; a_cnt is
-// zero on entry.
+// sorted entries with their Gaussians in vals0/vals1 and keys0/keys1), with the
+// offsets of the Gaussians' work items; a_cnt is zero on entry.
 hipError_t launch_backward_prepare(ngd_cull *c, hipStream_t s);
 // Whether the backward has a pass for the Gaussians with a handful of queries
-// ahead of its items (backward.hip).  The pass saves the items of these their
-// sums over the lanes and costs two launches, so it takes many candidates, many
-// Gaussians and many moments to pay.  Backward without it and with it, 10-D:
-// K = 262,144, 2^22 queries (281 candidates a Gaussian) 1,553 and 1,426 us, 2^20
-// (100) 726 and 621, 2^18 (43) 384 and 374, 2^17 (31) 308 and 315, 2^16 (22) 228
-// and 257; 2^18 queries, K = 131,072 (47) 279 and 268, 100,000 (45) 258 and 253,
-// 65,537 (44) 217 and 230.  8-D, 2^18, K = 131,072 (41) 335 and 314, 100,000 (42)
-// 291 and 302; 7-D, 2^20, K = 200,000 (88) 1,650 and 1,670; 6-D, 2^18, K = 262,144
-// (35) 1,269 and 1,296.
+// ahead of its items (backward.hip).  The pass spares the items of these their
+// sums over the lanes and costs two launches and a look at each Gaussian, so it
+// takes many Gaussians, moments and queries to pay.  Backward without it and with
+// it, n = 10, half of the queries near the Gaussians: K = 262,144, Q = 2^22 886
+// and 759 us, 2^20 535 and 416, 2^18 310 and 268, 2^16 198 and 203; K = 131,072,
+// 2^17 196 and 174; K = 100,000, 2^20 318 and 286; K = 65,536, 2^20 254 and 260.
+// n = 9: K = 200,000, 2^19 499 and 434; n = 8: K = 131,072, 2^18 330 and 337.
 inline bool backward_light(const ngd_cull *c)
 {
-    return c->n >= 8 && c->k >= 131072 && c->total >= 32 * c->k;
+    return c->n >= 9 && c->k >= 131072 && c->q >= c->k;
 }
-// The work items from the Gaussians' item counts (gitem_cnt).
-hipError_t launch_backward_items(ngd_cull *c, hipStream_t s);
+// The work items' Gaussians (gitem_g); -1 for those of a Gaussian that takes none
+// (skip not null and not negative there).
+hipError_t launch_backward_items(ngd_cull *c, const int32_t *skip, hipStream_t s);
 // Mean squared error over q x 3 and its gradient; rel_eps > 0: each error
 // weighted by 1 / (|f| + rel_eps)^2, the weight held constant.
 hipError_t launch_l2_loss(const float *f, const float *target, int64_t q, float *loss,

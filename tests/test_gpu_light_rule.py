@@ -1,14 +1,14 @@
 """The backward's pass for Gaussians with a handful of queries where it runs: at
-least 8 dimensions, 131,072 Gaussians, and 32 candidates of each on average.  Queries in an order that makes every Gaussian a candidate of every
-tile, so that the lists are long and the kept groups few; Gaussians on both
-sides of the pass's limits (8 kept entries, 32 queries of a group, 64 in all),
-and a mixture that leaves it everything (more than 8 kept entries on average)."""
+least 9 dimensions, 131,072 Gaussians, and as many queries.  Gaussians on both
+sides of its limits (8 kept entries, 32 queries of a group, 64 in all) and without
+any, and mixtures that leave it everything (more than 8 kept entries on average,
+fewer than one in four)."""
 
 import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import case, dev, host, normwise
+from gpu_helpers import case, dev, host, normwise, queries_of_gaussians
 from paper_2405_20067_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -25,46 +25,53 @@ def torch_cuda():
     return torch
 
 
-def _backward(mix, x, g, n, k, tile):
+def _backward(mix, x, g, proj, tile, tiling=0):
     from paper_2405_20067_amd import ngd
+    k, n = mix["mean"].shape
+    assert n >= 9 and k >= 131072 and x.shape[0] >= k
     m = ngd.Mixture(n, k)
     m.update(*(dev(mix[f]) for f in NAMES))
     p = ngd.default_params()
-    p.tile, p.tiling, p.n_proj, p.key_proj = tile, 2, 1, 1
+    p.tile, p.tiling, p.n_proj = tile, tiling, proj.shape[0]
+    p.key_proj = min(p.key_proj, p.n_proj)
     xd = dev(x)
-    c = ngd.Cull().build(m, xd, inputs.gen_projections(n, 1, seed=2), p)
+    c = ngd.Cull().build(m, xd, proj, p)
     got = [host(t) for t in ngd.eval_backward(m, c, xd, dev(g))]
-    again = [host(t) for t in ngd.eval_backward(m, c, xd, dev(g))]
+    # again, into buffers that hold something: every gradient is written
+    full = [dev(np.full_like(a, np.nan)) for a in got]
+    again = [host(t) for t in ngd.eval_backward(m, c, xd, dev(g), grads=full)]
     for a, b in zip(got, again):
         np.testing.assert_array_equal(a, b)
-    return got, c.stats()["total"], ngd.eval_stats(m, c, xd)["kept"], p.tau
+    return got, c.export(), ngd.eval_stats(m, c, xd)["kept"], p.tau
 
 
-@pytest.mark.parametrize("all_wide", [False, True])
-@pytest.mark.parametrize("n,k,tile,q", [(8, 131072, 64, 3001), (10, 131105, 100, 4999),
-                                        (12, 131135, 256, 12000)])
-def test_gradients(torch_cuda, n, k, tile, q, all_wide):
+@pytest.mark.parametrize("reach", ["own", "wide", "short"])
+@pytest.mark.parametrize("n,k,tile,q", [(9, 131072, 256, 131072), (10, 131105, 64, 131200),
+                                        (12, 131135, 60, 140000)])
+def test_gradients(torch_cuda, n, k, tile, q, reach):
     rng = np.random.default_rng(n)
-    mix, x, _ = case(n, k, q, seed=n + k)
-    wide = np.linspace(0, k - 1, 60).astype(np.int64)   # from one query to all of them
-    mix["factor"][wide] *= np.geomspace(1.0, 60.0, 60)[:, None].astype(np.float32)
+    mix, x, proj = case(n, k, q, seed=n + k, near=0.0 if reach == "short" else 1.0)
+    wide = np.linspace(0, k - 1, 60).astype(np.int64)   # from one query to many
+    far = mix["factor"][wide] * np.geomspace(1.0, 8.0, 60)[:, None].astype(np.float32)
+    mix["factor"][:] *= np.float32({"own": 1.0, "wide": 6.0, "short": 0.1}[reach])
+    mix["factor"][wide] = far
     mix["mean"][wide] = x[rng.integers(0, q, 60)]
-    if all_wide:
-        mix["factor"][:] *= np.float32(20.0)
+    alone = np.setdiff1d(np.arange(5, k, 977), wide)    # out of every query's reach
+    mix["mean"][alone] += np.float32(30.0)
     g = inputs.gen_grad_out(q, seed=n)
-    got, total, kept, _ = _backward(mix, x, g, n, k, tile)
-    assert total >= 32 * k
-    assert (kept > 32 * k) if all_wide else (kept < 8 * k)   # groups: 1 to 4 an entry
-    near = rng.integers(0, k, 3000)
-    d = oracle.msq_pairs(mix["mean"], mix["factor"], x, np.tile(np.arange(40), near.size),
-                         np.repeat(near, 40)).reshape(near.size, 40).min(1)
-    sel = np.unique(np.r_[wide, near[np.argsort(d)[:60]], near[:100], k - 1, 0]).astype(np.int64)
-    qoff = np.arange(sel.size + 1, dtype=np.int64) * q
-    qidx = np.tile(np.arange(q, dtype=np.int64), sel.size)
+    got, exp, kept, _ = _backward(mix, x, g, proj, tile)
+    print(f"kept {kept / k:.2f} groups a Gaussian")
+    per = -(-tile // 64)   # groups of an entry, at most
+    assert (kept > 8 * per * k if reach == "wide" else
+            4 * kept < k if reach == "short" else k * per < 4 * kept < 32 * k)
+    sel = np.unique(np.r_[wide, alone[:20], exp["gperm"][:50], rng.integers(0, k, 300)])
+    sel = sel.astype(np.int64)
+    qoff, qidx = queries_of_gaussians(exp, sel, q, tile)
     want = oracle.grad_lists(mix["mean"], mix["factor"], mix["weight"], mix["colour"], x, g,
                              sel, qoff, qidx)
     for name, a, b in zip(NAMES, got, want):
         assert np.all(np.isfinite(a)), name
+        assert not np.any(a[alone]), name
         assert normwise(a[sel], b) <= TOL_FP32, name
 
 
@@ -72,61 +79,71 @@ def test_gradients(torch_cuda, n, k, tile, q, all_wide):
 def test_not_a_number(torch_cuda, where):
     # one bad query: the gradients of the Gaussians that keep its group of 64
     # are not numbers, the others' are finite, as by work items
-    n, k, q, tile, bad = 8, 131075, 3001, 64, 1111
-    mix, x, _ = case(n, k, q, seed=3)
+    n, k, q, tile, bad = 9, 131075, 140000, 64, 1111
+    mix, x, proj = case(n, k, q, seed=3)
     g = inputs.gen_grad_out(q, seed=1)
     if where == "query":
         x[bad, 1] = np.nan
     else:
         g[bad, 2] = np.nan
-    got, total, _, tau = _backward(mix, x, g, n, k, tile)
-    assert total >= 32 * k
-    first = bad // 64 * 64
-    grp = np.arange(first, first + 64)
+    got, exp, kept, tau = _backward(mix, x, g, proj, tile)
+    assert 4 * kept >= k
+    at = int(np.flatnonzero(exp["perm"] == bad)[0])
+    t, grp = at // tile, at % tile // 64
+    others = exp["perm"][t * tile + grp * 64:min(t * tile + grp * 64 + 64, q)].astype(np.int64)
     if where == "query":
-        grp = grp[grp != bad]
-    idx = np.arange(k)
-    least = oracle.msq_pairs(mix["mean"], mix["factor"], x, np.tile(grp, k),
-                             np.repeat(idx, grp.size)).reshape(k, -1).min(1)
+        others = others[others != bad]
+    cand = exp["gperm"][exp["cand"][exp["tile_off"][t]:exp["tile_off"][t + 1]]].astype(np.int64)
+    least = oracle.msq_pairs(mix["mean"], mix["factor"], x, np.tile(others, cand.size),
+                             np.repeat(cand, others.size)).reshape(cand.size, -1).min(1)
     # the threshold in units of the squared distance, one unit off on both sides
     cut = 2.0 * np.log(2.0) * (np.log2(1.0 / tau) + 20.0)
-    kept, dropped = idx[least < cut - 1.0], idx[least > cut + 1.0]
-    assert kept.size > 0
+    keep = cand[least < cut - 1.0]
+    drop = np.setdiff1d(np.arange(k), cand[least < cut + 1.0])
+    assert keep.size > 0
     for name, a in zip(NAMES, got):
         a = a.reshape(k, -1)
-        assert np.all(np.isnan(a[kept]).any(1)), name
-        assert np.all(np.isfinite(a[dropped])), name
+        assert np.all(np.isnan(a[keep]).any(1)), name
+        assert np.all(np.isfinite(a[drop])), name
 
 
-@pytest.mark.parametrize("n", [8, 11])
+@pytest.mark.parametrize("n", [9, 11])
 def test_large_upstream_far_out(torch_cuda, n):
     # queries beyond the forward's threshold of 2^-33.3 in kept groups, with
     # upstream gradients that make them outweigh those within it
     rng = np.random.default_rng(n)
-    k, q, tile, at = 131073, 4096, 64, np.array([5, 170, 20000, 131072])
-    mix = dict(mean=rng.uniform(-0.2, 0.2, (k, n)).astype(np.float32),
+    k, near, tile, at = 131073, 4096, 64, np.array([5, 170, 20000, 131072])
+    q = near + k
+    # every other Gaussian sits on a query of its own, in a row far from the rest
+    mix = dict(mean=np.zeros((k, n), np.float32),
                factor=np.zeros((k, n * (n + 1) // 2), np.float32),
                weight=np.full(k, 0.5, np.float32),
                colour=rng.random((k, 3)).astype(np.float32))
+    row = np.zeros((k, n), np.float32)
+    row[:, 0] = 10.0 + 0.001 * np.arange(k)
+    mix["mean"][:] = row
     mix["mean"][at] = 0.0
     for a in range(n):
-        mix["factor"][:, a * (a + 1) // 2 + a] = 1e-5   # candidates of the tiles, never kept
+        mix["factor"][:, a * (a + 1) // 2 + a] = 1e-5
         mix["factor"][at, a * (a + 1) // 2 + a] = 0.1
     # exponents (base 2) of the four Gaussians' values; 200: nothing in float32
-    e = np.full(q, 200.0)
+    e = np.full(near, 200.0)
     e[[3, 70, 1000]] = 30.0
     e[20], e[90], e[91], e[1001] = 40.0, 60.0, 34.0, 110.0
-    u = rng.standard_normal((q, n))
+    u = rng.standard_normal((near, n))
     u /= np.linalg.norm(u, axis=1, keepdims=True)
-    x = (u * (0.1 * np.sqrt(2.0 * np.log(2.0) * e))[:, None]).astype(np.float32)
+    u *= (0.1 * np.sqrt(2.0 * np.log(2.0) * e))[:, None]
+    x = np.concatenate([u, row]).astype(np.float32)
     g = rng.standard_normal((q, 3)).astype(np.float32)
     g[20] *= 2.0**16
     g[90] *= 2.0**36
     g[1001] *= 2.0**86
-    got, total, kept, _ = _backward(mix, x, g, n, k, tile)
-    assert total >= 32 * k and kept == 3 * at.size
-    qoff = np.arange(at.size + 1, dtype=np.int64) * q
-    qidx = np.tile(np.arange(q, dtype=np.int64), at.size)
+    proj = np.zeros((1, n), np.float32)
+    proj[0, 0] = 1.0
+    got, _, kept, _ = _backward(mix, x, g, proj, tile, tiling=2)
+    assert k - at.size <= kept - 3 * at.size <= 2 * k
+    qoff = np.arange(at.size + 1, dtype=np.int64) * near
+    qidx = np.tile(np.arange(near, dtype=np.int64), at.size)
     want = oracle.grad_lists(mix["mean"], mix["factor"], mix["weight"], mix["colour"], x, g, at,
                              qoff, qidx)
     for name, a, b in zip(NAMES, got, want):
