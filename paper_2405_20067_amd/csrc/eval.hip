@@ -142,6 +142,16 @@ hipError_t dense_n(const ngd_mixture *mix, const float *queries, int64_t q, floa
     // Four queries a lane pay in one dimension only, whose pairs are cheaper than
     // the waits for their records (K = 1,000: Q = 2^20 268 us against 292, 2^18 67
     // against 82; n = 10, 2^20 2,204 against 1,966).
+    // Records beyond an XCD's L2 (4 MiB) bind by their own reading, which two or
+    // four queries a lane share: K = 262,144, Q = 2^18 150 ms with two and four
+    // waves, 180 with one; Q = 2^16 42 with four and sixteen, 54; K = 20,000, Q =
+    // 2^16 - 1 3.2 with two and sixteen, 3.8.
+    if (mix->k * int64_t(RecLayout<N>::R * sizeof(float)) > (int64_t(4) << 20) &&
+        q >= (int64_t(1) << 15)) {
+        if (q >= (int64_t(1) << 18)) return go(k_eval_dense<N, 2, 4, true>, 2 * kWave, 4);
+        if (q >= (int64_t(1) << 16)) return go(k_eval_dense<N, 4, 16, true>, 4 * kWave, 16);
+        return go(k_eval_dense<N, 2, 16, true>, 2 * kWave, 16);
+    }
     if constexpr (N == 1) {
         if (mix->k >= 64 && q >= (int64_t(1) << 16)) {
             if (q >= (int64_t(1) << 20)) return go(k_eval_dense<N, 4, 4, false>, 16 * kWave, 4);

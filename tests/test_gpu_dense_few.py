@@ -44,6 +44,21 @@ def test_launches(torch_cuda, n, q, k):
     test_few_gaussians(torch_cuda, n, q, k)
 
 
+# records of 4 MiB and one more: two or four queries a lane
+@pytest.mark.parametrize("k", [10485, 10486])
+@pytest.mark.parametrize("q", [(1 << 15) - 1, 1 << 15, (1 << 16) + 3, (1 << 18) + 65])
+def test_large_records(torch_cuda, q, k):
+    from paper_2405_20067_amd import ngd
+    n = 12
+    mix, x, _ = case(n, k, q, seed=q, sdiag=(2.0, 8.0), soff=0.5)
+    m = ngd.Mixture(n, k)
+    m.update(*(dev(mix[f]) for f in ("mean", "factor", "weight", "colour")))
+    got = host(ngd.eval_mixture(m, None, dev(x)))
+    at = np.unique(np.r_[0, q - 1, np.random.default_rng(k).integers(0, q, 300)])
+    want = oracle.eval_mixture(mix["mean"], mix["factor"], mix["weight"], mix["colour"], x[at])
+    assert normwise(got[at], want) <= TOL_FP32
+
+
 @pytest.mark.parametrize("q", [100, 1 << 17])
 def test_partial_sums(torch_cuda, q):
     # Gaussians of value 1 at every query, whose colours add up without rounding
