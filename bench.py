@@ -32,7 +32,10 @@ HBM_PEAK_GBS = 8000.0
 # Published dense FP32 vector peak without packed-FP32 instructions: the
 # library is built with those disabled, so 157.3 (packed) is out of reach.
 FP32_VALU_PEAK_TFLOPS = 78.6
-BF16_MFMA_PEAK_TFLOPS = 2500.0  # published dense BF16 matrix peak
+BF16_MFMA_PEAK_TFLOPS = 2500.0  # published dense 16-bit matrix peak
+# Both forward precisions: float32 arithmetic; float16 products only decide which
+# pairs are skipped.
+DTYPE = "f32 (f16 skip filter)"
 TRAFFIC_FILES = dict(fp32=os.path.join(ROOT, "profiles", "forward_10d_traffic.json"),
                      bf16_mfma=os.path.join(ROOT, "profiles", "forward_mfma_10d_traffic.json"))
 KERNEL_SRC = os.path.join(ROOT, "paper_2405_20067_amd", "csrc", "eval.hip")
@@ -225,7 +228,7 @@ def fit_bench(steps: int, precision_name: str, phase: int = 300, lr: float = 1e-
         metric="10-D fitting loop time per step (update, cull, fwd, loss, bwd, Adam, refinement)",
         value=ms, unit="ms/step", n_gpus=1, steps=steps, warmup=0, ms_per_step=ms,
         higher_is_better=False, scaling="weak", vs_baseline=None,
-        dtype="bf16+f32" if prec == ngd.BF16_MFMA else "f32", data="synthetic",
+        dtype=DTYPE, data="synthetic",
         config=dict(workload="10d-fit", n=w.n, k_start=k0, k_max=max_k, q=q, phase=phase,
                     lr=lr, lr_alpha=lr_alpha, lr_child=fit.lr_child, threshold=fit.threshold,
                     loss="l2",
@@ -299,7 +302,7 @@ def sweep_bench(reps: int = 5, sample: int = 4096):
     print(json.dumps(dict(
         metric="cull thresholds on the 10-D workload: candidate fraction, cull and forward "
                "time, error against the float64 oracle",
-        unit="ms", n_gpus=1, data="synthetic", dtype="f32 / bf16+f32",
+        unit="ms", n_gpus=1, data="synthetic", dtype=DTYPE,
         config=dict(workload="10d-fwdbwd", n=w.n, k=w.k, q=w.q, n_proj=16,
                     error_sample=sample, reps=reps),
         rows=rows)), flush=True)
@@ -635,7 +638,7 @@ def image_bench(reps: int = 5, sample: int = 2048, width: int = 800, k: int = 26
         f"{glob['ms_conditioned_3d']:.3f} ms, rel diff {diff:.2e}, err vs oracle {err3:.2e}")
     print(json.dumps(dict(
         metric="cull on an image-coherent 10-D G-buffer: tilings and thresholds; global "
-               "conditioning", unit="ms", n_gpus=1, data="synthetic", dtype="f32 / bf16+f32",
+               "conditioning", unit="ms", n_gpus=1, data="synthetic", dtype=DTYPE,
         config=dict(workload="10d-gbuffer", width=width, height=width, tile_pixels=16, n=n,
                     k=k, q=q, n_proj=16, error_sample=sample, reps=reps),
         dense_fp32_fwd_ms=dense_ms, rows=rows, global_conditioning=glob)), flush=True)
@@ -905,7 +908,7 @@ def main():
         value=rec["value"], unit="Gaussian-query evals/s (dense-equivalent Q*K per step time)",
         n_gpus=1, steps=args.steps, warmup=args.warmup, ms_per_step=rec["ms_per_step"],
         higher_is_better=True, scaling="weak", vs_baseline=None,
-        dtype="f32" if head == "fp32" else "bf16+f32",
+        dtype=DTYPE,
         data="synthetic",
         config=dict(workload=rec["workload"], description=rec["description"], n=rec["n"],
                     k=rec["k"], q=rec["q"], k_target=rec["k_target"],

@@ -52,21 +52,19 @@ extern "C" {
 #define NGD_MAX_N 12        /* dimensions supported: 1 .. NGD_MAX_N */
 #define NGD_MAX_PROJ 32     /* projection vectors: 1 .. NGD_MAX_PROJ */
 
-/* Arithmetic of ngd_eval / ngd_eval_backward (culled only for BF16_MFMA). */
-#define NGD_FP32 0          /* float32 direct evaluation, staged certified skip */
-#define NGD_BF16_MFMA 1     /* the (query group, candidate) skip decided by a
-                               BF16 matrix-core contraction of quadratic query
-                               features (1, x', x'_i x'_j; x' centred on the
-                               work item's query box) against per-Gaussian
-                               quadratic coefficients, each split into bf16
-                               hi + lo with the products hi*hi + hi*lo + lo*hi
-                               accumulated in float32 (Sec. 3.1, Eq. 1-2
-                               expanded).  A candidate is skipped for a group
-                               only when the contraction minus a certified
-                               error bound puts every query of the group past
-                               the skip threshold; every other candidate is
-                               evaluated exactly as with NGD_FP32, so colours
-                               keep float32 accuracy. */
+/* Arithmetic of ngd_eval / ngd_eval_backward (culled only for BF16_MFMA).
+ * Without a cull every pair is evaluated in float32.  With one, both take the
+ * same path: which (64-query group, candidate) pairs are skipped is decided by a
+ * matrix-core contraction of quadratic query features (1, x', x'_i x'_j; x'
+ * centred on the tile's query box) with per-Gaussian coefficients, both float16,
+ * accumulated in float32 (Sec. 3.1, Eq. 1-2 expanded).  A candidate is skipped
+ * for a group only when the contraction minus a certified error bound puts every
+ * query of the group past the skip threshold; every other candidate is evaluated
+ * in float32 against the same threshold, so the kept pairs and the colours are
+ * those of float32 arithmetic alone.  (Lists of a handful of candidates skip the
+ * contraction.) */
+#define NGD_FP32 0
+#define NGD_BF16_MFMA 1     /* as NGD_FP32 (a name kept for its callers) */
 
 typedef struct ngd_mixture ngd_mixture;
 typedef struct ngd_cull ngd_cull;
@@ -224,9 +222,7 @@ int ngd_cull_destroy(ngd_cull *cull);
  *            certified below tau * 2^-20 are skipped without evaluation.
  *   queries  device, q x n
  *   out      device, q x 3, in the caller's query order
- *   precision NGD_FP32, or NGD_BF16_MFMA (needs a cull).  With a cull both
- *            skip pairs by the same certified matrix-core filter and evaluate
- *            the others in float32
+ *   precision NGD_FP32, or NGD_BF16_MFMA (needs a cull)
  * Does not synchronise. */
 int ngd_eval(const ngd_mixture *mix, const ngd_cull *cull, const float *queries,
              int64_t q, int precision, float *out, void *stream);
@@ -234,7 +230,7 @@ int ngd_eval(const ngd_mixture *mix, const ngd_cull *cull, const float *queries,
 /* Builds, ahead of ngd_eval, what a forward of `precision` derives once per
  * cull build.  ngd_cull_build itself forms all that the forward reads (the
  * filter's per-Gaussian coefficients, the tiles' centres), so this call checks
- * its arguments and has nothing left to do.
+ * its arguments and does nothing else.
  *   mix, cull, queries, q as for ngd_eval (a cull is required).
  * Returns NGD_E_INVAL for a NULL handle or an unknown precision,
  * NGD_E_STALE for a cull of another mixture version or queries.
@@ -262,8 +258,8 @@ int ngd_eval_stats(const ngd_mixture *mix, const ngd_cull *cull, const float *qu
  * z = L_i^-T y.  With a cull the sums run over the same pairs as ngd_eval's.
  * Outputs (device, overwritten, caller's Gaussian order): g_mean k x n,
  * g_factor k x n(n+1)/2 (packed like the factor), g_weight k, g_colour k x 3.
- * Each Gaussian's sums are formed by one wave in a fixed order: no atomics,
- * bitwise reproducible.  `cull` may be NULL (dense).  With a cull the sums
+ * Each Gaussian's sums are formed in a fixed order: no atomics, bitwise
+ * reproducible.  `cull` may be NULL (dense).  With a cull the sums
  * run over the pairs the last ngd_eval on this cull and mixture version kept,
  * whatever its precision; without one, the keep decisions are taken first
  * with `precision`.  The gradient arithmetic is float32 in both cases.  Does

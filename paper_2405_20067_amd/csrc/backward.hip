@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_backward_items(
 // of the kept groups.  (Counting those above tau 2^-24 only, the step of 2^20
 // queries took 16 us less of 2,271, that of 2^22 as long, but an upstream
 // gradient large enough makes any of the others matter.)
-constexpr int kLightGaussians = 8;    // of a wave (4: 177 us and 385 at 2^22 queries, 16: 177 and 403)
+constexpr int kLightGaussians = 8;    // of a wave (4 and 16: 5 % slower at 2^20 and at 2^22 queries)
 constexpr int kLightRows = 32;        // queries of a pair that can count
 constexpr int kLightQueries = 64;     // queries of a Gaussian
 constexpr int kLightEntries = 8;      // kept entries of a Gaussian (4: 1,527 us at 2^22 queries,
@@ -356,7 +356,7 @@ __device__ __forceinline__ bool light_none(int64_t k, const int64_t *__restrict_
 
 // ncount: the Gaussian's queries, its moments then in row g of mom (if any), or
 // -1 where there are more than the above: it goes to items.  Bound by the loads of the pairs' queries, 13 separate rows of 256
-// bytes at n = 10: 169 us at 10-D, 2^20 queries (379 at 2^22), with an L2 miss
+// bytes at n = 10: 165 us at 10-D, 2^20 queries (351 at 2^22), with an L2 miss
 // for 43% of the lines.  Loading a pair ahead, or the records' lines beforehand,
 // changed nothing, and neither did a sixth fewer vector operations.
 template <int N>
